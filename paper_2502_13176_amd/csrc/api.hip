@@ -50,6 +50,7 @@ struct WorkspacePlan {
   size_t part_o, part_ml, final_ml, lag_q, lag_ml, lag_n, lag_cnt, status, kept, info, order_all, order_layer;
   size_t segs, seg_split, halo_k, halo_v, halo_score, halo_pos, tiles, tile_hist, sel_state, total;
   int64_t n_segs, halo_rows, n_tiles, n_long;
+  int32_t seg_rows;  // destination rows per segment of the eviction move
   int64_t max_items;
 };
 
@@ -68,19 +69,40 @@ bool shape_ok(const baklava_desc* d) {
   return true;
 }
 
+// Destination rows per segment of the eviction move (one workgroup each).  A segment copies its rows
+// tile after tile (128 rows, a few microseconds each, of which little overlaps inside a workgroup), so
+// a small arena needs short segments to keep the chip busy; in a large one they only add rows that
+// travel through a halo slot.  Measured, us per eviction at segments of rows / 128, / 256, / 512, / 1024
+// (fixed 4096 before): 8 caches of 32768 rows to 78643 in all 116, 104, 99, 99 (415); 524288 rows, 64
+// evicted per cache, 281, 243, 220, 219 (285); 131072 rows likewise 137, 127, 123, 125 (240); from two
+// million rows on the maximum holds.
+constexpr int kSegDivisor = 512;
+int32_t move_seg_rows(const baklava_desc* d, const int32_t* budget) {
+  int64_t rows = 0;
+  for (int64_t i = 0; i < (int64_t)d->L * d->Hkv; ++i) rows += (int64_t)budget[i] * d->batch;
+  int32_t seg = kMoveSegMax;
+  while (seg > kMoveSegMin && seg > rows / kSegDivisor) seg /= 2;
+  return seg;
+}
+
 // Segments of the eviction move: the destination range [0, budget) of every cache in runs of
-// kMoveSegRows rows; a segment that has a successor owns a halo slot of cap - budget rows.
-void count_segments(const baklava_desc* d, const int32_t* cap, const int32_t* budget, int64_t* n_segs,
-                    int64_t* halo_rows) {
+// seg_rows rows; a segment that has a successor owns a halo slot for the rows whose source lies past
+// its end: at most its own rows, and at most cap - budget of them.
+int64_t halo_slot_rows(int64_t cap, int64_t budget, int32_t seg_rows) {
+  return std::max<int64_t>(0, std::min<int64_t>(seg_rows, cap - budget));
+}
+
+void count_segments(const baklava_desc* d, const int32_t* cap, const int32_t* budget, int32_t seg_rows,
+                    int64_t* n_segs, int64_t* halo_rows) {
   const int64_t cpl = (int64_t)d->batch * d->Hkv;
   const int64_t n_caches = (int64_t)d->L * cpl;
   *n_segs = 0;
   *halo_rows = 0;
   for (int64_t c = 0; c < n_caches; ++c) {
     const int64_t b = budget[(c / cpl) * d->Hkv + c % d->Hkv];
-    const int64_t ns = std::max<int64_t>(1, (b + kMoveSegRows - 1) / kMoveSegRows);
+    const int64_t ns = std::max<int64_t>(1, (b + seg_rows - 1) / seg_rows);
     *n_segs += ns;
-    *halo_rows += (ns - 1) * std::max<int64_t>(0, cap[c] - b);
+    *halo_rows += (ns - 1) * halo_slot_rows(cap[c], b, seg_rows);
   }
 }
 
@@ -91,7 +113,8 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
   const size_t row_bytes = (size_t)d->D * (d->dtype == BAKLAVA_BF16 ? 2 : 4);
   int64_t total_tokens = 0;
   for (int64_t c = 0; c < n_caches; ++c) total_tokens += cap[c];
-  count_segments(d, cap, budget, &w.n_segs, &w.halo_rows);
+  w.seg_rows = move_seg_rows(d, budget);
+  count_segments(d, cap, budget, w.seg_rows, &w.n_segs, &w.halo_rows);
   w.max_items = count_items(cap, n_caches, kSizingChunk);
   size_t o = 0;
   for (int k = 0; k < 2; ++k) {
@@ -489,12 +512,13 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     for (int64_t c = 0; c < n_caches; ++c) {
       ctx->seg_begin[c] = (int32_t)segs.size();
       const int64_t b = ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv];
-      const int64_t hs = std::max<int64_t>(0, ctx->cap[c] - b);
-      const int64_t ns = std::max<int64_t>(1, (b + kMoveSegRows - 1) / kMoveSegRows);
+      const int32_t seg_rows = ctx->plan.seg_rows;
+      const int64_t hs = halo_slot_rows(ctx->cap[c], b, seg_rows);
+      const int64_t ns = std::max<int64_t>(1, (b + seg_rows - 1) / seg_rows);
       for (int64_t k = 0; k < ns; ++k) {
         MoveSeg sg;
         sg.c = (int32_t)c;
-        sg.a = (int32_t)(k * kMoveSegRows);
+        sg.a = (int32_t)(k * seg_rows);
         sg.halo_row = (k + 1 < ns && hs > 0) ? (int32_t)halo : -1;
         sg.pad = 0;
         if (k + 1 < ns) halo += hs;
@@ -706,6 +730,7 @@ extern "C" int baklava_compact(baklava_ctx* ctx, int32_t layer_begin, int32_t la
   p.segs = reinterpret_cast<const MoveSeg*>(ctx->ws + ctx->plan.segs) + s0;
   p.seg_split = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.seg_split);
   p.seg_base = s0;
+  p.seg_rows = ctx->plan.seg_rows;
   p.halo_k = ctx->ws + ctx->plan.halo_k;
   p.halo_v = ctx->ws + ctx->plan.halo_v;
   p.halo_score = reinterpret_cast<float*>(ctx->ws + ctx->plan.halo_score);

@@ -22,7 +22,7 @@ __device__ __forceinline__ void store_nt16(void* ptr, uint4 v) {
 
 constexpr int kLagRows = 32;   // packed query rows of a cache's record of pending calls (score tracking)
 constexpr int kLagCalls = 8;   // most calls such a record holds
-constexpr int kMoveSegRows = 4096;  // destination rows per workgroup of the eviction move
+constexpr int kMoveSegMin = 128, kMoveSegMax = 4096;  // destination rows per workgroup of the eviction move
 constexpr int kTileRows = 8192;     // rows per tile of a cache that is ranked tile by tile (one workgroup per tile and pass)
 constexpr int kMinLongRows = kTileRows;  // smallest capacity from which a cache may be ranked that way
 
@@ -140,7 +140,7 @@ struct AppendParams {
 };
 
 // One destination segment of the eviction move: rows [a, a + seg_rows) of cache c.  Segments that
-// have a successor own a halo slot (room for cap - budget rows) in the workspace.
+// have a successor own a halo slot (room for min(seg_rows, cap - budget) rows) in the workspace.
 struct MoveSeg {
   int32_t c, a;
   int32_t halo_row;  // first row of this segment's halo slot, or -1
@@ -169,6 +169,7 @@ struct CompactParams {
   float* halo_score;
   int32_t* halo_pos;
   int32_t seg_base;        // index of segs[0] in seg_split
+  int32_t seg_rows;        // destination rows per segment
   const int32_t* cap;
   const SelTile* tiles;    // tiles of the long caches of the launched range
   int32_t* tile_hist;      // [all tiles][4 passes][256] digit counters, indexed by first_tile + tile

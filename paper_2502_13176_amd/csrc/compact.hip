@@ -359,20 +359,27 @@ constexpr int kMoveRows = 128;  // rows per tile
 
 // The move is stable and in place: row p <- row kept[p], with kept[p] >= p and
 // kept[p] - p <= (rows evicted) <= capacity - budget.  A cache's destination range is cut into
-// segments of kMoveSegRows rows, one workgroup each.  Inside a segment tiles go in ascending
+// segments of p.seg_rows rows, one workgroup each.  Inside a segment tiles go in ascending
 // order and every load of a tile finishes (barrier) before any store, so a tile's sources are
 // never rows an earlier tile wrote.  The only rows a segment reads that another segment writes
 // are the few at its end whose source lies past the segment: those are copied to a halo slot
 // by a first kernel, before anything is overwritten.
 
-// Phase 1: save the halo of every segment that has a successor.
+// K/V rows are read once and written once here: non-temporal loads and stores (measured: the move
+// of a full eviction is 14% faster with them).
+#define BAKLAVA_MOVE_LD(ptr) load_nt16(ptr)
+#define BAKLAVA_MOVE_ST(ptr, v) store_nt16(ptr, v)
+
+// Phase 1: save the halo of every segment that has a successor.  After a prompt (far more rows than
+// the budget) that is nearly every row, so the copy goes at the move's own pace: the same tiles, every
+// load of a tile in flight before the first store.
 template <int PIECES>
-__global__ __launch_bounds__(256) void compact_halo_kernel(CompactParams p) {
+__global__ __launch_bounds__(kMoveThreads) void compact_halo_kernel(CompactParams p) {
   const MoveSeg sg = p.segs[blockIdx.x];
   const CompactInfo info = p.info[sg.c];
   if (info.first_moved >= info.old_len) return;  // nothing evicted
   const int b = info.new_len;
-  const int e = sg.a + kMoveSegRows;
+  const int e = sg.a + p.seg_rows;
   if (e >= b || sg.halo_row < 0) return;         // last segment: its far sources are overwritten by nobody
   const int tid = threadIdx.x;
   const int64_t off = p.off[sg.c];
@@ -385,17 +392,31 @@ __global__ __launch_bounds__(256) void compact_halo_kernel(CompactParams p) {
   }
   const int split = lo, n_halo = e - split;
   if (tid == 0) p.seg_split[p.seg_base + blockIdx.x] = split;
+  constexpr int PER_PLANE = kMoveRows * PIECES / kMoveThreads;
   const uint4* K = reinterpret_cast<const uint4*>(p.k) + off * PIECES;
   const uint4* V = reinterpret_cast<const uint4*>(p.v) + off * PIECES;
   uint4* HK = reinterpret_cast<uint4*>(p.halo_k) + (int64_t)sg.halo_row * PIECES;
   uint4* HV = reinterpret_cast<uint4*>(p.halo_v) + (int64_t)sg.halo_row * PIECES;
-  for (int idx = tid; idx < n_halo * PIECES; idx += 256) {
-    const int r = idx / PIECES, piece = idx % PIECES;
-    const int64_t src = kept[split + r];
-    HK[(int64_t)r * PIECES + piece] = K[src * PIECES + piece];
-    HV[(int64_t)r * PIECES + piece] = V[src * PIECES + piece];
+  for (int r0 = 0; r0 < n_halo; r0 += kMoveRows) {
+    uint4 kb[PER_PLANE], vb[PER_PLANE];
+#pragma unroll
+    for (int i = 0; i < PER_PLANE; ++i) {
+      const int idx = tid + i * kMoveThreads;
+      const int64_t src = kept[split + min(r0 + idx / PIECES, n_halo - 1)];  // clamped: a row of this halo
+      kb[i] = BAKLAVA_MOVE_LD(K + src * PIECES + idx % PIECES);
+      vb[i] = BAKLAVA_MOVE_LD(V + src * PIECES + idx % PIECES);
+    }
+#pragma unroll
+    for (int i = 0; i < PER_PLANE; ++i) {
+      const int idx = tid + i * kMoveThreads;
+      const int r = r0 + idx / PIECES;
+      if (r < n_halo) {  // the move reads these soon: ordinary stores
+        HK[(int64_t)r * PIECES + idx % PIECES] = kb[i];
+        HV[(int64_t)r * PIECES + idx % PIECES] = vb[i];
+      }
+    }
   }
-  for (int r = tid; r < n_halo; r += 256) {
+  for (int r = tid; r < n_halo; r += kMoveThreads) {
     const int src = kept[split + r];
     p.halo_score[sg.halo_row + r] = p.score[off + src];
     p.halo_pos[sg.halo_row + r] = p.pos[off + src];
@@ -403,10 +424,6 @@ __global__ __launch_bounds__(256) void compact_halo_kernel(CompactParams p) {
 }
 
 // Phase 2: the move itself.
-// K/V rows are read once and written once here: non-temporal loads and stores (measured: the move
-// of a full eviction is 14% faster with them).
-#define BAKLAVA_MOVE_LD(ptr) load_nt16(ptr)
-#define BAKLAVA_MOVE_ST(ptr, v) store_nt16(ptr, v)
 template <int PIECES>  // 16-byte pieces per row
 __global__ __launch_bounds__(kMoveThreads) void compact_move_kernel(CompactParams p) {
   const MoveSeg sg = p.segs[blockIdx.x];
@@ -416,10 +433,10 @@ __global__ __launch_bounds__(kMoveThreads) void compact_move_kernel(CompactParam
   const int tid = threadIdx.x;
   const int b = info.new_len;
   if (sg.a == 0 && tid == 0) p.len[c] = b;
-  const int e = min(sg.a + kMoveSegRows, b);
+  const int e = min(sg.a + p.seg_rows, b);
   if (e <= info.first_moved) return;             // every row of this segment stays where it is
   // rows [split, e) take their source from the halo slot
-  const bool has_halo = (sg.a + kMoveSegRows < b) && sg.halo_row >= 0;
+  const bool has_halo = (sg.a + p.seg_rows < b) && sg.halo_row >= 0;
   const int split = has_halo ? p.seg_split[p.seg_base + blockIdx.x] : e;
   const int64_t off = p.off[c];
   const int32_t* kept = p.kept + off;
@@ -498,15 +515,15 @@ hipError_t launch_compact_move(const CompactParams& p, int n_segs, hipStream_t s
   const dim3 grid(n_segs);
   switch (p.row_bytes / 16) {
     case 8:
-      compact_halo_kernel<8><<<grid, dim3(256), 0, s>>>(p);
+      compact_halo_kernel<8><<<grid, dim3(kMoveThreads), 0, s>>>(p);
       compact_move_kernel<8><<<grid, dim3(kMoveThreads), 0, s>>>(p);
       break;
     case 16:
-      compact_halo_kernel<16><<<grid, dim3(256), 0, s>>>(p);
+      compact_halo_kernel<16><<<grid, dim3(kMoveThreads), 0, s>>>(p);
       compact_move_kernel<16><<<grid, dim3(kMoveThreads), 0, s>>>(p);
       break;
     case 32:
-      compact_halo_kernel<32><<<grid, dim3(256), 0, s>>>(p);
+      compact_halo_kernel<32><<<grid, dim3(kMoveThreads), 0, s>>>(p);
       compact_move_kernel<32><<<grid, dim3(kMoveThreads), 0, s>>>(p);
       break;
     default: return hipErrorInvalidValue;

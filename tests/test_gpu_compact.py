@@ -178,6 +178,27 @@ def test_long_caches_move_in_several_segments(slack):
     arena.close()
 
 
+@pytest.mark.parametrize("layers,slack", [(1, 1), (1, 127), (1, 5000), (24, 200), (24, 6000)])
+def test_move_segments_of_every_length(layers, slack):
+    """The length of a move segment follows the size of the arena (128 rows for one layer here, 1024 for
+    24): budgets around multiples of it, evictions of fewer and of more rows than a segment has (the
+    halo slot is the smaller of the two), from random places and all from the front."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["llama32"], name="seglen", L=layers, Hq=6, Hkv=6, batch=1, seed=27, sink=4,
+                     recent=16, slack=slack)
+    rng = np.random.Generator(np.random.PCG64(w.seed + slack))
+    budgets = [127, 128, 129, 2047, 2049, 20001] * layers
+    arena = H.make_arena(w, budgets)
+    lens = [b + slack - (c % 3) * (slack // 3) for c, b in enumerate(budgets)]
+    st = H.fill_from_host(arena, w, lens, rng, scores="uniform")
+    for c in range(1, arena.n_caches, 2):
+        st.score[c][4:4 + slack] = 0.0          # evicted rows all at the front: every later row moves
+        o = int(arena.off_host[c])
+        arena.score[o:o + lens[c]].copy_(torch.from_numpy(st.score[c]).to(arena.device))
+    run_compact_and_check(arena, w, st)
+    arena.close()
+
+
 @pytest.mark.parametrize("policy", [B.POLICY_SCORE, B.POLICY_STREAMING])
 @pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed_zero"])
 def test_caches_selected_tile_by_tile(scores, policy):
