@@ -210,9 +210,9 @@ enum {
                                    record stay there until the next flush); 1: they resume.  Only a
                                    context created with track_scores can be switched to 1          */
   BAKLAVA_OPT_TILED_SELECT_ROWS = 8 /* eviction: caches whose capacity exceeds this many rows are ranked
-                                   by several workgroups (tiles of 8192 rows) instead of one.
-                                   >= 8192; default 36864, or 8192 for a context of fewer than 512
-                                   caches.  Synchronises like the CHUNK options                   */
+                                       by several workgroups (tiles of 8192 rows) instead of one.
+                                       >= 8192; default 65536, the most one workgroup ranks (larger
+                                       values act like it).  Synchronises like the CHUNK options    */
 };
 int baklava_set_option(baklava_ctx* ctx, int32_t option, int64_t value);
 

@@ -27,15 +27,6 @@ constexpr int kDefaultChunk = 512;        // launches over part of the model: sh
 constexpr int kDefaultChunkWhole = 256;   // launches over the whole model: shortest run; longer ones come from the item target
 constexpr int kWholeItemsPerCu = 5;       // whole-model launches aim at this many work items per compute unit
 constexpr int kMaxChunk = 1 << 22; // row offsets inside a work item stay below 2^32 bytes
-// Eviction: caches beyond this capacity are ranked by several workgroups.  One workgroup sweeps a cache
-// five times out of the L2 and is bound by latency (about 80 us for 32768 rows); with thousands of
-// caches in flight that latency is hidden and one workgroup per cache is the cheaper way up to about
-// that size (measured on the 2048 llama32 caches: 175 us one workgroup each, 240 us with a threshold
-// of 8192 rows), with a few caches (a prompt of one sequence: 8 caches of 32768 rows) it is not
-// (82 us against 47 us tile by tile).
-constexpr int kDefaultLongRows = 36864;
-constexpr int kFewCaches = 512;  // below this many caches every cache beyond one tile is ranked tile by tile
-
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 int64_t count_items(const int32_t* cap, int64_t n_caches, int chunk) {
@@ -170,6 +161,7 @@ struct baklava_ctx {
   std::vector<int32_t> order_all, order_layer;  // caches, longest first (whole model / inside each layer)
   std::vector<int32_t> seg_begin;               // cache -> first segment of the eviction move
   std::vector<int32_t> tile_begin;              // cache -> first tile of the tiled selection (long caches only have any)
+  std::vector<int32_t> n_wide;                  // layer -> caches with more than kHeldRows / 4 rows of capacity
   int32_t kernel_pref;
   bool layer_one_wave;   // default schedule of layer-range launches: one workgroup per compute unit
   int32_t target_items;  // > 0: layer-range launches lengthen their runs until a layer has at most this many items
@@ -532,7 +524,13 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
       return BAKLAVA_EHIP;
     }
   }
-  ctx->select_long_rows = n_caches < kFewCaches ? kMinLongRows : kDefaultLongRows;
+  // Eviction: a cache of up to kHeldRows rows is ranked by one workgroup that holds its scores in
+  // registers, a longer one tile by tile.  Measured, us per eviction, one workgroup against tiles: 8
+  // caches of 15000 rows 57 / 90, of 30000 87 / 103, of 60000 121 / 132; 256 caches 449 / 489, 862 / 914,
+  // 1716 / 1838.
+  ctx->select_long_rows = kHeldRows;
+  ctx->n_wide.assign(desc->L, 0);
+  for (int64_t c = 0; c < n_caches; ++c) ctx->n_wide[c / ctx->cpl] += ctx->cap[c] > kHeldRows / 4 ? 1 : 0;
   {
     const int st = build_tiles(ctx);
     if (st != BAKLAVA_OK) { delete ctx; return st; }
@@ -579,9 +577,9 @@ extern "C" int baklava_set_option(baklava_ctx* ctx, int32_t option, int64_t valu
       return BAKLAVA_OK;
     case BAKLAVA_OPT_TILED_SELECT_ROWS: {
       if (value < kMinLongRows || value > INT32_MAX) return BAKLAVA_EINVAL;
-      if ((int32_t)value == ctx->select_long_rows) return BAKLAVA_OK;
+      if (std::min<int64_t>(value, kHeldRows) == ctx->select_long_rows) return BAKLAVA_OK;
       const int32_t old = ctx->select_long_rows;
-      ctx->select_long_rows = (int32_t)value;
+      ctx->select_long_rows = (int32_t)std::min<int64_t>(value, kHeldRows);
       const int st = build_tiles(ctx);
       if (st != BAKLAVA_OK) ctx->select_long_rows = old;
       return st;
@@ -747,7 +745,8 @@ extern "C" int baklava_compact(baklava_ctx* ctx, int32_t layer_begin, int32_t la
   p.tile_hist = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.tile_hist);
   p.sel_state = reinterpret_cast<SelState*>(ctx->ws + ctx->plan.sel_state);
   p.long_rows = ctx->select_long_rows;
-  if (!hip_ok(launch_compact_select(p, (int)(c1 - c0), t1 - t0, s))) return BAKLAVA_EHIP;
+  const int n_wide = std::accumulate(ctx->n_wide.begin() + layer_begin, ctx->n_wide.begin() + layer_begin + layer_count, 0);
+  if (!hip_ok(launch_compact_select(p, (int)(c1 - c0), n_wide, whole || layer_count == 1, t1 - t0, s))) return BAKLAVA_EHIP;
   if (!hip_ok(launch_compact_move(p, s1 - s0, s))) return BAKLAVA_EHIP;
   for (int64_t c = c0; c < c1; ++c) {
     const int32_t b = ctx->budget[(c / ctx->cpl) * ctx->d.Hkv + c % ctx->d.Hkv];

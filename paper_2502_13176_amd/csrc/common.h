@@ -24,6 +24,7 @@ constexpr int kLagRows = 32;   // packed query rows of a cache's record of pendi
 constexpr int kLagCalls = 8;   // most calls such a record holds
 constexpr int kMoveSegMin = 128, kMoveSegMax = 4096;  // destination rows per workgroup of the eviction move
 constexpr int kTileRows = 8192;     // rows per tile of a cache that is ranked tile by tile (one workgroup per tile and pass)
+constexpr int kHeldRows = 65536;     // most rows of a cache that one workgroup ranks, in its registers
 constexpr int kMinLongRows = kTileRows;  // smallest capacity from which a cache may be ranked that way
 
 // One split-K work item (same layout as baklava_work_item of the public header): rows
@@ -202,7 +203,9 @@ hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t
 hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items, int max_count, hipStream_t s);
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s);
-hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_tiles, hipStream_t s);
+// n_wide: caches of the range with more than kHeldRows / 4 rows of capacity; sorted: they come first in p.order
+hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
+                                 hipStream_t s);
 hipError_t launch_compact_move(const CompactParams& p, int n_segs, hipStream_t s);
 hipError_t launch_stream_probe(void* dst, const void* src, int64_t bytes, int mode, hipStream_t s);
 

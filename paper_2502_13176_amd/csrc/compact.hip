@@ -1,7 +1,9 @@
 // Budget-enforcing eviction (f_evict, Eqs. 5-6): selection of the surviving rows (one workgroup
-// per cache, long caches first; caches beyond what one workgroup sweeps quickly are cut into tiles
+// per cache, long caches first; caches beyond what a workgroup's registers hold are cut into tiles
 // and go through one kernel per radix pass), then a stable in-place move (one workgroup per segment).
 #include "common.h"
+
+#include <algorithm>
 
 namespace baklava {
 
@@ -9,7 +11,6 @@ namespace {
 
 constexpr int kSelThreads = 512;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kSelUnroll = 8;  // score loads in flight per thread in the counting passes
 constexpr int kSelRows = 16;   // consecutive rows per thread in the emit pass (four 16-byte loads)
 constexpr int kEmitTile = kSelThreads * kSelRows;
 
@@ -190,56 +191,193 @@ __device__ __forceinline__ void emit_rows(const float* score, int32_t* kept, con
   }
 }
 
-// Selection for the caches one workgroup sweeps alone (capacity up to p.long_rows), long caches
-// first; longer caches are left to the tile kernels below.
-__global__ __launch_bounds__(kSelThreads) void compact_select_kernel(CompactParams p) {
+// ---- caches one workgroup ranks alone ----------------------------------------------------------
+// The middle of a cache of up to 1024 * KEYS rows is read once, into registers: row i * 1024 + t of the
+// middle is key i of thread t, every load in flight before the first use.  Three radix passes (11, 11
+// and 10 bits) count digits in LDS, and the stable emit takes its flags from the same registers: each
+// wavefront leaves its counts of surviving rows per block of 1024 rows, one workgroup scan turns them
+// into places, and a row's place inside its wavefront is a population count of the ballot below it.
+// Bound by vector issue (about 40 instructions per key on one compute unit) and the latency of a dozen
+// barriers, not by bandwidth.  Sweeping the scores once per pass (four passes of 8 bits and the emit, 512
+// threads) took 90 us for 512 caches of 128 to 32768 rows, this takes 53; tile by tile (below) 8 caches of
+// 32768 rows took 46 us in five kernels, here 36 in one.  KEYS = 16 (caches of up to 16384 rows) needs 54
+// registers, so two workgroups fit a compute unit; KEYS = 64 takes the register file for one.
+constexpr int kHeldThreads = 1024;
+constexpr int kHeldWaves = kHeldThreads / 64;
+constexpr int kHeldBins = 2048;
+
+// Inclusive prefix sum over the wavefront in six data-parallel-primitive adds: shifts inside the rows
+// of 16 lanes, then the last lane of a row to the next one, and lane 31 to the upper half.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Exclusive prefix sum of `v` over the workgroup of kHeldThreads; `sm` holds one word per wavefront and
+// is not read again after the barrier of the caller's next step.
+__device__ __forceinline__ int held_exclusive_scan(int v, int* sm) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int incl = wave_inclusive_scan(v);
+  if (lane == 63) sm[wave] = incl;
+  __syncthreads();
+  const int sums = wave_inclusive_scan(lane < kHeldWaves ? sm[lane] : 0);
+  const int before = __builtin_amdgcn_readlane(sums, max(wave, 1) - 1);
+  return (wave > 0 ? before : 0) + incl - v;
+}
+
+template <int KEYS>
+__global__ __launch_bounds__(kHeldThreads) void compact_select_kernel(CompactParams p, int cap_above, int cap_most) {
   const int c = p.order[blockIdx.x];
-  if (p.cap[c] > p.long_rows) return;
+  const int cap = p.cap[c];
+  if (cap <= cap_above || cap > cap_most) return;  // another launch's
   const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
   const SelGoal g = sel_goal(p, c);
   const int n = g.n;
   const int64_t off = p.off[c];
   int32_t* kept = p.kept + off;
-  const float* score = p.score + off;
 
   if (n <= g.b) {
     if (p.write_identity)
-      for (int j = tid; j < n; j += kSelThreads) kept[j] = j;
+      for (int j = tid; j < n; j += kHeldThreads) kept[j] = j;
     if (tid == 0) p.info[c] = CompactInfo{n, n, n, 0};
     return;
   }
 
-  __shared__ int hist[256];
-  __shared__ int sm_scan[kSelWaves];
-  __shared__ int sh_digit, sh_need, sh_first;
-  __shared__ uint32_t lds_key[kEmitKeyWords];
-
-  uint32_t thr = 0;
-  int need_eq = 0;
-  if (g.k > 0) {
-    // Radix select of the k-th largest key of the middle, 8 bits per pass, high digits first.
-    uint32_t prefix = 0, mask = 0;
-    int need = g.k;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      for (int i = tid; i < 256; i += kSelThreads) hist[i] = 0;
-      __syncthreads();
-      count_digits<kSelUnroll>(score, g.mid_lo, g.mid_hi, prefix, mask, shift, hist);
-      __syncthreads();
-      find_digit(hist, need, sm_scan, &sh_digit, &sh_need);
-      prefix |= (uint32_t)sh_digit << shift;
-      need = sh_need;
-      mask |= 0xffu << shift;
-      __syncthreads();
-    }
-    thr = prefix;
-    need_eq = need;  // rows whose key equals thr that still survive (oldest first)
+  // sink and recent rows: the first and the last places
+  for (int j = tid; j < g.mid_lo; j += kHeldThreads) kept[j] = j;
+  for (int j = g.mid_hi + tid; j < n; j += kHeldThreads) kept[j - (n - g.b)] = j;
+  if (g.k <= 0) {  // no middle row survives
+    if (tid == 0) p.info[c] = CompactInfo{g.b, g.mid_lo, n, 0};
+    return;
   }
 
-  if (tid == 0) sh_first = n;
+  __shared__ int hist[kHeldBins];
+  __shared__ int sm_scan[2 * kHeldWaves];
+  __shared__ int sh_digit, sh_need, sh_first;
+  __shared__ int sure_before[KEYS * kHeldWaves], eq_before[KEYS * kHeldWaves];
+
+  const int m = g.mid_hi - g.mid_lo;  // rows that compete, g.k < m of them survive
+  const float* score = p.score + off + g.mid_lo;
+  uint32_t key[KEYS];
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) key[i] = __float_as_uint(score[min(i * kHeldThreads + tid, m - 1)]);
+  hist[tid] = 0;
+  hist[tid + kHeldThreads] = 0;
+  if (tid == 0) sh_first = m;
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) {
+    // places past the middle hold key 0: no score but a NaN maps there, it ranks last, and it comes
+    // behind every row, so neither the threshold nor a survivor's place depends on these
+    const uint32_t x = score_key(__uint_as_float(key[i]));
+    key[i] = i * kHeldThreads + tid < m ? x : 0u;
+  }
   __syncthreads();
-  emit_rows(score, kept, g, thr, need_eq, 0, n, 0, 0, sm_scan, &sh_first, lds_key);
+
+  // Radix select of the k-th largest key.  64 lanes that meet on one counter would be served one after
+  // the other, so a wavefront whose keys all have the same digit (many equal scores) adds them up first.
+  uint32_t prefix = 0, mask = 0;
+  int need = g.k;
+#pragma unroll 1
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+    const uint32_t digits = pass == 2 ? 1023u : 2047u;
+#pragma unroll
+    for (int i = 0; i < KEYS; ++i) {
+      if (i * kHeldThreads < m) {
+        if ((key[i] & mask) == prefix) {
+          const int digit = (key[i] >> shift) & digits;
+          const uint64_t here = __ballot(true);
+          if (__ballot(digit == __builtin_amdgcn_readfirstlane(digit)) == here) {
+            if (__builtin_amdgcn_mbcnt_hi((uint32_t)(here >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)here, 0)) == 0)
+              atomicAdd(&hist[digit], __popcll(here));
+          } else {
+            atomicAdd(&hist[digit], 1);
+          }
+        }
+      }
+    }
+    __syncthreads();
+    // the digit of the need-th largest key: thread t looks at the digits 2047 - 2t and 2046 - 2t and
+    // leaves their counters cleared; exactly one digit has above < need <= above + its own count
+    const int d_hi = kHeldBins - 1 - 2 * tid;
+    const int c_hi = hist[d_hi], c_lo = hist[d_hi - 1];
+    hist[d_hi] = 0;
+    hist[d_hi - 1] = 0;
+    const int above = held_exclusive_scan(c_hi + c_lo, sm_scan);
+    if (above < need && above + c_hi >= need) {
+      sh_digit = d_hi;
+      sh_need = need - above;
+    } else if (above + c_hi < need && above + c_hi + c_lo >= need) {
+      sh_digit = d_hi - 1;
+      sh_need = need - above - c_hi;
+    }
+    __syncthreads();
+    prefix |= (uint32_t)sh_digit << shift;
+    need = sh_need;
+    mask |= digits << shift;
+  }
+  const uint32_t thr = prefix;
+  const int need_eq = need;  // rows whose key equals thr that still survive (oldest first)
+
+  // A row survives if its key exceeds the threshold, or if it is among the first need_eq rows whose key
+  // equals it; its place is (rows of the first kind before it) + min(rows with an equal key before it,
+  // need_eq).  Counts per (block of 1024 rows, wavefront) first: lane i collects its wavefront's counts
+  // of block i, the workgroup scans them in row order, and lane i gets block i's two places back.
+  static_assert(KEYS <= 64, "one lane per block");
+  int n_both = 0;
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) {
+    if (i * kHeldThreads < m) {
+      const int both = __popcll(__ballot(key[i] > thr)) | __popcll(__ballot(key[i] == thr)) << 16;
+      n_both = lane == i ? both : n_both;
+    }
+  }
+  if (lane < KEYS) {
+    sure_before[lane * kHeldWaves + wave] = n_both & 0xffff;
+    eq_before[lane * kHeldWaves + wave] = n_both >> 16;
+  }
   __syncthreads();
-  if (tid == 0) p.info[c] = CompactInfo{g.b, sh_first, n, 0};
+  int a = 0, e = 0;
+  if (tid < KEYS * kHeldWaves) { a = sure_before[tid]; e = eq_before[tid]; }
+  a = held_exclusive_scan(a, sm_scan);
+  e = held_exclusive_scan(e, sm_scan + kHeldWaves);
+  if (tid < KEYS * kHeldWaves) { sure_before[tid] = a; eq_before[tid] = e; }
+  __syncthreads();
+  int place_sure = 0, place_eq = 0;
+  if (lane < KEYS) {
+    place_sure = sure_before[lane * kHeldWaves + wave];
+    place_eq = eq_before[lane * kHeldWaves + wave];
+  }
+  int first_out = m;  // first row of this wavefront that does not survive
+  int32_t* out = kept + g.mid_lo;
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) {
+    if (i * kHeldThreads < m) {
+      const int r = i * kHeldThreads + tid;
+      const uint64_t ms = __ballot(key[i] > thr), me = __ballot(key[i] == thr);
+      const int eq0 = __builtin_amdgcn_readlane(place_eq, i);
+      int sb = __builtin_amdgcn_readlane(place_sure, i) + min(eq0, need_eq);
+      bool keep = key[i] > thr;
+      sb = __builtin_amdgcn_mbcnt_hi((uint32_t)(ms >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ms, sb));
+      if (me != 0 && eq0 < need_eq) {  // uniform over the wavefront
+        const int eb = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0));
+        sb += min(eb, need_eq - eq0);
+        keep = keep || (key[i] == thr && eq0 + eb < need_eq);
+      }
+      if (keep) out[sb] = g.mid_lo + r;
+      const uint64_t gone = __ballot(!keep);
+      if (gone != 0) first_out = min(first_out, i * kHeldThreads + wave * 64 + __ffsll((unsigned long long)gone) - 1);
+    }
+  }
+  if (lane == 0) atomicMin(&sh_first, first_out);
+  __syncthreads();
+  if (tid == 0) p.info[c] = CompactInfo{g.b, g.mid_lo + sh_first, n, 0};
 }
 
 // ---- caches too long for one workgroup -------------------------------------------------------
@@ -496,9 +634,21 @@ __global__ __launch_bounds__(kMoveThreads) void compact_move_kernel(CompactParam
 
 }  // namespace
 
-hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_tiles, hipStream_t s) {
+// The launch order holds the n_wide caches of more than kHeldRows / 4 rows first when `sorted`.
+hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
+                                 hipStream_t s) {
   if (n_caches <= 0) return hipSuccess;
-  compact_select_kernel<<<dim3(n_caches), dim3(kSelThreads), 0, s>>>(p);
+  constexpr int kNarrow = kHeldRows / 4;
+  const dim3 held(kHeldThreads);
+  if (n_wide > 0)
+    compact_select_kernel<kHeldRows / kHeldThreads>
+        <<<dim3(sorted ? n_wide : n_caches), held, 0, s>>>(p, kNarrow, p.long_rows);
+  if (n_wide < n_caches) {
+    CompactParams q = p;
+    if (sorted) q.order += n_wide;
+    compact_select_kernel<kNarrow / kHeldThreads>
+        <<<dim3(sorted ? n_caches - n_wide : n_caches), held, 0, s>>>(q, -1, std::min(kNarrow, p.long_rows));
+  }
   if (n_tiles > 0) {
     const dim3 grid(n_tiles), block(kSelThreads);
     compact_tile_count_kernel<0><<<grid, block, 0, s>>>(p);

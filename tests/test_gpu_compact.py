@@ -199,6 +199,39 @@ def test_move_segments_of_every_length(layers, slack):
     arena.close()
 
 
+@pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed", "infinite"])
+def test_caches_ranked_in_registers(scores):
+    """One workgroup ranks a cache of up to 65536 rows from its registers (blocks of 1024 rows, a narrow
+    kernel up to 16384 rows of capacity, tiles beyond 65536): middles of one row less, exactly and one
+    row more than a block, capacities on both sides of the two limits, one and all but one middle row to
+    keep, ties that span wavefronts and blocks, scores of the type's extremes."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="held", L=1, Hq=12, Hkv=12, batch=1, seed=28, sink=3,
+                     recent=5, slack=1100)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    budgets = [9, 63, 1030, 1031, 1032, 2055, 15284, 15285, 40000, 64436, 64437, 8]
+    arena = H.make_arena(w, budgets)
+    lens = [10, 72, 1031 + 8, 1033, 1032 + 1024, 2055 + 1, 16384, 16385, 41100, 65536, 65537, 1108]
+    st = H.fill_from_host(arena, w, lens, rng, scores="uniform")
+    for c, n in enumerate(lens):
+        if scores == "equal":
+            s = np.full(n, -0.5, dtype=np.float32)
+        elif scores == "coarse":
+            s = (rng.integers(0, 3, n) / 2).astype(np.float32)
+        elif scores == "signed":
+            s = (rng.standard_normal(n) * np.exp(rng.standard_normal(n) * 8)).astype(np.float32)
+        elif scores == "infinite":
+            big = np.finfo(np.float32).max
+            s = rng.choice(np.array([-np.inf, -big, -0.0, 0.0, 1e-45, big, np.inf], dtype=np.float32), n)
+        else:
+            continue
+        o = int(arena.off_host[c])
+        arena.score[o:o + n].copy_(torch.from_numpy(s).to(arena.device))
+        st.score[c] = s
+    run_compact_and_check(arena, w, st)
+    arena.close()
+
+
 @pytest.mark.parametrize("policy", [B.POLICY_SCORE, B.POLICY_STREAMING])
 @pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed_zero"])
 def test_caches_selected_tile_by_tile(scores, policy):
