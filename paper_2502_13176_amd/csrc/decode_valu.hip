@@ -1,13 +1,15 @@
 // Decode attention over ragged caches, vector-ALU version, plus the kernels every decode call
 // shares: split combine, score update, append, fill.
 //
-// Each work item (a run of rows of one cache) is one workgroup of four wavefronts.  A 256-byte
-// row is spread over 16 lanes as 16-byte pieces, so one wavefront load instruction fetches four
-// whole rows, fully coalesced.  Each lane group keeps its own running (max, sum, output) for
-// every query head of the group (online softmax, Eq. 1 re-associated) and the groups are merged
-// once at the end: no barrier and no cross-group traffic inside the streaming loop.
+// Each work item (a run of rows of one cache) is one workgroup.  A 256-byte row is spread over 16
+// lanes as 16-byte pieces, so one wavefront load instruction fetches four whole rows, fully
+// coalesced.  Each lane group keeps its own running (max, sum, output) for every query head of the
+// group (online softmax, Eq. 1 re-associated) and the groups are merged once at the end: no barrier
+// and no cross-group traffic inside the streaming loop.
 #include "common.h"
 #include "decode_tail.h"
+
+#include <type_traits>
 
 namespace baklava {
 
@@ -48,14 +50,43 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float* acc, int 
   m = mn;
 }
 
+// Sum over aligned groups of LPR lanes (8, 16 or 32), every lane of a group receiving it: the pairs of
+// a butterfly over lane distances 1, 2, 4, 8, 16, taken with data-parallel-primitive operands instead
+// of trips through the LDS crossbar (after the first two steps a quad holds equal values, so mirroring
+// a row pairs the same sums as exchanging its halves).
+template <int LPR>
+__device__ __forceinline__ float group_sum(float v) {
+  auto dpp = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v += dpp(v, std::integral_constant<int, 0xb1>{});   // quad_perm:[1,0,3,2]
+  v += dpp(v, std::integral_constant<int, 0x4e>{});   // quad_perm:[2,3,0,1]
+  v += dpp(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+  if (LPR >= 16) v += dpp(v, std::integral_constant<int, 0x140>{});  // row_mirror
+  if (LPR >= 32) v += __shfl_xor(v, 16);
+  return v;
+}
+
+// Wavefronts per workgroup.  One workgroup per compute unit is what a layer's launch has, so its
+// wavefronts alone must keep enough loads in flight (8 KB each, and the next 8 KB during the
+// arithmetic).  Four wavefronts without the tile ahead, with lane sums through the LDS crossbar and a
+// rescale on every tile, read the 67 MB of 32 fp32 caches (D = 64, two query heads each) in 32 us; this
+// takes 14.  16 where the accumulators leave 128 registers, 8 otherwise; up to four query heads the
+// loads bound it, at eight the vector ALUs do.
+template <int REGS> constexpr int valu_waves() { return REGS <= 16 ? 16 : 8; }
+
+// A logit may exceed the running reference by this much (log2 units) before the reference moves:
+// weights stay below 2^8 and the rescale of the accumulators is rare after the first rows.
+constexpr float kMaxSlack = 8.f;
+
 template <typename T, int D, int GT>
-__global__ __launch_bounds__(256) void decode_partial_valu(DecodeParams p) {
+__global__ __launch_bounds__((64 * valu_waves<GT * Row<T>::EPL>())) void decode_partial_valu(DecodeParams p) {
   constexpr int EPL = Row<T>::EPL;
   constexpr int LPR = D / EPL;   // lanes per row
   constexpr int RPW = 64 / LPR;  // rows per wavefront load
   constexpr int U = 4;           // rows in flight per lane
   constexpr int TILE = RPW * U;
-  constexpr int NW = 4;
+  constexpr int NW = valu_waves<GT * EPL>();
 
   const Item it = p.items[blockIdx.x];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -76,6 +107,20 @@ __global__ __launch_bounds__(256) void decode_partial_valu(DecodeParams p) {
   const int64_t row0 = off_c + it.start;
   const T* Kb = reinterpret_cast<const T*>(p.k) + row0 * D + sub * EPL;
   const T* Vb = reinterpret_cast<const T*>(p.v) + row0 * D + sub * EPL;
+
+  // Rows are clamped to the item's last live one; read once per step: non-temporal, so that the
+  // stream does not displace other cached data.
+  uint4 kraw[U], vraw[U];
+  auto load_tile = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = min(t0 + u * RPW + rg, cnt - 1);
+      kraw[u] = load_nt16(Kb + (int64_t)r * D);
+      vraw[u] = load_nt16(Vb + (int64_t)r * D);
+    }
+  };
+  int t0 = wave * TILE;
+  if (t0 < cnt) load_tile(t0);
 
   const int c_rel = it.c - p.cache_begin;
   const int64_t qrow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
@@ -102,20 +147,16 @@ __global__ __launch_bounds__(256) void decode_partial_valu(DecodeParams p) {
     for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
   }
 
-  for (int t0 = wave * TILE; t0 < cnt; t0 += NW * TILE) {
-    uint4 kraw[U], vraw[U];
+  for (; t0 < cnt; t0 += NW * TILE) {
+    uint4 kc[U], vc[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = min(t0 + u * RPW + rg, cnt - 1);  // clamped: always a live row of this item
-      // read once per step: non-temporal, so that the stream does not displace other cached data
-      kraw[u] = load_nt16(Kb + (int64_t)r * D);
-      vraw[u] = load_nt16(Vb + (int64_t)r * D);
-    }
+    for (int u = 0; u < U; ++u) { kc[u] = kraw[u]; vc[u] = vraw[u]; }
+    if (t0 + NW * TILE < cnt) load_tile(t0 + NW * TILE);  // the next tile is on its way during this one's arithmetic
     float s[U][GT];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float kf[EPL];
-      Row<T>::widen(kraw[u], kf);
+      Row<T>::widen(kc[u], kf);
       const int r = t0 + u * RPW + rg;
       const bool live = r < cnt;
 #pragma unroll
@@ -123,30 +164,40 @@ __global__ __launch_bounds__(256) void decode_partial_valu(DecodeParams p) {
         float d = 0.f;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) d = fmaf(qr[g][e], kf[e], d);
-#pragma unroll
-        for (int o = LPR / 2; o > 0; o >>= 1) d += __shfl_xor(d, o);
+        d = group_sum<LPR>(d);
         s[u][g] = live ? d : kNegInf;
+      }
+    }
+    float mx[GT];
+    bool moves = false;
+#pragma unroll
+    for (int g = 0; g < GT; ++g) {
+      mx[g] = s[0][g];
+#pragma unroll
+      for (int u = 1; u < U; ++u) mx[g] = fmaxf(mx[g], s[u][g]);
+      moves = moves || mx[g] > m[g] + kMaxSlack;
+    }
+    if (__any(moves)) {
+#pragma unroll
+      for (int g = 0; g < GT; ++g) {
+        const float mn = fmaxf(m[g], mx[g]);
+        const float alpha = fast_exp2(m[g] - ((mn == kNegInf) ? 0.f : mn));
+        m[g] = mn;
+        l[g] *= alpha;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[g][e] *= alpha;
       }
     }
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
-      float mx = s[0][g];
-#pragma unroll
-      for (int u = 1; u < U; ++u) mx = fmaxf(mx, s[u][g]);
-      const float mn = fmaxf(m[g], mx);
-      const float ms = (mn == kNegInf) ? 0.f : mn;
-      const float alpha = fast_exp2(m[g] - ms);
-      m[g] = mn;
-      l[g] *= alpha;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[g][e] *= alpha;
+      const float ms = (m[g] == kNegInf) ? 0.f : m[g];
 #pragma unroll
       for (int u = 0; u < U; ++u) s[u][g] = fast_exp2(s[u][g] - ms);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float vf[EPL];
-      Row<T>::widen(vraw[u], vf);
+      Row<T>::widen(vc[u], vf);
 #pragma unroll
       for (int g = 0; g < GT; ++g) {
         l[g] += s[u][g];
@@ -169,7 +220,7 @@ __global__ __launch_bounds__(256) void decode_partial_valu(DecodeParams p) {
     }
   }
 
-  // Hand the four wavefronts' results over through LDS.
+  // Hand the wavefronts' results over through LDS.
   __shared__ float sm[NW * GT * D + 2 * NW * GT];
   float* sm_o = sm;                  // [NW][GT][D]
   float* sm_m = sm + NW * GT * D;    // [NW][GT]
@@ -183,7 +234,7 @@ __global__ __launch_bounds__(256) void decode_partial_valu(DecodeParams p) {
     }
   }
   __syncthreads();
-  finish_item<D, GT>(p, it, G, n, sm_o, sm_m, sm_l);
+  finish_item<D, GT, NW>(p, it, G, n, sm_o, sm_m, sm_l);
 }
 
 // Merge of the split partials of one (cache, query head):
@@ -268,13 +319,18 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeParams p) {
 // call are final: the vector-ALU path's score update, launched right after its attention call.
 // Workgroup (x, y) updates rows [y * kScoreTile, +kScoreTile) of work item x, so that long work
 // items still spread over many workgroups.  Row layout as in the attention kernel above: a row
-// over D / EPL lanes, 64 / (D / EPL) rows per wavefront load.
-constexpr int kScoreTile = 1024;
+// over D / EPL lanes, 64 / (D / EPL) rows per wavefront load; a wavefront keeps eight of them in
+// flight, and lane u of a row's lanes adds the weight of the u-th one, so that the scores of a tile
+// are read and written by one instruction each.  One load in flight per wavefront and 1024 rows per
+// workgroup took 35 us for 33 MB of K, this takes 8.
+constexpr int kScoreTile = 256;
 template <typename T, int D, int GT>
 __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
   constexpr int EPL = Row<T>::EPL;
   constexpr int LPR = D / EPL;
   constexpr int RPW = 64 / LPR;
+  constexpr int U = 8;
+  static_assert(U <= LPR, "one lane of a row per row in flight");
   const Item it = p.items[blockIdx.x];
   const int G = p.G;
   const int cnt = min(it.start + it.count, p.len[it.c]) - it.start;
@@ -283,6 +339,14 @@ __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
   const int r_end = min(cnt, r_begin + kScoreTile);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPR, rg = lane / LPR;
+  const T* Kb = reinterpret_cast<const T*>(p.k) + it.row0 * D + sub * EPL;
+  uint4 kraw[U];
+  auto load_tile = [&](int r0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) kraw[u] = load_nt16(Kb + (int64_t)min(r0 + u * RPW + rg, r_end - 1) * D);
+  };
+  int r0 = r_begin + wave * (U * RPW);
+  if (r0 < r_end) load_tile(r0);
   const int c_rel = it.c - p.cache_begin;
   const T* qrows = reinterpret_cast<const T*>(p.q) +
                    ((int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G) * D;
@@ -301,23 +365,28 @@ __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
       inv[g] = p.ml[((int64_t)it.c * G + g) * 2 + 1];
     }
   }
-  const T* Kb = reinterpret_cast<const T*>(p.k) + it.row0 * D + sub * EPL;
   float* sc = p.score + it.row0;
-  for (int r0 = r_begin + wave * RPW; r0 < r_end; r0 += 4 * RPW) {
-    const int r = r0 + rg;
-    float kf[EPL];
-    Row<T>::widen(load_nt16(Kb + (int64_t)min(r, r_end - 1) * D), kf);
-    float w = 0.f;
+  for (; r0 < r_end; r0 += 4 * U * RPW) {
+    const int r = r0 + sub * RPW + rg;  // the row whose score this lane updates (sub < U)
+    const bool mine = sub < U && r < r_end;
+    const float old = mine ? sc[r] : 0.f;
+    float w_mine = 0.f;
 #pragma unroll
-    for (int g = 0; g < GT; ++g) {
-      float d = 0.f;
+    for (int u = 0; u < U; ++u) {
+      float kf[EPL];
+      Row<T>::widen(kraw[u], kf);
+      float w = 0.f;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) d = fmaf(qr[g][e], kf[e], d);
+      for (int g = 0; g < GT; ++g) {
+        float d = 0.f;
 #pragma unroll
-      for (int o = LPR / 2; o > 0; o >>= 1) d += __shfl_xor(d, o);
-      w += fast_exp2(d - M[g]) * inv[g];  // heads beyond G: 2^0 * 0
+        for (int e = 0; e < EPL; ++e) d = fmaf(qr[g][e], kf[e], d);
+        w += fast_exp2(group_sum<LPR>(d) - M[g]) * inv[g];  // heads beyond G: 2^0 * 0
+      }
+      w_mine = sub == u ? w : w_mine;
     }
-    if (r < r_end && sub == 0) sc[r] += w;
+    if (r0 + 4 * U * RPW < r_end) load_tile(r0 + 4 * U * RPW);
+    if (mine) sc[r] = old + w_mine;
   }
 }
 
@@ -349,12 +418,17 @@ __global__ void fill_i32_kernel(int32_t* dst, int32_t value, int64_t n) {
   if (i < n) dst[i] = value;
 }
 
+template <typename T, int D, int GT>
+void launch_valu(const DecodeParams& p, int n_items, hipStream_t s) {
+  decode_partial_valu<T, D, GT><<<dim3(n_items), dim3(64 * valu_waves<GT * Row<T>::EPL>()), 0, s>>>(p);
+}
+
 template <typename T, int D>
 hipError_t launch_valu_g(const DecodeParams& p, int n_items, hipStream_t s) {
-  const dim3 grid(n_items), block(256);
-  if (p.G <= 2) decode_partial_valu<T, D, 2><<<grid, block, 0, s>>>(p);
-  else if (p.G <= 4) decode_partial_valu<T, D, 4><<<grid, block, 0, s>>>(p);
-  else if (p.G <= 8) decode_partial_valu<T, D, 8><<<grid, block, 0, s>>>(p);
+  if (p.G <= 1) launch_valu<T, D, 1>(p, n_items, s);
+  else if (p.G <= 2) launch_valu<T, D, 2>(p, n_items, s);
+  else if (p.G <= 4) launch_valu<T, D, 4>(p, n_items, s);
+  else if (p.G <= 8) launch_valu<T, D, 8>(p, n_items, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -381,7 +455,8 @@ hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t
 
 template <typename T, int D>
 hipError_t launch_score_g(const ScoreParams& p, const dim3& grid, hipStream_t s) {
-  if (p.G <= 4) score_pass_kernel<T, D, 4><<<grid, dim3(256), 0, s>>>(p);
+  if (p.G <= 2) score_pass_kernel<T, D, 2><<<grid, dim3(256), 0, s>>>(p);
+  else if (p.G <= 4) score_pass_kernel<T, D, 4><<<grid, dim3(256), 0, s>>>(p);
   else if (p.G <= 8) score_pass_kernel<T, D, 8><<<grid, dim3(256), 0, s>>>(p);
   else return hipErrorInvalidValue;
   return hipGetLastError();

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import baklava_oracle as O
 from paper_2502_13176_amd import binding as B
 from paper_2502_13176_amd import synth
 
@@ -288,4 +289,37 @@ def test_kernel_timing_record(kernel, mode):
     H.check_decode_against_oracle(arena, w, st, q64, ref)
     with pytest.raises(B.BaklavaError):
         arena.set_option(B.OPT_TIME_KERNEL, 3)
+    arena.close()
+
+
+@pytest.mark.parametrize("dtype,D,G", [("f32", 64, 1), ("f32", 64, 4), ("f32", 128, 3), ("f32", 128, 8), ("bf16", 64, 1),
+                                       ("bf16", 64, 5), ("bf16", 64, 8), ("bf16", 128, 1)])
+def test_vector_kernel_tiles_and_rising_logits(dtype, D, G):
+    """The vector kernel's workgroups of 16 and of 8 wavefronts: lengths around a wavefront's and a
+    workgroup's tile, with logits that climb along the cache by less and by more than the reference
+    maximum may lag (8 in log2 units), and the scores its second pass adds."""
+    H = _h()
+    lens = [1, 15, 17, 32, 33, 127, 128, 129, 255, 257, 511, 512, 513, 1025]
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="valu", L=1, Hq=G * len(lens), Hkv=len(lens), D=D, batch=1,
+                     dtype=dtype, seed=91, sink=1, recent=1, slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed + G))
+    arena = H.make_arena(w, [2048] * len(lens), track=True)
+    arena.set_option(B.OPT_KERNEL, B.KERNEL_VALU)
+    q, q64 = H.make_q(w, rng, w.L)
+    for step in (0.0, 0.02, 40.0):                 # natural units of the logit per row
+        st = H.fill_from_host(arena, w, lens, rng)
+        for c, n in enumerate(lens):
+            # a component along the group's first query row that grows with the row
+            u = q64[0, 0, c * G] / np.dot(q64[0, 0, c * G], q64[0, 0, c * G]) * np.sqrt(D)
+            x = synth.storage_to_f64(st.K[c], dtype) + (step * np.minimum(np.arange(n), 30 if step > 1 else n))[:, None] * u
+            st.K[c] = x.astype(np.float32) if dtype == "f32" else synth.f32_to_bf16_bits(x.astype(np.float32))
+            o = int(arena.off_host[c])
+            arena.k[o:o + n].copy_(H.to_device_storage(st.K[c], dtype, arena.device))
+        H.check_decode_against_oracle(arena, w, st, q64, H.gpu_decode(arena, w, q))
+        post = H.download(arena, w)
+        for c, n in enumerate(lens):
+            l, b, hs = H.q_rows_of_cache(w, c)
+            _, p = O.decode_attn(q64[l, b, hs], synth.storage_to_f64(st.K[c], dtype), synth.storage_to_f64(st.V[c], dtype))
+            # fp32 logits of up to ~1200 in log2 units carry an absolute error of about 1e-4, so do the weights
+            assert np.max(np.abs(post.score[c] - p.sum(0))) <= 2e-3, (step, n)
     arena.close()
