@@ -70,6 +70,32 @@ def test_prompt_lengths_around_every_tile_boundary(T):
     print(f"T={T}: worst relative score error {worst:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("T", [1, 63, 65, 255, 256, 257, 511, 513])
+def test_many_sequences_take_two_tiles_per_wavefront(T):
+    """512 sequences: each workgroup takes 256 keys.  Every eighth sequence against the oracle, the others
+    by their mass (each attention row sums to 1) and against the kernel's narrow form on a part of them."""
+    H = _h()
+    dev = torch.device("cuda:0")
+    batch, Hkv, Hq = 64, 8, 16
+    rng = np.random.Generator(np.random.PCG64(9900 + T))
+    qb, kb, vb = (synth.payload(rng, (batch, h, T, 128), "bf16") for h in (Hq, Hkv, Hkv))
+    q, k, v = (H.to_device_storage(x, "bf16", dev) for x in (qb, kb, vb))
+    _, _, lse = B.profile_similarity(q, k, v, want_cos=False, want_lse=True)
+    score = torch.full((batch * Hkv * T,), float("nan"), dtype=torch.float32, device=dev)
+    B.prefill_scores(q, k, lse, score, batch, Hq, Hkv, T)
+    few = torch.full((2 * Hkv * T,), float("nan"), dtype=torch.float32, device=dev)
+    B.prefill_scores(q[:2], k[:2], lse[:2], few, 2, Hq, Hkv, T)
+    torch.cuda.synchronize()
+    got = score.cpu().numpy().astype(np.float64).reshape(batch, Hkv, T)
+    assert np.max(np.abs(got[:2].reshape(-1) - few.cpu().numpy())) <= SCORE_RTOL * max(1.0, got[:2].max())
+    assert np.max(np.abs(got.sum(2) - 2 * T)) <= 1e-4 * 2 * T
+    for b in range(0, batch, 8):
+        q64, k64 = synth.storage_to_f64(qb[b], "bf16"), synth.storage_to_f64(kb[b], "bf16")
+        h = (b // 8) % Hkv
+        want = O.prefill_scores(q64[2 * h:2 * h + 2], k64[h])
+        assert np.max(np.abs(got[b, h] - want) / np.maximum(1.0, want)) <= SCORE_RTOL
+
+
 @pytest.mark.parametrize("batch,Hq,Hkv", [(2, 8, 2), (1, 7, 1), (3, 2, 2), (1, 16, 1)])
 def test_head_grouping_and_batches(batch, Hq, Hkv):
     run_dense(batch, Hq, Hkv, 300, 9700 + Hq)
