@@ -380,7 +380,7 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
                                             sc.max_count.begin() + layer_begin + layer_count);
   hipError_t e = use_mfma ? launch_decode_mfma(p, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s,
                                                on_dispatch ? ev0 : nullptr, on_dispatch ? ev1 : nullptr)
-                          : launch_decode_valu(p, ctx->d.dtype, ctx->d.D, i1 - i0, s);
+                          : launch_decode_valu(p, ctx->d.dtype, ctx->d.D, i1 - i0, i1 - i0 <= ctx->n_cus, s);
   if (!hip_ok(e)) return BAKLAVA_EHIP;
   if (ctx->time_kernel) {
     if (!on_dispatch && !hip_ok(hipEventRecord(ev1, s))) return BAKLAVA_EHIP;

@@ -182,7 +182,8 @@ struct CompactParams {
 void note_hip_error(hipError_t e);
 
 // Launchers (defined next to their kernels).  All return hipError_t of the launch.
-hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, hipStream_t s);
+// one_wave: the launch has at most one workgroup per compute unit
+hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, bool one_wave, hipStream_t s);
 // max_count: longest work item of the launch (rows); one_wave: the launch has at most one workgroup per
 // compute unit, so a workgroup may take the whole LDS (score tracking keeps its new scores there)
 hipError_t launch_decode_mfma(const DecodeParams& p, int n_items, int max_count, bool one_wave, hipStream_t s,

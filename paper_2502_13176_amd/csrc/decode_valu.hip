@@ -67,26 +67,28 @@ __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
-// Wavefronts per workgroup.  One workgroup per compute unit is what a layer's launch has, so its
-// wavefronts alone must keep enough loads in flight (8 KB each, and the next 8 KB during the
-// arithmetic).  Four wavefronts without the tile ahead, with lane sums through the LDS crossbar and a
-// rescale on every tile, read the 67 MB of 32 fp32 caches (D = 64, two query heads each) in 32 us; this
-// takes 14.  16 where the accumulators leave 128 registers, 8 otherwise; up to four query heads the
-// loads bound it, at eight the vector ALUs do.
-template <int REGS> constexpr int valu_waves() { return REGS <= 16 ? 16 : 8; }
+// Wavefronts per workgroup of a launch that has at most one workgroup per compute unit: they alone must
+// keep enough loads in flight (8 KB each, and the next 8 KB during the arithmetic).  Four wavefronts
+// without the tile ahead, with lane sums through the LDS crossbar and a rescale on every tile, read the
+// 67 MB of 32 fp32 caches (D = 64, two query heads each) in 32 us; this takes 14.  16 where the
+// accumulators leave 128 registers, 8 otherwise; up to four query heads the loads bound it, at eight the
+// vector ALUs do.  With several workgroups per compute unit those fill it, and items are as short as 256
+// rows, one tile for each of eight wavefronts, so the merge at the end weighs more: four wavefronts then
+// (88 bf16 caches of 2500 rows per launch, D = 64, four query heads, eight steps of three layers and an
+// eviction: 639 us, with eight 1024, as it was before 894).
+template <int REGS> constexpr int wide_waves() { return REGS <= 16 ? 16 : 8; }
 
 // A logit may exceed the running reference by this much (log2 units) before the reference moves:
 // weights stay below 2^8 and the rescale of the accumulators is rare after the first rows.
 constexpr float kMaxSlack = 8.f;
 
-template <typename T, int D, int GT>
-__global__ __launch_bounds__((64 * valu_waves<GT * Row<T>::EPL>())) void decode_partial_valu(DecodeParams p) {
+template <typename T, int D, int GT, int NW>
+__global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
   constexpr int EPL = Row<T>::EPL;
   constexpr int LPR = D / EPL;   // lanes per row
   constexpr int RPW = 64 / LPR;  // rows per wavefront load
   constexpr int U = 4;           // rows in flight per lane
   constexpr int TILE = RPW * U;
-  constexpr int NW = valu_waves<GT * EPL>();
 
   const Item it = p.items[blockIdx.x];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -419,28 +421,30 @@ __global__ void fill_i32_kernel(int32_t* dst, int32_t value, int64_t n) {
 }
 
 template <typename T, int D, int GT>
-void launch_valu(const DecodeParams& p, int n_items, hipStream_t s) {
-  decode_partial_valu<T, D, GT><<<dim3(n_items), dim3(64 * valu_waves<GT * Row<T>::EPL>()), 0, s>>>(p);
+void launch_valu(const DecodeParams& p, int n_items, bool one_wave, hipStream_t s) {
+  constexpr int NW = wide_waves<GT * Row<T>::EPL>();
+  if (one_wave) decode_partial_valu<T, D, GT, NW><<<dim3(n_items), dim3(64 * NW), 0, s>>>(p);
+  else decode_partial_valu<T, D, GT, 4><<<dim3(n_items), dim3(256), 0, s>>>(p);
 }
 
 template <typename T, int D>
-hipError_t launch_valu_g(const DecodeParams& p, int n_items, hipStream_t s) {
-  if (p.G <= 1) launch_valu<T, D, 1>(p, n_items, s);
-  else if (p.G <= 2) launch_valu<T, D, 2>(p, n_items, s);
-  else if (p.G <= 4) launch_valu<T, D, 4>(p, n_items, s);
-  else if (p.G <= 8) launch_valu<T, D, 8>(p, n_items, s);
+hipError_t launch_valu_g(const DecodeParams& p, int n_items, bool one_wave, hipStream_t s) {
+  if (p.G <= 1) launch_valu<T, D, 1>(p, n_items, one_wave, s);
+  else if (p.G <= 2) launch_valu<T, D, 2>(p, n_items, one_wave, s);
+  else if (p.G <= 4) launch_valu<T, D, 4>(p, n_items, one_wave, s);
+  else if (p.G <= 8) launch_valu<T, D, 8>(p, n_items, one_wave, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, hipStream_t s) {
+hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, bool one_wave, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  if (dtype == 0 && D == 128) return launch_valu_g<uint16_t, 128>(p, n_items, s);
-  if (dtype == 0 && D == 64) return launch_valu_g<uint16_t, 64>(p, n_items, s);
-  if (dtype == 1 && D == 128) return launch_valu_g<float, 128>(p, n_items, s);
-  if (dtype == 1 && D == 64) return launch_valu_g<float, 64>(p, n_items, s);
+  if (dtype == 0 && D == 128) return launch_valu_g<uint16_t, 128>(p, n_items, one_wave, s);
+  if (dtype == 0 && D == 64) return launch_valu_g<uint16_t, 64>(p, n_items, one_wave, s);
+  if (dtype == 1 && D == 128) return launch_valu_g<float, 128>(p, n_items, one_wave, s);
+  if (dtype == 1 && D == 64) return launch_valu_g<float, 64>(p, n_items, one_wave, s);
   return hipErrorInvalidValue;
 }
 
