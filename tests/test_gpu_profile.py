@@ -62,6 +62,35 @@ def test_prompt_lengths_around_every_tile_boundary(T):
     print(f"T={T}: worst per-token error {wc:.2e}, worst mean error {wm:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("T,batch,Hq,Hkv", [(191, 1, 2, 1), (192, 3, 2, 2), (193, 1, 3, 3), (255, 1, 2, 1), (256, 2, 4, 2),
+                                            (383, 1, 2, 1), (385, 3, 3, 1), (513, 1, 2, 2), (1025, 1, 2, 1)])
+def test_pipelined_and_diagonal_tiles(T, batch, Hq, Hkv):
+    """Prompts whose last workgroup has one or two tiles on the diagonal, a tile that ends with the prompt
+    and one that does not, with none, two and more tiles in the pipeline before them, and numbers of KV
+    heads that do not divide the number of XCDs."""
+    rng = np.random.Generator(np.random.PCG64(9200 + T))
+    q = synth.payload(rng, (batch, Hq, T, 128), "bf16")
+    k = synth.payload(rng, (batch, Hkv, T, 128), "bf16", peaked=True)
+    v = synth.payload(rng, (batch, Hkv, T, 128), "bf16")
+    run_case(q, k, v)
+
+
+@pytest.mark.parametrize("T", [255, 257, 511])
+def test_many_workgroups_give_the_same_bits(T):
+    """Thousands of workgroups side by side, several times over: a tile that is overwritten before every
+    wavefront has read it would show as a difference between the calls."""
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(T)
+    q, k, v = (torch.randn((64, h, T, 128), generator=g, device="cuda:0").to(torch.bfloat16) for h in (16, 8, 8))
+    sim, cos, lse = B.profile_similarity(q, k, v, want_lse=True)
+    for _ in range(8):
+        sim2, cos2, lse2 = B.profile_similarity(q, k, v, want_lse=True)
+        assert torch.equal(sim, sim2) and torch.equal(cos, cos2) and torch.equal(lse, lse2)
+    for b in (0, 33, 63):
+        few = B.profile_similarity(q[b:b + 1].contiguous(), k[b:b + 1].contiguous(), v[b:b + 1].contiguous(), want_lse=True)
+        assert torch.equal(few[0][0], sim[b]) and torch.equal(few[1][0], cos[b]) and torch.equal(few[2][0], lse[b])
+
+
 @pytest.mark.parametrize("batch,Hq,Hkv", [(2, 8, 2), (1, 7, 1), (3, 2, 2), (1, 16, 1)])
 def test_head_grouping_and_batches(batch, Hq, Hkv):
     rng = np.random.Generator(np.random.PCG64(9100 + Hq))
