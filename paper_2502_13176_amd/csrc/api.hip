@@ -259,9 +259,9 @@ bool range_ok(const baklava_ctx* ctx, int32_t lb, int32_t lc) {
 
 // The weights of the calls on record go to the score plane now (see DecodeParams): a pass over the
 // K rows of the layer range, after which the records are empty.  Only the MFMA attention kernel
-// (bf16, D = 128) leaves calls on record.
+// (bf16) leaves calls on record.
 int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hipStream_t s) {
-  if (!ctx->d.track_scores || !(ctx->d.dtype == BAKLAVA_BF16 && ctx->d.D == 128)) return BAKLAVA_OK;
+  if (!ctx->d.track_scores || ctx->d.dtype != BAKLAVA_BF16) return BAKLAVA_OK;
   const int64_t c0 = (int64_t)layer_begin * ctx->cpl;
   const int64_t c1 = c0 + (int64_t)layer_count * ctx->cpl;
   const int which = (layer_begin == 0 && layer_count == ctx->d.L) ? 1 : 0;
@@ -278,7 +278,7 @@ int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hi
   p.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)ctx->d.D));
   const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
                                             sc.max_count.begin() + layer_begin + layer_count);
-  if (!hip_ok(launch_score_flush_mfma(p, i1 - i0, longest, s))) return BAKLAVA_EHIP;
+  if (!hip_ok(launch_score_flush_mfma(p, ctx->d.D, i1 - i0, longest, s))) return BAKLAVA_EHIP;
   if (!hip_ok(launch_fill_i32(p.lag_cnt + c0 * ctx->G, 0, (c1 - c0) * ctx->G, s))) return BAKLAVA_EHIP;
   return BAKLAVA_OK;
 }
@@ -324,8 +324,7 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   const baklava_ctx::Schedule& sc = ctx->sched[which];
   const int32_t i0 = sc.cib[c0], i1 = sc.cib[c1];
   hipStream_t s = (hipStream_t)stream;
-  const bool mfma_able = ctx->d.dtype == BAKLAVA_BF16 && ctx->d.D == 128;
-  const bool use_mfma = ctx->kernel_pref == 2 || (ctx->kernel_pref == 0 && mfma_able);
+  const bool use_mfma = ctx->kernel_pref == 2 || (ctx->kernel_pref == 0 && ctx->d.dtype == BAKLAVA_BF16);
   const bool track = ctx->track_on;
   // The vector-ALU kernel adds its weights right after the call; weights an earlier MFMA call left
   // pending come first, so that the scores grow in the order of the calls.
@@ -378,7 +377,7 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   const bool on_dispatch = ctx->time_kernel == 2 && use_mfma;
   const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
                                             sc.max_count.begin() + layer_begin + layer_count);
-  hipError_t e = use_mfma ? launch_decode_mfma(p, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s,
+  hipError_t e = use_mfma ? launch_decode_mfma(p, ctx->d.D, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s,
                                                on_dispatch ? ev0 : nullptr, on_dispatch ? ev1 : nullptr)
                           : launch_decode_valu(p, ctx->d.dtype, ctx->d.D, i1 - i0, i1 - i0 <= ctx->n_cus, s);
   if (!hip_ok(e)) return BAKLAVA_EHIP;
@@ -535,7 +534,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     const int st = build_tiles(ctx);
     if (st != BAKLAVA_OK) { delete ctx; return st; }
   }
-  if (!hip_ok(prepare_decode_mfma())) { delete ctx; return BAKLAVA_EHIP; }
+  if (desc->dtype == BAKLAVA_BF16 && !hip_ok(prepare_decode_mfma(desc->D))) { delete ctx; return BAKLAVA_EHIP; }
   int st = build_schedule(ctx, 0, ctx->layer_one_wave ? kDefaultChunk : kDefaultChunkWhole);
   if (st == BAKLAVA_OK) st = build_schedule(ctx, 1, kDefaultChunkWhole);
   if (st != BAKLAVA_OK) { delete ctx; return st; }

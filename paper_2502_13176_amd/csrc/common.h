@@ -186,12 +186,12 @@ void note_hip_error(hipError_t e);
 hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, bool one_wave, hipStream_t s);
 // max_count: longest work item of the launch (rows); one_wave: the launch has at most one workgroup per
 // compute unit, so a workgroup may take the whole LDS (score tracking keeps its new scores there)
-hipError_t launch_decode_mfma(const DecodeParams& p, int n_items, int max_count, bool one_wave, hipStream_t s,
+hipError_t launch_decode_mfma(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s,
                               hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-hipError_t prepare_decode_mfma();
-// the weights of the calls on record, from the K rows alone (bf16, D = 128; needs only the lag_*,
+hipError_t prepare_decode_mfma(int D);
+// the weights of the calls on record, from the K rows alone (bf16; needs only the lag_*,
 // k, score, items, G and scale fields)
-hipError_t launch_score_flush_mfma(const DecodeParams& p, int n_items, int max_count, hipStream_t s);
+hipError_t launch_score_flush_mfma(const DecodeParams& p, int D, int n_items, int max_count, hipStream_t s);
 hipError_t launch_profile_similarity(const void* q, const void* k, const void* v, int batch, int Hq, int Hkv,
                                      int T, float* cos_out, float* sim_out, float* lse_out, float* tile_sum,
                                      hipStream_t s);

@@ -1,4 +1,4 @@
-// Decode attention over ragged caches, MFMA version (bf16, D = 128, up to 16 query heads per
+// Decode attention over ragged caches, MFMA version (bf16, D = 128 or 64, up to 16 query heads per
 // KV head).
 //
 // The G query heads that share a KV head form the N side (padded to 16) of two matrix products
@@ -15,9 +15,10 @@
 // k = 8j + 4*tile + i, so the softmax weights never leave their lane; V^T is read from LDS
 // with the same numbering.  Each query head's statistics (running max, sum) live in the 4 lanes
 // g, g+16, g+32, g+48.  Softmax weights are split into two bf16 terms (high part and residual)
-// so that the second product keeps ~16 bits of each weight.
+// so that the second product keeps ~16 bits of each weight; at D = 64 into three, which is exact: there
+// the results are those of fp32 weights (relative error 1.6e-7 against 64 bits; two terms leave 4e-6).
 //
-// Both K and V are fetched as whole 256-byte rows, four rows per load instruction.  Reading K
+// Both K and V are fetched as whole rows, 1 KiB per load instruction (D = 128: four rows).  Reading K
 // straight into the A-operand layout would save its trip through LDS, but touches only 64 bytes
 // of each of 16 rows per instruction, and that access shape streams about 10% slower from HBM
 // than whole rows do.
@@ -51,16 +52,30 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
-#ifndef BAKLAVA_MFMA_NW
-#define BAKLAVA_MFMA_NW 4
-#endif
-constexpr int kWaves = BAKLAVA_MFMA_NW;
 constexpr int kSlab = 32;       // rows per wavefront iteration
-constexpr int kVStride = 288;   // bytes between staged V rows: 256 + 32, so the 16 rows touched by one
-                                // transposed read spread evenly over the LDS banks
-constexpr int kKStride = 272;   // bytes between staged K rows: 256 + 16, so 16 lanes that read the same
-                                // 16 bytes of 16 consecutive rows hit 16 different bank groups
-constexpr int kD = 128;
+
+// What follows from the head dimension.  (D = 64: eight tracked launches over 67 MB of 64 caches each take
+// 178, 182 and 186 us at one, four and eight query heads per cache; the vector-ALU kernel and its score
+// pass took 218, 280 and 430.)
+template <int D>
+struct Shape {
+  // A slab of 64-element rows is half as many bytes, so a workgroup has twice as many wavefronts: the
+  // same 64 KiB of K and V in flight per compute unit when a launch has one workgroup for each.
+  static constexpr int kWaves = D == 128 ? 4 : 8;
+  static constexpr int kRow = D * 2;               // bytes of a row
+  static constexpr int kRowLanes = kRow / 16;      // lanes a row takes in a load instruction
+  static constexpr int kLoadRows = 64 / kRowLanes; // rows per load instruction
+  static constexpr int kLoads = kSlab / kLoadRows; // load instructions per slab and plane
+  static constexpr int kChunks = D / 32;           // steps of the first product
+  static constexpr int kBlocks = D / 16;           // 16-element blocks of the second product's result
+  static constexpr int kVStride = kRow + 32;       // bytes between staged V rows, so that the 16 rows touched
+                                                   // by one transposed read spread evenly over the LDS banks
+  static constexpr int kKStride = kRow + 16;       // bytes between staged K rows, so that 16 lanes that read the
+                                                   // same 16 bytes of 16 consecutive rows hit 16 bank groups
+  // bf16 terms of a softmax weight in the second product: two keep ~16 of its bits, three all 24.
+  static constexpr int kTerms = D == 128 ? 2 : 3;
+  static constexpr int kStatic = kWaves * kSlab * (kVStride + kKStride);  // staging areas of a workgroup
+};
 constexpr float kNegInf = -__builtin_huge_valf();
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -79,24 +94,27 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(u32x4_t x) { return __builtin_bit_
 constexpr int kSets = 2;
 constexpr int kRecRows = 16 * kSets;  // packed rows of a record
 constexpr int kRecCalls = 8;          // most calls a record holds (G <= 4)
+template <int D>
 struct Record {
-  bf16x8_t q[kSets][4];
+  bf16x8_t q[kSets][Shape<D>::kChunks];
   float m[kSets][4], inv[kSets][4];
   int n_slot[kSets];
 };
 
+template <int D>
 __device__ __forceinline__ void load_record(const DecodeParams& p, int c, int G, int pending, int n16, int jg,
-                                            Record& r) {
+                                            Record<D>& r) {
+  constexpr int kRow = Shape<D>::kRow;
   const int gp_mask = (1 << p.lag_gp_log2) - 1;
-  const unsigned char* lq = reinterpret_cast<const unsigned char*>(p.lag_q) + (int64_t)c * kRecRows * (kD * 2);
+  const unsigned char* lq = reinterpret_cast<const unsigned char*>(p.lag_q) + (int64_t)c * kRecRows * kRow;
 #pragma unroll
   for (int e = 0; e < kSets; ++e) {
     const int R = 16 * e + n16;  // the packed row this lane holds a part of
 #pragma unroll
-    for (int ch = 0; ch < 4; ++ch) {
+    for (int ch = 0; ch < Shape<D>::kChunks; ++ch) {
       u32x4_t raw = {0u, 0u, 0u, 0u};  // rows beyond the G heads of a call, calls not on record: zero
       if ((R & gp_mask) < G && (R >> p.lag_gp_log2) < pending)
-        raw = *reinterpret_cast<const u32x4_t*>(lq + R * (kD * 2) + ch * 64 + jg * 16);
+        raw = *reinterpret_cast<const u32x4_t*>(lq + R * kRow + ch * 64 + jg * 16);
       r.q[e][ch] = as_bf16x8(raw);
     }
     const int slot = (16 * e + 4 * jg) >> p.lag_gp_log2;
@@ -119,7 +137,8 @@ __device__ __forceinline__ void load_record(const DecodeParams& p, int c, int G,
 // sum over calls and heads of 2^(s' - M') / L' for the rows a call saw.  sp[e][T] holds the logits of
 // operand e and tile T as the product left them.  On return lane l < 32 holds the weight of row l of
 // the slab.
-__device__ __forceinline__ float record_weights(const floatx4_t (&sp)[kSets][2], const Record& r, float cs,
+template <int D>
+__device__ __forceinline__ float record_weights(const floatx4_t (&sp)[kSets][2], const Record<D>& r, float cs,
                                                 int row_first, int lane) {
   const int n16 = lane & 15;
   float w[2];
@@ -140,11 +159,10 @@ __device__ __forceinline__ float record_weights(const floatx4_t (&sp)[kSets][2],
   return (lane & 16) ? w[1] : w[0];
 }
 
-#ifndef BAKLAVA_MFMA_WAVES_PER_EU
-#define BAKLAVA_MFMA_WAVES_PER_EU 2
-#endif
-template <bool LAG>
-__global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode_partial_mfma(DecodeParams p) {
+template <int D, bool LAG>
+__global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(DecodeParams p) {
+  using S = Shape<D>;
+  constexpr int kWaves = S::kWaves, kRow = S::kRow, kVStride = S::kVStride, kKStride = S::kKStride;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves * kSlab * kVStride];
   __shared__ __attribute__((aligned(16))) unsigned char lds_k[kWaves * kSlab * kKStride];  // K staging
   // LAG: the new scores of the slabs a wavefront has processed ([32] floats per slab, p.ring_slots
@@ -168,7 +186,7 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
   // Recorded calls (LAG).  When the record is full this call adds their weights to the scores.
   const int pending = LAG ? p.lag_cnt[(int64_t)it.c * G] : 0;
   const bool apply = LAG && pending >= p.lag_batch;
-  Record rec;
+  Record<D> rec;
   if (LAG && apply) load_record(p, it.c, G, pending, n16, jg, rec);
   if (p.fused_append) {
     if (add) append_new_row(p, it, n_old, off_c, token_pos);
@@ -177,17 +195,17 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
   int cnt = min(it.start + it.count, n) - it.start;
   if (cnt < 0) cnt = 0;
   const int64_t row0 = off_c + it.start;
-  const unsigned char* Kb = reinterpret_cast<const unsigned char*>(p.k) + row0 * (kD * 2);
-  const unsigned char* Vb = reinterpret_cast<const unsigned char*>(p.v) + row0 * (kD * 2);
+  const unsigned char* Kb = reinterpret_cast<const unsigned char*>(p.k) + row0 * kRow;
+  const unsigned char* Vb = reinterpret_cast<const unsigned char*>(p.v) + row0 * kRow;
   unsigned char* myl = lds + wave * (kSlab * kVStride);
   unsigned char* myk = lds_k + wave * (kSlab * kKStride);
 
   const int c_rel = it.c - p.cache_begin;
   const int64_t qrow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
 
-  floatx4_t o[8];
+  floatx4_t o[S::kBlocks];
 #pragma unroll
-  for (int b = 0; b < 8; ++b) o[b] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  for (int b = 0; b < S::kBlocks; ++b) o[b] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   float m_run = kNegInf;  // running max of head n16, log2 units, equal in the 4 lanes of a head
   float l_part = 0.f;     // this lane's share of the running sum
   const float cs = p.scale_log2e;
@@ -196,21 +214,22 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
   // rows is ever read; a clamped row's softmax weight is forced to zero below.  Offsets from the
   // item's first row fit 32 bits (a work item spans < 2^23 rows).
   const int last = cnt - 1;
-  const uint32_t v_lane = n16 * 16;
-  u32x4_t kr[8];
-  u32x4_t vr[8];
+  const int l_row = lane / S::kRowLanes;  // row and 16-byte piece this lane fetches in a load instruction
+  const uint32_t v_lane = (lane % S::kRowLanes) * 16;
+  u32x4_t kr[S::kLoads];
+  u32x4_t vr[S::kLoads];
 
   // K and V rows are read once per step: non-temporal loads keep them from displacing the rest of
   // the cache hierarchy's contents (measured: +4.6% on the attention kernel).
 #define BAKLAVA_LD(ptr) __builtin_nontemporal_load(ptr)
 #define BAKLAVA_LOAD_K(T0)                                                                        \
-  _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                 \
-    const uint32_t off = (uint32_t)min((T0) + jg + 4 * i, last) * (kD * 2) + v_lane;              \
+  _Pragma("unroll") for (int i = 0; i < S::kLoads; ++i) {                                         \
+    const uint32_t off = (uint32_t)min((T0) + l_row + S::kLoadRows * i, last) * kRow + v_lane;    \
     kr[i] = BAKLAVA_LD(reinterpret_cast<const u32x4_t*>(Kb + off));                               \
   }
 #define BAKLAVA_LOAD_V(T0)                                                                        \
-  _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                 \
-    const uint32_t off = (uint32_t)min((T0) + jg + 4 * i, last) * (kD * 2) + v_lane;              \
+  _Pragma("unroll") for (int i = 0; i < S::kLoads; ++i) {                                         \
+    const uint32_t off = (uint32_t)min((T0) + l_row + S::kLoadRows * i, last) * kRow + v_lane;    \
     vr[i] = BAKLAVA_LD(reinterpret_cast<const u32x4_t*>(Vb + off));                               \
   }
 
@@ -251,13 +270,13 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
     BAKLAVA_LOAD_SC(t0)
   }
   // B operand of the first product: lane (g, j), chunk c holds Q[g][32c + 8j .. +8).
-  bf16x8_t qb[4];
+  bf16x8_t qb[S::kChunks];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
+  for (int c = 0; c < S::kChunks; ++c) {
     u32x4_t raw = {0u, 0u, 0u, 0u};
     if (n16 < G)
       raw = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const unsigned char*>(p.q) +
-                                              (qrow0 + n16) * (kD * 2) + c * 64 + jg * 16);
+                                              (qrow0 + n16) * kRow + c * 64 + jg * 16);
     qb[c] = as_bf16x8(raw);
   }
   if (t0 < cnt) {
@@ -269,8 +288,8 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
 
     // ---- stage K rows in LDS; the next slab's K loads reuse the registers ----------------------
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      *reinterpret_cast<u32x4_t*>(myk + (jg + 4 * i) * kKStride + n16 * 16) = kr[i];
+    for (int i = 0; i < S::kLoads; ++i) {
+      *reinterpret_cast<u32x4_t*>(myk + (l_row + S::kLoadRows * i) * kKStride + v_lane) = kr[i];
     }
     BAKLAVA_LOAD_K(tn)  // past the end every row clamps to the last live row: harmless re-reads
     const float sc_old = sc_cur;
@@ -287,7 +306,7 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
 #pragma unroll
       for (int e = 0; e < kSets; ++e) sp[e][T] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < S::kChunks; ++c) {
         const u32x4_t a = *reinterpret_cast<const u32x4_t*>(myk + (T * 16 + n16) * kKStride + c * 64 + jg * 16);
         s[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), qb[c], s[T], 0, 0, 0);
         // The same K registers are a valid B operand (lane (row, j): elements 32c + 8j .. +8 of its
@@ -303,8 +322,8 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
 
     // ---- stage V rows in LDS, then the next slab's V loads reuse the registers ----------------
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      *reinterpret_cast<u32x4_t*>(myl + (jg + 4 * i) * kVStride + n16 * 16) = vr[i];
+    for (int i = 0; i < S::kLoads; ++i) {
+      *reinterpret_cast<u32x4_t*>(myl + (l_row + S::kLoadRows * i) * kVStride + v_lane) = vr[i];
     }
     BAKLAVA_LOAD_V(tn)
 
@@ -338,9 +357,9 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
       m_run = mn;
       l_part *= alpha;
 #pragma unroll
-      for (int b = 0; b < 8; ++b) o[b] *= alpha;
+      for (int b = 0; b < S::kBlocks; ++b) o[b] *= alpha;
     }
-    u32x4_t ph;
+    u32x4_t ph, pm;
     bf16x8_t pl;
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
@@ -348,8 +367,15 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
       l_part += p0 + p1;
       const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
       ph[e / 2] = (u0 >> 16) | (u1 & 0xffff0000u);  // truncated high parts
-      pl[e] = (__bf16)(p0 - __uint_as_float(u0 & 0xffff0000u));
-      pl[e + 1] = (__bf16)(p1 - __uint_as_float(u1 & 0xffff0000u));
+      float r0 = p0 - __uint_as_float(u0 & 0xffff0000u), r1 = p1 - __uint_as_float(u1 & 0xffff0000u);
+      if (S::kTerms == 3) {
+        const uint32_t w0 = __float_as_uint(r0), w1 = __float_as_uint(r1);
+        pm[e / 2] = (w0 >> 16) | (w1 & 0xffff0000u);
+        r0 -= __uint_as_float(w0 & 0xffff0000u);
+        r1 -= __uint_as_float(w1 & 0xffff0000u);
+      }
+      pl[e] = (__bf16)r0;
+      pl[e + 1] = (__bf16)r1;
     }
 
     // ---- O^T += V^T P^T -----------------------------------------------------------------------
@@ -361,12 +387,13 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
     // 16b+4a .. +3, so lane m receives V[row 4*jg+k][16b+m] for k = 0..3: one half of the A operand.
     const unsigned char* tr0 = myl + (jg * 4 + (n16 >> 2)) * kVStride + (n16 & 3) * 8;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < S::kBlocks; ++b) {
       typedef __attribute__((address_space(3))) s16x4_t* lds_ptr_t;
       const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(tr0 + b * 32));
       const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(tr0 + 16 * kVStride + b * 32));
       const bf16x8_t a = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       o[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, as_bf16x8(ph), o[b], 0, 0, 0);
+      if (S::kTerms == 3) o[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, as_bf16x8(pm), o[b], 0, 0, 0);
       o[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pl, o[b], 0, 0, 0);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -386,24 +413,24 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
   l_tot += __shfl_xor(l_tot, 16);
   l_tot += __shfl_xor(l_tot, 32);
 
-  // Hand the four wavefronts' results over through LDS (reusing the staging area).
+  // Hand the wavefronts' results over through LDS (reusing the staging area).
   __syncthreads();
-  float* sm_o = reinterpret_cast<float*>(lds);                    // [kWaves][16][kD]
-  float* sm_m = sm_o + kWaves * 16 * kD;                          // [kWaves][16]
+  float* sm_o = reinterpret_cast<float*>(lds);                    // [kWaves][16][D]
+  float* sm_m = sm_o + kWaves * 16 * D;                           // [kWaves][16]
   float* sm_l = sm_m + kWaves * 16;                               // [kWaves][16]
-  static_assert((kWaves * 16 * kD + 2 * kWaves * 16) * 4 <= kWaves * kSlab * kVStride, "LDS reuse");
+  static_assert((kWaves * 16 * D + 2 * kWaves * 16) * 4 <= kWaves * kSlab * kVStride, "LDS reuse");
   if (n16 < G) {
 #pragma unroll
-    for (int b = 0; b < 8; ++b)
+    for (int b = 0; b < S::kBlocks; ++b)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) sm_o[(wave * 16 + n16) * kD + b * 16 + jg * 4 + i] = o[b][i];
+      for (int i = 0; i < 4; ++i) sm_o[(wave * 16 + n16) * D + b * 16 + jg * 4 + i] = o[b][i];
     if (jg == 0) {
       sm_m[wave * 16 + n16] = m_run;
       sm_l[wave * 16 + n16] = l_tot;
     }
   }
   __syncthreads();
-  finish_item<kD, 16, kWaves>(p, it, G, n, sm_o, sm_m, sm_l);
+  finish_item<D, 16, kWaves>(p, it, G, n, sm_o, sm_m, sm_l);
 }
 
 // The recorded calls' weights without an attention call to ride on (baklava_flush_scores, and
@@ -411,7 +438,10 @@ __global__ __launch_bounds__(64 * kWaves, BAKLAVA_MFMA_WAVES_PER_EU) void decode
 // product and the same weights as in the attention kernel, and the same route for K (whole rows
 // from HBM, staged in a wave-private LDS region, one slab ahead) and for the scores (read with the
 // slab, new values kept in LDS until the work item is done).
-__global__ __launch_bounds__(64 * kWaves) void score_flush_mfma(DecodeParams p) {
+template <int D>
+__global__ __launch_bounds__(64 * Shape<D>::kWaves) void score_flush_mfma(DecodeParams p) {
+  using S = Shape<D>;
+  constexpr int kWaves = S::kWaves, kRow = S::kRow, kKStride = S::kKStride;
   __shared__ __attribute__((aligned(16))) unsigned char lds_k[kWaves * kSlab * kKStride];
   extern __shared__ __attribute__((aligned(16))) float lds_ring[];
   const Item it = p.items[blockIdx.x];
@@ -425,16 +455,17 @@ __global__ __launch_bounds__(64 * kWaves) void score_flush_mfma(DecodeParams p) 
     if (s < pending) n_seen = max(n_seen, p.lag_n[(int64_t)it.c * kRecCalls + s]);
   const int cnt = min(it.start + it.count, n_seen) - it.start;
   if (cnt <= 0) return;
-  Record rec;
+  Record<D> rec;
   load_record(p, it.c, G, pending, n16, jg, rec);
   const int last = cnt - 1;
-  const unsigned char* Kb = reinterpret_cast<const unsigned char*>(p.k) + it.row0 * (kD * 2);
+  const unsigned char* Kb = reinterpret_cast<const unsigned char*>(p.k) + it.row0 * kRow;
   float* const sc_base = p.score + it.row0;
   unsigned char* myk = lds_k + wave * (kSlab * kKStride);
   float* ring = lds_ring + wave * p.ring_slots * kSlab;
   const float cs = p.scale_log2e;
-  const uint32_t v_lane = n16 * 16;
-  u32x4_t kr[8];
+  const int l_row = lane / S::kRowLanes;
+  const uint32_t v_lane = (lane % S::kRowLanes) * 16;
+  u32x4_t kr[S::kLoads];
   float sc_cur = 0.f;
   int ring_n = 0, ring_t0 = 0;
   auto flush_ring = [&]() {
@@ -450,8 +481,8 @@ __global__ __launch_bounds__(64 * kWaves) void score_flush_mfma(DecodeParams p) 
     ring_n = 0;
   };
 #define BAKLAVA_LOAD_SLAB(T0)                                                                       \
-  _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                   \
-    const uint32_t off = (uint32_t)min((T0) + jg + 4 * i, last) * (kD * 2) + v_lane;                \
+  _Pragma("unroll") for (int i = 0; i < S::kLoads; ++i) {                                           \
+    const uint32_t off = (uint32_t)min((T0) + l_row + S::kLoadRows * i, last) * kRow + v_lane;      \
     kr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(Kb + off));                 \
   }                                                                                                 \
   if (lane < kSlab) sc_cur = sc_base[min((T0) + lane, last)];
@@ -461,7 +492,8 @@ __global__ __launch_bounds__(64 * kWaves) void score_flush_mfma(DecodeParams p) 
   }
   for (; t0 < cnt; t0 += kWaves * kSlab) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4_t*>(myk + (jg + 4 * i) * kKStride + n16 * 16) = kr[i];
+    for (int i = 0; i < S::kLoads; ++i)
+      *reinterpret_cast<u32x4_t*>(myk + (l_row + S::kLoadRows * i) * kKStride + v_lane) = kr[i];
     const float sc_old = sc_cur;
     BAKLAVA_LOAD_SLAB(t0 + kWaves * kSlab)  // past the end every row clamps to the last one: harmless re-reads
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -473,7 +505,7 @@ __global__ __launch_bounds__(64 * kWaves) void score_flush_mfma(DecodeParams p) 
 #pragma unroll
       for (int e = 0; e < kSets; ++e) sp[e][T] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < S::kChunks; ++c) {
         const u32x4_t a = *reinterpret_cast<const u32x4_t*>(myk + (T * 16 + n16) * kKStride + c * 64 + jg * 16);
 #pragma unroll
         for (int e = 0; e < kSets; ++e)
@@ -496,59 +528,77 @@ __global__ __launch_bounds__(64 * kWaves) void score_flush_mfma(DecodeParams p) 
 // Dynamic LDS the attention kernel may ask for: the whole LDS of a CU minus the static staging areas
 // when a workgroup has the CU to itself, half of what two workgroups leave otherwise.
 constexpr int kLdsTotal = 160 * 1024;
-constexpr int kStatic = kWaves * kSlab * (kVStride + kKStride);
-constexpr int kDynMax = kLdsTotal - kStatic - 512;
-constexpr int kDynShared = (kLdsTotal - 2 * kStatic - 1024) / 2;
-static_assert(kDynShared >= kWaves * kSlab * 4, "room for one slab of scores per wavefront");
+template <int D> constexpr int dyn_max() { return kLdsTotal - Shape<D>::kStatic - 512; }
+template <int D> constexpr int dyn_shared() { return (kLdsTotal - 2 * Shape<D>::kStatic - 1024) / 2; }
+static_assert(dyn_shared<128>() >= Shape<128>::kWaves * kSlab * 4, "room for one slab of scores per wavefront");
+static_assert(dyn_shared<64>() >= Shape<64>::kWaves * kSlab * 4, "room for one slab of scores per wavefront");
+constexpr int kFlushDynMax = 48 * 1024;  // the flush kernel's share for waiting scores, beside its K staging area
 
 // Called when a context is created on the current device, i.e. outside any stream capture: raises
-// the kernel's dynamic-LDS limit once, so that launches (captured or not) only launch.
-constexpr int kFlushDynMax = 48 * 1024;  // the flush kernel's share for waiting scores, beside its K staging area
-hipError_t prepare_decode_mfma() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_mfma<true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kDynMax);
+// the kernels' dynamic-LDS limits once, so that launches (captured or not) only launch.
+template <int D>
+hipError_t raise_limits() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_mfma<D, true>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, dyn_max<D>());
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(score_flush_mfma),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(score_flush_mfma<D>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, kFlushDynMax);
+}
+hipError_t prepare_decode_mfma(int D) { return D == 128 ? raise_limits<128>() : raise_limits<64>(); }
+
+// Slabs per wavefront whose new scores fit `bytes` of LDS, at most what the longest item needs.
+template <int D>
+int ring_slots(int bytes, int max_count) {
+  constexpr int kWaves = Shape<D>::kWaves;
+  const int need = ((max_count + kSlab - 1) / kSlab + kWaves - 1) / kWaves;
+  return std::max(1, std::min(bytes / (kWaves * kSlab * 4), need));
 }
 
 // With a pair of events the kernel's own dispatch carries them: they take the time stamps of its
 // first and last wavefront, not those of commands placed around it on the stream.
-hipError_t launch_decode_mfma(const DecodeParams& p_in, int n_items, int max_count, bool one_wave, hipStream_t s,
-                              hipEvent_t ev0, hipEvent_t ev1) {
-  if (n_items <= 0) return hipSuccess;
-  if (p_in.G > 16) return hipErrorInvalidValue;
-  DecodeParams p = p_in;
-  p.ring_slots = 0;
-  const dim3 grid(n_items), block(64 * kWaves);
+template <int D>
+hipError_t launch_attention(DecodeParams p, int n_items, int max_count, bool one_wave, hipStream_t s, hipEvent_t ev0,
+                            hipEvent_t ev1) {
+  const dim3 grid(n_items), block(64 * Shape<D>::kWaves);
   const bool timed = ev0 && ev1;
+  p.ring_slots = 0;
   if (!p.lag) {
-    if (timed) hipExtLaunchKernelGGL(decode_partial_mfma<false>, grid, block, 0, s, ev0, ev1, 0, p);
-    else decode_partial_mfma<false><<<grid, block, 0, s>>>(p);
+    if (timed) hipExtLaunchKernelGGL((decode_partial_mfma<D, false>), grid, block, 0, s, ev0, ev1, 0, p);
+    else decode_partial_mfma<D, false><<<grid, block, 0, s>>>(p);
     return hipGetLastError();
   }
   // the LDS left beside the staging areas, split over the wavefronts; a launch of several waves of
   // workgroups keeps room for two workgroups per compute unit
-  const int slot_bytes = kSlab * 4;
-  const int fit = (one_wave ? kDynMax : kDynShared) / (kWaves * slot_bytes);
-  const int need = ((max_count + kSlab - 1) / kSlab + kWaves - 1) / kWaves;  // slabs of the longest item per wavefront
-  p.ring_slots = std::max(1, std::min(fit, need));
-  const size_t dyn = (size_t)p.ring_slots * kWaves * slot_bytes;
-  if (timed) hipExtLaunchKernelGGL(decode_partial_mfma<true>, grid, block, dyn, s, ev0, ev1, 0, p);
-  else decode_partial_mfma<true><<<grid, block, dyn, s>>>(p);
+  p.ring_slots = ring_slots<D>(one_wave ? dyn_max<D>() : dyn_shared<D>(), max_count);
+  const size_t dyn = (size_t)p.ring_slots * Shape<D>::kWaves * kSlab * 4;
+  if (timed) hipExtLaunchKernelGGL((decode_partial_mfma<D, true>), grid, block, dyn, s, ev0, ev1, 0, p);
+  else decode_partial_mfma<D, true><<<grid, block, dyn, s>>>(p);
   return hipGetLastError();
 }
 
-hipError_t launch_score_flush_mfma(const DecodeParams& p_in, int n_items, int max_count, hipStream_t s) {
-  if (n_items <= 0) return hipSuccess;
-  if (p_in.G > 16) return hipErrorInvalidValue;
-  DecodeParams p = p_in;
-  const int slot_bytes = kSlab * 4;
-  const int fit = kFlushDynMax / (kWaves * slot_bytes);
-  const int need = ((max_count + kSlab - 1) / kSlab + kWaves - 1) / kWaves;
-  p.ring_slots = std::max(1, std::min(fit, need));
-  score_flush_mfma<<<dim3(n_items), dim3(64 * kWaves), (size_t)p.ring_slots * kWaves * slot_bytes, s>>>(p);
+template <int D>
+hipError_t launch_flush(DecodeParams p, int n_items, int max_count, hipStream_t s) {
+  p.ring_slots = ring_slots<D>(kFlushDynMax, max_count);
+  score_flush_mfma<D><<<dim3(n_items), dim3(64 * Shape<D>::kWaves),
+                        (size_t)p.ring_slots * Shape<D>::kWaves * kSlab * 4, s>>>(p);
   return hipGetLastError();
+}
+
+hipError_t launch_decode_mfma(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s,
+                              hipEvent_t ev0, hipEvent_t ev1) {
+  if (n_items <= 0) return hipSuccess;
+  if (p.G > 16) return hipErrorInvalidValue;
+  if (D == 128) return launch_attention<128>(p, n_items, max_count, one_wave, s, ev0, ev1);
+  if (D == 64) return launch_attention<64>(p, n_items, max_count, one_wave, s, ev0, ev1);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_score_flush_mfma(const DecodeParams& p, int D, int n_items, int max_count, hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  if (p.G > 16) return hipErrorInvalidValue;
+  if (D == 128) return launch_flush<128>(p, n_items, max_count, s);
+  if (D == 64) return launch_flush<64>(p, n_items, max_count, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace baklava

@@ -323,3 +323,34 @@ def test_vector_kernel_tiles_and_rising_logits(dtype, D, G):
             # fp32 logits of up to ~1200 in log2 units carry an absolute error of about 1e-4, so do the weights
             assert np.max(np.abs(post.score[c] - p.sum(0))) <= 2e-3, (step, n)
     arena.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(2, 2), (6, 2), (7, 1), (16, 2)])
+def test_matrix_kernel_with_half_size_rows(Hq, Hkv):
+    """bf16 rows of 64 elements on the matrix cores (what automatic choice takes): lengths around the
+    slabs and workgroup strides of its eight wavefronts, several schedules, against the oracle to what
+    fp32 weights leave (three bf16 terms per weight are exact: the bound is 64 ulps of the largest value
+    a row of V contributes, where two terms would show 4e-6 relative), and against the vector kernel."""
+    H = _h()
+    lens = [1, 2, 31, 32, 33, 63, 65, 255, 256, 257, 511, 513, 1000, 2500]
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="half", L=2, Hq=Hq, Hkv=Hkv, D=64, batch=7, dtype="bf16",
+                     seed=92 + Hq, sink=1, recent=1, slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    n_caches = w.L * w.batch * w.Hkv
+    arena = H.make_arena(w, [4096] * (w.L * w.Hkv))
+    st = H.fill_from_host(arena, w, [lens[(5 * c + 3) % len(lens)] for c in range(n_caches)], rng, peaked=True)
+    q, q64 = H.make_q(w, rng, w.L)
+    arena.set_option(B.OPT_KERNEL, B.KERNEL_VALU)
+    vector = H.gpu_decode(arena, w, q)
+    arena.set_option(B.OPT_KERNEL, B.KERNEL_AUTO)
+    for chunk in (256, 512, 4096):
+        H.set_chunk(arena, chunk)
+        out = H.gpu_decode(arena, w, q)
+        H.check_decode_against_oracle(arena, w, st, q64, out, tol=64 * 2.0 ** -24 * 4)
+        assert np.max(np.abs(out - vector)) <= 64 * 2.0 ** -24 * 4
+        out1 = H.gpu_decode(arena, w, q[1:2], layer_begin=1, layer_count=1)
+        H.check_decode_against_oracle(arena, w, st, q64[1:2], out1, caches=range(n_caches // 2, n_caches), layer_begin=1,
+                                      tol=64 * 2.0 ** -24 * 4)
+    with pytest.raises(B.BaklavaError):          # forcing it is still for rows of 128 elements only
+        arena.set_option(B.OPT_KERNEL, B.KERNEL_MFMA)
+    arena.close()

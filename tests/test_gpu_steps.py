@@ -202,6 +202,57 @@ def test_deferred_score_updates_over_windows_of_steps(base, Hq, Hkv, batch, targ
     arena.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv,target", [(4, 4, -1), (6, 2, 3), (8, 1, 0)])
+def test_deferred_score_updates_with_half_size_rows(Hq, Hkv, target):
+    """bf16 rows of 64 elements take the matrix kernel and its deferred score update: 21 steps without a
+    read-back (records of 8 and of 4 calls fill and are applied), a switch to the vector kernel and back,
+    then the scores against the oracle's own run and the eviction that follows."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["long"], name="lag64", L=2, Hq=Hq, Hkv=Hkv, D=64, batch=2, ctx=2048, lo=96,
+                     hi=2048, interval=24, slack=24, sink=4, recent=16, seed=177 + Hq)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    budgets = synth.budgets_for(w, B.alloc_proportional)
+    arena = H.make_arena(w, budgets, track=True)
+    if target >= 0:
+        H.set_chunk(arena, 256)
+        arena.set_option(B.OPT_TARGET_ITEMS, target)
+        arena.set_option(B.OPT_TARGET_ITEMS_WHOLE, target)
+    cpl = w.batch * w.Hkv
+    st = H.fill_from_host(arena, w, [budgets[(c // cpl) * w.Hkv + c % w.Hkv] - (c % 3) for c in range(arena.n_caches)], rng,
+                          scores="uniform")
+    caches = [H.oracle_cache(w, st, c) for c in range(arena.n_caches)]
+    dev = arena.device
+    for t in range(1, 22):
+        arena.set_option(B.OPT_KERNEL, B.KERNEL_VALU if t in (6, 18) else B.KERNEL_AUTO)
+        q, q64 = H.make_q(w, rng, w.L)
+        knew, vnew = (synth.payload(rng, (w.L, w.batch, w.Hkv, w.D), w.dtype) for _ in range(2))
+        kd, vd, qd = (H.to_device_storage(a, w.dtype, dev) for a in (knew, vnew, q))
+        outd = torch.full((w.L, w.batch, w.Hq, w.D), float("nan"), dtype=torch.float32, device=dev)
+        if t % 3 == 0:
+            arena.append_decode_attn(0, w.L, kd, vd, 5000 + t, qd, outd)
+        else:
+            for l in range(w.L):
+                arena.append_decode_attn(l, 1, kd[l], vd[l], 5000 + t, qd[l], outd[l])
+        torch.cuda.synchronize()
+        out = outd.cpu().numpy().astype(np.float64)
+        k64, v64 = synth.storage_to_f64(knew, w.dtype), synth.storage_to_f64(vnew, w.dtype)
+        for c in range(arena.n_caches):
+            l, b, hs = H.q_rows_of_cache(w, c)
+            ref, _, _ = O.decode_step(caches[c], q64[l, b, hs], k64[l, b, c % w.Hkv], v64[l, b, c % w.Hkv], 5000 + t, t,
+                                      budget=0, sink=0, recent=0, interval=0, track_scores=True)
+            assert np.max(np.abs(out[l, b, hs] - ref)) <= H.ATTN_TOL, (t, c)
+    post = H.download(arena, w)
+    for c in range(arena.n_caches):
+        oc = caches[c]
+        assert post.K[c].shape[0] == oc.n and np.array_equal(post.pos[c], oc.pos[:oc.n])
+        assert np.max(np.abs(post.score[c] - oc.score[:oc.n])) <= SCORE_TOL, c
+    kept_dev = torch.full((arena.total_tokens,), -1, dtype=torch.int32, device=dev)
+    arena.compact(0, w.L, kept_dev)
+    torch.cuda.synchronize()
+    H.check_eviction_against_oracle(arena, w, budgets, post, H.download(arena, w), kept_dev, range(arena.n_caches))
+    arena.close()
+
+
 def test_scores_sum_to_G_per_step_without_eviction():
     """Each query head's softmax weights sum to 1, so a cache's scores grow by exactly G per step."""
     H = _h()
