@@ -128,7 +128,7 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
   w.order_all = o;    o = align256(o + (size_t)n_caches * 4);
   w.order_layer = o;  o = align256(o + (size_t)n_caches * 4);
   w.segs = o;         o = align256(o + (size_t)w.n_segs * sizeof(MoveSeg));
-  w.seg_split = o;    o = align256(o + (size_t)w.n_segs * 4);
+  w.seg_split = o;    o = align256(o + (size_t)w.n_segs * 2 * 4);
   w.halo_k = o;       o = align256(o + (size_t)w.halo_rows * row_bytes);
   w.halo_v = o;       o = align256(o + (size_t)w.halo_rows * row_bytes);
   w.halo_score = o;   o = align256(o + (size_t)w.halo_rows * 4);

@@ -164,7 +164,8 @@ struct CompactParams {
   int32_t row_bytes;
   int32_t write_identity;  // 1: also write 0..n-1 for caches that evict nothing
   const MoveSeg* segs;     // segments of the launched cache range
-  int32_t* seg_split;      // [n_segs] first destination row of a segment whose source lies past its end
+  int32_t* seg_split;      // [n_segs, 2] first destination row of a segment whose source lies past its end, and
+                           // first one whose source lies past all destination rows of the cache
   void* halo_k;            // halo copies of the rows a segment needs from beyond its end
   void* halo_v;
   float* halo_score;
