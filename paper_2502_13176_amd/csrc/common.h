@@ -140,6 +140,14 @@ struct AppendParams {
   int32_t row_bytes;
 };
 
+constexpr int kLengthsPerLaunch = 512;
+struct LengthsParams {
+  int32_t* len;
+  int32_t* lag_cnt;                  // [n_caches, G]
+  int32_t count, G;                  // all caches of the context
+  int32_t value[kLengthsPerLaunch];
+};
+
 // One destination segment of the eviction move: rows [a, a + seg_rows) of cache c.  Segments that
 // have a successor own a halo slot (room for min(seg_rows, cap - budget) rows) in the workspace.
 struct MoveSeg {
@@ -204,6 +212,7 @@ hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t
 // max_count: the largest row count of a work item in the launched range (or a bound on it)
 hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items, int max_count, hipStream_t s);
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s);
+hipError_t launch_set_lengths(const LengthsParams& p, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s);
 // n_wide: caches of the range with more than kHeldRows / 4 rows of capacity; sorted: they come first in p.order
 hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,

@@ -415,6 +415,15 @@ __global__ __launch_bounds__(64) void append_kernel(AppendParams p) {
   if (lane == 0) p.len[c] = n + 1;
 }
 
+// Live lengths handed over among the kernel's arguments, and the records of pending calls emptied: one
+// small dispatch instead of a fill and a staged copy from pageable memory.
+__global__ __launch_bounds__(kLengthsPerLaunch) void set_lengths_kernel(LengthsParams p) {
+  const int c = threadIdx.x;
+  if (c >= p.count) return;
+  p.len[c] = p.value[c];
+  for (int g = 0; g < p.G; ++g) p.lag_cnt[c * p.G + g] = 0;
+}
+
 __global__ void fill_i32_kernel(int32_t* dst, int32_t value, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = value;
@@ -479,6 +488,12 @@ hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s) {
   if (n_caches <= 0) return hipSuccess;
   append_kernel<<<dim3(n_caches), dim3(64), 0, s>>>(p);
+  return hipGetLastError();
+}
+
+hipError_t launch_set_lengths(const LengthsParams& p, hipStream_t s) {
+  if (p.count <= 0) return hipSuccess;
+  set_lengths_kernel<<<dim3(1), dim3(kLengthsPerLaunch), 0, s>>>(p);
   return hipGetLastError();
 }
 
