@@ -202,7 +202,10 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   std::vector<int32_t> cib(ctx->n_caches + 1, 0), multi_begin(ctx->d.L + 1, 0);
   std::vector<MultiCache> multi;
   std::vector<int32_t> max_count(ctx->d.L, 0);
+  int32_t slot0 = 0;  // the items of a cache follow each other
   for (int64_t i = 0; i < n_items; ++i) {
+    if (items[i].start == 0) slot0 = items[i].slot;
+    items[i].reserved = slot0;
     const baklava_work_item& it = items[i];
     max_count[it.cache / ctx->cpl] = std::max(max_count[it.cache / ctx->cpl], it.count);
     if (it.start == 0) {
@@ -283,25 +286,19 @@ int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hi
   return BAKLAVA_OK;
 }
 
-// The vector-ALU path's score update for the call that has just been enqueued with query `q`.
-int score_pass(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, const void* q, hipStream_t s) {
-  const int64_t c0 = (int64_t)layer_begin * ctx->cpl;
-  const int64_t c1 = c0 + (int64_t)layer_count * ctx->cpl;
-  const int which = (layer_begin == 0 && layer_count == ctx->d.L) ? 1 : 0;
-  const baklava_ctx::Schedule& sc = ctx->sched[which];
-  const int32_t i0 = sc.cib[c0], i1 = sc.cib[c1];
+// The vector-ALU path's score update for the call that has just been enqueued, with the merge of its split
+// partials if asked for.
+int score_pass(baklava_ctx* ctx, const DecodeParams& d, int n_items, bool merge, int longest, hipStream_t s) {
   ScoreParams p;
-  p.k = ctx->d.k; p.q = q;
-  p.ml = reinterpret_cast<const float*>(ctx->ws + ctx->plan.final_ml);
-  p.len = ctx->d.len;
-  p.items = reinterpret_cast<const Item*>(ctx->ws + ctx->plan.items[which]) + i0;
-  p.score = ctx->d.score;
-  p.G = ctx->G; p.Hq = ctx->d.Hq; p.Hkv = ctx->d.Hkv;
-  p.cache_begin = (int32_t)c0;
-  p.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)ctx->d.D));
-  const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
-                                            sc.max_count.begin() + layer_begin + layer_count);
-  if (!hip_ok(launch_score_pass(p, ctx->d.dtype, ctx->d.D, i1 - i0, longest, s))) return BAKLAVA_EHIP;
+  p.k = d.k; p.q = d.q; p.out = d.out;
+  p.ml = d.final_ml; p.part_o = d.part_o; p.part_ml = d.part_ml;
+  p.rows = d.lag_n; p.len = d.len;
+  p.items = d.items;
+  p.score = d.score;
+  p.G = d.G; p.Hq = d.Hq; p.Hkv = d.Hkv;
+  p.cache_begin = d.cache_begin;
+  p.scale_log2e = d.scale_log2e;
+  if (!hip_ok(launch_score_pass(p, ctx->d.dtype, ctx->d.D, n_items, longest, merge, s))) return BAKLAVA_EHIP;
   return BAKLAVA_OK;
 }
 
@@ -359,6 +356,10 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   p.lag_batch = kLagRows >> ctx->lag_gp_log2;
   p.lag_gp_log2 = ctx->lag_gp_log2;
   p.ring_slots = 0;
+  // vector kernel, scores tracked: the score pass also does the combine kernel's work in small launches
+  const bool scores_now = track && !use_mfma;
+  const bool merge = scores_now && m1 > m0 && i1 - i0 <= ctx->n_cus;
+  p.keep_rows = merge ? 1 : 0;
   p.fused_append = fused ? 1 : 0;
   p.token_pos = token_pos;
   p.row_bytes = ctx->row_bytes;
@@ -385,10 +386,13 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
     if (!on_dispatch && !hip_ok(hipEventRecord(ev1, s))) return BAKLAVA_EHIP;
     ctx->ev_used += 1;
   }
-  if (!hip_ok(launch_combine(p, ctx->d.D, m1 - m0, s))) return BAKLAVA_EHIP;
+  if (!merge && !hip_ok(launch_combine(p, ctx->d.D, m1 - m0, s))) return BAKLAVA_EHIP;
+  if (scores_now) {
+    const int st = score_pass(ctx, p, i1 - i0, merge, longest, s);
+    if (st != BAKLAVA_OK) return st;
+  }
   if (fused && host_lengths)
     for (int64_t c = c0; c < c1; ++c) ctx->len[c] += 1;
-  if (track && !use_mfma) return score_pass(ctx, layer_begin, layer_count, q, s);
   return BAKLAVA_OK;
 }
 

@@ -33,7 +33,7 @@ constexpr int kMinLongRows = kTileRows;  // smallest capacity from which a cache
 struct Item {
   int32_t c, start, count, slot;
   int32_t nsplit;  // work items of this cache
-  int32_t pad;
+  int32_t slot0;   // partial slot of the cache's first item (filled in when the table is uploaded)
   int64_t row0;    // arena row of `start`: off[c] + start
 };
 
@@ -104,19 +104,25 @@ struct DecodeParams {
   int32_t lag_batch;               // calls a record holds: kLagRows / Gp
   int32_t lag_gp_log2;             // log2(Gp)
   int32_t ring_slots;              // MFMA kernel, lag: slabs per wavefront whose new scores wait in LDS
+  int32_t keep_rows;               // 1: leave the live rows of each cache in lag_n for the score pass (vector kernel)
   int32_t fused_append;            // 1: every cache of the range first receives its new row
   int32_t token_pos;
   int32_t row_bytes;
   float scale_log2e;               // log2(e) / sqrt(D)
 };
 
-// Score pass of the vector-ALU path over the K rows alone, right after its attention call:
-// score_j += sum_g 2^(q_g . k_j scale - M_g) / L_g over the live rows of every cache of the range.
+// Score pass of the vector-ALU path over the K rows alone, right after its attention kernel:
+// score_j += sum_g 2^(q_g . k_j scale - M_g) / L_g over the live rows of every cache of the range.  With
+// `merge` it merges the split partials as well, in place of the combine kernel.
 struct ScoreParams {
   const void* k;
   const void* q;                   // [layer_count, batch, Hq, D], the call's query rows
-  const float* ml;                 // final_ml of the call
-  const int32_t* len;
+  const float* ml;                 // final_ml of the call (with merge: of caches with a single work item)
+  const float* part_o;             // merge: split partials of the others
+  const float* part_ml;
+  float* out;
+  const int32_t* rows;             // merge: [n_caches, kLagCalls] live rows in this call (first entry)
+  int32_t* len;
   const Item* items;
   float* score;
   int32_t G, Hq, Hkv;
@@ -209,8 +215,10 @@ hipError_t launch_layer_similarity(const void* x_in, const void* x_out, int n_se
 hipError_t launch_prefill_scores(const void* q, const void* k, const float* lse, const int64_t* row_off,
                                  int batch, int Hq, int Hkv, int T, float* score, hipStream_t s);
 hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t s);
-// max_count: the largest row count of a work item in the launched range (or a bound on it)
-hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items, int max_count, hipStream_t s);
+// max_count: the largest row count of a work item in the launched range (or a bound on it); merge: the
+// pass merges the split partials too (p.rows must hold each cache's live rows)
+hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items, int max_count, bool merge,
+                             hipStream_t s);
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s);
 hipError_t launch_set_lengths(const LengthsParams& p, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s);

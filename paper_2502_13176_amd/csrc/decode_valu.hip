@@ -104,6 +104,7 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
     if (add) append_new_row(p, it, n_old, off_c, token_pos);
     else if (it.start == 0 && threadIdx.x == 0) *p.status = 1;
   }
+  if (p.keep_rows && it.start == 0 && threadIdx.x == 0) p.lag_n[(int64_t)it.c * kLagCalls] = n;
   int cnt = min(it.start + it.count, n) - it.start;
   if (cnt < 0) cnt = 0;
   const int64_t row0 = off_c + it.start;
@@ -325,8 +326,13 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeParams p) {
 // flight, and lane u of a row's lanes adds the weight of the u-th one, so that the scores of a tile
 // are read and written by one instruction each.  One load in flight per wavefront and 1024 rows per
 // workgroup took 35 us for 33 MB of K, this takes 8.
+// With MERGE a cache's normalisers are merged from its split partials by every workgroup for itself,
+// beside its first K loads, and a last slice of workgroups (one per cache) merges the outputs: the pass
+// takes the place of the combine kernel.  That saves a launch (eight tracked calls over 67 MB of fp32
+// caches, D = 64: 222 -> 203 us), but each workgroup pays for the merge, so launches of more workgroups than
+// compute units keep the kernel (128 caches, D = 128, eight query heads: 783 us with it, 832 without).
 constexpr int kScoreTile = 256;
-template <typename T, int D, int GT>
+template <typename T, int D, int GT, bool MERGE>
 __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
   constexpr int EPL = Row<T>::EPL;
   constexpr int LPR = D / EPL;
@@ -335,9 +341,13 @@ __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
   static_assert(U <= LPR, "one lane of a row per row in flight");
   const Item it = p.items[blockIdx.x];
   const int G = p.G;
-  const int cnt = min(it.start + it.count, p.len[it.c]) - it.start;
+  // (the merge advances len itself)
+  const int n = MERGE ? p.rows[(int64_t)it.c * kLagCalls] : p.len[it.c];
+  const bool merge = MERGE && blockIdx.y == gridDim.y - 1;
+  if (merge && (it.start != 0 || it.nsplit == 1)) return;
+  const int cnt = merge ? 0 : min(it.start + it.count, n) - it.start;
   const int r_begin = blockIdx.y * kScoreTile;
-  if (r_begin >= cnt) return;
+  if (!merge && r_begin >= cnt) return;
   const int r_end = min(cnt, r_begin + kScoreTile);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPR, rg = lane / LPR;
@@ -350,8 +360,46 @@ __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
   int r0 = r_begin + wave * (U * RPW);
   if (r0 < r_end) load_tile(r0);
   const int c_rel = it.c - p.cache_begin;
-  const T* qrows = reinterpret_cast<const T*>(p.q) +
-                   ((int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G) * D;
+  const int64_t qrow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
+  // (max, 1 / sum) of every query head over the cache's work items
+  __shared__ float sm_m[GT], sm_inv[GT];
+  if (!MERGE) {
+    // final_ml, read below
+  } else if (it.nsplit > 1) {
+    for (int g = wave; g < G; g += 4) {
+      float m = kNegInf, l = 0.f;
+      for (int s = lane; s < it.nsplit; s += 64) m = fmaxf(m, p.part_ml[((int64_t)(it.slot0 + s) * G + g) * 2]);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+      m = (m == kNegInf) ? 0.f : m;
+      for (int s = lane; s < it.nsplit; s += 64) {
+        const float* ml = p.part_ml + ((int64_t)(it.slot0 + s) * G + g) * 2;
+        l += ml[1] * fast_exp2(ml[0] - m);
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+      if (lane == 0) { sm_m[g] = m; sm_inv[g] = 1.f / l; }
+    }
+  } else if ((int)threadIdx.x < G) {
+    sm_m[threadIdx.x] = p.ml[((int64_t)it.c * G + threadIdx.x) * 2];
+    sm_inv[threadIdx.x] = p.ml[((int64_t)it.c * G + threadIdx.x) * 2 + 1];
+  }
+  if (MERGE) __syncthreads();
+  if (merge) {
+    // out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), as in the combine kernel
+    for (int idx = threadIdx.x; idx < G * D; idx += 256) {
+      const int g = idx / D, d = idx % D;
+      const float m = sm_m[g];
+      float o = 0.f;
+#pragma unroll 8
+      for (int s = it.slot0; s < it.slot0 + it.nsplit; ++s)
+        o += p.part_o[((int64_t)s * G + g) * D + d] * fast_exp2(p.part_ml[((int64_t)s * G + g) * 2] - m);
+      p.out[(qrow0 + g) * D + d] = o * sm_inv[g];
+    }
+    if (threadIdx.x == 0) p.len[it.c] = n;  // a fused append's row is now counted
+    return;
+  }
+  const T* qrows = reinterpret_cast<const T*>(p.q) + qrow0 * D;
   float qr[GT][EPL], M[GT], inv[GT];
 #pragma unroll
   for (int g = 0; g < GT; ++g) {
@@ -363,8 +411,8 @@ __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
       Row<T>::widen(*reinterpret_cast<const uint4*>(qrows + g * D + sub * EPL), qr[g]);
 #pragma unroll
       for (int e = 0; e < EPL; ++e) qr[g][e] *= p.scale_log2e;
-      M[g] = p.ml[((int64_t)it.c * G + g) * 2];
-      inv[g] = p.ml[((int64_t)it.c * G + g) * 2 + 1];
+      M[g] = MERGE ? sm_m[g] : p.ml[((int64_t)it.c * G + g) * 2];
+      inv[g] = MERGE ? sm_inv[g] : p.ml[((int64_t)it.c * G + g) * 2 + 1];
     }
   }
   float* sc = p.score + it.row0;
@@ -466,23 +514,30 @@ hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t
   return hipGetLastError();
 }
 
-template <typename T, int D>
+template <typename T, int D, bool MERGE>
 hipError_t launch_score_g(const ScoreParams& p, const dim3& grid, hipStream_t s) {
-  if (p.G <= 2) score_pass_kernel<T, D, 2><<<grid, dim3(256), 0, s>>>(p);
-  else if (p.G <= 4) score_pass_kernel<T, D, 4><<<grid, dim3(256), 0, s>>>(p);
-  else if (p.G <= 8) score_pass_kernel<T, D, 8><<<grid, dim3(256), 0, s>>>(p);
+  if (p.G <= 2) score_pass_kernel<T, D, 2, MERGE><<<grid, dim3(256), 0, s>>>(p);
+  else if (p.G <= 4) score_pass_kernel<T, D, 4, MERGE><<<grid, dim3(256), 0, s>>>(p);
+  else if (p.G <= 8) score_pass_kernel<T, D, 8, MERGE><<<grid, dim3(256), 0, s>>>(p);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items, int max_count, hipStream_t s) {
-  if (n_items <= 0 || max_count <= 0) return hipSuccess;
-  const dim3 grid(n_items, (max_count + kScoreTile - 1) / kScoreTile);
-  if (dtype == 0 && D == 128) return launch_score_g<uint16_t, 128>(p, grid, s);
-  if (dtype == 0 && D == 64) return launch_score_g<uint16_t, 64>(p, grid, s);
-  if (dtype == 1 && D == 128) return launch_score_g<float, 128>(p, grid, s);
-  if (dtype == 1 && D == 64) return launch_score_g<float, 64>(p, grid, s);
+template <bool MERGE>
+hipError_t launch_score(const ScoreParams& p, int dtype, int D, const dim3& grid, hipStream_t s) {
+  if (dtype == 0 && D == 128) return launch_score_g<uint16_t, 128, MERGE>(p, grid, s);
+  if (dtype == 0 && D == 64) return launch_score_g<uint16_t, 64, MERGE>(p, grid, s);
+  if (dtype == 1 && D == 128) return launch_score_g<float, 128, MERGE>(p, grid, s);
+  if (dtype == 1 && D == 64) return launch_score_g<float, 64, MERGE>(p, grid, s);
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items, int max_count, bool merge,
+                             hipStream_t s) {
+  if (n_items <= 0 || max_count <= 0) return hipSuccess;
+  const int tiles = (max_count + kScoreTile - 1) / kScoreTile;
+  return merge ? launch_score<true>(p, dtype, D, dim3(n_items, tiles + 1), s)
+               : launch_score<false>(p, dtype, D, dim3(n_items, tiles), s);
 }
 
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s) {

@@ -253,6 +253,58 @@ def test_deferred_score_updates_with_half_size_rows(Hq, Hkv, target):
     arena.close()
 
 
+@pytest.mark.parametrize("D,Hq,target", [(64, 2, 256), (64, 8, 7), (128, 6, 40), (64, 2, 300)])
+def test_score_pass_merges_the_partials_of_small_launches(D, Hq, target):
+    """fp32 caches, tracked: launches of at most one workgroup per compute unit merge the split partials in
+    the score pass (caches with one, two and more than 64 work items side by side), larger ones in the
+    combine kernel; fused appends into a cache that is full keep its length."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="merge", L=2, Hq=Hq, Hkv=2, D=D, batch=1, seed=93 + Hq, sink=1, recent=1,
+                     slack=3)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    budgets = [200, 500, 20000, 2]
+    arena = H.make_arena(w, budgets, track=True)
+    arena.set_option(B.OPT_CHUNK_TOKENS, 256)
+    arena.set_option(B.OPT_CHUNK_TOKENS_WHOLE, 256)
+    arena.set_option(B.OPT_TARGET_ITEMS, target)
+    arena.set_option(B.OPT_TARGET_ITEMS_WHOLE, target)
+    st = H.fill_from_host(arena, w, budgets, rng, scores="uniform")
+    caches = [H.oracle_cache(w, st, c) for c in range(arena.n_caches)]
+    dev = arena.device
+    for t in range(1, 4):
+        q, q64 = H.make_q(w, rng, w.L)
+        knew, vnew = (synth.payload(rng, (w.L, w.batch, w.Hkv, w.D), w.dtype) for _ in range(2))
+        kd, vd, qd = (H.to_device_storage(a, w.dtype, dev) for a in (knew, vnew, q))
+        outd = torch.full((w.L, w.batch, w.Hq, w.D), float("nan"), dtype=torch.float32, device=dev)
+        if t == 2:
+            arena.append_decode_attn(0, w.L, kd, vd, 50 + t, qd, outd)
+        else:
+            for l in range(w.L):
+                arena.append_decode_attn(l, 1, kd[l], vd[l], 50 + t, qd[l], outd[l])
+        torch.cuda.synchronize()
+        out = outd.cpu().numpy().astype(np.float64)
+        for c in range(arena.n_caches):
+            l, b, hs = H.q_rows_of_cache(w, c)
+            ref, _, _ = O.decode_step(caches[c], q64[l, b, hs], knew[l, b, c % 2].astype(np.float64),
+                                      vnew[l, b, c % 2].astype(np.float64), 50 + t, t, budget=0, sink=0, recent=0, interval=0,
+                                      track_scores=True)
+            assert np.max(np.abs(out[l, b, hs] - ref)) <= 2e-5, (t, c)    # fp32 throughout
+    post = H.download(arena, w)
+    for c in range(arena.n_caches):
+        assert post.K[c].shape[0] == caches[c].n
+        assert np.max(np.abs(post.score[c] - caches[c].score[:caches[c].n])) <= 2e-5, c
+    # every cache is full now: the replayable form attends them as they stand, scores included
+    pos = torch.full((1,), 99, dtype=torch.int32, device=dev)
+    arena.append_decode_attn_replay(0, w.L, kd, vd, pos, qd, outd)
+    torch.cuda.synchronize()
+    assert arena.len.cpu().tolist() == arena.cap_host.tolist()
+    after = H.download(arena, w)
+    for c in range(arena.n_caches):
+        gain = after.score[c].astype(np.float64).sum() - post.score[c].astype(np.float64).sum()
+        assert abs(gain - w.G) <= 1e-2, c          # fp32 sums of up to 20003 scores around 0.5
+    arena.close()
+
+
 def test_scores_sum_to_G_per_step_without_eviction():
     """Each query head's softmax weights sum to 1, so a cache's scores grow by exactly G per step."""
     H = _h()
