@@ -293,7 +293,9 @@ int baklava_sync_lengths(baklava_ctx* ctx, void* stream);
  * function: a pass over the K rows of the layer range alone.  After it the score plane of the
  * range holds every weight up to the latest call; without it the plane lacks at most the weights
  * of the calls on record, never anything else.  baklava_compact does this itself before it ranks
- * rows; baklava_reset and baklava_set_lengths drop what is on record.  The rows a recorded call
+ * rows; baklava_reset and baklava_set_lengths drop what is on record.  Only calls over bf16 rows of 128
+ * elements that take the MFMA kernel are recorded; all others (fp32, rows of 64 elements, BAKLAVA_OPT_KERNEL
+ * = 1) add their weights before they end, so that the plane is current.  The rows a recorded call
  * attended must keep their places until its weights are added: the library's own calls see to
  * that; a caller that rewrites arena rows itself calls baklava_set_lengths afterwards.
  * No-op without track_scores.  Enqueues kernels on `stream`, does not synchronise.

@@ -261,10 +261,10 @@ bool range_ok(const baklava_ctx* ctx, int32_t lb, int32_t lc) {
 }
 
 // The weights of the calls on record go to the score plane now (see DecodeParams): a pass over the
-// K rows of the layer range, after which the records are empty.  Only the MFMA attention kernel
-// (bf16) leaves calls on record.
+// K rows of the layer range, after which the records are empty.  Only the MFMA attention kernel over rows of
+// 128 elements leaves calls on record.
 int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hipStream_t s) {
-  if (!ctx->d.track_scores || ctx->d.dtype != BAKLAVA_BF16) return BAKLAVA_OK;
+  if (!ctx->d.track_scores || !(ctx->d.dtype == BAKLAVA_BF16 && ctx->d.D == 128)) return BAKLAVA_OK;
   const int64_t c0 = (int64_t)layer_begin * ctx->cpl;
   const int64_t c1 = c0 + (int64_t)layer_count * ctx->cpl;
   const int which = (layer_begin == 0 && layer_count == ctx->d.L) ? 1 : 0;
@@ -281,13 +281,13 @@ int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hi
   p.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)ctx->d.D));
   const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
                                             sc.max_count.begin() + layer_begin + layer_count);
-  if (!hip_ok(launch_score_flush_mfma(p, ctx->d.D, i1 - i0, longest, s))) return BAKLAVA_EHIP;
+  if (!hip_ok(launch_score_flush_mfma(p, i1 - i0, longest, s))) return BAKLAVA_EHIP;
   if (!hip_ok(launch_fill_i32(p.lag_cnt + c0 * ctx->G, 0, (c1 - c0) * ctx->G, s))) return BAKLAVA_EHIP;
   return BAKLAVA_OK;
 }
 
-// The vector-ALU path's score update for the call that has just been enqueued, with the merge of its split
-// partials if asked for.
+// The score update of calls that leave no record, for the one that has just been enqueued, with the merge of
+// its split partials if asked for.
 int score_pass(baklava_ctx* ctx, const DecodeParams& d, int n_items, bool merge, int longest, hipStream_t s) {
   ScoreParams p;
   p.k = d.k; p.q = d.q; p.out = d.out;
@@ -323,9 +323,12 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   hipStream_t s = (hipStream_t)stream;
   const bool use_mfma = ctx->kernel_pref == 2 || (ctx->kernel_pref == 0 && ctx->d.dtype == BAKLAVA_BF16);
   const bool track = ctx->track_on;
-  // The vector-ALU kernel adds its weights right after the call; weights an earlier MFMA call left
-  // pending come first, so that the scores grow in the order of the calls.
-  if (track && !use_mfma) {
+  // Scores are deferred over rows of 128 elements only: those of 64 have always been current when a call
+  // returns, and callers read them, set them or declare new lengths between calls without a flush.
+  const bool defer = track && use_mfma && ctx->d.D == 128;
+  // Other calls add their weights right away; weights an earlier call left pending come first, so that the
+  // scores grow in the order of the calls.
+  if (track && !defer) {
     const int st = flush_records(ctx, layer_begin, layer_count, s);
     if (st != BAKLAVA_OK) return st;
   }
@@ -352,13 +355,13 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   p.status = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.status);
   p.G = ctx->G; p.Hq = ctx->d.Hq; p.Hkv = ctx->d.Hkv; p.batch = ctx->d.batch;
   p.cache_begin = (int32_t)c0;
-  p.lag = (track && use_mfma) ? 1 : 0;
+  p.lag = defer ? 1 : 0;
   p.lag_batch = kLagRows >> ctx->lag_gp_log2;
   p.lag_gp_log2 = ctx->lag_gp_log2;
   p.ring_slots = 0;
   // vector kernel, scores tracked: the score pass also does the combine kernel's work in small launches
-  const bool scores_now = track && !use_mfma;
-  const bool merge = scores_now && m1 > m0 && i1 - i0 <= ctx->n_cus;
+  const bool scores_now = track && !defer;
+  const bool merge = scores_now && !use_mfma && m1 > m0 && i1 - i0 <= ctx->n_cus;
   p.keep_rows = merge ? 1 : 0;
   p.fused_append = fused ? 1 : 0;
   p.token_pos = token_pos;
@@ -538,7 +541,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     const int st = build_tiles(ctx);
     if (st != BAKLAVA_OK) { delete ctx; return st; }
   }
-  if (desc->dtype == BAKLAVA_BF16 && !hip_ok(prepare_decode_mfma(desc->D))) { delete ctx; return BAKLAVA_EHIP; }
+  if (desc->dtype == BAKLAVA_BF16 && desc->D == 128 && !hip_ok(prepare_decode_mfma())) { delete ctx; return BAKLAVA_EHIP; }
   int st = build_schedule(ctx, 0, ctx->layer_one_wave ? kDefaultChunk : kDefaultChunkWhole);
   if (st == BAKLAVA_OK) st = build_schedule(ctx, 1, kDefaultChunkWhole);
   if (st != BAKLAVA_OK) { delete ctx; return st; }

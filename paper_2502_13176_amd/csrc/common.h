@@ -111,7 +111,7 @@ struct DecodeParams {
   float scale_log2e;               // log2(e) / sqrt(D)
 };
 
-// Score pass of the vector-ALU path over the K rows alone, right after its attention kernel:
+// Score pass over the K rows alone, right after the attention kernel of a call that leaves no record:
 // score_j += sum_g 2^(q_g . k_j scale - M_g) / L_g over the live rows of every cache of the range.  With
 // `merge` it merges the split partials as well, in place of the combine kernel.
 struct ScoreParams {
@@ -203,10 +203,10 @@ hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_ite
 // compute unit, so a workgroup may take the whole LDS (score tracking keeps its new scores there)
 hipError_t launch_decode_mfma(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s,
                               hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-hipError_t prepare_decode_mfma(int D);
-// the weights of the calls on record, from the K rows alone (bf16; needs only the lag_*,
+hipError_t prepare_decode_mfma();
+// the weights of the calls on record, from the K rows alone (bf16, D = 128; needs only the lag_*,
 // k, score, items, G and scale fields)
-hipError_t launch_score_flush_mfma(const DecodeParams& p, int D, int n_items, int max_count, hipStream_t s);
+hipError_t launch_score_flush_mfma(const DecodeParams& p, int n_items, int max_count, hipStream_t s);
 hipError_t launch_profile_similarity(const void* q, const void* k, const void* v, int batch, int Hq, int Hkv,
                                      int T, float* cos_out, float* sim_out, float* lse_out, float* tile_sum,
                                      hipStream_t s);

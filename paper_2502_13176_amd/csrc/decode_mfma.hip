@@ -36,7 +36,8 @@
 // the scores are touched only on every (32 / G)-th call (every 8th at G <= 4).  On such a call the
 // scores of a slab are read with the slab and the new values wait in LDS until the work item is
 // done, so the extra HBM writes (4 bytes per row) fall at the end of a launch instead of between
-// the K/V reads.
+// the K/V reads.  This is for D = 128; at D = 64 a pass over the K rows right after the call keeps the
+// scores current.
 #include <hip/hip_ext.h>
 
 #include "common.h"
@@ -54,9 +55,9 @@ typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kSlab = 32;       // rows per wavefront iteration
 
-// What follows from the head dimension.  (D = 64: eight tracked launches over 67 MB of 64 caches each take
-// 178, 182 and 186 us at one, four and eight query heads per cache; the vector-ALU kernel and its score
-// pass took 218, 280 and 430.)
+// What follows from the head dimension.  (D = 64: a tracked call over 32 caches of 2500 rows, score pass
+// included, takes 14.3 us at four query heads per cache and 17.5 at eight; with the vector-ALU kernel 22.6 and
+// 31.2.  Records like those of D = 128 would make it 12.5 and 13.8.)
 template <int D>
 struct Shape {
   // A slab of 64-element rows is half as many bytes, so a workgroup has twice as many wavefronts: the
@@ -94,24 +95,22 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(u32x4_t x) { return __builtin_bit_
 constexpr int kSets = 2;
 constexpr int kRecRows = 16 * kSets;  // packed rows of a record
 constexpr int kRecCalls = 8;          // most calls a record holds (G <= 4)
-template <int D>
 struct Record {
-  bf16x8_t q[kSets][Shape<D>::kChunks];
+  bf16x8_t q[kSets][Shape<128>::kChunks];
   float m[kSets][4], inv[kSets][4];
   int n_slot[kSets];
 };
 
-template <int D>
 __device__ __forceinline__ void load_record(const DecodeParams& p, int c, int G, int pending, int n16, int jg,
-                                            Record<D>& r) {
-  constexpr int kRow = Shape<D>::kRow;
+                                            Record& r) {
+  constexpr int kRow = Shape<128>::kRow;
   const int gp_mask = (1 << p.lag_gp_log2) - 1;
   const unsigned char* lq = reinterpret_cast<const unsigned char*>(p.lag_q) + (int64_t)c * kRecRows * kRow;
 #pragma unroll
   for (int e = 0; e < kSets; ++e) {
     const int R = 16 * e + n16;  // the packed row this lane holds a part of
 #pragma unroll
-    for (int ch = 0; ch < Shape<D>::kChunks; ++ch) {
+    for (int ch = 0; ch < Shape<128>::kChunks; ++ch) {
       u32x4_t raw = {0u, 0u, 0u, 0u};  // rows beyond the G heads of a call, calls not on record: zero
       if ((R & gp_mask) < G && (R >> p.lag_gp_log2) < pending)
         raw = *reinterpret_cast<const u32x4_t*>(lq + R * kRow + ch * 64 + jg * 16);
@@ -137,8 +136,7 @@ __device__ __forceinline__ void load_record(const DecodeParams& p, int c, int G,
 // sum over calls and heads of 2^(s' - M') / L' for the rows a call saw.  sp[e][T] holds the logits of
 // operand e and tile T as the product left them.  On return lane l < 32 holds the weight of row l of
 // the slab.
-template <int D>
-__device__ __forceinline__ float record_weights(const floatx4_t (&sp)[kSets][2], const Record<D>& r, float cs,
+__device__ __forceinline__ float record_weights(const floatx4_t (&sp)[kSets][2], const Record& r, float cs,
                                                 int row_first, int lane) {
   const int n16 = lane & 15;
   float w[2];
@@ -161,6 +159,7 @@ __device__ __forceinline__ float record_weights(const floatx4_t (&sp)[kSets][2],
 
 template <int D, bool LAG>
 __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(DecodeParams p) {
+  static_assert(D == 128 || !LAG, "records hold rows of 128 elements");
   using S = Shape<D>;
   constexpr int kWaves = S::kWaves, kRow = S::kRow, kVStride = S::kVStride, kKStride = S::kKStride;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves * kSlab * kVStride];
@@ -186,7 +185,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
   // Recorded calls (LAG).  When the record is full this call adds their weights to the scores.
   const int pending = LAG ? p.lag_cnt[(int64_t)it.c * G] : 0;
   const bool apply = LAG && pending >= p.lag_batch;
-  Record<D> rec;
+  Record rec;
   if (LAG && apply) load_record(p, it.c, G, pending, n16, jg, rec);
   if (p.fused_append) {
     if (add) append_new_row(p, it, n_old, off_c, token_pos);
@@ -401,7 +400,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
   }
   if (APPLY && ring_n > 0) flush_ring();
   };  // stream_rows
-  if (LAG && apply) stream_rows(std::true_type{});
+  if (LAG && apply) stream_rows(std::integral_constant<bool, LAG>{});
   else stream_rows(std::false_type{});
 #undef BAKLAVA_LD
 #undef BAKLAVA_LOAD_K
@@ -438,9 +437,8 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
 // product and the same weights as in the attention kernel, and the same route for K (whole rows
 // from HBM, staged in a wave-private LDS region, one slab ahead) and for the scores (read with the
 // slab, new values kept in LDS until the work item is done).
-template <int D>
-__global__ __launch_bounds__(64 * Shape<D>::kWaves) void score_flush_mfma(DecodeParams p) {
-  using S = Shape<D>;
+__global__ __launch_bounds__(64 * Shape<128>::kWaves) void score_flush_mfma(DecodeParams p) {
+  using S = Shape<128>;
   constexpr int kWaves = S::kWaves, kRow = S::kRow, kKStride = S::kKStride;
   __shared__ __attribute__((aligned(16))) unsigned char lds_k[kWaves * kSlab * kKStride];
   extern __shared__ __attribute__((aligned(16))) float lds_ring[];
@@ -455,7 +453,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves) void score_flush_mfma(Decode
     if (s < pending) n_seen = max(n_seen, p.lag_n[(int64_t)it.c * kRecCalls + s]);
   const int cnt = min(it.start + it.count, n_seen) - it.start;
   if (cnt <= 0) return;
-  Record<D> rec;
+  Record rec;
   load_record(p, it.c, G, pending, n16, jg, rec);
   const int last = cnt - 1;
   const unsigned char* Kb = reinterpret_cast<const unsigned char*>(p.k) + it.row0 * kRow;
@@ -528,77 +526,62 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves) void score_flush_mfma(Decode
 // Dynamic LDS the attention kernel may ask for: the whole LDS of a CU minus the static staging areas
 // when a workgroup has the CU to itself, half of what two workgroups leave otherwise.
 constexpr int kLdsTotal = 160 * 1024;
-template <int D> constexpr int dyn_max() { return kLdsTotal - Shape<D>::kStatic - 512; }
-template <int D> constexpr int dyn_shared() { return (kLdsTotal - 2 * Shape<D>::kStatic - 1024) / 2; }
-static_assert(dyn_shared<128>() >= Shape<128>::kWaves * kSlab * 4, "room for one slab of scores per wavefront");
-static_assert(dyn_shared<64>() >= Shape<64>::kWaves * kSlab * 4, "room for one slab of scores per wavefront");
+constexpr int kStatic = Shape<128>::kStatic;
+constexpr int kDynMax = kLdsTotal - kStatic - 512;
+constexpr int kDynShared = (kLdsTotal - 2 * kStatic - 1024) / 2;
+static_assert(kDynShared >= Shape<128>::kWaves * kSlab * 4, "room for one slab of scores per wavefront");
 constexpr int kFlushDynMax = 48 * 1024;  // the flush kernel's share for waiting scores, beside its K staging area
 
-// Called when a context is created on the current device, i.e. outside any stream capture: raises
-// the kernels' dynamic-LDS limits once, so that launches (captured or not) only launch.
-template <int D>
-hipError_t raise_limits() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_mfma<D, true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, dyn_max<D>());
+// Called when a context that may leave records is created on the current device, i.e. outside any stream
+// capture: raises the kernels' dynamic-LDS limits once, so that launches (captured or not) only launch.
+hipError_t prepare_decode_mfma() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_mfma<128, true>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kDynMax);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(score_flush_mfma<D>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(score_flush_mfma),
                              hipFuncAttributeMaxDynamicSharedMemorySize, kFlushDynMax);
 }
-hipError_t prepare_decode_mfma(int D) { return D == 128 ? raise_limits<128>() : raise_limits<64>(); }
 
 // Slabs per wavefront whose new scores fit `bytes` of LDS, at most what the longest item needs.
-template <int D>
 int ring_slots(int bytes, int max_count) {
-  constexpr int kWaves = Shape<D>::kWaves;
+  constexpr int kWaves = Shape<128>::kWaves;
   const int need = ((max_count + kSlab - 1) / kSlab + kWaves - 1) / kWaves;
   return std::max(1, std::min(bytes / (kWaves * kSlab * 4), need));
 }
 
 // With a pair of events the kernel's own dispatch carries them: they take the time stamps of its
 // first and last wavefront, not those of commands placed around it on the stream.
-template <int D>
-hipError_t launch_attention(DecodeParams p, int n_items, int max_count, bool one_wave, hipStream_t s, hipEvent_t ev0,
-                            hipEvent_t ev1) {
+template <int D, bool LAG>
+hipError_t launch_attention(const DecodeParams& p, int n_items, size_t dyn, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const dim3 grid(n_items), block(64 * Shape<D>::kWaves);
-  const bool timed = ev0 && ev1;
-  p.ring_slots = 0;
-  if (!p.lag) {
-    if (timed) hipExtLaunchKernelGGL((decode_partial_mfma<D, false>), grid, block, 0, s, ev0, ev1, 0, p);
-    else decode_partial_mfma<D, false><<<grid, block, 0, s>>>(p);
-    return hipGetLastError();
-  }
-  // the LDS left beside the staging areas, split over the wavefronts; a launch of several waves of
-  // workgroups keeps room for two workgroups per compute unit
-  p.ring_slots = ring_slots<D>(one_wave ? dyn_max<D>() : dyn_shared<D>(), max_count);
-  const size_t dyn = (size_t)p.ring_slots * Shape<D>::kWaves * kSlab * 4;
-  if (timed) hipExtLaunchKernelGGL((decode_partial_mfma<D, true>), grid, block, dyn, s, ev0, ev1, 0, p);
-  else decode_partial_mfma<D, true><<<grid, block, dyn, s>>>(p);
+  if (ev0 && ev1) hipExtLaunchKernelGGL((decode_partial_mfma<D, LAG>), grid, block, dyn, s, ev0, ev1, 0, p);
+  else decode_partial_mfma<D, LAG><<<grid, block, dyn, s>>>(p);
   return hipGetLastError();
 }
 
-template <int D>
-hipError_t launch_flush(DecodeParams p, int n_items, int max_count, hipStream_t s) {
-  p.ring_slots = ring_slots<D>(kFlushDynMax, max_count);
-  score_flush_mfma<D><<<dim3(n_items), dim3(64 * Shape<D>::kWaves),
-                        (size_t)p.ring_slots * Shape<D>::kWaves * kSlab * 4, s>>>(p);
-  return hipGetLastError();
-}
-
-hipError_t launch_decode_mfma(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s,
+hipError_t launch_decode_mfma(const DecodeParams& p_in, int D, int n_items, int max_count, bool one_wave, hipStream_t s,
                               hipEvent_t ev0, hipEvent_t ev1) {
   if (n_items <= 0) return hipSuccess;
-  if (p.G > 16) return hipErrorInvalidValue;
-  if (D == 128) return launch_attention<128>(p, n_items, max_count, one_wave, s, ev0, ev1);
-  if (D == 64) return launch_attention<64>(p, n_items, max_count, one_wave, s, ev0, ev1);
-  return hipErrorInvalidValue;
+  if (p_in.G > 16 || (D != 128 && (D != 64 || p_in.lag))) return hipErrorInvalidValue;
+  DecodeParams p = p_in;
+  p.ring_slots = 0;
+  if (D == 64) return launch_attention<64, false>(p, n_items, 0, s, ev0, ev1);
+  if (!p.lag) return launch_attention<128, false>(p, n_items, 0, s, ev0, ev1);
+  // the LDS left beside the staging areas, split over the wavefronts; a launch of several waves of
+  // workgroups keeps room for two workgroups per compute unit
+  p.ring_slots = ring_slots(one_wave ? kDynMax : kDynShared, max_count);
+  const size_t dyn = (size_t)p.ring_slots * Shape<128>::kWaves * kSlab * 4;
+  return launch_attention<128, true>(p, n_items, dyn, s, ev0, ev1);
 }
 
-hipError_t launch_score_flush_mfma(const DecodeParams& p, int D, int n_items, int max_count, hipStream_t s) {
+hipError_t launch_score_flush_mfma(const DecodeParams& p_in, int n_items, int max_count, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  if (p.G > 16) return hipErrorInvalidValue;
-  if (D == 128) return launch_flush<128>(p, n_items, max_count, s);
-  if (D == 64) return launch_flush<64>(p, n_items, max_count, s);
-  return hipErrorInvalidValue;
+  if (p_in.G > 16) return hipErrorInvalidValue;
+  DecodeParams p = p_in;
+  p.ring_slots = ring_slots(kFlushDynMax, max_count);
+  const size_t dyn = (size_t)p.ring_slots * Shape<128>::kWaves * kSlab * 4;
+  score_flush_mfma<<<dim3(n_items), dim3(64 * Shape<128>::kWaves), dyn, s>>>(p);
+  return hipGetLastError();
 }
 
 }  // namespace baklava

@@ -319,7 +319,8 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeParams p) {
 
 // score_j += sum_g 2^(q_g . k_j scale - M_g) / L_g  (cumulative attention per cached token, summed
 // over the query heads that share the cache), from the K rows alone once the normalisers of the
-// call are final: the vector-ALU path's score update, launched right after its attention call.
+// call are final: the score update of the vector-ALU path and of bf16 rows of 64 elements, launched right
+// after the attention kernel.
 // Workgroup (x, y) updates rows [y * kScoreTile, +kScoreTile) of work item x, so that long work
 // items still spread over many workgroups.  Row layout as in the attention kernel above: a row
 // over D / EPL lanes, 64 / (D / EPL) rows per wavefront load; a wavefront keeps eight of them in

@@ -203,10 +203,10 @@ def test_deferred_score_updates_over_windows_of_steps(base, Hq, Hkv, batch, targ
 
 
 @pytest.mark.parametrize("Hq,Hkv,target", [(4, 4, -1), (6, 2, 3), (8, 1, 0)])
-def test_deferred_score_updates_with_half_size_rows(Hq, Hkv, target):
-    """bf16 rows of 64 elements take the matrix kernel and its deferred score update: 21 steps without a
-    read-back (records of 8 and of 4 calls fill and are applied), a switch to the vector kernel and back,
-    then the scores against the oracle's own run and the eviction that follows."""
+def test_score_updates_with_half_size_rows(Hq, Hkv, target):
+    """bf16 rows of 64 elements take the matrix kernel and the score pass: 21 steps without a read-back, a
+    switch to the vector kernel and back, then the scores against the oracle's own run and the eviction that
+    follows."""
     H = _h()
     w = synth.shrink(synth.WORKLOADS["long"], name="lag64", L=2, Hq=Hq, Hkv=Hkv, D=64, batch=2, ctx=2048, lo=96,
                      hi=2048, interval=24, slack=24, sink=4, recent=16, seed=177 + Hq)
@@ -530,3 +530,56 @@ def test_tiled_selection_threshold_does_not_change_the_result():
         results.append(kept_dev.cpu().numpy())
         arena.close()
     assert np.array_equal(results[0], results[1]) and np.array_equal(results[0], results[2])
+
+
+@pytest.mark.parametrize("Hq,Hkv,target", [(2, 2, -1), (6, 2, 3), (8, 1, 0)])
+def test_scores_of_half_size_rows_are_current_after_every_call(Hq, Hkv, target):
+    """bf16 rows of 64 elements: nothing is owed to the score plane when a call returns.  The plane is read
+    without a flush after every call; the caller then sets scores of its own, and declares the lengths anew:
+    neither loses a weight or receives an earlier call's."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["long"], name="now64", L=2, Hq=Hq, Hkv=Hkv, D=64, batch=2, ctx=2048, lo=96,
+                     hi=2048, interval=24, slack=24, sink=4, recent=16, seed=277 + Hq)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    budgets = synth.budgets_for(w, B.alloc_proportional)
+    arena = H.make_arena(w, budgets, track=True)
+    if target >= 0:
+        H.set_chunk(arena, 256)
+        arena.set_option(B.OPT_TARGET_ITEMS, target)
+        arena.set_option(B.OPT_TARGET_ITEMS_WHOLE, target)
+    cpl = w.batch * w.Hkv
+    st = H.fill_from_host(arena, w, [budgets[(c // cpl) * w.Hkv + c % w.Hkv] for c in range(arena.n_caches)], rng)
+    caches = [H.oracle_cache(w, st, c) for c in range(arena.n_caches)]
+    dev = arena.device
+    pos = torch.zeros((1,), dtype=torch.int32, device=dev)
+    for t in range(1, 11):
+        q, q64 = H.make_q(w, rng, w.L)
+        knew, vnew = (synth.payload(rng, (w.L, w.batch, w.Hkv, w.D), w.dtype) for _ in range(2))
+        kd, vd, qd = (H.to_device_storage(a, w.dtype, dev) for a in (knew, vnew, q))
+        outd = torch.full((w.L, w.batch, w.Hq, w.D), float("nan"), dtype=torch.float32, device=dev)
+        if t % 4 == 0:
+            arena.append_decode_attn(0, w.L, kd, vd, t, qd, outd)
+        elif t % 4 == 1:
+            pos.fill_(t)
+            arena.append_decode_attn_replay(0, w.L, kd, vd, pos, qd, outd)
+            arena.sync_lengths()
+        else:
+            for l in range(w.L):
+                arena.append_decode_attn(l, 1, kd[l], vd[l], t, qd[l], outd[l])
+        torch.cuda.synchronize()
+        out = outd.cpu().numpy().astype(np.float64)
+        k64, v64 = synth.storage_to_f64(knew, w.dtype), synth.storage_to_f64(vnew, w.dtype)
+        now = H.download(arena, w, flush=False)
+        for c in range(arena.n_caches):
+            l, b, hs = H.q_rows_of_cache(w, c)
+            ref, _, _ = O.decode_step(caches[c], q64[l, b, hs], k64[l, b, c % w.Hkv], v64[l, b, c % w.Hkv], t, t,
+                                      budget=0, sink=0, recent=0, interval=0, track_scores=True)
+            assert np.max(np.abs(out[l, b, hs] - ref)) <= 1e-5, (t, c)
+            assert np.max(np.abs(now.score[c] - caches[c].score[:caches[c].n])) <= 1e-5, (t, c)
+        if t == 3:
+            arena.set_lengths(arena.lengths())
+        if t == 6:
+            arena.score.zero_()
+            for oc in caches:
+                oc.score[:] = 0.0
+    arena.close()
