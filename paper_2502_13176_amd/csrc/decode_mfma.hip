@@ -78,6 +78,7 @@ struct Shape {
   static constexpr int kStatic = kWaves * kSlab * (kVStride + kKStride);  // staging areas of a workgroup
 };
 constexpr float kNegInf = -__builtin_huge_valf();
+constexpr float kLowest = -3.402823466e38f;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -205,7 +206,9 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
   floatx4_t o[S::kBlocks];
 #pragma unroll
   for (int b = 0; b < S::kBlocks; ++b) o[b] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  float m_run = kNegInf;  // running max of head n16, log2 units, equal in the 4 lanes of a head
+  // Running max of head n16, log2 units, equal in the 4 lanes of a head.  It starts at the lowest finite value,
+  // so that rows with a logit of -inf weigh 2^-inf = 0 and not 2^(-inf + inf), also before the first finite one.
+  float m_run = kLowest;
   float l_part = 0.f;     // this lane's share of the running sum
   const float cs = p.scale_log2e;
 
@@ -351,7 +354,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
     if (__any(mx > m_run)) {
       mx = fmaxf(mx, __shfl_xor(mx, 16));
       mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float mn = fmaxf(m_run, mx);  // finite: row t0 is live and belongs to this slab
+      const float mn = fmaxf(m_run, mx);
       const float alpha = fast_exp2(m_run - mn);
       m_run = mn;
       l_part *= alpha;

@@ -354,3 +354,28 @@ def test_matrix_kernel_with_half_size_rows(Hq, Hkv):
     with pytest.raises(B.BaklavaError):          # forcing it is still for rows of 128 elements only
         arena.set_option(B.OPT_KERNEL, B.KERNEL_MFMA)
     arena.close()
+
+
+@pytest.mark.parametrize("D,kernel", [(64, B.KERNEL_AUTO), (64, B.KERNEL_VALU), (128, B.KERNEL_MFMA), (128, B.KERNEL_VALU)])
+def test_rows_whose_logits_are_minus_infinity(D, kernel):
+    """Keys of the type's lowest value (a mask) give logits of -inf: such rows carry no weight, wherever they
+    fill a wavefront's first rows, a work item's, or all but one row of a cache."""
+    H = _h()
+    lens = [40, 300, 700, 1300]
+    masked = [39, 64, 512, 1299]                   # rows in front
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="masked", L=1, Hq=16, Hkv=4, D=D, batch=1, seed=94, sink=1, recent=1,
+                     slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    arena = H.make_arena(w, [2048] * 4)
+    arena.set_option(B.OPT_KERNEL, kernel)
+    st = H.fill_from_host(arena, w, lens, rng)
+    for c, n in enumerate(masked):
+        st.K[c][:n] = 0xFF7F                       # -3.4e38, times queries above zero
+        o = int(arena.off_host[c])
+        arena.k[o:o + lens[c]].copy_(H.to_device_storage(st.K[c], w.dtype, arena.device))
+    q, q64 = H.make_q(w, rng, w.L)
+    q, q64 = q & 0x7FFF, np.abs(q64)
+    for chunk in (256, 512, 2048):
+        H.set_chunk(arena, chunk)
+        H.check_decode_against_oracle(arena, w, st, q64, H.gpu_decode(arena, w, q))
+    arena.close()
