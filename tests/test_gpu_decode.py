@@ -379,3 +379,34 @@ def test_rows_whose_logits_are_minus_infinity(D, kernel):
         H.set_chunk(arena, chunk)
         H.check_decode_against_oracle(arena, w, st, q64, H.gpu_decode(arena, w, q))
     arena.close()
+
+
+@pytest.mark.parametrize("dtype,D,G", [("f32", 64, 1), ("f32", 128, 4), ("f32", 64, 8), ("bf16", 64, 2), ("bf16", 128, 8)])
+def test_values_near_the_ends_of_the_range(dtype, D, G):
+    """The vector kernel on values whose plain sum over the rows just fits fp32 and on values close to the
+    smallest normal number, with logits that rise along the cache by less than 8 in log2 units: weights above
+    1 would overflow the one, weights far below 1 would lose the other."""
+    H = _h()
+    n = 1025
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="range", L=1, Hq=G, Hkv=1, D=D, batch=1, dtype=dtype, seed=95, sink=1,
+                     recent=1, slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed + G))
+    arena = H.make_arena(w, [n])
+    arena.set_option(B.OPT_KERNEL, B.KERNEL_VALU)
+    H.set_chunk(arena, 2048)                       # one work item
+    st = H.fill_from_host(arena, w, [n], rng)
+    q = np.zeros((1, 1, G, D), dtype=np.float32)
+    q[..., 0] = np.sqrt(D)
+    K = np.zeros((n, D), dtype=np.float32)
+    K[256:, 0] = 5.375                             # 7.75 in log2 units
+    u = 1 + rng.random((n, D), dtype=np.float32)
+    store = (lambda x: x) if dtype == "f32" else synth.f32_to_bf16_bits
+    arena.k[:n].copy_(H.to_device_storage(store(K), dtype, arena.device))
+    for scale in (1e35, 2.0 ** -125):
+        V = store((u * np.float32(scale)).astype(np.float32))
+        arena.v[:n].copy_(H.to_device_storage(V, dtype, arena.device))
+        out = H.gpu_decode(arena, w, store(q))[0, 0]
+        ref, _ = O.decode_attn(synth.storage_to_f64(store(q), dtype)[0, 0], K.astype(np.float64), synth.storage_to_f64(V, dtype))
+        # 2^-125 and weights of 1 and 2^-7.75: a product's rounding at 2^-149 is at most 2^-17 of the smaller
+        assert np.max(np.abs(out / ref - 1)) <= 2e-5, scale
+    arena.close()
