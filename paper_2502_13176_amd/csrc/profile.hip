@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256, 2) void profile_attn_kernel(ProfileParams p) {
       uint32_t o = (off ^ (step * i)) + i * 4 * kRow;
       if (most < kKeyTile - 1) o = min(st_row + 4 * i, most) * kRow + o % kRow;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   :: "s"(dst + i * 4 * kRow), "v"(o), "s"(src) : "memory");
+                   :: "s"(dst + i * 4 * kRow), "v"(o), "s"(src) : "memory", "m0");
     }
   };
   auto stage_k = [&](int kt) { copy_rows(lds_k0 + (kt & 1) * (kKeyTile * kRow), Kb, kt, k_off, 64); };

@@ -294,3 +294,15 @@ def test_hand_worked_allocation_examples_through_the_library():
         hi = int(rng.integers(lo + 1, 13))
         Bt = int(rng.integers(m * lo, m * hi + 1))
         assert B.alloc_proportional(imp, Bt, lo, hi) == O.alloc_proportional(imp, Bt, lo, hi)
+
+
+def test_inline_assembly_declares_the_m0_it_writes():
+    """m0 is a register of the compiler's own: a statement that sets it has to say so."""
+    csrc = os.path.join(ROOT, "paper_2502_13176_amd", "csrc")
+    found = 0
+    for name in sorted(os.listdir(csrc)):
+        for stmt in re.findall(r"\basm\b[^;]*;", open(os.path.join(csrc, name)).read()):
+            if re.search(r"\bs_\w+ m0,", stmt):
+                found += 1
+                assert re.search(r':[^:]*"m0"', stmt), (name, stmt)
+    assert found > 0
