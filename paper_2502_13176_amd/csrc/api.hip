@@ -172,6 +172,7 @@ struct baklava_ctx {
   struct Schedule {
     int32_t chunk = 0;
     std::vector<int32_t> max_count;    // layer -> longest work item of the layer, rows
+    std::vector<int32_t> max_split;    // layer -> most work items of a cache
     std::vector<int32_t> cib;          // cache -> first item
     std::vector<int32_t> multi_begin;  // layer -> first entry of the list of multi-item caches
   } sched[2];                          // 0: layer sub-range launches, 1: whole-model launches
@@ -201,13 +202,14 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   // cache -> first partial slot, and the caches that need the combine kernel (in launch order)
   std::vector<int32_t> cib(ctx->n_caches + 1, 0), multi_begin(ctx->d.L + 1, 0);
   std::vector<MultiCache> multi;
-  std::vector<int32_t> max_count(ctx->d.L, 0);
+  std::vector<int32_t> max_count(ctx->d.L, 0), max_split(ctx->d.L, 0);
   int32_t slot0 = 0;  // the items of a cache follow each other
   for (int64_t i = 0; i < n_items; ++i) {
     if (items[i].start == 0) slot0 = items[i].slot;
     items[i].reserved = slot0;
     const baklava_work_item& it = items[i];
     max_count[it.cache / ctx->cpl] = std::max(max_count[it.cache / ctx->cpl], it.count);
+    max_split[it.cache / ctx->cpl] = std::max(max_split[it.cache / ctx->cpl], it.nsplit);
     if (it.start == 0) {
       cib[it.cache] = it.slot;
       if (it.nsplit > 1) {
@@ -228,6 +230,7 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   ctx->sched[which].multi_begin.swap(multi_begin);
   ctx->sched[which].chunk = chunk;
   ctx->sched[which].max_count.swap(max_count);
+  ctx->sched[which].max_split.swap(max_split);
   return BAKLAVA_OK;
 }
 
@@ -254,6 +257,21 @@ int build_tiles(baklava_ctx* ctx) {
     return BAKLAVA_EHIP;
   ctx->tile_begin.swap(tile_begin);
   return BAKLAVA_OK;
+}
+
+// Vector kernel, scores tracked: whether the score pass also does the combine kernel's work.  That saves a
+// launch (about 2 us), but every workgroup of the pass merges the normalisers of its cache for itself, and one
+// per cache all of its outputs, so a launch keeps the kernel if it has more work items than compute units, or a
+// cache of many work items.  us per call with the merge / the kernel, fp32, one layer, caches x work items each:
+//   D = 128, G = 8   8 x 16 47.8 / 49.0   4 x 32 50.0 / 49.5   2 x 64 55.9 / 51.0   1 x 127 69.6 / 54.1
+//   D = 128, G = 4   8 x 16 32.7 / 34.2   4 x 32 32.5 / 34.7   2 x 64 34.7 / 36.4   1 x 127 39.7 / 39.0
+//   D = 128, G = 2   8 x 16 26.0 / 27.4   4 x 32 25.9 / 27.9   2 x 64 26.5 / 29.4   1 x 127 27.6 / 31.9
+//   D = 64, G = 8    8 x 16 27.9 / 29.2   4 x 32 28.2 / 28.7   2 x 64 31.1 / 29.1   1 x 127 38.6 / 31.4
+//   D = 64, G = 2    8 x 16 15.9 / 18.1   4 x 32 16.2 / 17.6   2 x 64 17.5 / 17.9   1 x 127 21.0 / 20.0
+bool merge_in_score_pass(const baklava_ctx* ctx, int n_items, int most_split) {
+  if (most_split < 2 || n_items > ctx->n_cus) return false;
+  if (ctx->G > 4) return most_split <= 32;
+  return most_split <= 64 || (ctx->G <= 2 && ctx->d.D == 128);
 }
 
 bool range_ok(const baklava_ctx* ctx, int32_t lb, int32_t lc) {
@@ -359,9 +377,10 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   p.lag_batch = kLagRows >> ctx->lag_gp_log2;
   p.lag_gp_log2 = ctx->lag_gp_log2;
   p.ring_slots = 0;
-  // vector kernel, scores tracked: the score pass also does the combine kernel's work in small launches
   const bool scores_now = track && !defer;
-  const bool merge = scores_now && !use_mfma && m1 > m0 && i1 - i0 <= ctx->n_cus;
+  const int32_t most_split = *std::max_element(sc.max_split.begin() + layer_begin,
+                                               sc.max_split.begin() + layer_begin + layer_count);
+  const bool merge = scores_now && !use_mfma && merge_in_score_pass(ctx, i1 - i0, most_split);
   p.keep_rows = merge ? 1 : 0;
   p.fused_append = fused ? 1 : 0;
   p.token_pos = token_pos;

@@ -253,11 +253,13 @@ def test_score_updates_with_half_size_rows(Hq, Hkv, target):
     arena.close()
 
 
-@pytest.mark.parametrize("D,Hq,target", [(64, 2, 256), (64, 8, 7), (128, 6, 40), (64, 2, 300)])
+@pytest.mark.parametrize("D,Hq,target", [(64, 2, 256), (64, 8, 7), (128, 6, 40), (64, 2, 300), (128, 2, 256), (64, 16, 32),
+                                         (64, 16, 40)])
 def test_score_pass_merges_the_partials_of_small_launches(D, Hq, target):
     """fp32 caches, tracked: launches of at most one workgroup per compute unit merge the split partials in
-    the score pass (caches with one, two and more than 64 work items side by side), larger ones in the
-    combine kernel; fused appends into a cache that is full keep its length."""
+    the score pass (caches with one, two and more than 64 work items side by side), larger ones and those of
+    caches with many work items for their heads in the combine kernel; fused appends into a cache that is full
+    keep its length."""
     H = _h()
     w = synth.shrink(synth.WORKLOADS["tiny"], name="merge", L=2, Hq=Hq, Hkv=2, D=D, batch=1, seed=93 + Hq, sink=1, recent=1,
                      slack=3)
