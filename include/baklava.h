@@ -191,7 +191,9 @@ enum {
   BAKLAVA_OPT_CHUNK_TOKENS = 1, /* shortest run of rows per split-K work item for launches over part of
                                    the layers (multiple of 64, >= 256); the item target below may
                                    lengthen it                                                        */
-  BAKLAVA_OPT_KERNEL = 2,       /* 0 = automatic, 1 = vector-ALU kernel, 2 = MFMA kernel (bf16, D=128) */
+  BAKLAVA_OPT_KERNEL = 2,       /* 0 = automatic (MFMA kernel for bf16, vector-ALU kernel for F32), 1 =
+                                   vector-ALU kernel, 2 = MFMA kernel with recorded scores (bf16, D=128;
+                                   EINVAL otherwise, also at D=64, where automatic choice takes it)   */
   BAKLAVA_OPT_TIME_KERNEL = 3,  /* time every attention partial-kernel launch with a pair of HIP events
                                    (baklava_profile_read): 1 = recorded on the stream before and
                                    after the launch, 2 = carried by the kernel's own dispatch (MFMA

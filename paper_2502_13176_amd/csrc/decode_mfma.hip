@@ -56,8 +56,8 @@ typedef float floatx4_t __attribute__((ext_vector_type(4)));
 constexpr int kSlab = 32;       // rows per wavefront iteration
 
 // What follows from the head dimension.  (D = 64: a tracked call over 32 caches of 2500 rows, score pass
-// included, takes 14.3 us at four query heads per cache and 17.5 at eight; with the vector-ALU kernel 22.6 and
-// 31.2.  Records like those of D = 128 would make it 12.5 and 13.8.)
+// included, takes 14.8 us at four query heads per cache and 18.1 at eight; with the vector-ALU kernel 19.4 and
+// 28.3.  Records like those of D = 128 would make it 12.5 and 13.8.)
 template <int D>
 struct Shape {
   // A slab of 64-element rows is half as many bytes, so a workgroup has twice as many wavefronts: the

@@ -19,9 +19,10 @@
 // first half.  The tiles that cross the diagonal follow, masked, one step after the other.  The softmax
 // normaliser cancels in the cosine, so the output is never divided.
 //
-// 32 heads of 8192 tokens take 734 us (765 with 16x16x32 instructions, rows staged through registers and
-// products and exponentials in turn), two prompts of 700 tokens 21 us (29): the matrix pipe is 63%
-// busy at the 1.7 GHz that its power leaves (it was 40% at 2.4 GHz), 1.2 PFLOP/s executed.
+// 32 heads of 8192 tokens take 680 to 734 us box to box (727 to 765 with 16x16x32 instructions, rows staged
+// through registers and products and exponentials in turn), two prompts of 700 tokens 21 us (29): the matrix
+// pipe is 65% busy at the 1.7 GHz that its power leaves (it was 40% at 2.4 GHz), 1.13 to 1.22 PFLOP/s
+// executed.
 #include "common.h"
 
 namespace baklava {

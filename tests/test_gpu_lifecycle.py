@@ -72,7 +72,7 @@ def run_from_empty(w, budgets, policy, steps, chunks, kernel=B.KERNEL_AUTO, trac
 @pytest.mark.parametrize("dtype,D,Hq,Hkv,policy", [
     ("bf16", 128, 16, 1, B.POLICY_SCORE),       # 16 query heads per KV head: MFMA only
     ("bf16", 128, 6, 2, B.POLICY_STREAMING),
-    ("bf16", 64, 8, 2, B.POLICY_SCORE),         # vector-ALU kernel, 128-byte rows
+    ("bf16", 64, 8, 2, B.POLICY_SCORE),         # MFMA kernel, 128-byte rows
     ("f32", 128, 4, 2, B.POLICY_SCORE),         # vector-ALU kernel, 512-byte rows
     ("f32", 64, 7, 1, B.POLICY_STREAMING),
 ])
