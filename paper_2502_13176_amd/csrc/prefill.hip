@@ -367,7 +367,7 @@ hipError_t launch_prefill_scores(const void* q, const void* k, const float* lse,
   const int64_t wide = n_seq * ((((int64_t)T + 255) / 256 + 1) / 2);    // with two
   const int64_t tokens = (int64_t)(Hq / Hkv) * T;                       // rows of Q that a sequence streams
   if (narrow <= 512) return launch_tiles<1, true>(p, n_seq, s);
-  if (wide >= 512 && (T >= 1500 || tokens * wide >= 2800000)) return launch_tiles<2, true>(p, n_seq, s);
+  if (wide >= 512 && (T >= 1500 || (double)tokens * wide >= 2.8e6)) return launch_tiles<2, true>(p, n_seq, s);
   return launch_tiles<1, false>(p, n_seq, s);
 }
 
