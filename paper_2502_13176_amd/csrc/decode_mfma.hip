@@ -371,10 +371,15 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
       ph[e / 2] = (u0 >> 16) | (u1 & 0xffff0000u);  // truncated high parts
       float r0 = p0 - __uint_as_float(u0 & 0xffff0000u), r1 = p1 - __uint_as_float(u1 & 0xffff0000u);
       if (S::kTerms == 3) {
+        // No term of a weight above zero is zero (2^-126 instead, far below what fp32 resolves): an infinite
+        // element of V times a term of zero would be NaN.
+        const float t0 = fminf(p0, 0x1p-126f), t1 = fminf(p1, 0x1p-126f);
+        r0 = fmaxf(r0, t0);
+        r1 = fmaxf(r1, t1);
         const uint32_t w0 = __float_as_uint(r0), w1 = __float_as_uint(r1);
         pm[e / 2] = (w0 >> 16) | (w1 & 0xffff0000u);
-        r0 -= __uint_as_float(w0 & 0xffff0000u);
-        r1 -= __uint_as_float(w1 & 0xffff0000u);
+        r0 = fmaxf(r0 - __uint_as_float(w0 & 0xffff0000u), t0);
+        r1 = fmaxf(r1 - __uint_as_float(w1 & 0xffff0000u), t1);
       }
       pl[e] = (__bf16)r0;
       pl[e + 1] = (__bf16)r1;

@@ -433,3 +433,32 @@ def test_values_near_the_ends_of_the_range(dtype, D, G):
         # 2^-125 and weights of 1 and 2^-7.75: a product's rounding at 2^-149 is at most 2^-17 of the smaller
         assert np.max(np.abs(out / ref - 1)) <= 2e-5, scale
     arena.close()
+
+
+@pytest.mark.parametrize("kernel", [B.KERNEL_AUTO, B.KERNEL_VALU])
+def test_infinite_values_with_half_size_rows(kernel):
+    """bf16 rows of 64 elements: an infinite element of V makes that element of the outputs infinite, also in the
+    row with the largest weight (1, which needs one bf16 term only), and leaves the others alone."""
+    H = _h()
+    n, G = 700, 4
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="inf", L=1, Hq=G, Hkv=1, D=64, batch=1, seed=96, sink=1, recent=1, slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    arena = H.make_arena(w, [n])
+    arena.set_option(B.OPT_KERNEL, kernel)
+    st = H.fill_from_host(arena, w, [n], rng)
+    q, q64 = H.make_q(w, rng, w.L)
+    K = synth.storage_to_f64(st.K[0], "bf16")
+    _, p = O.decode_attn(q64[0, 0], K, synth.storage_to_f64(st.V[0], "bf16"))
+    for g in range(G):
+        st.V[0][np.argmax(p[g]), g] = 0x7F80                     # +inf
+        st.V[0][np.argsort(p[g])[n // 2], 8 + g] = 0xFF80        # -inf
+    arena.v[:n].copy_(H.to_device_storage(st.V[0], "bf16", arena.device))
+    ref, _ = O.decode_attn(q64[0, 0], K, synth.storage_to_f64(st.V[0], "bf16"))
+    assert np.isinf(ref).sum() == 2 * G * G
+    for chunk in (256, 1024):
+        H.set_chunk(arena, chunk)
+        out = H.gpu_decode(arena, w, q)[0, 0]
+        assert np.array_equal(np.isinf(ref), np.isinf(out)) and np.array_equal(ref[np.isinf(ref)], out[np.isinf(ref)])
+        fin = np.isfinite(ref)
+        assert np.max(np.abs(out[fin] - ref[fin])) <= 4e-6
+    arena.close()
