@@ -259,19 +259,27 @@ int build_tiles(baklava_ctx* ctx) {
   return BAKLAVA_OK;
 }
 
-// Vector kernel, scores tracked: whether the score pass also does the combine kernel's work.  That saves a
-// launch (about 2 us), but every workgroup of the pass merges the normalisers of its cache for itself, and one
-// per cache all of its outputs, so a launch keeps the kernel if it has more work items than compute units, or a
-// cache of many work items.  us per call with the merge / the kernel, fp32, one layer, caches x work items each:
-//   D = 128, G = 8   8 x 16 47.8 / 49.0   4 x 32 50.0 / 49.5   2 x 64 55.9 / 51.0   1 x 127 69.6 / 54.1
-//   D = 128, G = 4   8 x 16 32.7 / 34.2   4 x 32 32.5 / 34.7   2 x 64 34.7 / 36.4   1 x 127 39.7 / 39.0
-//   D = 128, G = 2   8 x 16 26.0 / 27.4   4 x 32 25.9 / 27.9   2 x 64 26.5 / 29.4   1 x 127 27.6 / 31.9
-//   D = 64, G = 8    8 x 16 27.9 / 29.2   4 x 32 28.2 / 28.7   2 x 64 31.1 / 29.1   1 x 127 38.6 / 31.4
-//   D = 64, G = 2    8 x 16 15.9 / 18.1   4 x 32 16.2 / 17.6   2 x 64 17.5 / 17.9   1 x 127 21.0 / 20.0
-bool merge_in_score_pass(const baklava_ctx* ctx, int n_items, int most_split) {
+// Whether the score pass also merges the split partials, in place of the combine kernel.  That saves a launch
+// (2 to 3 us), but every workgroup of the pass (256 rows of a work item) merges the normalisers of its cache for
+// itself, and one per cache all of its outputs: the merge pays while these are few, for the number of heads, and
+// while a cache has few work items.  us per tracked call with the merge / the kernel, one layer of caches x
+// rows, at G = 1, 4, 8 (workgroups of the pass; work items per cache):
+//   bf16, D = 64   8 x 4000 (128; 8)      10.8 / 13.8   11.8 / 13.9   14.1 / 15.0
+//                  8 x 16000 (512; 32)    14.2 / 15.0   15.4 / 16.7   22.9 / 19.6
+//                  2 x 64000 (504; 126)   19.9 / 18.4   21.9 / 20.0   35.8 / 23.1
+//                  4 x 64000 (1008; 63)   25.5 / 23.7   28.0 / 28.7   40.7 / 33.1
+//   fp32, D = 64   8 x 16000              20.5 / 21.7   25.7 / 27.2   37.3 / 34.7
+//                  2 x 64000              25.7 / 25.0   31.4 / 30.5   49.5 / 37.9
+//   fp32, D = 128  8 x 4000               21.8 / 23.7   30.2 / 32.2   46.0 / 47.7
+//                  8 x 16000              35.5 / 37.4   42.1 / 44.1   63.3 / 58.3
+//                  2 x 64000              38.8 / 40.8   52.4 / 48.6   85.8 / 62.1
+//                  16 x 16000 (1024; 16)  64.5 / 65.8   75.9 / 72.9   103 / 101
+bool merge_in_score_pass(const baklava_ctx* ctx, int n_items, int longest, int most_split) {
   if (most_split < 2 || n_items > ctx->n_cus) return false;
-  if (ctx->G > 4) return most_split <= 32;
-  return most_split <= 64 || (ctx->G <= 2 && ctx->d.D == 128);
+  const int64_t workgroups = (int64_t)n_items * ((longest + 255) / 256);
+  if (ctx->G > 4) return workgroups <= ctx->n_cus;
+  if (ctx->G > 2 || ctx->d.dtype == BAKLAVA_BF16) return workgroups <= 2 * ctx->n_cus && most_split <= 64;
+  return most_split <= 64 || ctx->d.D == 128;
 }
 
 bool range_ok(const baklava_ctx* ctx, int32_t lb, int32_t lc) {
@@ -378,9 +386,11 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   p.lag_gp_log2 = ctx->lag_gp_log2;
   p.ring_slots = 0;
   const bool scores_now = track && !defer;
+  const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
+                                            sc.max_count.begin() + layer_begin + layer_count);
   const int32_t most_split = *std::max_element(sc.max_split.begin() + layer_begin,
                                                sc.max_split.begin() + layer_begin + layer_count);
-  const bool merge = scores_now && !use_mfma && merge_in_score_pass(ctx, i1 - i0, most_split);
+  const bool merge = scores_now && merge_in_score_pass(ctx, i1 - i0, longest, most_split);
   p.keep_rows = merge ? 1 : 0;
   p.fused_append = fused ? 1 : 0;
   p.token_pos = token_pos;
@@ -398,8 +408,6 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
     if (!(ctx->time_kernel == 2 && use_mfma) && !hip_ok(hipEventRecord(ev0, s))) return BAKLAVA_EHIP;
   }
   const bool on_dispatch = ctx->time_kernel == 2 && use_mfma;
-  const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
-                                            sc.max_count.begin() + layer_begin + layer_count);
   hipError_t e = use_mfma ? launch_decode_mfma(p, ctx->d.D, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s,
                                                on_dispatch ? ev0 : nullptr, on_dispatch ? ev1 : nullptr)
                           : launch_decode_valu(p, ctx->d.dtype, ctx->d.D, i1 - i0, i1 - i0 <= ctx->n_cus, s);

@@ -104,7 +104,7 @@ struct DecodeParams {
   int32_t lag_batch;               // calls a record holds: kLagRows / Gp
   int32_t lag_gp_log2;             // log2(Gp)
   int32_t ring_slots;              // MFMA kernel, lag: slabs per wavefront whose new scores wait in LDS
-  int32_t keep_rows;               // 1: leave the live rows of each cache in lag_n for the score pass (vector kernel)
+  int32_t keep_rows;               // 1: leave the live rows of each cache in lag_n for the score pass (no records)
   int32_t fused_append;            // 1: every cache of the range first receives its new row
   int32_t token_pos;
   int32_t row_bytes;

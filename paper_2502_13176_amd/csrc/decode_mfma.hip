@@ -192,6 +192,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
     if (add) append_new_row(p, it, n_old, off_c, token_pos);
     else if (it.start == 0 && threadIdx.x == 0) *p.status = 1;
   }
+  if (D == 64 && p.keep_rows && it.start == 0 && threadIdx.x == 0) p.lag_n[(int64_t)it.c * kLagCalls] = n;
   int cnt = min(it.start + it.count, n) - it.start;
   if (cnt < 0) cnt = 0;
   const int64_t row0 = off_c + it.start;

@@ -331,9 +331,8 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeParams p) {
 // With MERGE a cache's normalisers are merged from its split partials by every workgroup for itself,
 // beside its first K loads, and a last slice of workgroups (one per cache) merges the outputs: the pass
 // takes the place of the combine kernel.  That saves a launch (eight tracked calls over 67 MB of fp32
-// caches, D = 64: 222 -> 203 us), but each workgroup pays for the merge: where it is taken is decided, with
-// both sides measured, by the caller (128 caches, D = 128, eight query heads, more work items than compute
-// units: 783 us with the combine kernel, 832 without).
+// caches, D = 64: 222 -> 203 us), but each workgroup pays for the merge: the caller's rule says where it is
+// taken, with both sides measured.
 constexpr int kScoreTile = 256;
 template <typename T, int D, int GT, bool MERGE>
 __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
