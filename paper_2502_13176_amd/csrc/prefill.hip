@@ -18,6 +18,8 @@
 // and n_blocks - 1 - i: equal work for every workgroup of a sequence.
 #include "common.h"
 
+#include <type_traits>
+
 namespace baklava {
 
 namespace {
@@ -27,14 +29,28 @@ typedef float floatx16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kD = 128;
+constexpr int kRow = kD * 2;                       // bytes of a row
 constexpr int kChunks = kD / 16;                   // 16 head-dim elements per matrix instruction
 constexpr int kWaves = 4;
 constexpr int kTokTile = 64;                       // tokens per LDS stage
-constexpr int kQStride = 272;                      // bytes between staged Q rows (conflict-free operand reads)
 constexpr float kNegInf = -__builtin_huge_valf();
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ bf16x8_t as_bf16x8(u32x4_t x) { return __builtin_bit_cast(bf16x8_t, x); }
+
+// Memory to LDS without a stop in registers: 64 lanes x 16 bytes (or 4) from `base` + the lane's offset to `lds`, in
+// lane order.  An instruction's own offset counts for both sides.
+__device__ __forceinline__ void copy_rows(uint32_t lds, const void* base, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void copy_rows_4(uint32_t lds, const void* base, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %1\n\tglobal_load_lds_dwordx4 %3, %1 offset:1024\n\t"
+               "global_load_lds_dwordx4 %4, %1 offset:2048\n\tglobal_load_lds_dwordx4 %5, %1 offset:3072"
+               :: "s"(lds), "s"(base), "v"(o0), "v"(o1), "v"(o2), "v"(o3) : "memory", "m0");
+}
+__device__ __forceinline__ void copy_words(uint32_t lds, const void* base, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" :: "s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
 
 struct PrefillParams {
   const unsigned char* q;    // [batch, Hq, T, D] bf16
@@ -46,18 +62,21 @@ struct PrefillParams {
   float scale_log2e;
 };
 
-// TILES: 32-key tiles per wavefront; PIPE: products of one tile beside the weights of the one before.  Bound
-// by vector issue: per 32 x 32 tile 16 exponentials of 16 cycles, 16 multiply-adds and 16 additions of 4 and 8
-// matrix instructions of 32, about 420 cycles if the matrix pipe runs beside the vector ALUs (the device runs this at about 1.9 GHz); what a stage costs
-// beside that (rows to LDS and back, barrier) is shared by twice as many products with two tiles.  16 x
-// 16 products one after the other with their weights took 5530 us for 32 heads of 32768 tokens and 160
-// for 2048 tokens; this takes 4100-4340 (two tiles) and 122 (one).  Without PIPE a wavefront takes 125
-// registers, so four workgroups share a compute unit and cover one another's waits: for launches of many
-// workgroups with a few stages each, where filling a pipeline costs more than it gives.
+// TILES: 32-key tiles per wavefront; PIPE: products of one tile beside the weights of the one before.  Bound by power
+// and vector issue: a probe of one 32 x 32 tile (8 matrix instructions of 32 cycles, 16 exponentials of 8, 16
+// multiply-adds and 16 additions of 4.4) takes 109 ns for the products alone, 107 for the rest, 143 for both, and on
+// random data the products alone run at 195 (1.37 PFLOP/s, what a large library product reaches; zeros run faster),
+// the whole kernel at 235.  What a stage costs beside that (rows to LDS and back, barrier) is shared by twice as many
+// products with two tiles.  Rows through registers, one stage ahead and with a wait for the normalisers in every
+// stage, took 4210 us for 32 heads of 32768 tokens, 468 for 8192 and 105 for 2048; this takes 3820, 316 and 84.
+// Without PIPE a wavefront takes 113 registers, so four workgroups share a compute unit and cover one another's
+// waits: for launches of many workgroups with a few stages each, where filling a pipeline costs more than it gives.
 template <int TILES, bool PIPE>
-__global__ __launch_bounds__(256, PIPE ? 2 : 4) void prefill_score_kernel(PrefillParams p) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds_q[2][kTokTile * kQStride];
-  __shared__ float lds_lse[2][kTokTile];
+__global__ __launch_bounds__(64 * kWaves, PIPE ? 2 : 4) void prefill_score_kernel(PrefillParams p) {
+  constexpr int kBufs = PIPE ? 4 : 2;         // stages in LDS (without pipeline four workgroups share a compute unit)
+  constexpr int kRowsPerWave = kTokTile / kWaves, kCopies = kRowsPerWave / 4;  // rows and copies of a wavefront per stage
+  __shared__ __attribute__((aligned(16))) unsigned char lds_q[kBufs][kTokTile * kRow];
+  __shared__ __attribute__((aligned(16))) float lds_lse[kBufs][kTokTile];
   constexpr int kKeysPerWave = 32 * TILES, kKeysPerWg = kWaves * kKeysPerWave;
 
   const int tid = threadIdx.x;
@@ -70,15 +89,16 @@ __global__ __launch_bounds__(256, PIPE ? 2 : 4) void prefill_score_kernel(Prefil
   const int G = p.Hq / p.Hkv;
   const int b = seq / p.Hkv, hk = seq % p.Hkv;
   const int64_t row0 = p.row_off ? p.row_off[seq] : (int64_t)seq * T;
-  const unsigned char* Kb = p.k + row0 * (kD * 2);
+  const unsigned char* Kb = p.k + row0 * kRow;
   const int64_t head0 = (int64_t)b * p.Hq + (int64_t)hk * G;
   const float cs = p.scale_log2e;
+  const int last_t0 = (T - 1) / kTokTile * kTokTile;  // first token of the prompt's last tile
 
 #pragma unroll 1
   for (int half = 0; half < 2; ++half) {
-  int lane = tid & 63, piece = tid, last_t0 = (T - 1) / kTokTile * kTokTile;
-  // four wavefronts per SIMD: a half forms anew what it derives from these, kept it would cost spilled registers
-  if constexpr (!PIPE) asm volatile("" : "+v"(lane), "+v"(piece), "+s"(last_t0));
+  int lane = tid & 63;
+  // four wavefronts per SIMD: a half forms anew what it derives from this, kept it would cost spilled registers
+  if constexpr (!PIPE) asm volatile("" : "+v"(lane));
   const int n32 = lane & 31, jh = lane >> 5;
   const int block = half == 0 ? pair : p.n_blocks - 1 - pair;
   if (half == 1 && block == pair) break;      // odd number of blocks: the middle one is alone
@@ -92,7 +112,7 @@ __global__ __launch_bounds__(256, PIPE ? 2 : 4) void prefill_score_kernel(Prefil
     const int row = min(jw0 + tt * 32 + n32, T - 1);  // keys past the prompt repeat the last one, never written
 #pragma unroll
     for (int c = 0; c < kChunks; ++c)
-      ka[tt][c] = as_bf16x8(*reinterpret_cast<const u32x4_t*>(Kb + (int64_t)row * (kD * 2) + c * 32 + jh * 16));
+      ka[tt][c] = as_bf16x8(*reinterpret_cast<const u32x4_t*>(Kb + (int64_t)row * kRow + c * 32 + jh * 16));
   }
 
   // Lane (token, j) of a product holds keys 8 (i / 4) + 4 j + i % 4 of the tile in its register i; so do
@@ -110,67 +130,80 @@ __global__ __launch_bounds__(256, PIPE ? 2 : 4) void prefill_score_kernel(Prefil
   const int n_tiles = (T + kTokTile - 1) / kTokTile - first_tile;
   const int n_stages = G * n_tiles;
 
-  // Rows past the prompt (in the last tile only, the first to be staged) repeat the last one; such a
-  // token has an infinite normaliser, so its weights are zero.  With PIPE addresses are a uniform base plus
-  // an offset that only changes after that tile.
-  u32x4_t qreg[4];
-  float lreg = 0.f;
-  uint32_t q_off[4], l_off = min(lane, T - 1 - last_t0) * 4u;
+  // Staging: rows of Q and their normalisers go from memory to LDS without a stop in registers, 4 rows (1 KiB of
+  // LDS, in lane order) per instruction, kBufs stages ahead: one stage ahead and through registers, every
+  // workgroup of a launch with one wavefront per SIMD waited for memory in every stage.  The 16-byte pieces of a
+  // row are permuted on the way (piece c of row r lies in slot c ^ (r % 16)), so that the operand reads spread
+  // over the banks.  Rows past the prompt (in the last tile, the first to be staged) repeat the last one; such a
+  // token's normaliser is taken as infinite where it is read.
+  // (Written out: the only result is in LDS.  A wavefront waits for its own copies of a stage before the barrier
+  // that publishes it; loads of the compiler's own in flight only make such a wait longer.)
+  const int st_row = wave * kRowsPerWave + lane / 16;
+  const uint32_t st_slot = ((lane % 16) ^ (st_row & 15)) * 16;  // 4 i rows further: ^ 64 i
+  const uint32_t lds_q0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)&lds_q[0][wave * kRowsPerWave * kRow];
+  const uint32_t lds_l0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)&lds_lse[0][0];
+  int ld_g = 0, ld_st = 0;                           // head and number of the next stage to copy
+  const int left0 = T - last_t0;                     // tokens of the prompt's last tile
+  uint32_t q_off = min(st_row, left0 - 1) * kRow + st_slot, l_off = min(lane, left0 - 1) * 4u;
+  const unsigned char* ld_q = p.q + (head0 * T + last_t0) * kRow;
+  const float* ld_l = p.lse + head0 * T + last_t0;
+  auto copy_stage = [&](int buf) {  // buf = ld_st % kBufs
+    const uint32_t dst = lds_q0 + buf * (kTokTile * kRow);
+    if (ld_st >= G || left0 == kTokTile) {
+      copy_rows_4(dst, ld_q, q_off, q_off ^ 64, q_off ^ 128, q_off ^ 192);
+    } else {  // rows of the last tile: none beyond the prompt's last one
 #pragma unroll
-  for (int i = 0; i < 4; ++i) q_off[i] = min(piece / 16 + i * 16, T - 1 - last_t0) * (kD * 2u) + (piece % 16) * 16u;
-  int ld_g = 0, ld_t0 = last_t0;  // head and first token of the next stage to load
-  auto load_stage = [&]() {
-    if constexpr (!PIPE) {  // offsets formed for every stage: kept, they would take registers
-      const int most = T - 1 - ld_t0;
-      const unsigned char* Qt = p.q + ((head0 + ld_g) * T + ld_t0) * (kD * 2);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        qreg[i] = *reinterpret_cast<const u32x4_t*>(Qt + (uint32_t)(min(piece / 16 + i * 16, most) * (kD * 2) + piece % 16 * 16));
-      if (wave == 0) {
-        lreg = p.lse[(head0 + ld_g) * T + ld_t0 + min(lane, most)];
-        if (lane > most) lreg = -kNegInf;
-      }
-      if (++ld_g == G) { ld_g = 0; ld_t0 -= kTokTile; }
-      return;
+      for (int i = 0; i < kCopies; ++i)
+        copy_rows(dst + i * 4 * kRow, ld_q, min(st_row + 4 * i, left0 - 1) * kRow + (st_slot ^ (64 * i)));
     }
-    const unsigned char* Qt = p.q + ((head0 + ld_g) * T + ld_t0) * (kD * 2);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) qreg[i] = *reinterpret_cast<const u32x4_t*>(Qt + q_off[i]);
-    if (wave == 0)
-      lreg = *reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(p.lse + (head0 + ld_g) * T + ld_t0) + l_off);
-    if (wave == 0 && ld_t0 == last_t0) lreg = last_t0 + lane < T ? lreg : -kNegInf;
+    static_assert(kCopies == 4, "copies written out");
+    // every wavefront brings all normalisers: the same values to the same places
+    copy_words(lds_l0 + buf * (kTokTile * 4), ld_l, l_off);
+    ++ld_st;
+    int64_t step = T;
     if (++ld_g == G) {
-      if (ld_t0 == last_t0) {
-        l_off = lane * 4u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) q_off[i] = (piece / 16 + i * 16) * (kD * 2u) + (piece % 16) * 16u;
-      }
       ld_g = 0;
-      ld_t0 -= kTokTile;
+      step -= (int64_t)G * T + kTokTile;
+      q_off = st_row * kRow + st_slot;
+      l_off = lane * 4u;
     }
+    ld_q += step * kRow;
+    ld_l += step;
   };
-  auto store_stage = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<u32x4_t*>(&lds_q[buf][(piece / 16 + i * 16) * kQStride + (piece % 16) * 16]) = qreg[i];
-    if (wave == 0) lds_lse[buf][lane] = lreg;
+  // Ends a stage (in buffer buf): the next one is published, and the buffer, whose rows every wavefront has read,
+  // takes the one kBufs further.  At most kBufs - 2 younger stages may be on their way meanwhile.
+  auto next_stage = [&](int buf) {  // with kBufs or more stages left after this one
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kBufs - 2) * (kCopies + 1)) : "memory");
+    __syncthreads();
+    copy_stage(buf);
+  };
+  auto last_stages = [&](int buf) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (ld_st < n_stages) copy_stage(buf);
   };
 
   // A stage holds two column tiles of 32 tokens.  The products of one run on the matrix pipe while the
   // vector ALUs turn the other's logits into weights; the second tile's are turned in the next stage.
   floatx16_t s0[TILES], s1[TILES];
-  float nl0 = 0.f, nl1 = 0.f;
+  float nl0 = 0.f, nl1 = 0.f;  // their tokens' normalisers
   // none yet: logits of -inf, weights of zero
 #pragma unroll
   for (int tt = 0; tt < TILES; ++tt)
 #pragma unroll
     for (int i = 0; i < 16; ++i) s1[tt][i] = kNegInf;
   // B operands of a column tile: lane (token, j), chunk c holds Q[token][16c + 8j .. +8).
-  auto read_tile = [&](bf16x8_t (&qt)[kChunks], float& nl, int buf, int nt) {
-    const unsigned char* qrow = &lds_q[buf][(nt * 32 + n32) * kQStride + jh * 16];
-    nl = -lds_lse[buf][nt * 32 + n32];
+  auto read_chunk = [&](int buf, int nt, int c) {
+    return as_bf16x8(*reinterpret_cast<const u32x4_t*>(&lds_q[buf][(nt * 32 + n32) * kRow + (((2 * c + jh) ^ (n32 & 15)) * 16)]));
+  };
+  // (left: tokens from the stage's first one to the end of the prompt)
+  auto read_norm = [&](int buf, int nt, int left) {
+    const float l = lds_lse[buf][nt * 32 + n32];
+    return nt * 32 + n32 < left ? l : -kNegInf;
+  };
+  auto read_tile = [&](bf16x8_t (&qt)[kChunks], int buf, int nt) {
 #pragma unroll
-    for (int c = 0; c < kChunks; ++c) qt[c] = as_bf16x8(*reinterpret_cast<const u32x4_t*>(qrow + c * 32));
+    for (int c = 0; c < kChunks; ++c) qt[c] = read_chunk(buf, nt, c);
   };
   auto products = [&](floatx16_t (&s)[TILES], const bf16x8_t (&qt)[kChunks]) {
 #pragma unroll
@@ -185,7 +218,7 @@ __global__ __launch_bounds__(256, PIPE ? 2 : 4) void prefill_score_kernel(Prefil
 #pragma unroll
     for (int tt = 0; tt < TILES; ++tt)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[tt][i] += fast_exp2(fmaf(s[tt][i], cs, nl));
+      for (int i = 0; i < 16; ++i) acc[tt][i] += fast_exp2(fmaf(s[tt][i], cs, -nl));
   };
   auto mask_tile = [&](floatx16_t (&s)[TILES], int tok0) {
 #pragma unroll
@@ -205,108 +238,117 @@ __global__ __launch_bounds__(256, PIPE ? 2 : 4) void prefill_score_kernel(Prefil
                         "+v"(acc[tt][14]), "+v"(acc[tt][15]));
   };
 
-  load_stage();
-  store_stage(0);
+#pragma unroll 1
+  for (int i = 0; i < min(kBufs, n_stages); ++i) copy_stage(i);
+  if (ld_st == kBufs) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kBufs - 1) * (kCopies + 1)) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (n_stages > 1) load_stage();
 
   // Tiles that start behind the workgroup's keys have no masked pair; the last ones (a tile per 64 keys
   // of the workgroup) cross the diagonal.
   const int n_below = PIPE ? max(0, (T + kTokTile - 1) / kTokTile - (j0 + kKeysPerWg) / kTokTile) * G : 0;
-  int st = 0;
+  int st = 0, t0 = last_t0, g = 0;  // stage, its first token, its head
+  auto advance = [&]() {
+    ++st;
+    if (++g == G) { g = 0; t0 -= kTokTile; }
+  };
   bf16x8_t qa[kChunks];
-  float nla;
-  if constexpr (TILES == 1 && PIPE) {
-    // The barrier of a stage sits between its two tiles: the rows of the next stage are in LDS before the
-    // second tile's products start, so every operand is read one tile ahead of its use.
+  if constexpr (PIPE) {
+    // (kBufs stages per turn, so that LDS addresses are constant offsets; what is left goes with the masked ones)
     bf16x8_t qb[kChunks];
-    float nlb;
-    if (n_below > 0) read_tile(qa, nla, 0, 0);
-    for (; st < n_below; ++st) {  // at least one stage follows
-      const int buf = st & 1;
-      read_tile(qb, nlb, buf, 1);
-      products(s0, qa);
-      add_weights(s1, nl1);
-      nl0 = nla;
-      settle();
-      store_stage(buf ^ 1);  // its tiles were read before the previous stage's barrier
-      __syncthreads();
-      if (st + 2 < n_stages) load_stage();
-      read_tile(qa, nla, buf ^ 1, 0);
-      products(s1, qb);
-      add_weights(s0, nl0);
-      nl1 = nlb;
-      settle();
+    float nla, nlb;
+    auto stage = [&](auto b) {
+      constexpr int buf = decltype(b)::value;
+      if constexpr (TILES == 1) {
+        // The end of a stage sits between its two tiles: the rows of the next stage are in LDS before the
+        // second tile's products start, so every operand is read one tile ahead of its use.
+        read_tile(qb, buf, 1);
+        nlb = read_norm(buf, 1, T - t0);
+        products(s0, qa);
+        add_weights(s1, nl1);
+        nl0 = nla;
+        settle();
+        next_stage(buf);
+        advance();
+        read_tile(qa, (buf + 1) % kBufs, 0);
+        nla = read_norm((buf + 1) % kBufs, 0, T - t0);
+        products(s1, qb);
+        add_weights(s0, nl0);
+        nl1 = nlb;
+        settle();
+      } else {
+        // no registers left for operands one tile ahead: the other wavefront of the SIMD covers the reads
+        read_tile(qa, buf, 0);
+        nl0 = read_norm(buf, 0, T - t0);
+        products(s0, qa);
+        add_weights(s1, nl1);
+        settle();
+        read_tile(qa, buf, 1);
+        nl1 = read_norm(buf, 1, T - t0);
+        products(s1, qa);
+        add_weights(s0, nl0);
+        settle();
+        next_stage(buf);
+        advance();
+      }
+    };
+    if (TILES == 1 && n_below >= kBufs) { read_tile(qa, 0, 0); nla = read_norm(0, 0, T - t0); }
+    while (st + kBufs <= min(n_below, n_stages - kBufs)) {  // the last of them still has a stage to copy
+      stage(std::integral_constant<int, 0>{});
+      stage(std::integral_constant<int, 1>{});
+      stage(std::integral_constant<int, 2>{});
+      stage(std::integral_constant<int, 3>{});
     }
-  } else if constexpr (PIPE) {
-    // no registers left for operands one tile ahead: the other wavefront of the SIMD covers the reads
-    for (; st < n_below; ++st) {
-      const int buf = st & 1;
-      read_tile(qa, nl0, buf, 0);
-      products(s0, qa);
-      add_weights(s1, nl1);
-      settle();
-      read_tile(qa, nl1, buf, 1);
-      products(s1, qa);
-      add_weights(s0, nl0);
-      settle();
-      store_stage(buf ^ 1);
-      __syncthreads();
-      if (st + 2 < n_stages) load_stage();
-    }
+    static_assert(kBufs == 4, "stages written out");
   }
-  int t0 = last_t0 - n_below / G * kTokTile, g = 0;
   if constexpr (PIPE && TILES == 1) {
     int tok1 = T;  // first token of the tile in s1
-    for (; st < n_stages; ++st) {
-      const int buf = st & 1;
+    while (st < n_stages) {
+      const int buf = st % kBufs;
       if (t0 + kTokTile - 1 >= jw0) {  // else every token precedes every key of this wavefront
         mask_tile(s1, tok1);
         add_weights(s1, nl1);
-        read_tile(qa, nl0, buf, 0);
+        read_tile(qa, buf, 0);
+        nl0 = read_norm(buf, 0, T - t0);
         products(s0, qa);
-        read_tile(qa, nl1, buf, 1);
+        read_tile(qa, buf, 1);
+        nl1 = read_norm(buf, 1, T - t0);
         products(s1, qa);
         mask_tile(s0, t0);
         add_weights(s0, nl0);
         tok1 = t0 + 32;
       }
-      if (st + 1 < n_stages) store_stage(buf ^ 1);
-      __syncthreads();
-      if (st + 2 < n_stages) load_stage();
-      if (++g == G) { g = 0; t0 -= kTokTile; }
+      last_stages(buf);
+      advance();
     }
     mask_tile(s1, tok1);
     add_weights(s1, nl1);
   } else {
     if (PIPE) add_weights(s1, nl1);
-    for (; st < n_stages; ++st) {
-      const int buf = st & 1;
+    while (st < n_stages) {
+      const int buf = st % kBufs;
 #pragma unroll 1
       for (int nt = 0; nt < 2; ++nt) {
         const int tok0 = t0 + nt * 32;
         if (tok0 >= T || tok0 + 31 < jw0) continue;  // past the prompt, or before every key of this wavefront
-        const unsigned char* qrow = &lds_q[buf][(nt * 32 + n32) * kQStride + jh * 16];
 #pragma unroll
         for (int c = 0; c < kChunks; ++c) {
-          const bf16x8_t q1 = as_bf16x8(*reinterpret_cast<const u32x4_t*>(qrow + c * 32));
+          const bf16x8_t q1 = read_chunk(buf, nt, c);
 #pragma unroll
           for (int tt = 0; tt < TILES; ++tt) {
             const floatx16_t zero = {};
             s0[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[tt][c], q1, c == 0 ? zero : s0[tt], 0, 0, 0);
           }
         }
-        nl0 = -lds_lse[buf][nt * 32 + n32];
+        nl0 = read_norm(buf, nt, T - t0);
         if (tok0 < jw0 + kKeysPerWave - 1) {
           asm volatile("" ::: "memory");  // keeps this a branch: below the diagonal nothing is masked
           mask_tile(s0, tok0);
         }
         add_weights(s0, nl0);
       }
-      if (st + 1 < n_stages) store_stage(buf ^ 1);
-      __syncthreads();
-      if (st + 2 < n_stages) load_stage();
-      if (++g == G) { g = 0; t0 -= kTokTile; }
+      last_stages(buf);
+      advance();
     }
   }
 
@@ -332,10 +374,11 @@ __global__ __launch_bounds__(256, PIPE ? 2 : 4) void prefill_score_kernel(Prefil
 
 template <int TILES, bool PIPE>
 hipError_t launch_tiles(PrefillParams p, int64_t n_seq, hipStream_t s) {
-  p.n_blocks = (p.T + kWaves * 32 * TILES - 1) / (kWaves * 32 * TILES);
+  constexpr int kKeysPerWg = kWaves * 32 * TILES;
+  p.n_blocks = (p.T + kKeysPerWg - 1) / kKeysPerWg;
   const int64_t n_wg = n_seq * ((p.n_blocks + 1) / 2);
   if (n_wg <= 0 || n_wg > INT32_MAX) return hipErrorInvalidValue;
-  prefill_score_kernel<TILES, PIPE><<<dim3((unsigned)n_wg), dim3(256), 0, s>>>(p);
+  prefill_score_kernel<TILES, PIPE><<<dim3((unsigned)n_wg), dim3(64 * kWaves), 0, s>>>(p);
   return hipGetLastError();
 }
 
@@ -352,22 +395,28 @@ hipError_t launch_prefill_scores(const void* q, const void* k, const float* lse,
   p.T = T; p.Hq = Hq; p.Hkv = Hkv;
   p.n_blocks = 0;
   p.scale_log2e = 1.4426950408889634f / sqrtf((float)kD);
-  // One tile per wavefront, pipelined, while that gives at most two workgroups to each of the 256 compute units.
-  // Beyond, two tiles once they fill the chip twice over, if the prompt is long against a workgroup's masked
-  // stages (twice as many with two tiles) or the launch is large enough for fewer stages to outweigh them;
-  // otherwise the form without pipeline.  us with one tile / two tiles / without pipeline (and with 16 x 16
-  // products, one form for all), sequences x tokens x query heads of each:
-  //   8 x 8192 x 4       468 /  663 /  716 ( 596)    256 x 1999 x 1    187 /  163 /  176 ( 183)
-  //   32 x 8192 x 4     1260 / 1071 / 1289 (1275)    512 x 1300 x 1    199 /  170 /  161 ( 174)
-  //   64 x 3000 x 4      399 /  376 /  369 ( 367)    256 x 900 x 4     171 /  163 /  156 ( 166)
-  //   128 x 1999 x 4     342 /  311 /  336 ( 347)    1024 x 100 x 4    32 /   45 /   25 (  29)
-  //   256 x 1100 x 8     555 /  460 /  497 ( 477)    1024 x 64 x 1     9.6 / 13.0 / 7.2 ( 7.2)
+  // One tile per wavefront, pipelined, while that gives at most two workgroups to each of the 256 compute units (or
+  // three, for a prompt of some length), but for very short prompts; from 8192 tokens on two tiles as soon as they
+  // give every compute unit a workgroup.  Beyond, two tiles once they fill the chip twice over, if the prompt is long
+  // against a workgroup's masked stages (twice as many with two tiles) or the launch is large enough for fewer stages
+  // to outweigh them; otherwise the form without pipeline.  us with one tile / two tiles / without pipeline,
+  // sequences x tokens x query heads of each:
+  //   8 x 2000 x 4        84 /  156 /  118      128 x 1999 x 4      295 /  295 /  298
+  //   8 x 8192 x 4       316 /  498 /  489      256 x 700 x 4        94 /   93 /   89
+  //   8 x 16384 x 4     1072 / 1024 / 1220      256 x 1300 x 8      626 /  626 /  603
+  //   32 x 6000 x 4      603 /  648 /  650      512 x 513 x 8       264 /  274 /  224
+  //   32 x 8192 x 4     1082 /  972 / 1130      512 x 1300 x 8     1372 / 1177 / 1268
+  //   64 x 3000 x 4      310 /  355 /  331      1024 x 100 x 4     30.2 / 39.8 / 23.9
+  // Over 334 shapes (8 to 1024 sequences of 64 to 16384 tokens, 1 to 8 heads) the rule is within 0.4% of the best on
+  // average and 15% at worst (512 x 200 x 1: 15.8 against 13.8).
   const int64_t n_seq = (int64_t)batch * Hkv;
   const int64_t narrow = n_seq * ((((int64_t)T + 127) / 128 + 1) / 2);  // workgroups with one tile
   const int64_t wide = n_seq * ((((int64_t)T + 255) / 256 + 1) / 2);    // with two
   const int64_t tokens = (int64_t)(Hq / Hkv) * T;                       // rows of Q that a sequence streams
-  if (narrow <= 512) return launch_tiles<1, true>(p, n_seq, s);
-  if (wide >= 512 && (T >= 1500 || (double)tokens * wide >= 2.8e6)) return launch_tiles<2, true>(p, n_seq, s);
+  if (narrow <= 512 && T >= 8192 && wide >= 256) return launch_tiles<2, true>(p, n_seq, s);
+  if (narrow <= 512 && (T > 256 || n_seq <= 256)) return launch_tiles<1, true>(p, n_seq, s);
+  if (narrow <= 768 && T >= 2000) return launch_tiles<1, true>(p, n_seq, s);
+  if (wide >= 512 && (T >= 1700 || (double)tokens * wide >= 7e6)) return launch_tiles<2, true>(p, n_seq, s);
   return launch_tiles<1, false>(p, n_seq, s);
 }
 

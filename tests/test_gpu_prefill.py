@@ -105,6 +105,14 @@ def test_head_grouping_and_batches(batch, Hq, Hkv):
     run_dense(batch, Hq, Hkv, 300, 9700 + Hq)
 
 
+@pytest.mark.parametrize("T", [320, 384, 448, 511, 513, 577, 640, 700, 1601])
+@pytest.mark.parametrize("G", [1, 3])
+def test_stages_around_a_turn_of_the_pipeline(T, G):
+    """One and three query heads per KV head: the stages below the diagonal end anywhere in a turn of four, and
+    few follow, so that the copies ahead meet the end of the prompt inside a turn."""
+    run_dense(1, G, 1, T, 9750 + T + G)
+
+
 def test_peaked_and_large_logits():
     run_dense(1, 4, 2, 350, 9800, peaked=True, qscale=4.0)
 
