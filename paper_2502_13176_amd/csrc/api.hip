@@ -38,7 +38,7 @@ int64_t count_items(const int32_t* cap, int64_t n_caches, int chunk) {
 struct WorkspacePlan {
   // index 0: schedule for launches over a layer sub-range, 1: for launches over the whole model
   size_t items[2], multi[2];
-  size_t part_o, part_ml, final_ml, lag_q, lag_ml, lag_n, lag_cnt, status, kept, info, order_all, order_layer;
+  size_t part_o, part_ml, final_ml, logits, lag_q, lag_ml, lag_n, lag_cnt, status, kept, info, order_all, order_layer;
   size_t segs, seg_split, halo_k, halo_v, halo_score, halo_pos, tiles, tile_hist, sel_state, total;
   int64_t n_segs, halo_rows, n_tiles, n_long;
   int32_t seg_rows;  // destination rows per segment of the eviction move
@@ -59,6 +59,9 @@ bool shape_ok(const baklava_desc* d) {
   if ((int64_t)d->L * d->batch * d->Hkv > INT32_MAX) return false;
   return true;
 }
+
+// Scores are deferred over bf16 rows of 128 elements only (see decode_impl).
+bool keeps_records(const baklava_desc* d) { return d->dtype == BAKLAVA_BF16 && d->D == 128; }
 
 // Destination rows per segment of the eviction move (one workgroup each).  A segment copies its rows
 // tile after tile (128 rows, a few microseconds each, of which little overlaps inside a workgroup), so
@@ -115,11 +118,12 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
   w.part_o = o;       o = align256(o + (size_t)w.max_items * G * d->D * 4);
   w.part_ml = o;      o = align256(o + (size_t)w.max_items * G * 2 * 4);
   w.final_ml = o;     o = align256(o + (size_t)n_caches * G * 2 * 4);
-  // the record of the pending calls of every cache (score tracking): 32 packed query rows, their
-  // (max, 1/sum), the rows each call saw, the count of pending calls per head
-  const bool track = d->track_scores != 0;
-  w.lag_q = o;        o = align256(o + (track ? (size_t)n_caches * kLagRows * row_bytes : 0));
-  w.lag_ml = o;       o = align256(o + (track ? (size_t)n_caches * kLagRows * 2 * 4 : 0));
+  // score tracking: the record of the pending calls of every cache (32 packed query rows, their (max, 1/sum), the
+  // rows each call saw, the count of pending calls per head), or the logits of a call where there are no records
+  const bool track = d->track_scores != 0, records = track && keeps_records(d);
+  w.logits = o;       o = align256(o + (track && !records ? (size_t)total_tokens * G * 4 : 0));
+  w.lag_q = o;        o = align256(o + (records ? (size_t)n_caches * kLagRows * row_bytes : 0));
+  w.lag_ml = o;       o = align256(o + (records ? (size_t)n_caches * kLagRows * 2 * 4 : 0));
   w.lag_n = o;        o = align256(o + (size_t)n_caches * kLagCalls * 4);
   w.lag_cnt = o;      o = align256(o + (size_t)n_caches * G * 4);
   w.status = o;       o = align256(o + 256);
@@ -152,7 +156,7 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
 
 struct baklava_ctx {
   baklava_desc d;
-  int64_t n_caches;
+  int64_t n_caches, total_tokens;
   int32_t cpl;  // caches per layer
   int32_t G;
   int32_t row_bytes;
@@ -172,7 +176,6 @@ struct baklava_ctx {
   struct Schedule {
     int32_t chunk = 0;
     std::vector<int32_t> max_count;    // layer -> longest work item of the layer, rows
-    std::vector<int32_t> max_split;    // layer -> most work items of a cache
     std::vector<int32_t> cib;          // cache -> first item
     std::vector<int32_t> multi_begin;  // layer -> first entry of the list of multi-item caches
   } sched[2];                          // 0: layer sub-range launches, 1: whole-model launches
@@ -202,14 +205,13 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   // cache -> first partial slot, and the caches that need the combine kernel (in launch order)
   std::vector<int32_t> cib(ctx->n_caches + 1, 0), multi_begin(ctx->d.L + 1, 0);
   std::vector<MultiCache> multi;
-  std::vector<int32_t> max_count(ctx->d.L, 0), max_split(ctx->d.L, 0);
+  std::vector<int32_t> max_count(ctx->d.L, 0);
   int32_t slot0 = 0;  // the items of a cache follow each other
   for (int64_t i = 0; i < n_items; ++i) {
     if (items[i].start == 0) slot0 = items[i].slot;
     items[i].reserved = slot0;
     const baklava_work_item& it = items[i];
     max_count[it.cache / ctx->cpl] = std::max(max_count[it.cache / ctx->cpl], it.count);
-    max_split[it.cache / ctx->cpl] = std::max(max_split[it.cache / ctx->cpl], it.nsplit);
     if (it.start == 0) {
       cib[it.cache] = it.slot;
       if (it.nsplit > 1) {
@@ -230,7 +232,6 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   ctx->sched[which].multi_begin.swap(multi_begin);
   ctx->sched[which].chunk = chunk;
   ctx->sched[which].max_count.swap(max_count);
-  ctx->sched[which].max_split.swap(max_split);
   return BAKLAVA_OK;
 }
 
@@ -259,29 +260,6 @@ int build_tiles(baklava_ctx* ctx) {
   return BAKLAVA_OK;
 }
 
-// Whether the score pass also merges the split partials, in place of the combine kernel.  That saves a launch
-// (2 to 3 us), but every workgroup of the pass (256 rows of a work item) merges the normalisers of its cache for
-// itself, and one per cache all of its outputs: the merge pays while these are few, for the number of heads, and
-// while a cache has few work items.  us per tracked call with the merge / the kernel, one layer of caches x
-// rows, at G = 1, 4, 8 (workgroups of the pass; work items per cache):
-//   bf16, D = 64   8 x 4000 (128; 8)      10.8 / 13.8   11.8 / 13.9   14.1 / 15.0
-//                  8 x 16000 (512; 32)    14.2 / 15.0   15.4 / 16.7   22.9 / 19.6
-//                  2 x 64000 (504; 126)   19.9 / 18.4   21.9 / 20.0   35.8 / 23.1
-//                  4 x 64000 (1008; 63)   25.5 / 23.7   28.0 / 28.7   40.7 / 33.1
-//   fp32, D = 64   8 x 16000              20.5 / 21.7   25.7 / 27.2   37.3 / 34.7
-//                  2 x 64000              25.7 / 25.0   31.4 / 30.5   49.5 / 37.9
-//   fp32, D = 128  8 x 4000               21.8 / 23.7   30.2 / 32.2   46.0 / 47.7
-//                  8 x 16000              35.5 / 37.4   42.1 / 44.1   63.3 / 58.3
-//                  2 x 64000              38.8 / 40.8   52.4 / 48.6   85.8 / 62.1
-//                  16 x 16000 (1024; 16)  64.5 / 65.8   75.9 / 72.9   103 / 101
-bool merge_in_score_pass(const baklava_ctx* ctx, int n_items, int longest, int most_split) {
-  if (most_split < 2 || n_items > ctx->n_cus) return false;
-  const int64_t workgroups = (int64_t)n_items * ((longest + 255) / 256);
-  if (ctx->G > 4) return workgroups <= ctx->n_cus;
-  if (ctx->G > 2 || ctx->d.dtype == BAKLAVA_BF16) return workgroups <= 2 * ctx->n_cus && most_split <= 64;
-  return most_split <= 64 || ctx->d.D == 128;
-}
-
 bool range_ok(const baklava_ctx* ctx, int32_t lb, int32_t lc) {
   return lb >= 0 && lc > 0 && (int64_t)lb + lc <= ctx->d.L;
 }
@@ -290,7 +268,7 @@ bool range_ok(const baklava_ctx* ctx, int32_t lb, int32_t lc) {
 // K rows of the layer range, after which the records are empty.  Only the MFMA attention kernel over rows of
 // 128 elements leaves calls on record.
 int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hipStream_t s) {
-  if (!ctx->d.track_scores || !(ctx->d.dtype == BAKLAVA_BF16 && ctx->d.D == 128)) return BAKLAVA_OK;
+  if (!ctx->d.track_scores || !keeps_records(&ctx->d)) return BAKLAVA_OK;
   const int64_t c0 = (int64_t)layer_begin * ctx->cpl;
   const int64_t c1 = c0 + (int64_t)layer_count * ctx->cpl;
   const int which = (layer_begin == 0 && layer_count == ctx->d.L) ? 1 : 0;
@@ -312,19 +290,19 @@ int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hi
   return BAKLAVA_OK;
 }
 
-// The score update of calls that leave no record, for the one that has just been enqueued, with the merge of
-// its split partials if asked for.
-int score_pass(baklava_ctx* ctx, const DecodeParams& d, int n_items, bool merge, int longest, hipStream_t s) {
+// The score update of a call on the vector kernel over rows whose calls are otherwise recorded, for the one that
+// has just been enqueued.
+int score_pass(baklava_ctx* ctx, const DecodeParams& d, int n_items, int longest, hipStream_t s) {
   ScoreParams p;
-  p.k = d.k; p.q = d.q; p.out = d.out;
-  p.ml = d.final_ml; p.part_o = d.part_o; p.part_ml = d.part_ml;
-  p.rows = d.lag_n; p.len = d.len;
+  p.k = d.k; p.q = d.q;
+  p.ml = d.final_ml;
+  p.len = d.len;
   p.items = d.items;
   p.score = d.score;
   p.G = d.G; p.Hq = d.Hq; p.Hkv = d.Hkv;
   p.cache_begin = d.cache_begin;
   p.scale_log2e = d.scale_log2e;
-  if (!hip_ok(launch_score_pass(p, ctx->d.dtype, ctx->d.D, n_items, longest, merge, s))) return BAKLAVA_EHIP;
+  if (!hip_ok(launch_score_pass(p, n_items, longest, s))) return BAKLAVA_EHIP;
   return BAKLAVA_OK;
 }
 
@@ -385,13 +363,11 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   p.lag_batch = kLagRows >> ctx->lag_gp_log2;
   p.lag_gp_log2 = ctx->lag_gp_log2;
   p.ring_slots = 0;
-  const bool scores_now = track && !defer;
+  const bool from_logits = track && !keeps_records(&ctx->d);
+  p.logits = from_logits ? reinterpret_cast<float*>(ctx->ws + ctx->plan.logits) : nullptr;
+  p.logit_stride = ctx->total_tokens;
   const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
                                             sc.max_count.begin() + layer_begin + layer_count);
-  const int32_t most_split = *std::max_element(sc.max_split.begin() + layer_begin,
-                                               sc.max_split.begin() + layer_begin + layer_count);
-  const bool merge = scores_now && merge_in_score_pass(ctx, i1 - i0, longest, most_split);
-  p.keep_rows = merge ? 1 : 0;
   p.fused_append = fused ? 1 : 0;
   p.token_pos = token_pos;
   p.row_bytes = ctx->row_bytes;
@@ -410,16 +386,20 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   const bool on_dispatch = ctx->time_kernel == 2 && use_mfma;
   hipError_t e = use_mfma ? launch_decode_mfma(p, ctx->d.D, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s,
                                                on_dispatch ? ev0 : nullptr, on_dispatch ? ev1 : nullptr)
-                          : launch_decode_valu(p, ctx->d.dtype, ctx->d.D, i1 - i0, i1 - i0 <= ctx->n_cus, s);
+                          : launch_decode_valu(p, ctx->d.dtype, ctx->d.D, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s);
   if (!hip_ok(e)) return BAKLAVA_EHIP;
   if (ctx->time_kernel) {
     if (!on_dispatch && !hip_ok(hipEventRecord(ev1, s))) return BAKLAVA_EHIP;
     ctx->ev_used += 1;
   }
-  if (!merge && !hip_ok(launch_combine(p, ctx->d.D, m1 - m0, s))) return BAKLAVA_EHIP;
-  if (scores_now) {
-    const int st = score_pass(ctx, p, i1 - i0, merge, longest, s);
-    if (st != BAKLAVA_OK) return st;
+  if (from_logits) {
+    if (!hip_ok(launch_finish(p, ctx->d.D, m1 - m0, i1 - i0, longest, s))) return BAKLAVA_EHIP;
+  } else {
+    if (!hip_ok(launch_combine(p, ctx->d.D, m1 - m0, s))) return BAKLAVA_EHIP;
+    if (track && !defer) {
+      const int st = score_pass(ctx, p, i1 - i0, longest, s);
+      if (st != BAKLAVA_OK) return st;
+    }
   }
   if (fused && host_lengths)
     for (int64_t c = c0; c < c1; ++c) ctx->len[c] += 1;
@@ -472,6 +452,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
   if (!ctx) return BAKLAVA_ENOMEM;
   ctx->d = *desc;
   ctx->n_caches = n_caches;
+  ctx->total_tokens = packed;
   ctx->cpl = desc->batch * desc->Hkv;
   ctx->G = desc->Hq / desc->Hkv;
   ctx->row_bytes = desc->D * (desc->dtype == BAKLAVA_BF16 ? 2 : 4);
@@ -568,7 +549,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     const int st = build_tiles(ctx);
     if (st != BAKLAVA_OK) { delete ctx; return st; }
   }
-  if (desc->dtype == BAKLAVA_BF16 && desc->D == 128 && !hip_ok(prepare_decode_mfma())) { delete ctx; return BAKLAVA_EHIP; }
+  if (desc->dtype == BAKLAVA_BF16 && !hip_ok(prepare_decode_mfma())) { delete ctx; return BAKLAVA_EHIP; }
   int st = build_schedule(ctx, 0, ctx->layer_one_wave ? kDefaultChunk : kDefaultChunkWhole);
   if (st == BAKLAVA_OK) st = build_schedule(ctx, 1, kDefaultChunkWhole);
   if (st != BAKLAVA_OK) { delete ctx; return st; }

@@ -103,26 +103,25 @@ struct DecodeParams {
   int32_t lag;                     // 1: record this call, apply the pending ones when due (MFMA kernel)
   int32_t lag_batch;               // calls a record holds: kLagRows / Gp
   int32_t lag_gp_log2;             // log2(Gp)
-  int32_t ring_slots;              // MFMA kernel, lag: slabs per wavefront whose new scores wait in LDS
-  int32_t keep_rows;               // 1: leave the live rows of each cache in lag_n for the score pass (no records)
+  int32_t ring_slots;              // slabs (tiles) per wavefront whose new scores (logits) wait in LDS
+  // Score tracking without records: the attention kernel leaves the scaled logits of the call (log2 units) here,
+  // head g of arena row r at logits[g * logit_stride + r], and the live rows of each cache in lag_n; the kernel
+  // behind it merges the split partials and adds the weights to the scores.  Null: not asked for.
+  float* logits;
+  int64_t logit_stride;
   int32_t fused_append;            // 1: every cache of the range first receives its new row
   int32_t token_pos;
   int32_t row_bytes;
   float scale_log2e;               // log2(e) / sqrt(D)
 };
 
-// Score pass over the K rows alone, right after the attention kernel of a call that leaves no record:
-// score_j += sum_g 2^(q_g . k_j scale - M_g) / L_g over the live rows of every cache of the range.  With
-// `merge` it merges the split partials as well, in place of the combine kernel.
+// Score pass over the K rows alone (bf16 rows of 128 elements on the vector kernel), behind the combine kernel:
+// score_j += sum_g 2^(q_g . k_j scale - M_g) / L_g over the live rows of every cache of the range.
 struct ScoreParams {
   const void* k;
   const void* q;                   // [layer_count, batch, Hq, D], the call's query rows
-  const float* ml;                 // final_ml of the call (with merge: of caches with a single work item)
-  const float* part_o;             // merge: split partials of the others
-  const float* part_ml;
-  float* out;
-  const int32_t* rows;             // merge: [n_caches, kLagCalls] live rows in this call (first entry)
-  int32_t* len;
+  const float* ml;                 // final_ml of the call
+  const int32_t* len;
   const Item* items;
   float* score;
   int32_t G, Hq, Hkv;
@@ -197,10 +196,10 @@ struct CompactParams {
 void note_hip_error(hipError_t e);
 
 // Launchers (defined next to their kernels).  All return hipError_t of the launch.
-// one_wave: the launch has at most one workgroup per compute unit
-hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, bool one_wave, hipStream_t s);
 // max_count: longest work item of the launch (rows); one_wave: the launch has at most one workgroup per
-// compute unit, so a workgroup may take the whole LDS (score tracking keeps its new scores there)
+// compute unit, so a workgroup may take the whole LDS (score tracking keeps its new scores or logits there)
+hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, int max_count, bool one_wave,
+                              hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s,
                               hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t prepare_decode_mfma();
@@ -215,10 +214,10 @@ hipError_t launch_layer_similarity(const void* x_in, const void* x_out, int n_se
 hipError_t launch_prefill_scores(const void* q, const void* k, const float* lse, const int64_t* row_off,
                                  int batch, int Hq, int Hkv, int T, float* score, hipStream_t s);
 hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t s);
-// max_count: the largest row count of a work item in the launched range (or a bound on it); merge: the
-// pass merges the split partials too (p.rows must hold each cache's live rows)
-hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items, int max_count, bool merge,
-                             hipStream_t s);
+// the end of a tracked call without records: split partials merged, weights added to the scores from p.logits
+hipError_t launch_finish(const DecodeParams& p, int D, int n_multi, int n_items, int max_count, hipStream_t s);
+// max_count: the largest row count of a work item in the launched range (or a bound on it)
+hipError_t launch_score_pass(const ScoreParams& p, int n_items, int max_count, hipStream_t s);
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s);
 hipError_t launch_set_lengths(const LengthsParams& p, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s);

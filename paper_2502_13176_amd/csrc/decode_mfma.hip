@@ -36,8 +36,8 @@
 // the scores are touched only on every (32 / G)-th call (every 8th at G <= 4).  On such a call the
 // scores of a slab are read with the slab and the new values wait in LDS until the work item is
 // done, so the extra HBM writes (4 bytes per row) fall at the end of a launch instead of between
-// the K/V reads.  This is for D = 128; at D = 64 a pass over the K rows right after the call keeps the
-// scores current.
+// the K/V reads.  This is for D = 128; at D = 64, where scores are current when a call returns, the logits go to
+// the workspace at the end of a work item, for the kernel that merges the split partials.
 #include <hip/hip_ext.h>
 
 #include "common.h"
@@ -55,9 +55,7 @@ typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kSlab = 32;       // rows per wavefront iteration
 
-// What follows from the head dimension.  (D = 64: a tracked call over 32 caches of 2500 rows, score pass
-// included, takes 14.8 us at four query heads per cache and 18.1 at eight; with the vector-ALU kernel 19.4 and
-// 28.3.  Records like those of D = 128 would make it 12.5 and 13.8.)
+// What follows from the head dimension.
 template <int D>
 struct Shape {
   // A slab of 64-element rows is half as many bytes, so a workgroup has twice as many wavefronts: the
@@ -158,9 +156,11 @@ __device__ __forceinline__ float record_weights(const floatx4_t (&sp)[kSets][2],
   return (lane & 16) ? w[1] : w[0];
 }
 
-template <int D, bool LAG>
+// TRACK: the call counts for the scores.  At D = 128 it is recorded (LAG), at D = 64 its scaled logits go to p.logits
+// for the kernel behind this one (KEEP).
+template <int D, bool TRACK>
 __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(DecodeParams p) {
-  static_assert(D == 128 || !LAG, "records hold rows of 128 elements");
+  constexpr bool LAG = TRACK && D == 128, KEEP = TRACK && D == 64;
   using S = Shape<D>;
   constexpr int kWaves = S::kWaves, kRow = S::kRow, kVStride = S::kVStride, kKStride = S::kKStride;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves * kSlab * kVStride];
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
     if (add) append_new_row(p, it, n_old, off_c, token_pos);
     else if (it.start == 0 && threadIdx.x == 0) *p.status = 1;
   }
-  if (D == 64 && p.keep_rows && it.start == 0 && threadIdx.x == 0) p.lag_n[(int64_t)it.c * kLagCalls] = n;
+  if (KEEP && it.start == 0 && threadIdx.x == 0) p.lag_n[(int64_t)it.c * kLagCalls] = n;
   int cnt = min(it.start + it.count, n) - it.start;
   if (cnt < 0) cnt = 0;
   const int64_t row0 = off_c + it.start;
@@ -243,7 +243,12 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
   float sc_cur = 0.f;
 #define BAKLAVA_LOAD_SC(T0) \
   if (APPLY && lane < kSlab) sc_cur = sc_base[min((T0) + lane, last)];
-  float* ring = lds_ring + wave * p.ring_slots * kSlab;
+  // KEEP: the logits of a slab wait there as well, [G][32] per slab.
+  float* ring = lds_ring + wave * p.ring_slots * kSlab * (KEEP ? G : 1);
+  // (no area of its own: the logits of a slab pass through this wavefront's K staging area, whose rows have been read)
+  if (KEEP && p.ring_slots == 0) ring = reinterpret_cast<float*>(myk);
+  const int ring_most = KEEP && p.ring_slots == 0 ? 1 : p.ring_slots;
+  static_assert(kSlab * S::kKStride >= 8 * kSlab * 4, "logits of eight heads");
   int ring_n = 0;         // slabs held in the LDS area
   int ring_t0 = 0;        // first row of the oldest one; the others follow at kWaves * kSlab rows each
   auto flush_ring = [&]() {
@@ -251,9 +256,17 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // two slabs per store instruction: lanes 0..31 take an even slot, lanes 32..63 the next one
-    for (int sidx = lane >> 5; sidx < ring_n; sidx += 2) {
-      const int r = ring_t0 + sidx * (kWaves * kSlab) + (lane & 31);
-      if (r < cnt) sc_base[r] = ring[sidx * kSlab + (lane & 31)];
+    if (KEEP) {
+      for (int g = 0; g < G; ++g)
+        for (int sidx = lane >> 5; sidx < ring_n; sidx += 2) {
+          const int r = ring_t0 + sidx * (kWaves * kSlab) + (lane & 31);
+          if (r < cnt) p.logits[g * p.logit_stride + row0 + r] = ring[(sidx * G + g) * kSlab + (lane & 31)];
+        }
+    } else {
+      for (int sidx = lane >> 5; sidx < ring_n; sidx += 2) {
+        const int r = ring_t0 + sidx * (kWaves * kSlab) + (lane & 31);
+        if (r < cnt) sc_base[r] = ring[sidx * kSlab + (lane & 31)];
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();  // the area may be written again
@@ -349,6 +362,15 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
       if (lane < kSlab) ring[ring_n * kSlab + lane] = sc_old + wr;  // lane l: row l of the slab
       if (++ring_n == p.ring_slots) flush_ring();
     }
+    if (KEEP) {
+      if (ring_n == 0) ring_t0 = t0;
+      if (n16 < G) {
+        float* at = ring + (ring_n * G + n16) * kSlab + jg * 4;
+        *reinterpret_cast<floatx4_t*>(at) = floatx4_t{x[0], x[1], x[2], x[3]};
+        *reinterpret_cast<floatx4_t*>(at + 16) = floatx4_t{x[4], x[5], x[6], x[7]};
+      }
+      if (++ring_n == ring_most) flush_ring();
+    }
     float mx = x[0];
 #pragma unroll
     for (int e = 1; e < 8; ++e) mx = fmaxf(mx, x[e]);
@@ -407,7 +429,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
-  if (APPLY && ring_n > 0) flush_ring();
+  if ((APPLY || KEEP) && ring_n > 0) flush_ring();
   };  // stream_rows
   if (LAG && apply) stream_rows(std::integral_constant<bool, LAG>{});
   else stream_rows(std::false_type{});
@@ -535,36 +557,39 @@ __global__ __launch_bounds__(64 * Shape<128>::kWaves) void score_flush_mfma(Deco
 // Dynamic LDS the attention kernel may ask for: the whole LDS of a CU minus the static staging areas
 // when a workgroup has the CU to itself, half of what two workgroups leave otherwise.
 constexpr int kLdsTotal = 160 * 1024;
-constexpr int kStatic = Shape<128>::kStatic;
-constexpr int kDynMax = kLdsTotal - kStatic - 512;
-constexpr int kDynShared = (kLdsTotal - 2 * kStatic - 1024) / 2;
+template <int D> constexpr int dyn_max() { return kLdsTotal - Shape<D>::kStatic - 512; }
+constexpr int kDynShared = (kLdsTotal - 2 * Shape<128>::kStatic - 1024) / 2;
 static_assert(kDynShared >= Shape<128>::kWaves * kSlab * 4, "room for one slab of scores per wavefront");
 constexpr int kFlushDynMax = 48 * 1024;  // the flush kernel's share for waiting scores, beside its K staging area
 
-// Called when a context that may leave records is created on the current device, i.e. outside any stream
+// Called when a context over bf16 rows is created on the current device, i.e. outside any stream
 // capture: raises the kernels' dynamic-LDS limits once, so that launches (captured or not) only launch.
 hipError_t prepare_decode_mfma() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_mfma<128, true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kDynMax);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, dyn_max<128>());
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_mfma<64, true>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, dyn_max<64>());
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(score_flush_mfma),
                              hipFuncAttributeMaxDynamicSharedMemorySize, kFlushDynMax);
 }
 
-// Slabs per wavefront whose new scores fit `bytes` of LDS, at most what the longest item needs.
-int ring_slots(int bytes, int max_count) {
-  constexpr int kWaves = Shape<128>::kWaves;
+// Slabs per wavefront of which `heads` values per row fit `bytes` of LDS, at most what the longest item needs.
+template <int D>
+int ring_slots(int bytes, int max_count, int heads) {
+  constexpr int kWaves = Shape<D>::kWaves;
   const int need = ((max_count + kSlab - 1) / kSlab + kWaves - 1) / kWaves;
-  return std::max(1, std::min(bytes / (kWaves * kSlab * 4), need));
+  return std::max(1, std::min(bytes / (kWaves * kSlab * 4 * heads), need));
 }
 
 // With a pair of events the kernel's own dispatch carries them: they take the time stamps of its
 // first and last wavefront, not those of commands placed around it on the stream.
-template <int D, bool LAG>
+template <int D, bool TRACK>
 hipError_t launch_attention(const DecodeParams& p, int n_items, size_t dyn, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const dim3 grid(n_items), block(64 * Shape<D>::kWaves);
-  if (ev0 && ev1) hipExtLaunchKernelGGL((decode_partial_mfma<D, LAG>), grid, block, dyn, s, ev0, ev1, 0, p);
-  else decode_partial_mfma<D, LAG><<<grid, block, dyn, s>>>(p);
+  if (ev0 && ev1) hipExtLaunchKernelGGL((decode_partial_mfma<D, TRACK>), grid, block, dyn, s, ev0, ev1, 0, p);
+  else decode_partial_mfma<D, TRACK><<<grid, block, dyn, s>>>(p);
   return hipGetLastError();
 }
 
@@ -574,11 +599,21 @@ hipError_t launch_decode_mfma(const DecodeParams& p_in, int D, int n_items, int 
   if (p_in.G > 16 || (D != 128 && (D != 64 || p_in.lag))) return hipErrorInvalidValue;
   DecodeParams p = p_in;
   p.ring_slots = 0;
-  if (D == 64) return launch_attention<64, false>(p, n_items, 0, s, ev0, ev1);
+  if (D == 64) {
+    if (!p.logits) return launch_attention<64, false>(p, n_items, 0, s, ev0, ev1);
+    // An area of its own for the waiting logits only where a workgroup has its compute unit to itself: beside one, two
+    // workgroups do not fit.  Several steps and the flush, us (start: K read again by a pass of its own), all waiting /
+    // stored as they come / through the staging area, whole-model launches over 4 layers of 64 caches of 4096 rows: G =
+    // 1 222 / 228 / 227 (297), 4 296 / 289 / 272 (336), 8 358 / 357 / 330 (434); 96 caches of 2500 rows per layer
+    // launch, 8: 583 / 482 / 469 (626).
+    p.ring_slots = one_wave ? ring_slots<64>(dyn_max<64>(), max_count, p.G) : 0;
+    const size_t dyn = (size_t)p.ring_slots * Shape<64>::kWaves * kSlab * 4 * p.G;
+    return launch_attention<64, true>(p, n_items, dyn, s, ev0, ev1);
+  }
   if (!p.lag) return launch_attention<128, false>(p, n_items, 0, s, ev0, ev1);
   // the LDS left beside the staging areas, split over the wavefronts; a launch of several waves of
   // workgroups keeps room for two workgroups per compute unit
-  p.ring_slots = ring_slots(one_wave ? kDynMax : kDynShared, max_count);
+  p.ring_slots = ring_slots<128>(one_wave ? dyn_max<128>() : kDynShared, max_count, 1);
   const size_t dyn = (size_t)p.ring_slots * Shape<128>::kWaves * kSlab * 4;
   return launch_attention<128, true>(p, n_items, dyn, s, ev0, ev1);
 }
@@ -587,7 +622,7 @@ hipError_t launch_score_flush_mfma(const DecodeParams& p_in, int n_items, int ma
   if (n_items <= 0) return hipSuccess;
   if (p_in.G > 16) return hipErrorInvalidValue;
   DecodeParams p = p_in;
-  p.ring_slots = ring_slots(kFlushDynMax, max_count);
+  p.ring_slots = ring_slots<128>(kFlushDynMax, max_count, 1);
   const size_t dyn = (size_t)p.ring_slots * Shape<128>::kWaves * kSlab * 4;
   score_flush_mfma<<<dim3(n_items), dim3(64 * Shape<128>::kWaves), dyn, s>>>(p);
   return hipGetLastError();

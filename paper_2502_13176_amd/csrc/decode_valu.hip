@@ -9,6 +9,7 @@
 #include "common.h"
 #include "decode_tail.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace baklava {
@@ -67,6 +68,18 @@ __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
+// v[i] of N values that every lane holds, i the lane's own: a tree of selects by the bits of i (depth first, so that
+// few values wait).
+template <int N>
+__device__ __forceinline__ float select_own(const float* v, int i) {
+  if constexpr (N == 1) {
+    return v[0];
+  } else {
+    const float lo = select_own<N / 2>(v, i), hi = select_own<N / 2>(v + N / 2, i);
+    return (i & (N / 2)) ? hi : lo;
+  }
+}
+
 // Wavefronts per workgroup of a launch that has at most one workgroup per compute unit: they alone must
 // keep enough loads in flight (8 KB each, and the next 8 KB during the arithmetic).  Four wavefronts
 // without the tile ahead, with lane sums through the LDS crossbar and a rescale on every tile, read the
@@ -78,7 +91,10 @@ __device__ __forceinline__ float group_sum(float v) {
 // eviction: 639 us, with eight 1024, as it was before 894).
 template <int REGS> constexpr int wide_waves() { return REGS <= 16 ? 16 : 8; }
 
-template <typename T, int D, int GT, int NW>
+// KEEP (score tracking): the scaled logits of the call go to p.logits for the kernel behind this one.  They wait in
+// LDS until the work item is done (or a wavefront's part of the area is full): stores between the loads would slow
+// the stream far beyond their bytes.
+template <typename T, int D, int GT, int NW, bool KEEP>
 __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
   constexpr int EPL = Row<T>::EPL;
   constexpr int LPR = D / EPL;   // lanes per row
@@ -100,7 +116,7 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
     if (add) append_new_row(p, it, n_old, off_c, token_pos);
     else if (it.start == 0 && threadIdx.x == 0) *p.status = 1;
   }
-  if (p.keep_rows && it.start == 0 && threadIdx.x == 0) p.lag_n[(int64_t)it.c * kLagCalls] = n;
+  if (KEEP && it.start == 0 && threadIdx.x == 0) p.lag_n[(int64_t)it.c * kLagCalls] = n;
   int cnt = min(it.start + it.count, n) - it.start;
   if (cnt < 0) cnt = 0;
   const int64_t row0 = off_c + it.start;
@@ -146,6 +162,25 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
     for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
   }
 
+  extern __shared__ __attribute__((aligned(16))) float lds_ring[];
+  float* const ring = lds_ring + (KEEP ? wave * p.ring_slots * (GT * TILE) : 0);  // [tile][head][row]
+  int ring_n = 0;   // tiles in this wavefront's part
+  int ring_t0 = 0;  // first row of the oldest one; the others follow at NW * TILE rows each
+  auto flush_ring = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    int i = lane;
+    asm volatile("" : "+v"(i));  // what follows from it is formed here, not kept in registers over the loop
+    for (; i < ring_n * (GT * TILE); i += 64) {
+      const int g = i / TILE % GT, r = ring_t0 + i / (GT * TILE) * (NW * TILE) + i % TILE;
+      if (g < G && r < cnt) p.logits[g * p.logit_stride + row0 + r] = ring[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();  // the area may be written again
+    ring_n = 0;
+  };
+
   for (; t0 < cnt; t0 += NW * TILE) {
     uint4 kc[U], vc[U];
 #pragma unroll
@@ -166,6 +201,17 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
         d = group_sum<LPR>(d);
         s[u][g] = live ? d : kNegInf;
       }
+    }
+    if (KEEP) {  // the lanes of a row hold all of its logits: each stores one
+      if (ring_n == 0) ring_t0 = t0;
+      constexpr int kPer = U * GT < LPR ? U * GT : LPR;
+#pragma unroll
+      for (int j = 0; j < U * GT; j += kPer) {
+        const int i = j + sub;
+        const float mine = select_own<kPer>(&s[0][0] + j, sub);
+        if (sub < kPer) ring[(ring_n * GT + i % GT) * TILE + i / GT * RPW + rg] = mine;
+      }
+      if (++ring_n == p.ring_slots) flush_ring();
     }
     float mx[GT];
     bool moves = false;
@@ -211,6 +257,8 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
     }
   }
 
+  if (KEEP && ring_n > 0) flush_ring();
+
   // Merge the lane groups of a wavefront (lanes with equal `sub`).
 #pragma unroll
   for (int o = LPR; o < 64; o <<= 1) {
@@ -246,12 +294,12 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
 // which is the softmax of Eq. 7 with the sum over rows regrouped by split.  One workgroup per
 // (cache with several work items, query head); 256 / D thread groups share the splits.
 template <int D>
-__global__ __launch_bounds__(256) void combine_kernel(DecodeParams p) {
+__device__ __forceinline__ void combine_head(const DecodeParams& p, int block) {
   constexpr int GROUPS = 256 / D;
   const int G = p.G;
-  const MultiCache mc = p.multi[blockIdx.x / G];
+  const MultiCache mc = p.multi[block / G];
   const int c = mc.c;
-  const int g = blockIdx.x % G;
+  const int g = block % G;
   const int tid = threadIdx.x;
   const int d = tid % D, grp = tid / D;
   const int ib = mc.slot_begin, ie = mc.slot_end;
@@ -318,56 +366,44 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeParams p) {
   }
 }
 
-// score_j += sum_g 2^(q_g . k_j scale - M_g) / L_g  (cumulative attention per cached token, summed
-// over the query heads that share the cache), from the K rows alone once the normalisers of the
-// call are final: the score update of the vector-ALU path and of bf16 rows of 64 elements, launched right
-// after the attention kernel.
-// Workgroup (x, y) updates rows [y * kScoreTile, +kScoreTile) of work item x, so that long work
-// items still spread over many workgroups.  Row layout as in the attention kernel above: a row
-// over D / EPL lanes, 64 / (D / EPL) rows per wavefront load; a wavefront keeps eight of them in
-// flight, and lane u of a row's lanes adds the weight of the u-th one, so that the scores of a tile
-// are read and written by one instruction each.  One load in flight per wavefront and 1024 rows per
-// workgroup took 35 us for 33 MB of K, this takes 8.
-// With MERGE a cache's normalisers are merged from its split partials by every workgroup for itself,
-// beside its first K loads, and a last slice of workgroups (one per cache) merges the outputs: the pass
-// takes the place of the combine kernel.  That saves a launch (eight tracked calls over 67 MB of fp32
-// caches, D = 64: 222 -> 203 us), but each workgroup pays for the merge: the caller's rule says where it is
-// taken, with both sides measured.
-constexpr int kScoreTile = 256;
-template <typename T, int D, int GT, bool MERGE>
-__global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
-  constexpr int EPL = Row<T>::EPL;
-  constexpr int LPR = D / EPL;
-  constexpr int RPW = 64 / LPR;
-  constexpr int U = 8;
-  static_assert(U <= LPR, "one lane of a row per row in flight");
-  const Item it = p.items[blockIdx.x];
+template <int D>
+__global__ __launch_bounds__(256) void combine_kernel(DecodeParams p) { combine_head<D>(p, blockIdx.x); }
+
+// The end of a tracked call without records: in place of the combine kernel (the first n_combine workgroups, one per
+// cache with several work items and query head) and of a pass over the K rows,
+//   score_j += sum_g 2^(x_gj - M_g) / L_g   (cumulative attention per cached token, summed over the query heads)
+// from the logits x that the attention kernel has left.  The other workgroups take kFinishRows rows of a work item
+// each and merge their cache's normalisers from the split partials for themselves, behind the loads of the rows.
+// Reads 4 G bytes per row where a pass over the K rows read the row and formed the products again: 8 tracked calls
+// over 67 MB of fp32 caches (D = 64, two query heads) take 167 us (203), four steps of two layers of 32 caches of 4096
+// rows, D = 128, eight heads, 377 (499), bf16, D = 64, eight heads, 154 (199).
+constexpr int kFinishRows = 512;
+template <int D, int GT>
+__global__ __launch_bounds__(256) void finish_kernel(DecodeParams p, int n_combine, int tiles) {
+  if ((int)blockIdx.x < n_combine) {
+    combine_head<D>(p, blockIdx.x);
+    return;
+  }
+  const int b = blockIdx.x - n_combine;
+  const Item it = p.items[b / tiles];
   const int G = p.G;
-  // (the merge advances len itself)
-  const int n = MERGE ? p.rows[(int64_t)it.c * kLagCalls] : p.len[it.c];
-  const bool merge = MERGE && blockIdx.y == gridDim.y - 1;
-  if (merge && (it.start != 0 || it.nsplit == 1)) return;
-  const int cnt = merge ? 0 : min(it.start + it.count, n) - it.start;
-  const int r_begin = blockIdx.y * kScoreTile;
-  if (!merge && r_begin >= cnt) return;
-  const int r_end = min(cnt, r_begin + kScoreTile);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = lane % LPR, rg = lane / LPR;
-  const T* Kb = reinterpret_cast<const T*>(p.k) + it.row0 * D + sub * EPL;
-  uint4 kraw[U];
-  auto load_tile = [&](int r0) {
+  const int n = p.lag_n[(int64_t)it.c * kLagCalls];  // (len may already count this call's new row, or not yet)
+  const int cnt = min(it.start + it.count, n) - it.start;
+  const int r_begin = b % tiles * kFinishRows;
+  if (r_begin >= cnt) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int R = kFinishRows / 256;
+  float x[R][GT], old[R];
 #pragma unroll
-    for (int u = 0; u < U; ++u) kraw[u] = load_nt16(Kb + (int64_t)min(r0 + u * RPW + rg, r_end - 1) * D);
-  };
-  int r0 = r_begin + wave * (U * RPW);
-  if (r0 < r_end) load_tile(r0);
-  const int c_rel = it.c - p.cache_begin;
-  const int64_t qrow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
+  for (int k = 0; k < R; ++k) {
+    const int64_t row = it.row0 + min(r_begin + k * 256 + tid, cnt - 1);
+#pragma unroll
+    for (int g = 0; g < GT; ++g) x[k][g] = p.logits[min(g, G - 1) * p.logit_stride + row];
+    old[k] = p.score[row];
+  }
   // (max, 1 / sum) of every query head over the cache's work items
   __shared__ float sm_m[GT], sm_inv[GT];
-  if (!MERGE) {
-    // final_ml, read below
-  } else if (it.nsplit > 1) {
+  if (it.nsplit > 1) {
     for (int g = wave; g < G; g += 4) {
       float m = kNegInf, l = 0.f;
       for (int s = lane; s < it.nsplit; s += 64) m = fmaxf(m, p.part_ml[((int64_t)(it.slot0 + s) * G + g) * 2]);
@@ -382,25 +418,55 @@ __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
       for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
       if (lane == 0) { sm_m[g] = m; sm_inv[g] = 1.f / l; }
     }
-  } else if ((int)threadIdx.x < G) {
-    sm_m[threadIdx.x] = p.ml[((int64_t)it.c * G + threadIdx.x) * 2];
-    sm_inv[threadIdx.x] = p.ml[((int64_t)it.c * G + threadIdx.x) * 2 + 1];
+  } else if (tid < G) {
+    sm_m[tid] = p.final_ml[((int64_t)it.c * G + tid) * 2];
+    sm_inv[tid] = p.final_ml[((int64_t)it.c * G + tid) * 2 + 1];
   }
-  if (MERGE) __syncthreads();
-  if (merge) {
-    // out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), as in the combine kernel
-    for (int idx = threadIdx.x; idx < G * D; idx += 256) {
-      const int g = idx / D, d = idx % D;
-      const float m = sm_m[g];
-      float o = 0.f;
-#pragma unroll 8
-      for (int s = it.slot0; s < it.slot0 + it.nsplit; ++s)
-        o += p.part_o[((int64_t)s * G + g) * D + d] * fast_exp2(p.part_ml[((int64_t)s * G + g) * 2] - m);
-      p.out[(qrow0 + g) * D + d] = o * sm_inv[g];
-    }
-    if (threadIdx.x == 0) p.len[it.c] = n;  // a fused append's row is now counted
-    return;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int r = r_begin + k * 256 + tid;
+    float w = 0.f;
+#pragma unroll
+    for (int g = 0; g < GT; ++g)
+      if (g < G) w += fast_exp2(x[k][g] - sm_m[g]) * sm_inv[g];
+    if (r < cnt) p.score[it.row0 + r] = old[k] + w;
   }
+}
+
+// The score update of the vector kernel over rows whose calls are otherwise recorded (bf16, D = 128), right after the
+// combine kernel: a pass over the K rows.
+// Workgroup (x, y) updates rows [y * kScoreTile, +kScoreTile) of work item x, so that long work
+// items still spread over many workgroups.  Row layout as in the attention kernel above: a row
+// over D / EPL lanes, 64 / (D / EPL) rows per wavefront load; a wavefront keeps eight of them in
+// flight, and lane u of a row's lanes adds the weight of the u-th one, so that the scores of a tile
+// are read and written by one instruction each.
+constexpr int kScoreTile = 256;
+template <typename T, int D, int GT>
+__global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
+  constexpr int EPL = Row<T>::EPL;
+  constexpr int LPR = D / EPL;
+  constexpr int RPW = 64 / LPR;
+  constexpr int U = 8;
+  static_assert(U <= LPR, "one lane of a row per row in flight");
+  const Item it = p.items[blockIdx.x];
+  const int G = p.G;
+  const int cnt = min(it.start + it.count, p.len[it.c]) - it.start;
+  const int r_begin = blockIdx.y * kScoreTile;
+  if (r_begin >= cnt) return;
+  const int r_end = min(cnt, r_begin + kScoreTile);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int sub = lane % LPR, rg = lane / LPR;
+  const T* Kb = reinterpret_cast<const T*>(p.k) + it.row0 * D + sub * EPL;
+  uint4 kraw[U];
+  auto load_tile = [&](int r0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) kraw[u] = load_nt16(Kb + (int64_t)min(r0 + u * RPW + rg, r_end - 1) * D);
+  };
+  int r0 = r_begin + wave * (U * RPW);
+  if (r0 < r_end) load_tile(r0);
+  const int c_rel = it.c - p.cache_begin;
+  const int64_t qrow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
   const T* qrows = reinterpret_cast<const T*>(p.q) + qrow0 * D;
   float qr[GT][EPL], M[GT], inv[GT];
 #pragma unroll
@@ -413,8 +479,8 @@ __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
       Row<T>::widen(*reinterpret_cast<const uint4*>(qrows + g * D + sub * EPL), qr[g]);
 #pragma unroll
       for (int e = 0; e < EPL; ++e) qr[g][e] *= p.scale_log2e;
-      M[g] = MERGE ? sm_m[g] : p.ml[((int64_t)it.c * G + g) * 2];
-      inv[g] = MERGE ? sm_inv[g] : p.ml[((int64_t)it.c * G + g) * 2 + 1];
+      M[g] = p.ml[((int64_t)it.c * G + g) * 2];
+      inv[g] = p.ml[((int64_t)it.c * G + g) * 2 + 1];
     }
   }
   float* sc = p.score + it.row0;
@@ -479,31 +545,54 @@ __global__ void fill_i32_kernel(int32_t* dst, int32_t value, int64_t n) {
   if (i < n) dst[i] = value;
 }
 
+// LDS for the logits that wait (KEEP), beside the hand-over area: within the 64 KiB that need no attribute in a launch
+// of one workgroup per compute unit, less where several share one.
+constexpr int kRingAlone = 60 * 1024, kRingShared = 16 * 1024;
+
+template <typename T, int D, int GT, int NW>
+void launch_valu_nw(DecodeParams p, int n_items, int max_count, bool one_wave, hipStream_t s) {
+  const dim3 grid(n_items), block(64 * NW);
+  if constexpr (Row<T>::EPL == 8 && D == 128) p.logits = nullptr;  // (calls over these rows leave none)
+  if (!p.logits) {
+    decode_partial_valu<T, D, GT, NW, false><<<grid, block, 0, s>>>(p);
+    return;
+  }
+  if constexpr (!(Row<T>::EPL == 8 && D == 128)) {
+    constexpr int kTile = 64 / (D / Row<T>::EPL) * 4, kSlot = GT * kTile * 4;  // rows of a tile, bytes of its logits
+    constexpr int kHandOver = (NW * GT * D + 2 * NW * GT) * 4;
+    const int room = one_wave ? kRingAlone - kHandOver : kRingShared;
+    const int need = (max_count + NW * kTile - 1) / (NW * kTile);
+    p.ring_slots = std::max(1, std::min(room / (NW * kSlot), need));
+    decode_partial_valu<T, D, GT, NW, true><<<grid, block, (size_t)p.ring_slots * NW * kSlot, s>>>(p);
+  }
+}
+
 template <typename T, int D, int GT>
-void launch_valu(const DecodeParams& p, int n_items, bool one_wave, hipStream_t s) {
+void launch_valu(const DecodeParams& p, int n_items, int max_count, bool one_wave, hipStream_t s) {
   constexpr int NW = wide_waves<GT * Row<T>::EPL>();
-  if (one_wave) decode_partial_valu<T, D, GT, NW><<<dim3(n_items), dim3(64 * NW), 0, s>>>(p);
-  else decode_partial_valu<T, D, GT, 4><<<dim3(n_items), dim3(256), 0, s>>>(p);
+  if (one_wave) launch_valu_nw<T, D, GT, NW>(p, n_items, max_count, one_wave, s);
+  else launch_valu_nw<T, D, GT, 4>(p, n_items, max_count, one_wave, s);
 }
 
 template <typename T, int D>
-hipError_t launch_valu_g(const DecodeParams& p, int n_items, bool one_wave, hipStream_t s) {
-  if (p.G <= 1) launch_valu<T, D, 1>(p, n_items, one_wave, s);
-  else if (p.G <= 2) launch_valu<T, D, 2>(p, n_items, one_wave, s);
-  else if (p.G <= 4) launch_valu<T, D, 4>(p, n_items, one_wave, s);
-  else if (p.G <= 8) launch_valu<T, D, 8>(p, n_items, one_wave, s);
+hipError_t launch_valu_g(const DecodeParams& p, int n_items, int max_count, bool one_wave, hipStream_t s) {
+  if (p.G <= 1) launch_valu<T, D, 1>(p, n_items, max_count, one_wave, s);
+  else if (p.G <= 2) launch_valu<T, D, 2>(p, n_items, max_count, one_wave, s);
+  else if (p.G <= 4) launch_valu<T, D, 4>(p, n_items, max_count, one_wave, s);
+  else if (p.G <= 8) launch_valu<T, D, 8>(p, n_items, max_count, one_wave, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, bool one_wave, hipStream_t s) {
+hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_items, int max_count, bool one_wave,
+                              hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  if (dtype == 0 && D == 128) return launch_valu_g<uint16_t, 128>(p, n_items, one_wave, s);
-  if (dtype == 0 && D == 64) return launch_valu_g<uint16_t, 64>(p, n_items, one_wave, s);
-  if (dtype == 1 && D == 128) return launch_valu_g<float, 128>(p, n_items, one_wave, s);
-  if (dtype == 1 && D == 64) return launch_valu_g<float, 64>(p, n_items, one_wave, s);
+  if (dtype == 0 && D == 128) return launch_valu_g<uint16_t, 128>(p, n_items, max_count, one_wave, s);
+  if (dtype == 0 && D == 64) return launch_valu_g<uint16_t, 64>(p, n_items, max_count, one_wave, s);
+  if (dtype == 1 && D == 128) return launch_valu_g<float, 128>(p, n_items, max_count, one_wave, s);
+  if (dtype == 1 && D == 64) return launch_valu_g<float, 64>(p, n_items, max_count, one_wave, s);
   return hipErrorInvalidValue;
 }
 
@@ -516,30 +605,33 @@ hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t
   return hipGetLastError();
 }
 
-template <typename T, int D, bool MERGE>
-hipError_t launch_score_g(const ScoreParams& p, const dim3& grid, hipStream_t s) {
-  if (p.G <= 2) score_pass_kernel<T, D, 2, MERGE><<<grid, dim3(256), 0, s>>>(p);
-  else if (p.G <= 4) score_pass_kernel<T, D, 4, MERGE><<<grid, dim3(256), 0, s>>>(p);
-  else if (p.G <= 8) score_pass_kernel<T, D, 8, MERGE><<<grid, dim3(256), 0, s>>>(p);
+template <int D>
+hipError_t launch_finish_d(const DecodeParams& p, int n_multi, int n_items, int max_count, hipStream_t s) {
+  const int tiles = (max_count + kFinishRows - 1) / kFinishRows, n_combine = n_multi * p.G;
+  const dim3 grid(n_combine + n_items * tiles), block(256);
+  if (p.G <= 1) finish_kernel<D, 1><<<grid, block, 0, s>>>(p, n_combine, tiles);
+  else if (p.G <= 2) finish_kernel<D, 2><<<grid, block, 0, s>>>(p, n_combine, tiles);
+  else if (p.G <= 4) finish_kernel<D, 4><<<grid, block, 0, s>>>(p, n_combine, tiles);
+  else if (p.G <= 8) finish_kernel<D, 8><<<grid, block, 0, s>>>(p, n_combine, tiles);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-template <bool MERGE>
-hipError_t launch_score(const ScoreParams& p, int dtype, int D, const dim3& grid, hipStream_t s) {
-  if (dtype == 0 && D == 128) return launch_score_g<uint16_t, 128, MERGE>(p, grid, s);
-  if (dtype == 0 && D == 64) return launch_score_g<uint16_t, 64, MERGE>(p, grid, s);
-  if (dtype == 1 && D == 128) return launch_score_g<float, 128, MERGE>(p, grid, s);
-  if (dtype == 1 && D == 64) return launch_score_g<float, 64, MERGE>(p, grid, s);
+hipError_t launch_finish(const DecodeParams& p, int D, int n_multi, int n_items, int max_count, hipStream_t s) {
+  if (n_items <= 0 || max_count <= 0) return hipSuccess;
+  if (D == 128) return launch_finish_d<128>(p, n_multi, n_items, max_count, s);
+  if (D == 64) return launch_finish_d<64>(p, n_multi, n_items, max_count, s);
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_score_pass(const ScoreParams& p, int dtype, int D, int n_items, int max_count, bool merge,
-                             hipStream_t s) {
+hipError_t launch_score_pass(const ScoreParams& p, int n_items, int max_count, hipStream_t s) {
   if (n_items <= 0 || max_count <= 0) return hipSuccess;
-  const int tiles = (max_count + kScoreTile - 1) / kScoreTile;
-  return merge ? launch_score<true>(p, dtype, D, dim3(n_items, tiles + 1), s)
-               : launch_score<false>(p, dtype, D, dim3(n_items, tiles), s);
+  const dim3 grid(n_items, (max_count + kScoreTile - 1) / kScoreTile), block(256);
+  if (p.G <= 2) score_pass_kernel<uint16_t, 128, 2><<<grid, block, 0, s>>>(p);
+  else if (p.G <= 4) score_pass_kernel<uint16_t, 128, 4><<<grid, block, 0, s>>>(p);
+  else if (p.G <= 8) score_pass_kernel<uint16_t, 128, 8><<<grid, block, 0, s>>>(p);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s) {

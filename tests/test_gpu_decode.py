@@ -328,6 +328,39 @@ def test_vector_kernel_tiles_and_rising_logits(dtype, D, G):
     arena.close()
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("G", [1, 3, 8])
+def test_scores_from_the_logits_of_a_call(dtype, D, G):
+    """Tracked calls that leave no record keep their logits in LDS until a work item ends: work items longer than
+    that area holds, launches of one and of several workgroups per compute unit, ragged ends, caches with one work
+    item and with several.  The scores of two calls against the oracle's weights."""
+    H = _h()
+    ring = [1, 33, 255, 511, 513, 1281, 2560, 2561, 6000]
+    many = [1 + (37 * i) % 700 for i in range(300)]
+    for lens, chunk in ((ring, 8192), (ring, 256), (many, 256)):
+        w = synth.shrink(synth.WORKLOADS["tiny"], name="logits", L=1, Hq=G * len(lens), Hkv=len(lens), D=D, batch=1,
+                         dtype=dtype, seed=97, sink=1, recent=1, slack=0)
+        rng = np.random.Generator(np.random.PCG64(w.seed + G))
+        arena = H.make_arena(w, [max(8, n) for n in lens], track=True)
+        H.set_chunk(arena, chunk)
+        st = H.fill_from_host(arena, w, lens, rng)
+        want = [np.zeros(n) for n in lens]
+        for _ in range(2):
+            q, q64 = H.make_q(w, rng, w.L)
+            H.gpu_decode(arena, w, q)
+            for c in range(0, len(lens), 1 if lens is ring else 7):
+                l, b, hs = H.q_rows_of_cache(w, c)
+                _, p = O.decode_attn(q64[l, b, hs], synth.storage_to_f64(st.K[c], dtype), synth.storage_to_f64(st.V[c], dtype))
+                want[c] += p.sum(0)
+        post = H.download(arena, w)
+        for c in range(0, len(lens), 1 if lens is ring else 7):
+            # 2 G weights of at most 1, each from a logit of at most about 16 with an error of a few units of 2^-24
+            assert np.max(np.abs(post.score[c] - want[c])) <= 2 * G * 2.0 ** -19, (lens[c], chunk)
+        for c in range(len(lens)):
+            assert abs(post.score[c].astype(np.float64).sum() - 2 * G) <= 2 * G * 2.0 ** -17, (lens[c], chunk)
+        arena.close()
+
+
 def _two_term_attention(q, K, V):
     """Attention in 64 bits but for the weights, which are cut to two bf16 terms (high part and residual)."""
     s = (q @ K.T) * (np.log2(np.e) / np.sqrt(K.shape[1]))
