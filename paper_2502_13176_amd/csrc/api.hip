@@ -39,7 +39,7 @@ struct WorkspacePlan {
   // index 0: schedule for launches over a layer sub-range, 1: for launches over the whole model
   size_t items[2], multi[2];
   size_t part_o, part_ml, final_ml, logits, lag_q, lag_ml, lag_n, lag_cnt, status, kept, info, order_all, order_layer;
-  size_t segs, seg_split, halo_k, halo_v, halo_score, halo_pos, tiles, tile_hist, sel_state, total;
+  size_t segs, seg_split, halo_k, halo_v, halo_score, halo_pos, tiles, spread, tile_hist, sel_state, total;
   int64_t n_segs, halo_rows, n_tiles, n_long;
   int32_t seg_rows;  // destination rows per segment of the eviction move
   int64_t max_items;
@@ -146,6 +146,7 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
       w.n_long += 1;
     }
   w.tiles = o;        o = align256(o + (size_t)w.n_tiles * sizeof(SelTile));
+  w.spread = o;       o = align256(o + (size_t)(w.n_tiles + n_caches) * sizeof(SelTile));
   w.tile_hist = o;    o = align256(o + (size_t)w.n_tiles * 4 * 256 * 4);
   w.sel_state = o;    o = align256(o + (size_t)w.n_long * 4 * sizeof(SelState));
   w.total = o;
@@ -165,7 +166,8 @@ struct baklava_ctx {
   std::vector<int32_t> order_all, order_layer;  // caches, longest first (whole model / inside each layer)
   std::vector<int32_t> seg_begin;               // cache -> first segment of the eviction move
   std::vector<int32_t> tile_begin;              // cache -> first tile of the tiled selection (long caches only have any)
-  std::vector<int32_t> n_wide;                  // layer -> caches with more than kHeldRows / 4 rows of capacity
+  std::vector<int32_t> spread_begin;            // cache -> first tile of the selection by several workgroups per cache
+  std::vector<int32_t> n_wide;                  // layer -> caches with more than kNarrowRows rows of capacity
   int32_t kernel_pref;
   bool layer_one_wave;   // default schedule of layer-range launches: one workgroup per compute unit
   int32_t target_items;  // > 0: layer-range launches lengthen their runs until a layer has at most this many items
@@ -235,29 +237,54 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   return BAKLAVA_OK;
 }
 
-// Tile table of the eviction's selection for long caches (depends on capacities and the threshold
-// only), in cache order, so that the tiles of a layer range are a contiguous slice.
+// Tile tables of the eviction's selection (they depend on capacities and the threshold only), in cache order, so that
+// the tiles of a layer range are a contiguous slice: one of the long caches, one of all others (spread; a single entry
+// for those of up to kNarrowRows rows).  The two share the tile counters.
 int build_tiles(baklava_ctx* ctx) {
-  std::vector<SelTile> tiles;
+  std::vector<SelTile> tiles, spread;
   const int64_t n_caches = ctx->n_caches;
-  std::vector<int32_t> tile_begin(n_caches + 1, 0);
-  int32_t n_long = 0;
+  std::vector<int32_t> tile_begin(n_caches + 1, 0), spread_begin(n_caches + 1, 0);
+  int32_t n_long = 0, counters = 0;
   for (int64_t c = 0; c < n_caches; ++c) {
     tile_begin[c] = (int32_t)tiles.size();
-    if (ctx->cap[c] <= ctx->select_long_rows) continue;
-    const int32_t nt = (int32_t)(((int64_t)ctx->cap[c] + kTileRows - 1) / kTileRows);
-    const int32_t first = (int32_t)tiles.size();
-    for (int32_t t = 0; t < nt; ++t) tiles.push_back(SelTile{(int32_t)c, t, first, nt, n_long, 0});
-    n_long += 1;
+    spread_begin[c] = (int32_t)spread.size();
+    const bool is_long = ctx->cap[c] > ctx->select_long_rows;
+    const int32_t nt = is_long || ctx->cap[c] > kNarrowRows ? (int32_t)(((int64_t)ctx->cap[c] + kTileRows - 1) / kTileRows) : 1;
+    for (int32_t t = 0; t < nt; ++t)
+      (is_long ? tiles : spread).push_back(SelTile{(int32_t)c, t, counters, nt, is_long ? n_long : 0, 0});
+    if (is_long || nt > 1) counters += nt;
+    n_long += is_long ? 1 : 0;
   }
   tile_begin[n_caches] = (int32_t)tiles.size();
-  if ((int64_t)tiles.size() > ctx->plan.n_tiles || n_long > ctx->plan.n_long) return BAKLAVA_ECAPACITY;
-  if (!hip_ok(hipDeviceSynchronize())) return BAKLAVA_EHIP;  // no launch may still read the old table
-  if (!tiles.empty() &&
-      !hip_ok(hipMemcpy(ctx->ws + ctx->plan.tiles, tiles.data(), tiles.size() * sizeof(SelTile), hipMemcpyHostToDevice)))
+  spread_begin[n_caches] = (int32_t)spread.size();
+  if (counters > ctx->plan.n_tiles || (int64_t)spread.size() > ctx->plan.n_tiles + n_caches || n_long > ctx->plan.n_long)
+    return BAKLAVA_ECAPACITY;
+  if (!hip_ok(hipDeviceSynchronize())) return BAKLAVA_EHIP;  // no launch may still read the old tables
+  if ((!tiles.empty() &&
+       !hip_ok(hipMemcpy(ctx->ws + ctx->plan.tiles, tiles.data(), tiles.size() * sizeof(SelTile), hipMemcpyHostToDevice))) ||
+      (!spread.empty() &&
+       !hip_ok(hipMemcpy(ctx->ws + ctx->plan.spread, spread.data(), spread.size() * sizeof(SelTile), hipMemcpyHostToDevice))))
     return BAKLAVA_EHIP;
   ctx->tile_begin.swap(tile_begin);
+  ctx->spread_begin.swap(spread_begin);
   return BAKLAVA_OK;
+}
+
+// Whether several workgroups rank each of the range's caches of more than kNarrowRows rows.  Every one of them reads the
+// scores of its cache, so this pays while they leave compute units idle.  us per eviction, one workgroup per cache /
+// spread (workgroups): caches of 20000 rows 64 102 / 91 (192), 128 160 / 161 (384), 256 302 / 317 (768); of 32768 rows
+// 64 140 / 127 (256), 128 225 / 228 (512); of 50000 rows 32 150 / 135 (224), 64 222 / 227 (448).
+// Beside caches that need one workgroup only the line lies further out: 104 caches of 16385 to 32832 rows (416) and 408
+// shorter ones, rankings of 53 us in two launches / 45.
+bool spread_selection(const baklava_ctx* ctx, int64_t c0, int64_t c1) {
+  int64_t tiles = 0;
+  bool all_wide = true;
+  for (int64_t c = c0; c < c1; ++c) {
+    const int32_t nt = ctx->spread_begin[c + 1] - ctx->spread_begin[c];
+    tiles += nt > 1 ? nt : 0;
+    all_wide = all_wide && nt != 1;
+  }
+  return tiles > 0 && 2 * tiles <= (all_wide ? 3 : 4) * (int64_t)ctx->n_cus;
 }
 
 bool range_ok(const baklava_ctx* ctx, int32_t lb, int32_t lc) {
@@ -544,7 +571,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
   // 1716 / 1838.
   ctx->select_long_rows = kHeldRows;
   ctx->n_wide.assign(desc->L, 0);
-  for (int64_t c = 0; c < n_caches; ++c) ctx->n_wide[c / ctx->cpl] += ctx->cap[c] > kHeldRows / 4 ? 1 : 0;
+  for (int64_t c = 0; c < n_caches; ++c) ctx->n_wide[c / ctx->cpl] += ctx->cap[c] > kNarrowRows ? 1 : 0;
   {
     const int st = build_tiles(ctx);
     if (st != BAKLAVA_OK) { delete ctx; return st; }
@@ -770,7 +797,12 @@ extern "C" int baklava_compact(baklava_ctx* ctx, int32_t layer_begin, int32_t la
   p.sel_state = reinterpret_cast<SelState*>(ctx->ws + ctx->plan.sel_state);
   p.long_rows = ctx->select_long_rows;
   const int n_wide = std::accumulate(ctx->n_wide.begin() + layer_begin, ctx->n_wide.begin() + layer_begin + layer_count, 0);
-  if (!hip_ok(launch_compact_select(p, (int)(c1 - c0), n_wide, whole || layer_count == 1, t1 - t0, s))) return BAKLAVA_EHIP;
+  const int32_t sp0 = ctx->spread_begin[c0], n_spread = ctx->spread_begin[c1] - sp0;
+  const bool spread = spread_selection(ctx, c0, c1);
+  if (!hip_ok(launch_compact_select(p, (int)(c1 - c0), n_wide, whole || layer_count == 1, t1 - t0,
+                                    reinterpret_cast<const SelTile*>(ctx->ws + ctx->plan.spread) + sp0,
+                                    spread ? n_spread : 0, s)))
+    return BAKLAVA_EHIP;
   if (!hip_ok(launch_compact_move(p, s1 - s0, s))) return BAKLAVA_EHIP;
   for (int64_t c = c0; c < c1; ++c) {
     const int32_t b = ctx->budget[(c / ctx->cpl) * ctx->d.Hkv + c % ctx->d.Hkv];

@@ -25,6 +25,7 @@ constexpr int kLagCalls = 8;   // most calls such a record holds
 constexpr int kMoveSegMin = 128, kMoveSegMax = 4096;  // destination rows per workgroup of the eviction move
 constexpr int kTileRows = 8192;     // rows per tile of a cache that is ranked tile by tile (one workgroup per tile and pass)
 constexpr int kHeldRows = 65536;     // most rows of a cache that one workgroup ranks, in its registers
+constexpr int kNarrowRows = kHeldRows / 4;  // most rows of a cache of which two such workgroups fit a compute unit
 constexpr int kMinLongRows = kTileRows;  // smallest capacity from which a cache may be ranked that way
 
 // One split-K work item (same layout as baklava_work_item of the public header): rows
@@ -45,10 +46,10 @@ struct CompactInfo {
   int32_t pad;
 };
 
-// One tile of a cache that is too long for one workgroup's selection.
+// One tile of a cache that several workgroups rank (or, in the second table, the only one of a short cache).
 struct SelTile {
   int32_t c, tile;
-  int32_t first_tile;  // index of the cache's tile 0 in the tile table
+  int32_t first_tile;  // index of the counters of the cache's tile 0
   int32_t n_tiles;     // tiles of the cache
   int32_t long_idx;    // index of the cache among the caches that are ranked this way
   int32_t pad;
@@ -221,9 +222,10 @@ hipError_t launch_score_pass(const ScoreParams& p, int n_items, int max_count, h
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s);
 hipError_t launch_set_lengths(const LengthsParams& p, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s);
-// n_wide: caches of the range with more than kHeldRows / 4 rows of capacity; sorted: they come first in p.order
+// n_wide: caches of the range with more than kNarrowRows rows of capacity; sorted: they come first in p.order
+// n_spread > 0: the caches of up to p.long_rows rows are ranked by the workgroups spread[0 .. n_spread)
 hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
-                                 hipStream_t s);
+                                 const SelTile* spread, int n_spread, hipStream_t s);
 hipError_t launch_compact_move(const CompactParams& p, int n_segs, hipStream_t s);
 hipError_t launch_stream_probe(void* dst, const void* src, int64_t bytes, int mode, hipStream_t s);
 

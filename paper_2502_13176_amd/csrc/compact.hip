@@ -218,6 +218,22 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
   return v;
 }
 
+// Word i of an array that the whole workgroup reads or writes: a uniform base and a 32-bit offset (i < 2^30).
+template <typename T>
+__device__ __forceinline__ T word_at(const T* base, int i) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)i * 4u);
+}
+// Word `block` + the thread's number of m, the last one in place of those past it.
+template <typename T>
+__device__ __forceinline__ T block_word(const T* base, int block, int m) {
+  const int b = min(block, m - 1);
+  return word_at(base + b, min((int)threadIdx.x, m - 1 - b));
+}
+template <typename T>
+__device__ __forceinline__ void set_word(T* base, int i, T v) {
+  *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + (uint32_t)i * 4u) = v;
+}
+
 // Exclusive prefix sum of `v` over the workgroup of kHeldThreads; `sm` holds one word per wavefront and
 // is not read again after the barrier of the caller's next step.
 __device__ __forceinline__ int held_exclusive_scan(int v, int* sm) {
@@ -230,13 +246,139 @@ __device__ __forceinline__ int held_exclusive_scan(int v, int* sm) {
   return (wave > 0 ? before : 0) + incl - v;
 }
 
+// One key more of digit `digit`.  64 lanes that meet on one counter would be served one after the other, so a
+// wavefront whose active lanes all have the same digit (many equal scores) adds them up first.
+__device__ __forceinline__ void count_key(int* hist, int digit) {
+  const uint64_t here = __ballot(true);
+  if (__ballot(digit == __builtin_amdgcn_readfirstlane(digit)) == here) {
+    if (__builtin_amdgcn_mbcnt_hi((uint32_t)(here >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)here, 0)) == 0)
+      atomicAdd(&hist[digit], __popcll(here));
+  } else {
+    atomicAdd(&hist[digit], 1);
+  }
+}
+
+// LDS of a workgroup that ranks.
 template <int KEYS>
-__global__ __launch_bounds__(kHeldThreads) void compact_select_kernel(CompactParams p, int cap_above, int cap_most) {
-  const int c = p.order[blockIdx.x];
-  const int cap = p.cap[c];
-  if (cap <= cap_above || cap > cap_most) return;  // another launch's
+struct HeldShared {
+  int hist[kHeldBins];
+  int scan[2 * kHeldWaves];
+  int digit, need, first;
+  int sure_before[KEYS * kHeldWaves], eq_before[KEYS * kHeldWaves];
+};
+
+// The digit of the need-th largest key from the counters of a pass; need becomes its rank among the keys of that
+// digit.  Thread t looks at the digits 2047 - 2t (c_hi keys) and 2046 - 2t (c_lo): exactly one digit has above <
+// need <= above + its own count.  Ends with a barrier.
+__device__ __forceinline__ int held_find_digit(int c_hi, int c_lo, int& need, int* scan, int* sh_digit, int* sh_need) {
+  const int d_hi = kHeldBins - 1 - 2 * threadIdx.x;
+  const int above = held_exclusive_scan(c_hi + c_lo, scan);
+  if (above < need && above + c_hi >= need) {
+    *sh_digit = d_hi;
+    *sh_need = need - above;
+  } else if (above + c_hi < need && above + c_hi + c_lo >= need) {
+    *sh_digit = d_hi - 1;
+    *sh_need = need - above - c_hi;
+  }
+  __syncthreads();
+  need = *sh_need;
+  return *sh_digit;
+}
+template <int KEYS>
+__device__ __forceinline__ int held_find_digit(HeldShared<KEYS>& sm, int& need) {  // leaves the counters cleared
+  const int d_hi = kHeldBins - 1 - 2 * threadIdx.x;
+  const int c_hi = sm.hist[d_hi], c_lo = sm.hist[d_hi - 1];
+  sm.hist[d_hi] = 0;
+  sm.hist[d_hi - 1] = 0;
+  return held_find_digit(c_hi, c_lo, need, sm.scan, &sm.digit, &sm.need);
+}
+
+// Scores of m rows, row i * 1024 + t as key i of thread t.  Places past the m rows hold key 0: no score but a NaN
+// maps there, it ranks last, and they come behind every row, so neither the threshold nor a survivor's place depends
+// on these.
+template <int KEYS>
+__device__ __forceinline__ void held_load(const float* score, int m, uint32_t (&key)[KEYS]) {
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) key[i] = __float_as_uint(block_word(score, i * kHeldThreads, m));
+}
+template <int KEYS>
+__device__ __forceinline__ void held_map(int m, uint32_t (&key)[KEYS]) {
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) {
+    const uint32_t x = score_key(__uint_as_float(key[i]));
+    key[i] = i * kHeldThreads + (int)threadIdx.x < m ? x : 0u;
+  }
+}
+
+// Stable emit of the m rows behind the keys, cache rows row0 .. row0 + m.  A row survives if its key exceeds the
+// threshold, or if it is among the first need_eq rows of the cache whose key equals it; its place in `out` is (rows of
+// the first kind before it) + min(rows with an equal key before it, need_eq), of which sure_base and eq_base lie
+// before row0.  Counts per (block of 1024 rows, wavefront) first: lane i collects its wavefront's counts of block i,
+// the workgroup scans them in row order, and lane i gets block i's two places back.  Lowers sm.first to the first row
+// (from row0) that does not survive.
+template <int KEYS>
+__device__ __forceinline__ void held_emit(HeldShared<KEYS>& sm, const uint32_t (&key)[KEYS], int m, uint32_t thr,
+                                          int need_eq, int sure_base, int eq_base, int row0, int32_t* out) {
+  static_assert(KEYS <= 64, "one lane per block");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int n_both = 0;
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) {
+    if (i * kHeldThreads < m) {
+      const int both = __popcll(__ballot(key[i] > thr)) | __popcll(__ballot(key[i] == thr)) << 16;
+      n_both = lane == i ? both : n_both;
+    }
+  }
+  if (lane < KEYS) {
+    sm.sure_before[lane * kHeldWaves + wave] = n_both & 0xffff;
+    sm.eq_before[lane * kHeldWaves + wave] = n_both >> 16;
+  }
+  __syncthreads();
+  int a = 0, e = 0;
+  if (tid < KEYS * kHeldWaves) { a = sm.sure_before[tid]; e = sm.eq_before[tid]; }
+  if (KEYS * kHeldThreads < 65536) {  // both counts in one scan
+    const int both = held_exclusive_scan(a | e << 16, sm.scan);
+    a = both & 0xffff;
+    e = (uint32_t)both >> 16;
+  } else {
+    a = held_exclusive_scan(a, sm.scan);
+    e = held_exclusive_scan(e, sm.scan + kHeldWaves);
+  }
+  if (tid < KEYS * kHeldWaves) { sm.sure_before[tid] = a; sm.eq_before[tid] = e; }
+  __syncthreads();
+  int place_sure = 0, place_eq = 0;
+  if (lane < KEYS) {
+    place_sure = sm.sure_before[lane * kHeldWaves + wave] + sure_base;
+    place_eq = sm.eq_before[lane * kHeldWaves + wave] + eq_base;
+  }
+  int first_out = m;  // first row of this wavefront that does not survive
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) {
+    if (i * kHeldThreads < m) {
+      const int r = i * kHeldThreads + tid;
+      const uint64_t ms = __ballot(key[i] > thr), me = __ballot(key[i] == thr);
+      const int eq0 = __builtin_amdgcn_readlane(place_eq, i);
+      int sb = __builtin_amdgcn_readlane(place_sure, i) + min(eq0, need_eq);
+      bool keep = key[i] > thr;
+      sb = __builtin_amdgcn_mbcnt_hi((uint32_t)(ms >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ms, sb));
+      if (me != 0 && eq0 < need_eq) {  // uniform over the wavefront
+        const int eb = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0));
+        sb += min(eb, need_eq - eq0);
+        keep = keep || (key[i] == thr && eq0 + eb < need_eq);
+      }
+      if (keep) set_word(out, sb, row0 + r);
+      const uint64_t gone = __ballot(!keep);
+      if (gone != 0) first_out = min(first_out, i * kHeldThreads + wave * 64 + __ffsll((unsigned long long)gone) - 1);
+    }
+  }
+  if (lane == 0) atomicMin(&sm.first, first_out);
+  __syncthreads();
+}
+
+// The whole selection of one cache of up to 1024 * KEYS rows by this workgroup.
+template <int KEYS>
+__device__ __forceinline__ void select_whole(const CompactParams& p, int c, HeldShared<KEYS>& sm) {
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
   const SelGoal g = sel_goal(p, c);
   const int n = g.n;
   const int64_t off = p.off[c];
@@ -257,30 +399,16 @@ __global__ __launch_bounds__(kHeldThreads) void compact_select_kernel(CompactPar
     return;
   }
 
-  __shared__ int hist[kHeldBins];
-  __shared__ int sm_scan[2 * kHeldWaves];
-  __shared__ int sh_digit, sh_need, sh_first;
-  __shared__ int sure_before[KEYS * kHeldWaves], eq_before[KEYS * kHeldWaves];
-
   const int m = g.mid_hi - g.mid_lo;  // rows that compete, g.k < m of them survive
-  const float* score = p.score + off + g.mid_lo;
   uint32_t key[KEYS];
-#pragma unroll
-  for (int i = 0; i < KEYS; ++i) key[i] = __float_as_uint(score[min(i * kHeldThreads + tid, m - 1)]);
-  hist[tid] = 0;
-  hist[tid + kHeldThreads] = 0;
-  if (tid == 0) sh_first = m;
-#pragma unroll
-  for (int i = 0; i < KEYS; ++i) {
-    // places past the middle hold key 0: no score but a NaN maps there, it ranks last, and it comes
-    // behind every row, so neither the threshold nor a survivor's place depends on these
-    const uint32_t x = score_key(__uint_as_float(key[i]));
-    key[i] = i * kHeldThreads + tid < m ? x : 0u;
-  }
+  held_load(p.score + off + g.mid_lo, m, key);
+  sm.hist[tid] = 0;
+  sm.hist[tid + kHeldThreads] = 0;
+  if (tid == 0) sm.first = m;
+  held_map(m, key);
   __syncthreads();
 
-  // Radix select of the k-th largest key.  64 lanes that meet on one counter would be served one after
-  // the other, so a wavefront whose keys all have the same digit (many equal scores) adds them up first.
+  // radix select of the k-th largest key
   uint32_t prefix = 0, mask = 0;
   int need = g.k;
 #pragma unroll 1
@@ -288,96 +416,226 @@ __global__ __launch_bounds__(kHeldThreads) void compact_select_kernel(CompactPar
     const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
     const uint32_t digits = pass == 2 ? 1023u : 2047u;
 #pragma unroll
-    for (int i = 0; i < KEYS; ++i) {
-      if (i * kHeldThreads < m) {
-        if ((key[i] & mask) == prefix) {
-          const int digit = (key[i] >> shift) & digits;
-          const uint64_t here = __ballot(true);
-          if (__ballot(digit == __builtin_amdgcn_readfirstlane(digit)) == here) {
-            if (__builtin_amdgcn_mbcnt_hi((uint32_t)(here >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)here, 0)) == 0)
-              atomicAdd(&hist[digit], __popcll(here));
-          } else {
-            atomicAdd(&hist[digit], 1);
-          }
-        }
-      }
-    }
+    for (int i = 0; i < KEYS; ++i)
+      if (i * kHeldThreads < m && (key[i] & mask) == prefix) count_key(sm.hist, (key[i] >> shift) & digits);
     __syncthreads();
-    // the digit of the need-th largest key: thread t looks at the digits 2047 - 2t and 2046 - 2t and
-    // leaves their counters cleared; exactly one digit has above < need <= above + its own count
-    const int d_hi = kHeldBins - 1 - 2 * tid;
-    const int c_hi = hist[d_hi], c_lo = hist[d_hi - 1];
-    hist[d_hi] = 0;
-    hist[d_hi - 1] = 0;
-    const int above = held_exclusive_scan(c_hi + c_lo, sm_scan);
-    if (above < need && above + c_hi >= need) {
-      sh_digit = d_hi;
-      sh_need = need - above;
-    } else if (above + c_hi < need && above + c_hi + c_lo >= need) {
-      sh_digit = d_hi - 1;
-      sh_need = need - above - c_hi;
-    }
-    __syncthreads();
-    prefix |= (uint32_t)sh_digit << shift;
-    need = sh_need;
+    prefix |= (uint32_t)held_find_digit(sm, need) << shift;
     mask |= digits << shift;
   }
-  const uint32_t thr = prefix;
-  const int need_eq = need;  // rows whose key equals thr that still survive (oldest first)
+  // need: rows whose key equals the threshold that still survive (oldest first)
+  held_emit(sm, key, m, prefix, need, 0, 0, g.mid_lo, kept + g.mid_lo);
+  if (tid == 0) p.info[c] = CompactInfo{g.b, g.mid_lo + sm.first, n, 0};
+}
 
-  // A row survives if its key exceeds the threshold, or if it is among the first need_eq rows whose key
-  // equals it; its place is (rows of the first kind before it) + min(rows with an equal key before it,
-  // need_eq).  Counts per (block of 1024 rows, wavefront) first: lane i collects its wavefront's counts
-  // of block i, the workgroup scans them in row order, and lane i gets block i's two places back.
-  static_assert(KEYS <= 64, "one lane per block");
-  int n_both = 0;
-#pragma unroll
-  for (int i = 0; i < KEYS; ++i) {
-    if (i * kHeldThreads < m) {
-      const int both = __popcll(__ballot(key[i] > thr)) | __popcll(__ballot(key[i] == thr)) << 16;
-      n_both = lane == i ? both : n_both;
-    }
+template <int KEYS>
+__global__ __launch_bounds__(kHeldThreads) void compact_select_kernel(CompactParams p, int cap_above, int cap_most) {
+  __shared__ HeldShared<KEYS> sm;
+  const int c = p.order[blockIdx.x];
+  const int cap = p.cap[c];
+  if (cap <= cap_above || cap > cap_most) return;  // another launch's
+  select_whole<KEYS>(p, c, sm);
+}
+
+// ---- few caches: several workgroups to each ------------------------------------------------------
+// One workgroup on each of a few caches leaves most of the chip idle.  Here a cache is cut into tiles of kTileRows rows,
+// one workgroup each, in two kernels.  The first counts the keys of every tile by their leading 11 bits and leaves
+// the counters in the workspace.  In the second every workgroup adds up the counters of its cache, finds the threshold's
+// leading digit, collects in LDS the keys of the whole cache that have it (an eighth of them, say), ranks those by their
+// other bits for itself, and emits its own tile.  Reading the cache's scores once more in every workgroup costs less than the launches that
+// would share the work (about 5 us each behind one another).  A cache of up to kNarrowRows rows is ranked whole by the
+// first kernel.  us per eviction, one workgroup per cache / spread: 8 caches of 20000 rows 47 / 35, of 32768 56 / 41, of
+// 64000 82 / 62; the ranking of 8 caches of 32768 rows takes 17 us in all (35), of which 4.7 pass until the other rows
+// with the digit are collected, 2.7 with the emit and the rest with barriers.
+constexpr int kTileKeys = kTileRows / kHeldThreads;
+constexpr int kMostTiles = kHeldRows / kTileRows;
+constexpr int kListKeys = 2048;  // keys with the threshold's leading digit that LDS holds for each wavefront
+
+// Rows of the middle that a tile holds.
+__device__ __forceinline__ void tile_range(const SelGoal& g, int tile, int& lo, int& hi) {
+  lo = max(g.mid_lo, tile * kTileRows);
+  hi = min(g.mid_hi, (tile + 1) * kTileRows);
+}
+
+__global__ __launch_bounds__(kHeldThreads) void compact_spread_count_kernel(CompactParams p) {
+  __shared__ HeldShared<kNarrowRows / kHeldThreads> sm;
+  const SelTile tl = p.tiles[blockIdx.x];
+  if (tl.n_tiles == 1) {
+    select_whole<kNarrowRows / kHeldThreads>(p, tl.c, sm);
+    return;
   }
-  if (lane < KEYS) {
-    sure_before[lane * kHeldWaves + wave] = n_both & 0xffff;
-    eq_before[lane * kHeldWaves + wave] = n_both >> 16;
+  const int tid = threadIdx.x;
+  const SelGoal g = sel_goal(p, tl.c);
+  if (tl.tile == 0 && tid == 0)  // the second kernel lowers first_moved with atomicMin
+    p.info[tl.c] = g.n <= g.b ? CompactInfo{g.n, g.n, g.n, 0} : CompactInfo{g.b, g.k > 0 ? g.n : g.mid_lo, g.n, 0};
+  if (g.n <= g.b || g.k <= 0) return;
+  int lo, hi;
+  tile_range(g, tl.tile, lo, hi);
+  const int m = max(0, hi - lo);
+  uint32_t key[kTileKeys];
+  if (m > 0) held_load(p.score + p.off[tl.c] + lo, m, key);
+  sm.hist[tid] = 0;
+  sm.hist[tid + kHeldThreads] = 0;
+  __syncthreads();
+  if (m > 0) {
+    held_map(m, key);
+#pragma unroll
+    for (int i = 0; i < kTileKeys; ++i)
+      if (i * kHeldThreads + tid < m) count_key(sm.hist, key[i] >> 21);
   }
   __syncthreads();
-  int a = 0, e = 0;
-  if (tid < KEYS * kHeldWaves) { a = sure_before[tid]; e = eq_before[tid]; }
-  a = held_exclusive_scan(a, sm_scan);
-  e = held_exclusive_scan(e, sm_scan + kHeldWaves);
-  if (tid < KEYS * kHeldWaves) { sure_before[tid] = a; eq_before[tid] = e; }
-  __syncthreads();
-  int place_sure = 0, place_eq = 0;
-  if (lane < KEYS) {
-    place_sure = sure_before[lane * kHeldWaves + wave];
-    place_eq = eq_before[lane * kHeldWaves + wave];
+  // two counters of at most kTileRows each to a word
+  uint32_t* out = reinterpret_cast<uint32_t*>(p.tile_hist) + (int64_t)(tl.first_tile + tl.tile) * (kHeldBins / 2);
+  out[tid] = (uint32_t)sm.hist[2 * tid] | (uint32_t)sm.hist[2 * tid + 1] << 16;
+}
+
+__global__ __launch_bounds__(kHeldThreads) void compact_spread_emit_kernel(CompactParams p) {
+  __shared__ HeldShared<kTileKeys> sm;
+  __shared__ uint32_t cand[kHeldWaves * kListKeys];
+  __shared__ int sure_before, eq_before;
+  const SelTile tl = p.tiles[blockIdx.x];
+  if (tl.n_tiles == 1) return;  // done
+  const int tid = threadIdx.x, lane = tid & 63;
+  const SelGoal g = sel_goal(p, tl.c);
+  const int n = g.n;
+  const int64_t off = p.off[tl.c];
+  int32_t* kept = p.kept + off;
+  const int j_begin = tl.tile * kTileRows, j_end = min(n, j_begin + kTileRows);
+  if (n <= g.b) {
+    if (p.write_identity)
+      for (int j = j_begin + tid; j < j_end; j += kHeldThreads) kept[j] = j;
+    return;
   }
-  int first_out = m;  // first row of this wavefront that does not survive
-  int32_t* out = kept + g.mid_lo;
+  int lo, hi;
+  tile_range(g, tl.tile, lo, hi);
+  const int m = hi - lo;
+  const bool ranks = g.k > 0 && m > 0;  // uniform over the workgroup
+  const int m_all = g.mid_hi - g.mid_lo, front = lo - g.mid_lo;
+  const float* score = p.score + off + g.mid_lo;  // the middle: m_all rows, `front` of them before the tile
+  auto load_round = [&](float (&x)[kTileKeys], int r0) {
 #pragma unroll
-  for (int i = 0; i < KEYS; ++i) {
-    if (i * kHeldThreads < m) {
-      const int r = i * kHeldThreads + tid;
-      const uint64_t ms = __ballot(key[i] > thr), me = __ballot(key[i] == thr);
-      const int eq0 = __builtin_amdgcn_readlane(place_eq, i);
-      int sb = __builtin_amdgcn_readlane(place_sure, i) + min(eq0, need_eq);
-      bool keep = key[i] > thr;
-      sb = __builtin_amdgcn_mbcnt_hi((uint32_t)(ms >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ms, sb));
-      if (me != 0 && eq0 < need_eq) {  // uniform over the wavefront
-        const int eb = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0));
-        sb += min(eb, need_eq - eq0);
-        keep = keep || (key[i] == thr && eq0 + eb < need_eq);
+    for (int i = 0; i < kTileKeys; ++i) x[i] = block_word(score, r0 + i * kHeldThreads, m_all);
+  };
+  float first_round[kTileKeys];
+  uint32_t w[kMostTiles];
+  if (ranks) {
+    // counters of this thread's two digits in the cache's tiles
+    const uint32_t* th = reinterpret_cast<const uint32_t*>(p.tile_hist) + (int64_t)tl.first_tile * (kHeldBins / 2);
+#pragma unroll
+    for (int j = 0; j < kMostTiles; ++j) w[j] = th[(int64_t)min(j, tl.n_tiles - 1) * (kHeldBins / 2) + kHeldThreads - 1 - tid];
+    load_round(first_round, 0);
+  }
+  // sink and recent rows of the tile
+  for (int j = j_begin + tid; j < min(j_end, g.mid_lo); j += kHeldThreads) kept[j] = j;
+  for (int j = max(j_begin, g.mid_hi) + tid; j < j_end; j += kHeldThreads) kept[j - (n - g.b)] = j;
+  if (!ranks) return;  // nothing to rank, or none of it here
+
+  sm.hist[tid] = 0;
+  sm.hist[tid + kHeldThreads] = 0;
+  if (tid == 0) {
+    sm.first = m;
+    sure_before = eq_before = 0;
+  }
+  int c_hi = 0, c_lo = 0, f_hi = 0, f_lo = 0;
+#pragma unroll
+  for (int j = 0; j < kMostTiles; ++j) {
+    if (j < tl.n_tiles) { c_hi += w[j] >> 16; c_lo += w[j] & 0xffff; }
+    if (j < tl.tile) { f_hi += w[j] >> 16; f_lo += w[j] & 0xffff; }
+  }
+  int need = g.k;
+  const int d1 = held_find_digit(c_hi, c_lo, need, sm.scan, &sm.digit, &sm.need);
+  const int t_hi = kHeldBins - 1 - 2 * tid;
+  int sure = (t_hi > d1 ? f_hi : 0) + (t_hi - 1 > d1 ? f_lo : 0);  // rows before the tile that survive: larger digits
+
+  // Every row of the middle whose key has that digit, a round of 8192 rows at a time and the next one on its way.
+  // The digit is compared as it lies in the score (bits inverted where the key inverts them: scores below zero; -0 is
+  // folded onto +0).  f(first row, the scores' bits: those whose leading digit is `lead` count)
+  const uint32_t lead = d1 < kHeldBins / 2 ? (uint32_t)(kHeldBins - 1 - d1) : (uint32_t)(d1 - kHeldBins / 2);
+  const uint32_t inv = d1 < kHeldBins / 2 ? 0xffffffffu : 0u;
+  const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);  // first row of this wavefront in a block of 1024
+  auto sweep = [&](auto f) {
+    float next[kTileKeys];
+#pragma unroll
+    for (int i = 0; i < kTileKeys; ++i) next[i] = first_round[i];
+#pragma unroll 1
+    for (int r0 = 0; r0 < m_all; r0 += kTileRows) {
+      uint32_t x[kTileKeys];
+#pragma unroll
+      for (int i = 0; i < kTileKeys; ++i) x[i] = __float_as_uint(next[i] + 0.0f);
+      if (r0 + kTileRows < m_all) {
+        load_round(next, r0 + kTileRows);
+      } else {  // places past the last row repeat it: they get another digit
+#pragma unroll
+        for (int i = 0; i < kTileKeys; ++i) x[i] = r0 + i * kHeldThreads + tid < m_all ? x[i] : (lead ^ 1) << 21;
       }
-      if (keep) out[sb] = g.mid_lo + r;
-      const uint64_t gone = __ballot(!keep);
-      if (gone != 0) first_out = min(first_out, i * kHeldThreads + wave * 64 + __ffsll((unsigned long long)gone) - 1);
+      f(r0, x);
     }
-  }
-  if (lane == 0) atomicMin(&sh_first, first_out);
+  };
+  // (a list for each wavefront, in the order of the rows: no counter to wait for, and those before the tile come first)
+  int n_mine = 0, n_front = 0;
+  bool fits = true;
+  uint32_t* const mine = cand + wave0 / 64 * kListKeys;
+  sweep([&](int r0, const uint32_t (&x)[kTileKeys]) {
+    fits = fits && n_mine + 64 * kTileKeys <= kListKeys;
+#pragma unroll
+    for (int i = 0; i < kTileKeys; ++i) {
+      const bool hit = x[i] >> 21 == lead;
+      const uint64_t b = __ballot(hit);
+      if (fits && hit)
+        mine[__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, n_mine))] = x[i];
+      n_mine += __popcll(b);
+    }
+    if (r0 + kTileRows <= front) {
+      n_front = n_mine;
+    } else if (r0 < front) {  // the tile begins in this round
+#pragma unroll
+      for (int i = 0; i < kTileKeys; ++i)
+        n_front += __popcll(__ballot(x[i] >> 21 == lead && r0 + i * kHeldThreads + tid < front));
+    }
+  });
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // f(key bits, whether the row lies before the tile) for every candidate, from LDS, or, where they are too many for the
+  // list, from another sweep over the scores.
+  auto each = [&](auto f) {
+    if (fits) {
+      for (int r = lane; r < n_mine; r += 64) f(mine[r] ^ inv, r < n_front);
+    } else {
+      sweep([&](int r0, const uint32_t (&x)[kTileKeys]) {
+#pragma unroll 1
+        for (int i = 0; i < kTileKeys; ++i) {
+          uint32_t v = 0;
+#pragma unroll
+          for (int k = 0; k < kTileKeys; ++k) v = k == i ? x[k] : v;
+          if (v >> 21 == lead) f(v ^ inv, r0 + i * kHeldThreads + tid < front);
+        }
+      });
+    }
+  };
+  each([&](uint32_t x, bool) { count_key(sm.hist, x >> 10 & 2047); });
   __syncthreads();
-  if (tid == 0) p.info[c] = CompactInfo{g.b, g.mid_lo + sh_first, n, 0};
+  const int d2 = held_find_digit(sm, need);
+  each([&](uint32_t x, bool) {
+    if ((int)(x >> 10 & 2047) == d2) count_key(sm.hist, x & 1023);
+  });
+  uint32_t key[kTileKeys];
+  held_load(score + front, m, key);
+  __syncthreads();
+  const int d3 = held_find_digit(sm, need);
+  const uint32_t low = (uint32_t)d2 << 10 | (uint32_t)d3;
+  int eq = 0;  // candidates before the tile that equal the threshold
+  each([&](uint32_t x, bool before) {
+    sure += before && (x & 0x1fffffu) > low ? 1 : 0;
+    eq += before && (x & 0x1fffffu) == low ? 1 : 0;
+  });
+  sure = wave_inclusive_scan(sure);
+  eq = wave_inclusive_scan(eq);
+  if (lane == 63 && sure != 0) atomicAdd(&sure_before, sure);
+  if (lane == 63 && eq != 0) atomicAdd(&eq_before, eq);
+  held_map(m, key);
+  __syncthreads();
+  held_emit(sm, key, m, (uint32_t)d1 << 21 | low, need, sure_before, eq_before, lo, kept + g.mid_lo);
+  if (tid == 0 && sm.first < m) atomicMin(&p.info[tl.c].first_moved, lo + sm.first);
 }
 
 // ---- caches too long for one workgroup -------------------------------------------------------
@@ -645,20 +903,25 @@ __global__ __launch_bounds__(kMoveThreads) void compact_move_kernel(CompactParam
 
 }  // namespace
 
-// The launch order holds the n_wide caches of more than kHeldRows / 4 rows first when `sorted`.
+// The launch order holds the n_wide caches of more than kNarrowRows rows first when `sorted`.
 hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
-                                 hipStream_t s) {
+                                 const SelTile* spread, int n_spread, hipStream_t s) {
   if (n_caches <= 0) return hipSuccess;
-  constexpr int kNarrow = kHeldRows / 4;
   const dim3 held(kHeldThreads);
-  if (n_wide > 0)
-    compact_select_kernel<kHeldRows / kHeldThreads>
-        <<<dim3(sorted ? n_wide : n_caches), held, 0, s>>>(p, kNarrow, p.long_rows);
-  if (n_wide < n_caches) {
-    CompactParams q = p;
-    if (sorted) q.order += n_wide;
-    compact_select_kernel<kNarrow / kHeldThreads>
-        <<<dim3(sorted ? n_caches - n_wide : n_caches), held, 0, s>>>(q, -1, std::min(kNarrow, p.long_rows));
+  CompactParams q = p;
+  if (n_spread > 0) {
+    q.tiles = spread;
+    compact_spread_count_kernel<<<dim3(n_spread), held, 0, s>>>(q);
+    compact_spread_emit_kernel<<<dim3(n_spread), held, 0, s>>>(q);
+  } else {
+    if (n_wide > 0)
+      compact_select_kernel<kHeldRows / kHeldThreads>
+          <<<dim3(sorted ? n_wide : n_caches), held, 0, s>>>(p, kNarrowRows, p.long_rows);
+    if (n_wide < n_caches) {
+      if (sorted) q.order += n_wide;
+      compact_select_kernel<kNarrowRows / kHeldThreads>
+          <<<dim3(sorted ? n_caches - n_wide : n_caches), held, 0, s>>>(q, -1, std::min(kNarrowRows, p.long_rows));
+    }
   }
   if (n_tiles > 0) {
     const dim3 grid(n_tiles), block(kSelThreads);

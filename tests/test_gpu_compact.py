@@ -270,6 +270,47 @@ def test_caches_selected_tile_by_tile(scores, policy):
     arena.close()
 
 
+@pytest.mark.parametrize("policy", [B.POLICY_SCORE, B.POLICY_STREAMING])
+@pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed_zero", "negative", "close", "ends"])
+def test_few_caches_ranked_by_several_workgroups(scores, policy):
+    """Caches of 16385 to 65536 rows of capacity, few enough that each is ranked by one workgroup per 8192 rows, beside
+    short ones ranked by one: capacities at the edges of a tile and of the range, live lengths in the first, a middle and
+    the last tile and at the budget, no survivors in the middle, ties across tiles, more keys that share their leading
+    bits than LDS holds (equal and close scores), scores of both signs and at the ends of the type."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="spread", L=2, Hq=5, Hkv=5, batch=1, seed=27, sink=4, recent=16,
+                     slack=41000)
+    rng = np.random.Generator(np.random.PCG64(w.seed + policy))
+    budgets = [20, 500, 8192, 16000, 24536, 21, 8150, 300, 24535, 12000]
+    arena = H.make_arena(w, budgets, policy=policy)
+    lens = [41020, 8193, 49192, 16001, 65536, 24577, 8150, 41300, 65535, 30000]
+    assert max(arena.cap_host) == 65536 and all(n <= c for n, c in zip(lens, arena.cap_host))
+    st = H.fill_from_host(arena, w, lens, rng, scores="uniform")
+    if scores != "uniform":
+        for c, n in enumerate(lens):
+            if scores == "equal":
+                s = np.full(n, 0.25, dtype=np.float32)
+            elif scores == "coarse":
+                s = (rng.integers(0, 7, n) / 8).astype(np.float32)
+            elif scores == "negative":
+                s = (rng.random(n) * 2 - 1.5).astype(np.float32)
+            elif scores == "close":
+                s = np.float32(0.75) + (rng.integers(0, 3000, n) * 2.0 ** -24).astype(np.float32)
+            elif scores == "ends":
+                s = rng.choice(np.array([-np.inf, -3.4e38, -1e-45, -0.0, 0.0, 1e-45, 3.4e38, np.inf], dtype=np.float32), n)
+            else:
+                s = np.where(rng.random(n) < 0.5, np.float32(0.0), np.float32(-0.0)).astype(np.float32)
+                s[rng.integers(0, n, 40)] = rng.random(40).astype(np.float32)
+                s[rng.integers(0, n, 40)] = -rng.random(40).astype(np.float32)
+            o = int(arena.off_host[c])
+            arena.score[o:o + n].copy_(torch.from_numpy(s).to(arena.device))
+            st.score[c] = s
+    after = run_compact_and_check(arena, w, st, policy=policy, layer_begin=1, layer_count=1)
+    after = run_compact_and_check(arena, w, after, policy=policy)
+    run_compact_and_check(arena, w, after, policy=policy)                                      # nothing left to evict
+    arena.close()
+
+
 @pytest.mark.parametrize("seed", list(range(500, 512)))
 def test_seeded_random_evictions(seed):
     """Random cache sizes on both sides of the threshold for tile-by-tile selection, random budgets, sink
