@@ -178,6 +178,7 @@ struct baklava_ctx {
   struct Schedule {
     int32_t chunk = 0;
     std::vector<int32_t> max_count;    // layer -> longest work item of the layer, rows
+    std::vector<int32_t> max_split;    // layer -> most work items of a cache
     std::vector<int32_t> cib;          // cache -> first item
     std::vector<int32_t> multi_begin;  // layer -> first entry of the list of multi-item caches
   } sched[2];                          // 0: layer sub-range launches, 1: whole-model launches
@@ -207,13 +208,14 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   // cache -> first partial slot, and the caches that need the combine kernel (in launch order)
   std::vector<int32_t> cib(ctx->n_caches + 1, 0), multi_begin(ctx->d.L + 1, 0);
   std::vector<MultiCache> multi;
-  std::vector<int32_t> max_count(ctx->d.L, 0);
+  std::vector<int32_t> max_count(ctx->d.L, 0), max_split(ctx->d.L, 0);
   int32_t slot0 = 0;  // the items of a cache follow each other
   for (int64_t i = 0; i < n_items; ++i) {
     if (items[i].start == 0) slot0 = items[i].slot;
     items[i].reserved = slot0;
     const baklava_work_item& it = items[i];
     max_count[it.cache / ctx->cpl] = std::max(max_count[it.cache / ctx->cpl], it.count);
+    max_split[it.cache / ctx->cpl] = std::max(max_split[it.cache / ctx->cpl], it.nsplit);
     if (it.start == 0) {
       cib[it.cache] = it.slot;
       if (it.nsplit > 1) {
@@ -234,6 +236,7 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   ctx->sched[which].multi_begin.swap(multi_begin);
   ctx->sched[which].chunk = chunk;
   ctx->sched[which].max_count.swap(max_count);
+  ctx->sched[which].max_split.swap(max_split);
   return BAKLAVA_OK;
 }
 
@@ -419,10 +422,12 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
     if (!on_dispatch && !hip_ok(hipEventRecord(ev1, s))) return BAKLAVA_EHIP;
     ctx->ev_used += 1;
   }
+  const int32_t most_split = *std::max_element(sc.max_split.begin() + layer_begin,
+                                               sc.max_split.begin() + layer_begin + layer_count);
   if (from_logits) {
-    if (!hip_ok(launch_finish(p, ctx->d.D, m1 - m0, i1 - i0, longest, s))) return BAKLAVA_EHIP;
+    if (!hip_ok(launch_finish(p, ctx->d.D, m1 - m0, most_split, i1 - i0, longest, s))) return BAKLAVA_EHIP;
   } else {
-    if (!hip_ok(launch_combine(p, ctx->d.D, m1 - m0, s))) return BAKLAVA_EHIP;
+    if (!hip_ok(launch_combine(p, ctx->d.D, m1 - m0, most_split, s))) return BAKLAVA_EHIP;
     if (track && !defer) {
       const int st = score_pass(ctx, p, i1 - i0, longest, s);
       if (st != BAKLAVA_OK) return st;

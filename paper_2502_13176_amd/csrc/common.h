@@ -214,9 +214,11 @@ hipError_t launch_layer_similarity(const void* x_in, const void* x_out, int n_se
                                    float* cos_out, float* sim_out, float* tile_sum, hipStream_t s);
 hipError_t launch_prefill_scores(const void* q, const void* k, const float* lse, const int64_t* row_off,
                                  int batch, int Hq, int Hkv, int T, float* score, hipStream_t s);
-hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t s);
+// most_split: work items of the cache that has most of them
+hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, int most_split, hipStream_t s);
 // the end of a tracked call without records: split partials merged, weights added to the scores from p.logits
-hipError_t launch_finish(const DecodeParams& p, int D, int n_multi, int n_items, int max_count, hipStream_t s);
+hipError_t launch_finish(const DecodeParams& p, int D, int n_multi, int most_split, int n_items, int max_count,
+                         hipStream_t s);
 // max_count: the largest row count of a work item in the launched range (or a bound on it)
 hipError_t launch_score_pass(const ScoreParams& p, int n_items, int max_count, hipStream_t s);
 hipError_t launch_append(const AppendParams& p, int n_caches, hipStream_t s);

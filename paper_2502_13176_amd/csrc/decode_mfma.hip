@@ -189,7 +189,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
   Record rec;
   if (LAG && apply) load_record(p, it.c, G, pending, n16, jg, rec);
   if (p.fused_append) {
-    if (add) append_new_row(p, it, n_old, off_c, token_pos);
+    if (add) append_new_row<64 * kWaves>(p, it, n_old, off_c, token_pos);
     else if (it.start == 0 && threadIdx.x == 0) *p.status = 1;
   }
   if (KEEP && it.start == 0 && threadIdx.x == 0) p.lag_n[(int64_t)it.c * kLagCalls] = n;
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(64 * Shape<D>::kWaves, 2) void decode_partial_mfma(
   unsigned char* myk = lds_k + wave * (kSlab * kKStride);
 
   const int c_rel = it.c - p.cache_begin;
-  const int64_t qrow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
+  const int64_t qrow0 = (int64_t)c_rel * G;  // (Hq = Hkv G: the query rows of the caches follow each other)
 
   floatx4_t o[S::kBlocks];
 #pragma unroll

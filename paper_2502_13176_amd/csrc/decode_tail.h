@@ -16,6 +16,7 @@ __device__ __forceinline__ float tail_exp2(float x) { return __builtin_amdgcn_ex
 // slot `n_old` copies the new row there before it starts streaming.  The barrier makes the row
 // visible to every wavefront of this workgroup; no other workgroup reads that slot.  The caller
 // has checked n_old < capacity (uniform over the workgroup).
+template <int THREADS>
 __device__ __forceinline__ void append_new_row(const DecodeParams& p, const Item& it, int n_old,
                                                int64_t off_c, int token_pos) {
   if (!(n_old >= it.start && n_old < it.start + it.count)) return;  // uniform over the workgroup
@@ -29,7 +30,7 @@ __device__ __forceinline__ void append_new_row(const DecodeParams& p, const Item
     char* dst = reinterpret_cast<char*>(plane ? p.v : p.k) + row * p.row_bytes + piece * 16;
     *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
   }
-  if (tid == (int)blockDim.x - 1) {
+  if (tid == THREADS - 1) {
     p.score[row] = 0.f;
     p.pos[row] = token_pos;
   }
@@ -53,7 +54,7 @@ __device__ __forceinline__ void finish_item(const DecodeParams& p, const Item& i
   const int c = it.c;
   const bool single = it.nsplit == 1;
   const int c_rel = c - p.cache_begin;
-  const int64_t orow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
+  const int64_t orow0 = (int64_t)c_rel * G;
 
   for (int idx = tid; idx < G * D; idx += 64 * NW) {
     const int g = idx / D, d = idx % D;

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
   const int n = n_old + add;
   const int token_pos = p.token_pos_dev ? *p.token_pos_dev : p.token_pos;
   if (p.fused_append) {
-    if (add) append_new_row(p, it, n_old, off_c, token_pos);
+    if (add) append_new_row<64 * NW>(p, it, n_old, off_c, token_pos);
     else if (it.start == 0 && threadIdx.x == 0) *p.status = 1;
   }
   if (KEEP && it.start == 0 && threadIdx.x == 0) p.lag_n[(int64_t)it.c * kLagCalls] = n;
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
   if (t0 < cnt) load_tile(t0);
 
   const int c_rel = it.c - p.cache_begin;
-  const int64_t qrow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
+  const int64_t qrow0 = (int64_t)c_rel * G;
   float qr[GT][EPL];
 #pragma unroll
   for (int g = 0; g < GT; ++g) {
@@ -291,74 +291,96 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_valu(DecodeParams p) {
 
 // Merge of the split partials of one (cache, query head):
 //   out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M)
-// which is the softmax of Eq. 7 with the sum over rows regrouped by split.  One workgroup per
-// (cache with several work items, query head); 256 / D thread groups share the splits.
-template <int D>
-__device__ __forceinline__ void combine_head(const DecodeParams& p, int block) {
-  constexpr int GROUPS = 256 / D;
+// which is the softmax of Eq. 7 with the sum over rows regrouped by split.  One workgroup per (cache with several work
+// items, query head); THREADS / D thread groups share the splits.  A kernel this small is a chain of latencies: what
+// does not depend on the maximum M is requested before it is formed (the first kAhead outputs of every group, the
+// record's inputs), every wavefront forms M and the splits' factors for itself, one split per lane, and a group then
+// reads the factor of a split from its lane, so that the sums over splits are plain multiply-adds, kAhead outputs at a
+// time.  A layer of 8 caches of up to 8192 rows: 9.9 us per attention call (10.5 with a running rescale per split and
+// integer divisions in front of the first loads), of 131072 rows 48.4 (54).
+template <int D, int THREADS>
+__device__ __forceinline__ void combine_head(const DecodeParams& p, int multi, int g) {
+  constexpr int GROUPS = THREADS / D, kAhead = 8, kHeld = 4;
   const int G = p.G;
-  const MultiCache mc = p.multi[block / G];
+  const MultiCache mc = p.multi[multi];
   const int c = mc.c;
-  const int g = block % G;
-  const int tid = threadIdx.x;
-  const int d = tid % D, grp = tid / D;
-  const int ib = mc.slot_begin, ie = mc.slot_end;
-  // where this call's record goes; read by every thread before the barrier below, written after it
-  const int slot = p.lag ? lag_slot(p, p.lag_cnt[(int64_t)c * G + g]) : 0;
-  float m = kNegInf, l = 0.f, o = 0.f;
-#pragma unroll 8
-  for (int s = ib + grp; s < ie; s += GROUPS) {
-    const float ms = p.part_ml[((int64_t)s * G + g) * 2];
-    const float ls = p.part_ml[((int64_t)s * G + g) * 2 + 1];
-    const float os = p.part_o[((int64_t)s * G + g) * D + d];
-    const float mn = fmaxf(m, ms);
-    const float msafe = (mn == kNegInf) ? 0.f : mn;
-    const float a = fast_exp2(m - msafe), b = fast_exp2(ms - msafe);
-    l = l * a + ls * b;
-    o = o * a + os * b;
-    m = mn;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int d = tid % D, grp = __builtin_amdgcn_readfirstlane(tid / D);  // (D is a multiple of 64)
+  const int n_split = mc.slot_end - mc.slot_begin;
+  const int64_t first = (int64_t)mc.slot_begin * G + g;  // partial s of this head: first + s * G
+  const float2* ml = reinterpret_cast<const float2*>(p.part_ml) + first;
+  const float* po = p.part_o + first * D + d;
+  float2 held[kHeld];  // split 64 h + lane
+#pragma unroll
+  for (int h = 0; h < kHeld; ++h) {
+    held[h] = make_float2(kNegInf, 0.f);
+    if (64 * h + lane < n_split) held[h] = ml[(64 * h + lane) * G];
   }
-  __shared__ float red_o[GROUPS][D], red_m[GROUPS], red_l[GROUPS];
+  auto load_outputs = [&](float (&v)[kAhead], int s0) {  // of splits s0, s0 + GROUPS, ...: past the last one it again
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) v[k] = po[(int64_t)min(s0 + k * GROUPS, n_split - 1) * (G * D)];
+  };
+  float v[kAhead];
+  load_outputs(v, grp);
+  const int64_t orow = (int64_t)(c - p.cache_begin) * G + g;
+  // where this call's record goes, and what it takes; read by every thread before the barrier below, written after it
+  const int slot = p.lag ? lag_slot(p, p.lag_cnt[(int64_t)c * G + g]) : 0;
+  uint4 q_piece = make_uint4(0, 0, 0, 0);
+  if (p.lag && tid * 16 < p.row_bytes)
+    q_piece = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(p.q) + orow * p.row_bytes)[tid];
+  const int n_old = p.len[c];
+  const int n_now = n_old + (p.fused_append && n_old < p.cap[c] ? 1 : 0);  // live rows after this call
+
+  float m = kNegInf;
+#pragma unroll
+  for (int h = 0; h < kHeld; ++h) m = fmaxf(m, held[h].x);
+  for (int s = 64 * kHeld + lane; s < n_split; s += 64) m = fmaxf(m, ml[s * G].x);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  m = (m == kNegInf) ? 0.f : m;
+  float o = 0.f, l = 0.f;
+  // 64 splits, one per lane; outputs of kAhead splits per group at a time, the first ones on their way already
+  auto add_splits = [&](int s0, float2 mine) {
+    const float a = fast_exp2(mine.x - m);
+    l += a * mine.y;
+    const int end = min(n_split, s0 + 64);
+    for (int s = s0 + grp; s < end; s += kAhead * GROUPS) {
+      if (s != grp) load_outputs(v, s);
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+        if (s + k * GROUPS < end)
+          o = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), s + k * GROUPS - s0)), v[k], o);
+    }
+  };
+  static_assert(64 % GROUPS == 0, "a group's splits of every 64 start at its number");
+#pragma unroll
+  for (int h = 0; h < kHeld; ++h)
+    if (64 * h < n_split) add_splits(64 * h, held[h]);
+  for (int s0 = 64 * kHeld; s0 < n_split; s0 += 64)
+    add_splits(s0, s0 + lane < n_split ? ml[(s0 + lane) * G] : make_float2(kNegInf, 0.f));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+  __shared__ float red_o[GROUPS][D];
   red_o[grp][d] = o;
-  if (d == 0) { red_m[grp] = m; red_l[grp] = l; }
   __syncthreads();
   if (grp == 0) {
-    float mm = red_m[0];
 #pragma unroll
-    for (int w = 1; w < GROUPS; ++w) mm = fmaxf(mm, red_m[w]);
-    const float ms = (mm == kNegInf) ? 0.f : mm;
-    float ll = 0.f, oo = 0.f;
-#pragma unroll
-    for (int w = 0; w < GROUPS; ++w) {
-      const float a = fast_exp2(red_m[w] - ms);
-      ll += red_l[w] * a;
-      oo += red_o[w][d] * a;
-    }
-    const float inv = 1.f / ll;
-    const int c_rel = c - p.cache_begin;
-    const int64_t orow = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G + g;
-    int n_now = 0;  // live rows after this call (thread 0 of head 0's block)
-    p.out[orow * D + d] = oo * inv;
+    for (int w = 1; w < GROUPS; ++w) o += red_o[w][d];
+    const float inv = 1.f / l;
+    p.out[orow * D + d] = o * inv;
     if (d == 0) {
-      p.final_ml[((int64_t)c * G + g) * 2 + 0] = ms;
+      p.final_ml[((int64_t)c * G + g) * 2 + 0] = m;
       p.final_ml[((int64_t)c * G + g) * 2 + 1] = inv;
-      if (g == 0) {
-        int n = p.len[c];
-        if (p.fused_append && n < p.cap[c]) p.len[c] = ++n;  // the fused append's row is now counted
-        n_now = n;
-      }
+      if (g == 0 && n_now != n_old) p.len[c] = n_now;  // the fused append's row is now counted
     }
     // This head's part of the record a later score pass over the cache needs (see DecodeParams).
     // Each block reads and writes the pending-call counter of its own head only.
     if (p.lag) {
-      const int64_t m = (int64_t)c * kLagRows + (slot << p.lag_gp_log2) + g;
-      if (tid * 16 < p.row_bytes) {
-        const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(p.q) + orow * p.row_bytes);
-        reinterpret_cast<uint4*>(reinterpret_cast<char*>(p.lag_q) + m * p.row_bytes)[tid] = src[tid];
-      }
+      const int64_t r = (int64_t)c * kLagRows + (slot << p.lag_gp_log2) + g;
+      if (tid * 16 < p.row_bytes) reinterpret_cast<uint4*>(reinterpret_cast<char*>(p.lag_q) + r * p.row_bytes)[tid] = q_piece;
       if (d == 0) {
-        p.lag_ml[m * 2 + 0] = ms;
-        p.lag_ml[m * 2 + 1] = inv;
+        p.lag_ml[r * 2 + 0] = m;
+        p.lag_ml[r * 2 + 1] = inv;
         if (g == 0) p.lag_n[(int64_t)c * kLagCalls + slot] = n_now;
         p.lag_cnt[(int64_t)c * G + g] = slot + 1;
       }
@@ -366,37 +388,40 @@ __device__ __forceinline__ void combine_head(const DecodeParams& p, int block) {
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void combine_kernel(DecodeParams p) { combine_head<D>(p, blockIdx.x); }
+constexpr int kFinishRowsPerThread = 2;
+
+template <int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void combine_kernel(DecodeParams p) {
+  combine_head<D, THREADS>(p, blockIdx.x, blockIdx.y);
+}
 
 // The end of a tracked call without records: in place of the combine kernel (the first n_combine workgroups, one per
 // cache with several work items and query head) and of a pass over the K rows,
 //   score_j += sum_g 2^(x_gj - M_g) / L_g   (cumulative attention per cached token, summed over the query heads)
-// from the logits x that the attention kernel has left.  The other workgroups take kFinishRows rows of a work item
-// each and merge their cache's normalisers from the split partials for themselves, behind the loads of the rows.
+// from the logits x that the attention kernel has left.  The other workgroups take two rows per thread of a work item
+// and merge their cache's normalisers from the split partials for themselves, behind the loads of the rows.
 // Reads 4 G bytes per row where a pass over the K rows read the row and formed the products again: 8 tracked calls
 // over 67 MB of fp32 caches (D = 64, two query heads) take 167 us (203), four steps of two layers of 32 caches of 4096
 // rows, D = 128, eight heads, 377 (499), bf16, D = 64, eight heads, 154 (199).
-constexpr int kFinishRows = 512;
-template <int D, int GT>
-__global__ __launch_bounds__(256) void finish_kernel(DecodeParams p, int n_combine, int tiles) {
+template <int D, int GT, int THREADS>
+__global__ __launch_bounds__(THREADS) void finish_kernel(DecodeParams p, int n_combine, int tiles) {
+  constexpr int R = kFinishRowsPerThread, kRows = R * THREADS;
   if ((int)blockIdx.x < n_combine) {
-    combine_head<D>(p, blockIdx.x);
+    combine_head<D, THREADS>(p, (uint32_t)blockIdx.x / (uint32_t)p.G, (uint32_t)blockIdx.x % (uint32_t)p.G);
     return;
   }
-  const int b = blockIdx.x - n_combine;
-  const Item it = p.items[b / tiles];
+  const uint32_t b = blockIdx.x - n_combine;
+  const Item it = p.items[b / (uint32_t)tiles];
   const int G = p.G;
   const int n = p.lag_n[(int64_t)it.c * kLagCalls];  // (len may already count this call's new row, or not yet)
   const int cnt = min(it.start + it.count, n) - it.start;
-  const int r_begin = b % tiles * kFinishRows;
+  const int r_begin = b % (uint32_t)tiles * kRows;
   if (r_begin >= cnt) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int R = kFinishRows / 256;
   float x[R][GT], old[R];
 #pragma unroll
   for (int k = 0; k < R; ++k) {
-    const int64_t row = it.row0 + min(r_begin + k * 256 + tid, cnt - 1);
+    const int64_t row = it.row0 + min(r_begin + k * THREADS + tid, cnt - 1);
 #pragma unroll
     for (int g = 0; g < GT; ++g) x[k][g] = p.logits[min(g, G - 1) * p.logit_stride + row];
     old[k] = p.score[row];
@@ -404,7 +429,7 @@ __global__ __launch_bounds__(256) void finish_kernel(DecodeParams p, int n_combi
   // (max, 1 / sum) of every query head over the cache's work items
   __shared__ float sm_m[GT], sm_inv[GT];
   if (it.nsplit > 1) {
-    for (int g = wave; g < G; g += 4) {
+    for (int g = wave; g < G; g += THREADS / 64) {
       float m = kNegInf, l = 0.f;
       for (int s = lane; s < it.nsplit; s += 64) m = fmaxf(m, p.part_ml[((int64_t)(it.slot0 + s) * G + g) * 2]);
 #pragma unroll
@@ -425,7 +450,7 @@ __global__ __launch_bounds__(256) void finish_kernel(DecodeParams p, int n_combi
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < R; ++k) {
-    const int r = r_begin + k * 256 + tid;
+    const int r = r_begin + k * THREADS + tid;
     float w = 0.f;
 #pragma unroll
     for (int g = 0; g < GT; ++g)
@@ -466,7 +491,7 @@ __global__ __launch_bounds__(256) void score_pass_kernel(ScoreParams p) {
   int r0 = r_begin + wave * (U * RPW);
   if (r0 < r_end) load_tile(r0);
   const int c_rel = it.c - p.cache_begin;
-  const int64_t qrow0 = (int64_t)(c_rel / p.Hkv) * p.Hq + (int64_t)(c_rel % p.Hkv) * G;
+  const int64_t qrow0 = (int64_t)c_rel * G;
   const T* qrows = reinterpret_cast<const T*>(p.q) + qrow0 * D;
   float qr[GT][EPL], M[GT], inv[GT];
 #pragma unroll
@@ -596,31 +621,47 @@ hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_ite
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, hipStream_t s) {
+// Caches of more work items than this are merged by 1024 threads per head instead of 256.  us per call, 256 / 1024: a
+// layer of 8 caches of up to 8192 rows (about 80 work items) 10.2 / 9.9, of 131072 rows 54.8 / 48.4; 32 caches (20) 18.5 /
+// 18.0; at 16 and fewer equal.
+constexpr int kManySplits = 16;
+
+hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, int most_split, hipStream_t s) {
   if (n_multi <= 0) return hipSuccess;
-  const dim3 grid(n_multi * p.G), block(256);
-  if (D == 128) combine_kernel<128><<<grid, block, 0, s>>>(p);
-  else if (D == 64) combine_kernel<64><<<grid, block, 0, s>>>(p);
-  else return hipErrorInvalidValue;
+  const dim3 grid(n_multi, p.G);
+  if (most_split > kManySplits) {
+    if (D == 128) combine_kernel<128, 1024><<<grid, dim3(1024), 0, s>>>(p);
+    else if (D == 64) combine_kernel<64, 1024><<<grid, dim3(1024), 0, s>>>(p);
+    else return hipErrorInvalidValue;
+  } else {
+    if (D == 128) combine_kernel<128, 256><<<grid, dim3(256), 0, s>>>(p);
+    else if (D == 64) combine_kernel<64, 256><<<grid, dim3(256), 0, s>>>(p);
+    else return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
-template <int D>
+template <int D, int THREADS>
 hipError_t launch_finish_d(const DecodeParams& p, int n_multi, int n_items, int max_count, hipStream_t s) {
-  const int tiles = (max_count + kFinishRows - 1) / kFinishRows, n_combine = n_multi * p.G;
-  const dim3 grid(n_combine + n_items * tiles), block(256);
-  if (p.G <= 1) finish_kernel<D, 1><<<grid, block, 0, s>>>(p, n_combine, tiles);
-  else if (p.G <= 2) finish_kernel<D, 2><<<grid, block, 0, s>>>(p, n_combine, tiles);
-  else if (p.G <= 4) finish_kernel<D, 4><<<grid, block, 0, s>>>(p, n_combine, tiles);
-  else if (p.G <= 8) finish_kernel<D, 8><<<grid, block, 0, s>>>(p, n_combine, tiles);
+  constexpr int kRows = kFinishRowsPerThread * THREADS;
+  const int tiles = (max_count + kRows - 1) / kRows, n_combine = n_multi * p.G;
+  const dim3 grid(n_combine + n_items * tiles), block(THREADS);
+  if (p.G <= 1) finish_kernel<D, 1, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles);
+  else if (p.G <= 2) finish_kernel<D, 2, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles);
+  else if (p.G <= 4) finish_kernel<D, 4, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles);
+  else if (p.G <= 8) finish_kernel<D, 8, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_finish(const DecodeParams& p, int D, int n_multi, int n_items, int max_count, hipStream_t s) {
+hipError_t launch_finish(const DecodeParams& p, int D, int n_multi, int most_split, int n_items, int max_count,
+                         hipStream_t s) {
   if (n_items <= 0 || max_count <= 0) return hipSuccess;
-  if (D == 128) return launch_finish_d<128>(p, n_multi, n_items, max_count, s);
-  if (D == 64) return launch_finish_d<64>(p, n_multi, n_items, max_count, s);
+  const bool wide = most_split > kManySplits;
+  if (D == 128) return wide ? launch_finish_d<128, 1024>(p, n_multi, n_items, max_count, s)
+                            : launch_finish_d<128, 256>(p, n_multi, n_items, max_count, s);
+  if (D == 64) return wide ? launch_finish_d<64, 1024>(p, n_multi, n_items, max_count, s)
+                           : launch_finish_d<64, 256>(p, n_multi, n_items, max_count, s);
   return hipErrorInvalidValue;
 }
 

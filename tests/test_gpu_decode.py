@@ -361,6 +361,35 @@ def test_scores_from_the_logits_of_a_call(dtype, D, G):
         arena.close()
 
 
+@pytest.mark.parametrize("splits", [[2, 3, 8, 9, 15, 16], [1, 2, 17, 31, 63, 64, 65, 128, 129, 255, 256, 257, 300]])
+@pytest.mark.parametrize("dtype,D,track", [("bf16", 128, False), ("bf16", 128, True), ("bf16", 64, False), ("f32", 64, True)])
+def test_merge_of_many_work_items(splits, dtype, D, track):
+    """Caches of up to 300 work items, around the numbers of splits that a thread group, a wavefront's lanes and its
+    registers hold, merged by 256 and by 1024 threads: outputs (and scores) against the oracle."""
+    H = _h()
+    G = 3
+    lens = [256 * k - 5 for k in splits]
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="merge", L=1, Hq=G * len(lens), Hkv=len(lens), D=D, batch=1, dtype=dtype,
+                     seed=98, sink=1, recent=1, slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed + len(splits)))
+    arena = H.make_arena(w, lens, track=track)
+    for target in (B.OPT_TARGET_ITEMS, B.OPT_TARGET_ITEMS_WHOLE):
+        arena.set_option(target, 0)                # runs of exactly 256 rows
+    H.set_chunk(arena, 512)
+    H.set_chunk(arena, 256)
+    st = H.fill_from_host(arena, w, lens, rng, peaked=True)
+    q, q64 = H.make_q(w, rng, w.L)
+    # two bf16 terms per weight leave up to 2^-16 of a value of about 4, fp32 weights a few units of 2^-24 of the logits
+    H.check_decode_against_oracle(arena, w, st, q64, H.gpu_decode(arena, w, q), tol=1e-4 if D == 128 else 64 * 2.0 ** -22)
+    if track:
+        post = H.download(arena, w)
+        for c in range(arena.n_caches):
+            l, b, hs = H.q_rows_of_cache(w, c)
+            _, p = O.decode_attn(q64[l, b, hs], synth.storage_to_f64(st.K[c], dtype), synth.storage_to_f64(st.V[c], dtype))
+            assert np.max(np.abs(post.score[c] - p.sum(0))) <= G * 2.0 ** -16
+    arena.close()
+
+
 def _two_term_attention(q, K, V):
     """Attention in 64 bits but for the weights, which are cut to two bf16 terms (high part and residual)."""
     s = (q @ K.T) * (np.log2(np.e) / np.sqrt(K.shape[1]))
