@@ -242,12 +242,14 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
 
 // Tile tables of the eviction's selection (they depend on capacities and the threshold only), in cache order, so that
 // the tiles of a layer range are a contiguous slice: one of the long caches, one of all others (spread; a single entry
-// for those of up to kNarrowRows rows).  The two share the tile counters.
+// for those of up to kNarrowRows rows).  The two share the tile counters.  Without a cache of several tiles the second
+// table is never read, and not uploaded.
 int build_tiles(baklava_ctx* ctx) {
   std::vector<SelTile> tiles, spread;
   const int64_t n_caches = ctx->n_caches;
   std::vector<int32_t> tile_begin(n_caches + 1, 0), spread_begin(n_caches + 1, 0);
   int32_t n_long = 0, counters = 0;
+  bool any_spread = false;
   for (int64_t c = 0; c < n_caches; ++c) {
     tile_begin[c] = (int32_t)tiles.size();
     spread_begin[c] = (int32_t)spread.size();
@@ -256,6 +258,7 @@ int build_tiles(baklava_ctx* ctx) {
     for (int32_t t = 0; t < nt; ++t)
       (is_long ? tiles : spread).push_back(SelTile{(int32_t)c, t, counters, nt, is_long ? n_long : 0, 0});
     if (is_long || nt > 1) counters += nt;
+    any_spread = any_spread || (!is_long && nt > 1);
     n_long += is_long ? 1 : 0;
   }
   tile_begin[n_caches] = (int32_t)tiles.size();
@@ -265,7 +268,7 @@ int build_tiles(baklava_ctx* ctx) {
   if (!hip_ok(hipDeviceSynchronize())) return BAKLAVA_EHIP;  // no launch may still read the old tables
   if ((!tiles.empty() &&
        !hip_ok(hipMemcpy(ctx->ws + ctx->plan.tiles, tiles.data(), tiles.size() * sizeof(SelTile), hipMemcpyHostToDevice))) ||
-      (!spread.empty() &&
+      (any_spread &&
        !hip_ok(hipMemcpy(ctx->ws + ctx->plan.spread, spread.data(), spread.size() * sizeof(SelTile), hipMemcpyHostToDevice))))
     return BAKLAVA_EHIP;
   ctx->tile_begin.swap(tile_begin);
