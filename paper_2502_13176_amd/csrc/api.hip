@@ -533,10 +533,14 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
   for (int32_t l = 0; l < desc->L; ++l)
     std::stable_sort(ctx->order_layer.begin() + (int64_t)l * ctx->cpl,
                      ctx->order_layer.begin() + (int64_t)(l + 1) * ctx->cpl, longer);
-  if (!hip_ok(hipMemcpy(ctx->ws + ctx->plan.order_all, ctx->order_all.data(), n_caches * 4, hipMemcpyHostToDevice)) ||
-      !hip_ok(hipMemcpy(ctx->ws + ctx->plan.order_layer, ctx->order_layer.data(), n_caches * 4, hipMemcpyHostToDevice))) {
-    delete ctx;
-    return BAKLAVA_EHIP;
+  {  // the two lie next to each other in the workspace: one copy (each takes about 20 us)
+    std::vector<int32_t> both((ctx->plan.order_layer - ctx->plan.order_all) / 4 + n_caches, 0);
+    std::copy(ctx->order_all.begin(), ctx->order_all.end(), both.begin());
+    std::copy(ctx->order_layer.begin(), ctx->order_layer.end(), both.end() - n_caches);
+    if (!hip_ok(hipMemcpy(ctx->ws + ctx->plan.order_all, both.data(), both.size() * 4, hipMemcpyHostToDevice))) {
+      delete ctx;
+      return BAKLAVA_EHIP;
+    }
   }
   // No call is pending for the score pass, and the status word is clear.
   if (!hip_ok(hipMemset(ctx->ws + ctx->plan.lag_cnt, 0, (size_t)n_caches * ctx->G * 4)) ||
