@@ -205,7 +205,10 @@ enum {
                                    layer, until a layer has at most this many work items; 0: off.
                                    Default: the device's number of compute units (one wave of
                                    workgroups) while a layer holds at most a quarter as many caches,
-                                   otherwise five times that number, with a shortest run of 256 rows */
+                                   otherwise five times that number, with a shortest run of 256 rows.
+                                   The default schedules also cut runs of fewer rows where a launch of
+                                   split caches would have fewer work items than compute units; setting
+                                   another run length or item target ends that                       */
   BAKLAVA_OPT_TARGET_ITEMS_WHOLE = 6, /* the same for launches over all layers at once.  Default: five
                                    times the device's number of compute units                      */
   BAKLAVA_OPT_TRACK_SCORES = 7, /* 0: attention calls stop adding to the scores (calls already on

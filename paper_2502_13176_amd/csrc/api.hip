@@ -8,6 +8,7 @@
 
 #include "baklava.h"
 #include "common.h"
+#include "plan.h"
 
 using namespace baklava;
 
@@ -26,6 +27,8 @@ constexpr int kSizingChunk = 256;  // the workspace is sized for chunks of at le
 constexpr int kDefaultChunk = 512;        // launches over part of the model: shortest run (the item target lengthens it)
 constexpr int kDefaultChunkWhole = 256;   // launches over the whole model: shortest run; longer ones come from the item target
 constexpr int kWholeItemsPerCu = 5;       // whole-model launches aim at this many work items per compute unit
+constexpr int kShortestRun = 64;          // where those would leave compute units idle (see build_schedule)
+constexpr int kMostFillItems = 512;       // most work items such short runs are cut for (sizes the workspace)
 constexpr int kMaxChunk = 1 << 22; // row offsets inside a work item stay below 2^32 bytes
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -109,7 +112,12 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
   for (int64_t c = 0; c < n_caches; ++c) total_tokens += cap[c];
   w.seg_rows = move_seg_rows(d, budget);
   count_segments(d, cap, budget, w.seg_rows, &w.n_segs, &w.halo_rows);
-  w.max_items = count_items(cap, n_caches, kSizingChunk);
+  // runs of at least kSizingChunk rows, or the shorter ones of the layers that those would not fill the chip with
+  const int64_t cpl = (int64_t)d->batch * d->Hkv;
+  w.max_items = 0;
+  for (int32_t l = 0; l < d->L; ++l)
+    w.max_items += std::max(count_items(cap + l * cpl, cpl, kSizingChunk),
+                            std::min<int64_t>(count_items(cap + l * cpl, cpl, kShortestRun), kMostFillItems));
   size_t o = 0;
   for (int k = 0; k < 2; ++k) {
     w.items[k] = o;   o = align256(o + (size_t)w.max_items * sizeof(Item));
@@ -177,6 +185,7 @@ struct baklava_ctx {
   int32_t lag_gp_log2;         // score tracking: log2 of G rounded up to 4, 8 or 16 (rows a call takes in a record)
   struct Schedule {
     int32_t chunk = 0;
+    bool fill = false;                 // runs of fewer rows where those would leave compute units idle (the default)
     std::vector<int32_t> max_count;    // layer -> longest work item of the layer, rows
     std::vector<int32_t> max_split;    // layer -> most work items of a cache
     std::vector<int32_t> cib;          // cache -> first item
@@ -196,13 +205,23 @@ namespace {
 // serves launches over a layer sub-range (launch order inside each layer, so a layer range is a
 // contiguous slice), schedule 1 launches over the whole model.  The table depends on capacities
 // only, so it is uploaded once; the kernels clamp each run to the live length.
-int build_schedule(baklava_ctx* ctx, int which, int chunk) {
+//
+// fill: the default schedules, until an option asks for a run length or an item count.  A launch whose caches the
+// shortest run already cuts, so that it merges partials anyway, but into fewer work items than there are compute units,
+// takes runs of 64 rows and more, as long as they make one wave: a compute unit reads some 30 to 45 GB/s whatever it
+// is given.  us per call of a layer of 8 caches (shortest run 512) / now, bf16, D = 128, four query heads, tracked:
+// 8192 rows in all 13.7 / 12.0, 32768 14.9 / 12.7, 65536 16.1 / 15.0; attention alone, one head, 8192 10.1 / 7.6; fp32,
+// D = 128, four heads, 8192 20.1 / 10.4, 32768 22.1 / 15.3.  Runs of at least 128 rows are equal but in the vector kernel
+// (8192 rows as before, 12.7).  A launch of unsplit caches stays: cut, it would need a merge (8 bf16 caches of 384 rows 6.2
+// us, cut 7.3; of 128 rows 4.4, cut 7.2), except on the vector kernel from four heads on, whose shortest run is 256 rows
+// (fp32, D = 128, four heads, 8 caches of 320 rows 11.8, cut 9.4; of 192 rows 9.4, cut 9.5).
+int build_schedule(baklava_ctx* ctx, int which, int chunk, bool fill) {
   int64_t n_items = 0;
   std::vector<baklava_work_item> items((size_t)ctx->plan.max_items);
-  const int st = baklava_plan_schedule(ctx->off.data(), ctx->cap.data(), ctx->d.L, ctx->cpl, chunk,
-                                       which == 0 ? ctx->target_items : ctx->target_items_whole, which,
-                                       ctx->plan.max_items,
-                                       items.data(), &n_items);
+  const int st = plan_schedule(ctx->off.data(), ctx->cap.data(), ctx->d.L, ctx->cpl, chunk,
+                               which == 0 ? ctx->target_items : ctx->target_items_whole, kShortestRun,
+                               fill ? std::min(ctx->n_cus, kMostFillItems) : 0, which, ctx->plan.max_items,
+                               items.data(), &n_items);
   if (st != BAKLAVA_OK) return st;
   static_assert(sizeof(baklava_work_item) == sizeof(Item), "work item layouts must match");
   // cache -> first partial slot, and the caches that need the combine kernel (in launch order)
@@ -235,6 +254,7 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk) {
   ctx->sched[which].cib.swap(cib);
   ctx->sched[which].multi_begin.swap(multi_begin);
   ctx->sched[which].chunk = chunk;
+  ctx->sched[which].fill = fill;
   ctx->sched[which].max_count.swap(max_count);
   ctx->sched[which].max_split.swap(max_split);
   return BAKLAVA_OK;
@@ -589,8 +609,9 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     if (st != BAKLAVA_OK) { delete ctx; return st; }
   }
   if (desc->dtype == BAKLAVA_BF16 && !hip_ok(prepare_decode_mfma())) { delete ctx; return BAKLAVA_EHIP; }
-  int st = build_schedule(ctx, 0, ctx->layer_one_wave ? kDefaultChunk : kDefaultChunkWhole);
-  if (st == BAKLAVA_OK) st = build_schedule(ctx, 1, kDefaultChunkWhole);
+  const bool slow_rows = desc->dtype == BAKLAVA_F32 && ctx->G >= 4;  // (see build_schedule)
+  int st = build_schedule(ctx, 0, ctx->layer_one_wave && !slow_rows ? kDefaultChunk : kDefaultChunkWhole, true);
+  if (st == BAKLAVA_OK) st = build_schedule(ctx, 1, kDefaultChunkWhole, true);
   if (st != BAKLAVA_OK) { delete ctx; return st; }
   *out = ctx;
   return BAKLAVA_OK;
@@ -610,8 +631,8 @@ extern "C" int baklava_set_option(baklava_ctx* ctx, int32_t option, int64_t valu
     case BAKLAVA_OPT_CHUNK_TOKENS_WHOLE: {
       if (value < kMinChunk || value % 64 || value > kMaxChunk) return BAKLAVA_EINVAL;
       const int which = option == BAKLAVA_OPT_CHUNK_TOKENS ? 0 : 1;
-      if ((int32_t)value == ctx->sched[which].chunk) return BAKLAVA_OK;
-      return build_schedule(ctx, which, (int32_t)value);
+      if ((int32_t)value == ctx->sched[which].chunk && !ctx->sched[which].fill) return BAKLAVA_OK;
+      return build_schedule(ctx, which, (int32_t)value, false);
     }
     case BAKLAVA_OPT_TARGET_ITEMS:
     case BAKLAVA_OPT_TARGET_ITEMS_WHOLE: {
@@ -620,7 +641,7 @@ extern "C" int baklava_set_option(baklava_ctx* ctx, int32_t option, int64_t valu
       int32_t& target = which == 0 ? ctx->target_items : ctx->target_items_whole;
       if ((int32_t)value == target) return BAKLAVA_OK;
       target = (int32_t)value;
-      return build_schedule(ctx, which, ctx->sched[which].chunk);
+      return build_schedule(ctx, which, ctx->sched[which].chunk, false);
     }
     case BAKLAVA_OPT_KERNEL:
       if (value < 0 || value > 2) return BAKLAVA_EINVAL;

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "baklava.h"
+#include "plan.h"
 
 namespace {
 
@@ -191,11 +192,13 @@ extern "C" int baklava_alloc_two_level(const double* layer_importance, const dou
   return BAKLAVA_OK;
 }
 
-// Split-K schedule: runs of equal length over each cache's capacity, in launch order.
-extern "C" int baklava_plan_schedule(const int64_t* off_host, const int32_t* cap_host, int32_t L,
-                                     int32_t caches_per_layer, int32_t chunk, int32_t target_items,
-                                     int32_t whole_model, int64_t max_items, baklava_work_item* items_out,
-                                     int64_t* n_items_out) {
+// Split-K schedule: runs of equal length over each cache's capacity, in launch order.  With fill_items > 0 a launch
+// unit in which runs of `chunk` rows split some cache, but give fewer than fill_items work items, gets shorter ones, of
+// at least `shortest` rows, up to that many items.
+int baklava::plan_schedule(const int64_t* off_host, const int32_t* cap_host, int32_t L, int32_t caches_per_layer,
+                           int32_t chunk, int32_t target_items, int32_t shortest, int32_t fill_items,
+                           int32_t whole_model, int64_t max_items, baklava_work_item* items_out,
+                           int64_t* n_items_out) {
   if (!off_host || !cap_host || !n_items_out || L <= 0 || caches_per_layer <= 0) return BAKLAVA_EINVAL;
   if (chunk < 256 || chunk % 64 || chunk > (1 << 22) || max_items < 0 || target_items < 0) return BAKLAVA_EINVAL;
   if (whole_model != 0 && whole_model != 1) return BAKLAVA_EINVAL;
@@ -209,7 +212,7 @@ extern "C" int baklava_plan_schedule(const int64_t* off_host, const int32_t* cap
   const int64_t n_units = whole_model ? 1 : L;
   const int64_t unit_caches = whole_model ? n_caches : caches_per_layer;
   std::vector<int64_t> cache_run(n_caches, chunk);
-  if (target_items > 0) {
+  if (target_items > 0 || fill_items > 0) {
     for (int64_t u = 0; u < n_units; ++u) {
       const int64_t c0 = u * unit_caches, c1 = c0 + unit_caches;
       auto items_at = [&](int64_t run) {
@@ -217,11 +220,18 @@ extern "C" int baklava_plan_schedule(const int64_t* off_host, const int32_t* cap
         for (int64_t c = c0; c < c1; ++c) n += runs(c, run);
         return n;
       };
+      int64_t unit_chunk = chunk, unit_target = target_items;
+      const int64_t at_chunk = items_at(chunk);
+      if (at_chunk > unit_caches && at_chunk < fill_items) {
+        unit_chunk = shortest;
+        unit_target = fill_items;
+        std::fill(cache_run.begin() + c0, cache_run.begin() + c1, unit_chunk);
+      }
       // a unit never has fewer items than caches
-      const int64_t target = std::max<int64_t>(target_items, unit_caches);
-      if (items_at(chunk) <= target) continue;
+      const int64_t target = std::max<int64_t>(unit_target, unit_caches);
+      if (unit_target <= 0 || items_at(unit_chunk) <= target) continue;
       // the shortest run length, in steps of 64 rows, that meets the target (items_at is non-increasing)
-      int64_t lo = chunk / 64, hi = (int64_t(1) << 31) / 64;
+      int64_t lo = unit_chunk / 64, hi = (int64_t(1) << 31) / 64;
       while (hi - lo > 1) {
         const int64_t mid = (lo + hi) / 2;
         if (items_at(mid * 64) > target) lo = mid; else hi = mid;
@@ -231,7 +241,7 @@ extern "C" int baklava_plan_schedule(const int64_t* off_host, const int32_t* cap
       // inside a cache the runs are then made equal: no run grows, the count stays
       for (int64_t c = c0; c < c1; ++c) {
         const int64_t n = runs(c, unit_run);
-        cache_run[c] = std::max<int64_t>(chunk, round64(((int64_t)cap_host[c] + n - 1) / n));
+        cache_run[c] = std::max<int64_t>(unit_chunk, round64(((int64_t)cap_host[c] + n - 1) / n));
       }
     }
   }
@@ -270,4 +280,12 @@ extern "C" int baklava_plan_schedule(const int64_t* off_host, const int32_t* cap
     }
   }
   return BAKLAVA_OK;
+}
+
+extern "C" int baklava_plan_schedule(const int64_t* off_host, const int32_t* cap_host, int32_t L,
+                                     int32_t caches_per_layer, int32_t chunk, int32_t target_items,
+                                     int32_t whole_model, int64_t max_items, baklava_work_item* items_out,
+                                     int64_t* n_items_out) {
+  return baklava::plan_schedule(off_host, cap_host, L, caches_per_layer, chunk, target_items, chunk, 0, whole_model,
+                                max_items, items_out, n_items_out);
 }

@@ -524,3 +524,41 @@ def test_infinite_values_with_half_size_rows(kernel):
         fin = np.isfinite(ref)
         assert np.max(np.abs(out[fin] - ref[fin])) <= 4e-6
     arena.close()
+
+
+@pytest.mark.parametrize("dtype,D,G", [("bf16", 128, 4), ("bf16", 128, 16), ("bf16", 64, 2), ("f32", 64, 1), ("f32", 128, 5)])
+@pytest.mark.parametrize("track", [False, True])
+def test_short_runs_of_small_launches(dtype, D, G, track):
+    """The default schedules of layers that runs of 256 or 512 rows would not fill the chip with: runs of 64 rows and
+    more, lengths around them, layers of split and of unsplit caches, against the oracle, per layer and all at once; a
+    run length set to the default's shortest is followed."""
+    H = _h()
+    lens = [64, 65, 63, 1, 513, 640, 577, 2, 1000, 1089, 704, 129, 300, 256, 200, 320]  # four layers of four caches
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="runs", L=4, Hq=2 * G, Hkv=2, D=D, batch=2, dtype=dtype, seed=97 + G,
+                     sink=1, recent=1, slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    budgets = [max(lens[4 * l + h], lens[4 * l + 2 + h]) + 3 for l in range(w.L) for h in range(2)]
+    arena = H.make_arena(w, budgets, track=track)
+    st = H.fill_from_host(arena, w, lens, rng)
+    q, q64 = H.make_q(w, rng, w.L)
+    ref_w = np.zeros(arena.total_tokens)
+    for c in range(arena.n_caches):
+        l, b, hs = H.q_rows_of_cache(w, c)
+        _, p = O.decode_attn(q64[l, b, hs], synth.storage_to_f64(st.K[c], dtype), synth.storage_to_f64(st.V[c], dtype))
+        ref_w[arena.off_host[c]:arena.off_host[c] + lens[c]] = p.sum(0)
+    tol = 5 * 2.0 ** -17  # two bf16 terms of a weight leave 2^-17 of it, elements of V are below 5
+    calls = 0
+    for chunk in (None, 512):
+        if chunk:
+            arena.set_option(B.OPT_CHUNK_TOKENS, chunk)
+        H.check_decode_against_oracle(arena, w, st, q64, H.gpu_decode(arena, w, q), tol=tol)
+        for l in range(w.L):
+            out = H.gpu_decode(arena, w, q[l:l + 1], layer_begin=l, layer_count=1)
+            H.check_decode_against_oracle(arena, w, st, q64[l:l + 1], out, caches=range(4 * l, 4 * l + 4), layer_begin=l, tol=tol)
+        calls += 2
+    if track:
+        got = H.download(arena, w).score
+        for c in range(arena.n_caches):
+            o = int(arena.off_host[c])
+            assert np.max(np.abs(got[c] - calls * ref_w[o:o + lens[c]])) <= 2e-6 * calls * G  # fp32 logits of up to 16 in log2 units
+    arena.close()
