@@ -2,11 +2,12 @@
 // output hidden state of a layer, token by token, and its mean over the prompt.
 //
 // HBM-bound: every hidden-state row is read once (2 * hidden * 2 bytes per token for bf16).  One
-// wavefront per token row: 64 lanes x 16 bytes per load instruction, all loads of a row pair in
-// flight before the first use, non-temporal (read once); three dot products per row reduced over
-// the wavefront.  A workgroup takes 16 consecutive rows and writes the sum of their cosines; a
+// wavefront per token row, or per two or four short ones: 64 lanes x 16 bytes per load instruction, all
+// loads of the row pairs in flight before the first use, non-temporal (read once); three dot products
+// per row reduced over the wavefront.  A workgroup takes 16 consecutive rows and writes the sum of their cosines; a
 // second small kernel adds the workgroup sums in a fixed order (deterministic, no atomics).
 #include <mutex>
+#include <type_traits>
 
 #include "baklava.h"
 #include "common.h"
@@ -40,40 +41,88 @@ __device__ __forceinline__ void accumulate(uint4 a, uint4 b, float& dot, float& 
   }
 }
 
+// Sum over the 16 lanes of a row of lanes, every lane receiving it: the pairs of a butterfly over lane distances 8, 4,
+// 2, 1 (lanes that a rotation reaches in place of the partner hold the same sum as it).
+__device__ __forceinline__ float row_sum(float v) {
+  auto dpp = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v += dpp(v, std::integral_constant<int, 0x128>{});  // row_ror:8
+  v += dpp(v, std::integral_constant<int, 0x124>{});  // row_ror:4
+  v += dpp(v, std::integral_constant<int, 0x122>{});  // row_ror:2
+  v += dpp(v, std::integral_constant<int, 0x121>{});  // row_ror:1
+  return v;
+}
+
+// A wavefront's four rows are taken ROWS at a time, up to 8 KB of each tensor in flight: row by row, short rows spent
+// their time on one memory latency each (hidden 512, 768 and 1024 all took 93 to 97 us for 32 x 4096 tokens).  A sum
+// over 64 lanes goes to the 64 / ROWS lanes that keep its row in the first steps, so four rows cost 9 exchanges and 12
+// rotations instead of 72 exchanges.
+template <int ROWS>
 __global__ __launch_bounds__(256) void layer_cosine_kernel(LayerParams p) {
+  constexpr int kPieces = 8 / ROWS, kPerWave = kRowsPerWg / kWaves;
   __shared__ float wave_sum[kWaves];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int seq = blockIdx.x / p.n_tiles, tile = blockIdx.x % p.n_tiles;
   const int64_t row_bytes = (int64_t)p.hidden * 2;
   float wsum = 0.f;
-  for (int r = wave; r < kRowsPerWg; r += kWaves) {
-    const int t = tile * kRowsPerWg + r;
-    if (t >= p.T) break;  // uniform per wavefront
-    const unsigned char* a = p.x_in + ((int64_t)seq * p.T + t) * row_bytes;
-    const unsigned char* b = p.x_out + ((int64_t)seq * p.T + t) * row_bytes;
-    float dot = 0.f, na = 0.f, nb = 0.f;
-    // 8 pieces of 1 KiB per tensor in flight per wavefront (a 4096-wide row is one pass)
-    for (int64_t h0 = (int64_t)lane * 16; h0 < row_bytes; h0 += 8 * 1024) {
-      uint4 av[8], bv[8];
+  for (int k = 0; k < kPerWave; k += ROWS) {
+    const int t0 = tile * kRowsPerWg + wave + k * kWaves;  // rows t0, t0 + 4, ...
+    if (t0 >= p.T) break;
+    int64_t at[ROWS];
+    float dot[ROWS], na[ROWS], nb[ROWS];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+    for (int r = 0; r < ROWS; ++r) {
+      at[r] = ((int64_t)seq * p.T + min(t0 + r * kWaves, p.T - 1)) * row_bytes;  // past the prompt: its last row
+      dot[r] = na[r] = nb[r] = 0.f;
+    }
+    // (a 4096-wide row is one pass)
+    for (int64_t h0 = (int64_t)lane * 16; h0 < row_bytes; h0 += kPieces * 1024) {
+      uint4 av[ROWS][kPieces], bv[ROWS][kPieces];
+#pragma unroll
+      for (int u = 0; u < kPieces; ++u) {
         const int64_t o = h0 + u * 1024;
-        av[u] = make_uint4(0, 0, 0, 0);
-        bv[u] = make_uint4(0, 0, 0, 0);
-        if (o < row_bytes) { av[u] = load_nt16(a + o); bv[u] = load_nt16(b + o); }
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) av[r][u] = bv[r][u] = make_uint4(0, 0, 0, 0);
+        if (o < row_bytes) {
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) {
+            av[r][u] = load_nt16(p.x_in + at[r] + o);
+            bv[r][u] = load_nt16(p.x_out + at[r] + o);
+          }
+        }
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) accumulate(av[u], bv[u], dot, na, nb);
+      for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int u = 0; u < kPieces; ++u) accumulate(av[r][u], bv[r][u], dot[r], na[r], nb[r]);
+    }
+    // lanes 64 / ROWS * r and on keep row r
+    int off = 32;
+#pragma unroll
+    for (int n = ROWS / 2; n > 0; n /= 2, off /= 2) {
+      const bool upper = lane & off;
+#pragma unroll
+      for (int r = 0; r < n; ++r) {
+        auto fold = [&](float (&v)[ROWS]) { v[r] = (upper ? v[r + n] : v[r]) + __shfl_xor(upper ? v[r] : v[r + n], off); };
+        fold(dot);
+        fold(na);
+        fold(nb);
+      }
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      dot += __shfl_xor(dot, off);
-      na += __shfl_xor(na, off);
-      nb += __shfl_xor(nb, off);
+    for (; off >= 16; off /= 2) {
+      dot[0] += __shfl_xor(dot[0], off);
+      na[0] += __shfl_xor(na[0], off);
+      nb[0] += __shfl_xor(nb[0], off);
     }
-    const float c = dot / fmaxf(sqrtf(na) * sqrtf(nb), kCosEps);
-    if (lane == 0 && p.cos_out) p.cos_out[(int64_t)seq * p.T + t] = c;
-    wsum += c;
+    const float d = row_sum(dot[0]), a = row_sum(na[0]), b = row_sum(nb[0]);
+    const float c = d / fmaxf(sqrtf(a) * sqrtf(b), kCosEps);
+    const int t = t0 + lane / (64 / ROWS) * kWaves;
+    if (lane % (64 / ROWS) == 0 && p.cos_out && t < p.T) p.cos_out[(int64_t)seq * p.T + t] = c;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+      if (t0 + r * kWaves < p.T) wsum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), r * (64 / ROWS)));
   }
   if (lane == 0) wave_sum[wave] = wsum;
   __syncthreads();
@@ -103,7 +152,13 @@ hipError_t launch_layer_similarity(const void* x_in, const void* x_out, int n_se
   p.n_tiles = (T + kRowsPerWg - 1) / kRowsPerWg;
   const int64_t n_wg = (int64_t)n_seq * p.n_tiles;
   if (n_wg <= 0 || n_wg > INT32_MAX) return hipErrorInvalidValue;
-  layer_cosine_kernel<<<dim3((unsigned)n_wg), dim3(256), 0, s>>>(p);
+  // As many rows at a time as 8 KB of a tensor hold, but one from 3.5 KB on, where enough is in flight anyway.  us, row by
+  // row / so, 32 prompts of 4096 tokens: hidden 512 89.9 / 43.9, 768 92.5 / 62.9, 1024 95.8 / 84.4, 1152 (28 prompts)
+  // 103 / 82.7, 1536 (21) 84.0 / 81.9, 1792 (18) 83.5 / 81.8, two rows at 2048 (16) 87.2 / 88.3; 32 prompts of 1000
+  // tokens: 512 27.4 / 16.2, 1024 30.1 / 24.0, 1536 35.6 / 33.9.
+  if (hidden <= 1024) layer_cosine_kernel<4><<<dim3((unsigned)n_wg), dim3(256), 0, s>>>(p);
+  else if (hidden <= 1792) layer_cosine_kernel<2><<<dim3((unsigned)n_wg), dim3(256), 0, s>>>(p);
+  else layer_cosine_kernel<1><<<dim3((unsigned)n_wg), dim3(256), 0, s>>>(p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   layer_mean_kernel<<<dim3(n_seq), dim3(64), 0, s>>>(tile_sum, sim_out, p.n_tiles, T);

@@ -47,6 +47,17 @@ def test_shapes_around_every_tile_boundary(n_seq, T, hidden):
     run_case(a, b)
 
 
+@pytest.mark.parametrize("hidden", [504, 512, 520, 1016, 1024, 1032, 1536, 1784, 1792, 1800])
+@pytest.mark.parametrize("T", [1, 4, 5, 12, 13, 29])
+def test_short_rows_taken_several_at_a_time(T, hidden):
+    """Rows of up to 3.5 KB, of which a wavefront takes two or four at once: hidden sizes around the lines between the
+    forms and prompts that end inside a wavefront's rows."""
+    rng = np.random.Generator(np.random.PCG64(9960 + 40 * T + hidden))
+    a = synth.payload(rng, (2, T, hidden), "bf16")
+    b = synth.payload(rng, (2, T, hidden), "bf16")
+    run_case(a, b)
+
+
 def test_residual_stream_shaped_rows_and_special_rows():
     """Output = input + a small update (what a transformer layer does), from nearly unchanged to
     strongly changed; identical, opposite and zero rows."""
