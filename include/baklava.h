@@ -209,8 +209,9 @@ enum {
                                    The default schedules also cut runs of fewer rows where a launch of
                                    split caches would have fewer work items than compute units; setting
                                    another run length or item target ends that                       */
-  BAKLAVA_OPT_TARGET_ITEMS_WHOLE = 6, /* the same for launches over all layers at once.  Default: five
-                                   times the device's number of compute units                      */
+  BAKLAVA_OPT_TARGET_ITEMS_WHOLE = 6, /* the same for launches over all layers at once.  Default: two to
+                                   five times the device's number of compute units, by the number of
+                                   caches and rows                                                  */
   BAKLAVA_OPT_TRACK_SCORES = 7, /* 0: attention calls stop adding to the scores (calls already on
                                    record stay there until the next flush); 1: they resume.  Only a
                                    context created with track_scores can be switched to 1          */

@@ -26,7 +26,7 @@ constexpr int kMinChunk = 256;
 constexpr int kSizingChunk = 256;  // the workspace is sized for chunks of at least this many rows
 constexpr int kDefaultChunk = 512;        // launches over part of the model: shortest run (the item target lengthens it)
 constexpr int kDefaultChunkWhole = 256;   // launches over the whole model: shortest run; longer ones come from the item target
-constexpr int kWholeItemsPerCu = 5;       // whole-model launches aim at this many work items per compute unit
+constexpr int kWholeItemsPerCu = 5;       // launches over many caches aim at this many work items per compute unit
 constexpr int kShortestRun = 64;          // where those would leave compute units idle (see build_schedule)
 constexpr int kMostFillItems = 512;       // most work items such short runs are cut for (sizes the workspace)
 constexpr int kMaxChunk = 1 << 22; // row offsets inside a work item stay below 2^32 bytes
@@ -200,6 +200,21 @@ struct baklava_ctx {
 };
 
 namespace {
+
+// Work items per compute unit that a launch over the whole model aims at: runs long enough to amortise the per-item
+// costs (a merge of the wavefronts, and of the split partials), yet enough of them to even out the load.  Two run side by
+// side on a compute unit, so two are best while every cache can still be cut into about four (as for one wave of a layer),
+// three up to the next line and five beyond; where two would make runs of more than 8192 rows, four, whose scores fit
+// the LDS they wait in.  us per call with five / by the rule, attention alone and tracked: bf16, D = 128, four heads, 32
+// caches of 4096 rows 17.1 / 16.4 and 24.8 / 22.9, 64 27.9 / 24.9 and 36.6 / 33.0, 128 47.2 / 45.0 and 59.4 / 55.9, 192
+// (three) 66.7 / 65.3 and 82.1 / 80.3; D = 64, 64 18.1 / 15.3 and 29.6 / 24.1; fp32, D = 128, 64 53.3 / 47.0 and 68.9 / 55.8;
+// 128 caches of 65536 rows (four) 632 / 627 and 733 / 724, with two 628 and 736; 256 of 8192 rows with four instead of five
+// 160 / 163 (one head) and 165 / 165, with two 197.
+int whole_items_per_cu(int64_t n_caches, int64_t rows, int64_t cus) {
+  if (4 * n_caches <= 2 * cus) return rows <= 2 * cus * 8192 ? 2 : 4;
+  if (4 * n_caches <= 3 * cus) return 3;
+  return kWholeItemsPerCu;
+}
 
 // Builds one of the two split-K schedules with the host planner and uploads it.  Schedule 0
 // serves launches over a layer sub-range (launch order inside each layer, so a layer range is a
@@ -533,9 +548,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     ctx->layer_one_wave = (int64_t)ctx->cpl * 4 <= cus;
     ctx->target_items = ctx->layer_one_wave ? cus : kWholeItemsPerCu * cus;
     ctx->n_cus = cus;
-    // Whole-model launches: runs long enough to amortise the per-item costs, yet enough items for
-    // the dispatcher to even out the load over several waves of workgroups.
-    ctx->target_items_whole = kWholeItemsPerCu * cus;
+    ctx->target_items_whole = whole_items_per_cu(n_caches, packed, cus) * cus;
   }
   ctx->time_kernel = 0;
   ctx->track_on = desc->track_scores != 0;

@@ -526,7 +526,7 @@ def test_infinite_values_with_half_size_rows(kernel):
     arena.close()
 
 
-@pytest.mark.parametrize("dtype,D,G", [("bf16", 128, 4), ("bf16", 128, 16), ("bf16", 64, 2), ("f32", 64, 1), ("f32", 128, 5)])
+@pytest.mark.parametrize("dtype,D,G", [("bf16", 128, 4), ("bf16", 128, 16), ("bf16", 64, 2), ("f32", 64, 1), ("f32", 64, 3), ("f32", 128, 4), ("f32", 128, 5)])
 @pytest.mark.parametrize("track", [False, True])
 def test_short_runs_of_small_launches(dtype, D, G, track):
     """The default schedules of layers that runs of 256 or 512 rows would not fill the chip with: runs of 64 rows and
@@ -561,4 +561,21 @@ def test_short_runs_of_small_launches(dtype, D, G, track):
         for c in range(arena.n_caches):
             o = int(arena.off_host[c])
             assert np.max(np.abs(got[c] - calls * ref_w[o:o + lens[c]])) <= 2e-6 * calls * G  # fp32 logits of up to 16 in log2 units
+    arena.close()
+
+
+@pytest.mark.parametrize("batch", [64, 65, 96, 97])
+def test_work_items_of_whole_model_launches(batch):
+    """Numbers of caches around the lines at which a launch over all layers aims at two, three and five work items per
+    compute unit, ragged lengths, against the oracle."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="whole", L=1, Hq=4, Hkv=2, D=64, batch=batch, seed=120 + batch, sink=1,
+                     recent=1, slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    arena = H.make_arena(w, [1300, 700])
+    lens = [int(rng.integers(1, 1301 if c % 2 == 0 else 701)) for c in range(arena.n_caches)]
+    st = H.fill_from_host(arena, w, lens, rng)
+    q, q64 = H.make_q(w, rng, 1)
+    # three bf16 terms of a weight are exact: fp32 logits, weights and sums of up to 1300 rows
+    H.check_decode_against_oracle(arena, w, st, q64, H.gpu_decode(arena, w, q), tol=64 * 2.0 ** -24 * 4)
     arena.close()
