@@ -89,7 +89,10 @@ __device__ __forceinline__ float select_own(const float* v, int i) {
 // rows, one tile for each of eight wavefronts, so the merge at the end weighs more: four wavefronts then
 // (88 bf16 caches of 2500 rows per launch, D = 64, four query heads, eight steps of three layers and an
 // eviction: 639 us, with eight 1024, as it was before 894).
-template <int REGS> constexpr int wide_waves() { return REGS <= 16 ? 16 : 8; }
+// (16 at four fp32 query heads leave 128 registers where the loop takes 136, so that it spills and loads less far ahead:
+// us per call, 16 / 8, a layer of 32 caches of 4096 rows, D = 128, 29.8 / 28.2, tracked 39.5 / 32.3, 8 caches of 4096
+// rows 15.5 / 14.0 and 18.8 / 16.4; D = 64 20.0 / 18.3 and 24.4 / 22.2.)
+template <int GT, int EPL> constexpr int wide_waves() { return GT < 4 && GT * EPL <= 16 ? 16 : 8; }
 
 // KEEP (score tracking): the scaled logits of the call go to p.logits for the kernel behind this one.  They wait in
 // LDS until the work item is done (or a wavefront's part of the area is full): stores between the loads would slow
@@ -594,7 +597,7 @@ void launch_valu_nw(DecodeParams p, int n_items, int max_count, bool one_wave, h
 
 template <typename T, int D, int GT>
 void launch_valu(const DecodeParams& p, int n_items, int max_count, bool one_wave, hipStream_t s) {
-  constexpr int NW = wide_waves<GT * Row<T>::EPL>();
+  constexpr int NW = wide_waves<GT, Row<T>::EPL>();
   if (one_wave) launch_valu_nw<T, D, GT, NW>(p, n_items, max_count, one_wave, s);
   else launch_valu_nw<T, D, GT, 4>(p, n_items, max_count, one_wave, s);
 }
