@@ -226,10 +226,11 @@ int whole_items_per_cu(int64_t n_caches, int64_t rows, int64_t cus) {
 // takes runs of 64 rows and more, as long as they make one wave: a compute unit reads some 30 to 45 GB/s whatever it
 // is given.  us per call of a layer of 8 caches (shortest run 512) / now, bf16, D = 128, four query heads, tracked:
 // 8192 rows in all 13.7 / 12.0, 32768 14.9 / 12.7, 65536 16.1 / 15.0; attention alone, one head, 8192 10.1 / 7.6; fp32,
-// D = 128, four heads, 8192 20.1 / 10.4, 32768 22.1 / 15.3.  Runs of at least 128 rows are equal but in the vector kernel
-// (8192 rows as before, 12.7).  A launch of unsplit caches stays: cut, it would need a merge (8 bf16 caches of 384 rows 6.2
-// us, cut 7.3; of 128 rows 4.4, cut 7.2), except on the vector kernel from four heads on, whose shortest run is 256 rows
-// (fp32, D = 128, four heads, 8 caches of 320 rows 11.8, cut 9.4; of 192 rows 9.4, cut 9.5).
+// D = 128, four heads, 8192 20.1 / 10.1, 32768 22.1 / 13.9.  Runs of at least 128 rows are equal but in the vector kernel
+// (8192 rows 12.7).  A launch of unsplit caches stays: cut, it would need a merge (8 bf16 caches of 384 rows 6.2 us, cut
+// 7.3; of 128 rows 4.4, cut 7.2), except on the vector kernel from four heads on, whose shortest run is 256 rows (8 caches,
+// four heads, D = 128, 320 rows 12.2, cut 9.2, 500 rows 17.1, cut 9.3; D = 64, 264 rows 7.8, cut 8.3, tracked 13.1, cut
+// 11.1, 384 rows 8.8, cut 8.2; eight heads 264 rows 12.8, cut 11.1).
 int build_schedule(baklava_ctx* ctx, int which, int chunk, bool fill) {
   int64_t n_items = 0;
   std::vector<baklava_work_item> items((size_t)ctx->plan.max_items);
