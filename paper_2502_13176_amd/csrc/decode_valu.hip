@@ -403,22 +403,29 @@ __global__ __launch_bounds__(THREADS) void combine_kernel(DecodeParams p) {
 //   score_j += sum_g 2^(x_gj - M_g) / L_g   (cumulative attention per cached token, summed over the query heads)
 // from the logits x that the attention kernel has left.  The other workgroups take two rows per thread of a work item
 // and merge their cache's normalisers from the split partials for themselves, behind the loads of the rows.
+// (n_items > 0: a grid of two dimensions, the first row of workgroups for the partials, then one per tile of rows.)
 // Reads 4 G bytes per row where a pass over the K rows read the row and formed the products again: 8 tracked calls
 // over 67 MB of fp32 caches (D = 64, two query heads) take 167 us (203), four steps of two layers of 32 caches of 4096
 // rows, D = 128, eight heads, 377 (499), bf16, D = 64, eight heads, 154 (199).
 template <int D, int GT, int THREADS>
-__global__ __launch_bounds__(THREADS) void finish_kernel(DecodeParams p, int n_combine, int tiles) {
+__global__ __launch_bounds__(THREADS) void finish_kernel(DecodeParams p, int n_combine, int tiles, int n_items) {
   constexpr int R = kFinishRowsPerThread, kRows = R * THREADS;
-  if ((int)blockIdx.x < n_combine) {
+  if ((int)blockIdx.x < n_combine && blockIdx.y == 0) {
     combine_head<D, THREADS>(p, (uint32_t)blockIdx.x / (uint32_t)p.G, (uint32_t)blockIdx.x % (uint32_t)p.G);
     return;
   }
-  const uint32_t b = blockIdx.x - n_combine;
-  const Item it = p.items[b / (uint32_t)tiles];
+  uint32_t item = blockIdx.x, tile = blockIdx.y - 1;
+  if (n_items == 0) {
+    item = (blockIdx.x - n_combine) / (uint32_t)tiles;
+    tile = (blockIdx.x - n_combine) % (uint32_t)tiles;
+  } else if (blockIdx.y == 0 || (int)item >= n_items) {
+    return;
+  }
+  const Item it = p.items[item];
   const int G = p.G;
   const int n = p.lag_n[(int64_t)it.c * kLagCalls];  // (len may already count this call's new row, or not yet)
   const int cnt = min(it.start + it.count, n) - it.start;
-  const int r_begin = b % (uint32_t)tiles * kRows;
+  const int r_begin = tile * kRows;
   if (r_begin >= cnt) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float x[R][GT], old[R];
@@ -626,13 +633,15 @@ hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_ite
 
 // Caches of more work items than this are merged by 1024 threads per head instead of 256.  us per call, 256 / 1024: a
 // layer of 8 caches of up to 8192 rows (about 80 work items) 10.2 / 9.9, of 131072 rows 54.8 / 48.4; 32 caches (20) 18.5 /
-// 18.0; at 16 and fewer equal.
+// 18.0; at 16 and fewer equal.  (n_x: workgroups that the grid's first dimension has to hold.)
 constexpr int kManySplits = 16;
+constexpr int64_t kMostThreads = (int64_t)1 << 32;  // a grid dimension holds fewer; one of more runs in part, without an error
+bool merge_by_1024(int most_split, int64_t n_x) { return most_split > kManySplits && n_x < kMostThreads / 1024; }
 
 hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, int most_split, hipStream_t s) {
   if (n_multi <= 0) return hipSuccess;
   const dim3 grid(n_multi, p.G);
-  if (most_split > kManySplits) {
+  if (merge_by_1024(most_split, n_multi)) {
     if (D == 128) combine_kernel<128, 1024><<<grid, dim3(1024), 0, s>>>(p);
     else if (D == 64) combine_kernel<64, 1024><<<grid, dim3(1024), 0, s>>>(p);
     else return hipErrorInvalidValue;
@@ -646,13 +655,19 @@ hipError_t launch_combine(const DecodeParams& p, int D, int n_multi, int most_sp
 
 template <int D, int THREADS>
 hipError_t launch_finish_d(const DecodeParams& p, int n_multi, int n_items, int max_count, hipStream_t s) {
+  // One grid dimension while it holds all workgroups; work items times the tiles of the longest one may be 2^32 threads
+  // and more (65536 caches, one of 131072 rows), and then take two.  (Two always: a layer of 8 caches of 32768 rows in
+  // all, bf16, D = 64, four heads, 10.5 / 11.2 us per call, for the workgroups that have nothing to do.)
   constexpr int kRows = kFinishRowsPerThread * THREADS;
   const int tiles = (max_count + kRows - 1) / kRows, n_combine = n_multi * p.G;
-  const dim3 grid(n_combine + n_items * tiles), block(THREADS);
-  if (p.G <= 1) finish_kernel<D, 1, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles);
-  else if (p.G <= 2) finish_kernel<D, 2, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles);
-  else if (p.G <= 4) finish_kernel<D, 4, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles);
-  else if (p.G <= 8) finish_kernel<D, 8, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles);
+  const int64_t all = n_combine + (int64_t)n_items * tiles;
+  const bool flat = all < kMostThreads / THREADS;
+  const dim3 grid(flat ? (unsigned)all : (unsigned)std::max(n_combine, n_items), flat ? 1 : 1 + tiles), block(THREADS);
+  const int n = flat ? 0 : n_items;
+  if (p.G <= 1) finish_kernel<D, 1, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles, n);
+  else if (p.G <= 2) finish_kernel<D, 2, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles, n);
+  else if (p.G <= 4) finish_kernel<D, 4, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles, n);
+  else if (p.G <= 8) finish_kernel<D, 8, THREADS><<<grid, block, 0, s>>>(p, n_combine, tiles, n);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -660,7 +675,7 @@ hipError_t launch_finish_d(const DecodeParams& p, int n_multi, int n_items, int 
 hipError_t launch_finish(const DecodeParams& p, int D, int n_multi, int most_split, int n_items, int max_count,
                          hipStream_t s) {
   if (n_items <= 0 || max_count <= 0) return hipSuccess;
-  const bool wide = most_split > kManySplits;
+  const bool wide = merge_by_1024(most_split, std::max<int64_t>((int64_t)n_multi * p.G, n_items));
   if (D == 128) return wide ? launch_finish_d<128, 1024>(p, n_multi, n_items, max_count, s)
                             : launch_finish_d<128, 256>(p, n_multi, n_items, max_count, s);
   if (D == 64) return wide ? launch_finish_d<64, 1024>(p, n_multi, n_items, max_count, s)

@@ -579,3 +579,45 @@ def test_work_items_of_whole_model_launches(batch):
     # three bf16 terms of a weight are exact: fp32 logits, weights and sums of up to 1300 rows
     H.check_decode_against_oracle(arena, w, st, q64, H.gpu_decode(arena, w, q), tol=64 * 2.0 ** -24 * 4)
     arena.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tracked_launch_over_many_caches_beside_a_long_one(dtype):
+    """65536 caches, one of 131072 rows: work items times the tiles of the longest one are more threads than a grid
+    dimension holds.  A tracked call and a fused one over all of them: outputs, scores, lengths on both sides."""
+    n, long_rows = 65536, 131072
+    arena = B.Arena(1, n, n, 64, 1, dtype, [1] * (n - 1) + [long_rows], 1, 0, 0, B.POLICY_SCORE, True)
+    gen = torch.Generator(device=arena.device)
+    gen.manual_seed(41)
+    for t in (arena.k, arena.v):
+        t.normal_(generator=gen)
+    lens = np.asarray(arena.cap_host) - 1
+    arena.set_lengths(lens)
+    q, kn, vn = (torch.randn((1, 1, n, 64), generator=gen, device=arena.device).to(arena.k.dtype) for _ in range(3))
+    out = torch.full((1, 1, n, 64), float("nan"), dtype=torch.float32, device=arena.device)
+    off = torch.from_numpy(arena.off_host[:-1]).to(arena.device)
+    o = int(arena.off_host[-1])
+
+    def long_cache(m):
+        p = torch.softmax(arena.k[o:o + m].double() @ q[0, 0, -1].double() / 8.0, 0)
+        return p @ arena.v[o:o + m].double(), p
+
+    arena.decode_attn(0, 1, q, out)
+    ref, p = long_cache(long_rows)
+    assert torch.equal(out[0, 0, :-1], arena.v[off].float())                     # one row: all of its weight
+    assert torch.equal(arena.score[off], torch.ones(n - 1, device=arena.device))
+    # fp32 sums of 131072 weights and logits of up to about 10: well inside 2^-16
+    assert (out[0, 0, -1].double() - ref).abs().max() <= 2.0 ** -16
+    assert (arena.score[o:o + long_rows].double() - p).abs().max() <= 2.0 ** -16
+    arena.append_decode_attn(0, 1, kn, vn, 7, q, out)
+    assert arena.lengths().tolist() == arena.len.cpu().tolist() == (lens + 1).tolist()
+    ref, p2 = long_cache(long_rows + 1)
+    assert (out[0, 0, -1].double() - ref).abs().max() <= 2.0 ** -16
+    p2[:long_rows] += p
+    assert (arena.score[o:o + long_rows + 1].double() - p2).abs().max() <= 2.0 ** -15
+    two = torch.softmax((torch.stack([arena.k[off], arena.k[off + 1]]).double() * q[0, 0, :-1].double()).sum(2) / 8.0, 0)
+    want = two[0, :, None] * arena.v[off].double() + two[1, :, None] * arena.v[off + 1].double()
+    assert (out[0, 0, :-1].double() - want).abs().max() <= 2.0 ** -16
+    assert (arena.score[off].double() - 1 - two[0]).abs().max() <= 2.0 ** -16
+    assert (arena.score[off + 1].double() - two[1]).abs().max() <= 2.0 ** -16
+    arena.close()
