@@ -2,6 +2,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <numeric>
 #include <vector>
@@ -39,8 +40,9 @@ int64_t count_items(const int32_t* cap, int64_t n_caches, int chunk) {
 }
 
 struct WorkspacePlan {
-  // index 0: schedule for launches over a layer sub-range, 1: for launches over the whole model
-  size_t items[2], multi[2];
+  // index 0: schedule for launches over a layer sub-range, 1: for launches over the whole model, 2: for launches over
+  // several layers where that of a single one would cut needlessly short runs (see schedule_for)
+  size_t items[3], multi[3];
   size_t part_o, part_ml, final_ml, logits, lag_q, lag_ml, lag_n, lag_cnt, status, kept, info, order_all, order_layer;
   size_t segs, seg_split, halo_k, halo_v, halo_score, halo_pos, tiles, spread, tile_hist, sel_state, total;
   int64_t n_segs, halo_rows, n_tiles, n_long;
@@ -119,9 +121,9 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
     w.max_items += std::max(count_items(cap + l * cpl, cpl, kSizingChunk),
                             std::min<int64_t>(count_items(cap + l * cpl, cpl, kShortestRun), kMostFillItems));
   size_t o = 0;
-  for (int k = 0; k < 2; ++k) {
-    w.items[k] = o;   o = align256(o + (size_t)w.max_items * sizeof(Item));
-    w.multi[k] = o;   o = align256(o + (size_t)n_caches * sizeof(MultiCache));
+  for (int k = 0; k < 3; ++k) {  // (the third only where a launch can hold several layers, but not all)
+    w.multi[k] = o;   o = align256(o + (k < 2 || d->L > 2 ? (size_t)n_caches * sizeof(MultiCache) : 0));
+    w.items[k] = o;   o = align256(o + (k < 2 || d->L > 2 ? (size_t)w.max_items * sizeof(Item) : 0));
   }
   w.part_o = o;       o = align256(o + (size_t)w.max_items * G * d->D * 4);
   w.part_ml = o;      o = align256(o + (size_t)w.max_items * G * 2 * 4);
@@ -190,7 +192,7 @@ struct baklava_ctx {
     std::vector<int32_t> max_split;    // layer -> most work items of a cache
     std::vector<int32_t> cib;          // cache -> first item
     std::vector<int32_t> multi_begin;  // layer -> first entry of the list of multi-item caches
-  } sched[2];                          // 0: layer sub-range launches, 1: whole-model launches
+  } sched[3];                          // 0: layer sub-range launches, 1: whole-model launches, 2: see schedule_for
   WorkspacePlan plan;
   char* ws;
   int32_t time_kernel;         // 0 off, 1 events recorded around the attention kernel, 2 events carried by its dispatch
@@ -216,8 +218,8 @@ int whole_items_per_cu(int64_t n_caches, int64_t rows, int64_t cus) {
   return kWholeItemsPerCu;
 }
 
-// Builds one of the two split-K schedules with the host planner and uploads it.  Schedule 0
-// serves launches over a layer sub-range (launch order inside each layer, so a layer range is a
+// Builds one of the split-K schedules with the host planner and uploads it.  Schedules 0 and 2
+// serve launches over a layer sub-range (launch order inside each layer, so a layer range is a
 // contiguous slice), schedule 1 launches over the whole model.  The table depends on capacities
 // only, so it is uploaded once; the kernels clamp each run to the live length.
 //
@@ -233,16 +235,23 @@ int whole_items_per_cu(int64_t n_caches, int64_t rows, int64_t cus) {
 // 11.1, 384 rows 8.8, cut 8.2; eight heads 264 rows 12.8, cut 11.1).
 int build_schedule(baklava_ctx* ctx, int which, int chunk, bool fill) {
   int64_t n_items = 0;
-  std::vector<baklava_work_item> items((size_t)ctx->plan.max_items);
+  // The list of multi-item caches and the work items lie next to each other in the workspace, so they are formed that
+  // way here and travel in one copy (each takes about 20 us).
+  const size_t front = ctx->plan.items[which] - ctx->plan.multi[which];
+  std::unique_ptr<char[]> both(new (std::nothrow) char[front + (size_t)ctx->plan.max_items * sizeof(Item)]);
+  if (!both) return BAKLAVA_ENOMEM;
+  MultiCache* const multi = reinterpret_cast<MultiCache*>(both.get());
+  baklava_work_item* const items = reinterpret_cast<baklava_work_item*>(both.get() + front);
   const int st = plan_schedule(ctx->off.data(), ctx->cap.data(), ctx->d.L, ctx->cpl, chunk,
-                               which == 0 ? ctx->target_items : ctx->target_items_whole, kShortestRun,
-                               fill ? std::min(ctx->n_cus, kMostFillItems) : 0, which, ctx->plan.max_items,
-                               items.data(), &n_items);
+                               which == 1 ? ctx->target_items_whole : ctx->target_items, kShortestRun,
+                               fill ? std::min(ctx->n_cus, kMostFillItems) : 0, which == 1, ctx->plan.max_items,
+                               items, &n_items);
   if (st != BAKLAVA_OK) return st;
+  if (which == 2 && n_items == ctx->sched[0].cib.back()) return BAKLAVA_OK;  // the same work items: schedule 0 serves
   static_assert(sizeof(baklava_work_item) == sizeof(Item), "work item layouts must match");
   // cache -> first partial slot, and the caches that need the combine kernel (in launch order)
   std::vector<int32_t> cib(ctx->n_caches + 1, 0), multi_begin(ctx->d.L + 1, 0);
-  std::vector<MultiCache> multi;
+  size_t n_multi = 0;
   std::vector<int32_t> max_count(ctx->d.L, 0), max_split(ctx->d.L, 0);
   int32_t slot0 = 0;  // the items of a cache follow each other
   for (int64_t i = 0; i < n_items; ++i) {
@@ -254,7 +263,7 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk, bool fill) {
     if (it.start == 0) {
       cib[it.cache] = it.slot;
       if (it.nsplit > 1) {
-        multi.push_back(MultiCache{it.cache, it.slot, it.slot + it.nsplit, 0});
+        multi[n_multi++] = MultiCache{it.cache, it.slot, it.slot + it.nsplit, 0};
         multi_begin[it.cache / ctx->cpl + 1] += 1;
       }
     }
@@ -262,10 +271,10 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk, bool fill) {
   cib[ctx->n_caches] = (int32_t)n_items;
   for (int32_t l = 0; l < ctx->d.L; ++l) multi_begin[l + 1] += multi_begin[l];
   if (!hip_ok(hipDeviceSynchronize())) return BAKLAVA_EHIP;  // no launch may still read the old table
-  if (!hip_ok(hipMemcpy(ctx->ws + ctx->plan.items[which], items.data(), (size_t)n_items * sizeof(Item),
-                        hipMemcpyHostToDevice)) ||
-      (!multi.empty() &&
-       !hip_ok(hipMemcpy(ctx->ws + ctx->plan.multi[which], multi.data(), multi.size() * sizeof(MultiCache), hipMemcpyHostToDevice))))
+  const size_t skip = n_multi ? 0 : front;
+  std::memset(multi + n_multi, 0, n_multi ? front - n_multi * sizeof(MultiCache) : 0);
+  if (!hip_ok(hipMemcpy(ctx->ws + ctx->plan.multi[which] + skip, both.get() + skip, front - skip + (size_t)n_items * sizeof(Item),
+                        hipMemcpyHostToDevice)))
     return BAKLAVA_EHIP;
   ctx->sched[which].cib.swap(cib);
   ctx->sched[which].multi_begin.swap(multi_begin);
@@ -274,6 +283,27 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk, bool fill) {
   ctx->sched[which].max_count.swap(max_count);
   ctx->sched[which].max_split.swap(max_split);
   return BAKLAVA_OK;
+}
+
+// fp32 rows for four query heads and more: the vector kernel is bound by its arithmetic, so short runs pay earlier.
+bool slow_rows(const baklava_ctx* ctx) { return ctx->d.dtype == BAKLAVA_F32 && ctx->G >= 4; }
+
+// Which schedule a launch over the layers takes.  The short runs of schedule 0 give a single layer a work item for every
+// compute unit; over several layers that is more work items than the launch needs, each with its share of the merge.
+// Beyond two for each compute unit (four where rows are slow) a launch takes the runs that the layers would have
+// without the fill.  us per call over 2, 3, 4, 5, 7 layers of 8 caches, short runs / without, four query heads:
+//   bf16, D = 128    8192 rows a layer   8.7 / 10.9    9.2 / 11.4   10.7 / 11.5   11.9 / 11.7   13.8 / 12.1
+//                   32768               12.8 / 12.8   14.5 / 13.5   18.3 / 17.7   19.5 / 19.9   25.4 / 22.2
+//                   65536               17.0 / 19.0   21.9 / 21.5   27.3 / 27.8   29.8 / 31.8   41.8 / 41.4
+//   D = 64, tracked 16384               12.5 / 12.1   15.1 / 13.5   17.5 / 13.6   20.6 / 16.4   25.8 / 16.9
+//   fp32, D = 128    8192               12.2 / 21.3   12.9 / 21.6   14.6 / 21.7   15.2 / 21.9   18.6 / 22.3
+//                   32768               19.7 / 22.0   24.1 / 23.1   31.7 / 30.8   33.8 / 35.5   46.1 / 41.8
+int schedule_for(const baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count) {
+  if (layer_begin == 0 && layer_count == ctx->d.L) return 1;
+  const baklava_ctx::Schedule& sc = ctx->sched[0];
+  if (layer_count == 1 || !sc.fill || ctx->sched[2].cib.empty()) return 0;
+  const int32_t c0 = layer_begin * ctx->cpl, c1 = c0 + layer_count * ctx->cpl;
+  return sc.cib[c1] - sc.cib[c0] > (slow_rows(ctx) ? 4 : 2) * ctx->n_cus ? 2 : 0;
 }
 
 // Tile tables of the eviction's selection (they depend on capacities and the threshold only), in cache order, so that
@@ -340,7 +370,7 @@ int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hi
   if (!ctx->d.track_scores || !keeps_records(&ctx->d)) return BAKLAVA_OK;
   const int64_t c0 = (int64_t)layer_begin * ctx->cpl;
   const int64_t c1 = c0 + (int64_t)layer_count * ctx->cpl;
-  const int which = (layer_begin == 0 && layer_count == ctx->d.L) ? 1 : 0;
+  const int which = schedule_for(ctx, layer_begin, layer_count);
   const baklava_ctx::Schedule& sc = ctx->sched[which];
   const int32_t i0 = sc.cib[c0], i1 = sc.cib[c1];
   DecodeParams p{};
@@ -389,8 +419,7 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
       if (!fused && ctx->len[c] <= 0) return BAKLAVA_ESTATE;
     }
   }
-  const bool whole = layer_begin == 0 && layer_count == ctx->d.L;
-  const int which = whole ? 1 : 0;
+  const int which = schedule_for(ctx, layer_begin, layer_count);
   const baklava_ctx::Schedule& sc = ctx->sched[which];
   const int32_t i0 = sc.cib[c0], i1 = sc.cib[c1];
   hipStream_t s = (hipStream_t)stream;
@@ -623,9 +652,11 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     if (st != BAKLAVA_OK) { delete ctx; return st; }
   }
   if (desc->dtype == BAKLAVA_BF16 && !hip_ok(prepare_decode_mfma())) { delete ctx; return BAKLAVA_EHIP; }
-  const bool slow_rows = desc->dtype == BAKLAVA_F32 && ctx->G >= 4;  // (see build_schedule)
-  int st = build_schedule(ctx, 0, ctx->layer_one_wave && !slow_rows ? kDefaultChunk : kDefaultChunkWhole, true);
+  const int chunk = ctx->layer_one_wave ? kDefaultChunk : kDefaultChunkWhole;
+  const int chunk_layer = slow_rows(ctx) ? kDefaultChunkWhole : chunk;  // (see build_schedule)
+  int st = build_schedule(ctx, 0, chunk_layer, true);
   if (st == BAKLAVA_OK) st = build_schedule(ctx, 1, kDefaultChunkWhole, true);
+  if (st == BAKLAVA_OK && desc->L > 2) st = build_schedule(ctx, 2, chunk, false);
   if (st != BAKLAVA_OK) { delete ctx; return st; }
   *out = ctx;
   return BAKLAVA_OK;

@@ -621,3 +621,44 @@ def test_tracked_launch_over_many_caches_beside_a_long_one(dtype):
     assert (arena.score[off].double() - 1 - two[0]).abs().max() <= 2.0 ** -16
     assert (arena.score[off + 1].double() - two[1]).abs().max() <= 2.0 ** -16
     arena.close()
+
+
+@pytest.mark.parametrize("dtype,D,G,track", [("bf16", 128, 4, False), ("bf16", 128, 4, True), ("bf16", 64, 2, True), ("f32", 64, 2, True), ("f32", 128, 4, False)])
+def test_launches_over_several_layers(dtype, D, G, track):
+    """Launches over some of the layers: short runs fill the chip for one layer or two, over more layers the launch
+    takes the longer ones it would take if they had been asked for (bit for bit), against the oracle, with steps that
+    append and a flush of the range in between."""
+    H = _h()
+    L, rows = 9, [1500, 700, 2600, 513, 3100, 64, 4000, 1999]
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="several", L=L, Hq=8 * G, Hkv=8, D=D, batch=1, dtype=dtype, seed=131,
+                     sink=1, recent=1, slack=4)
+    budgets = [rows[(h + l) % 8] for l in range(L) for h in range(8)]
+    arenas = [H.make_arena(w, budgets, track=track) for _ in range(2)]
+    arenas[1].set_option(B.OPT_CHUNK_TOKENS, 512)                 # the default's shortest run, asked for
+    states = [H.fill_from_host(a, w, budgets, np.random.Generator(np.random.PCG64(132)), scores="zero") for a in arenas]
+    rng = np.random.Generator(np.random.PCG64(133))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for lb, lc in ((0, 8), (1, 8), (1, 2), (3, 1)):
+        q, q64 = H.make_q(w, rng, lc)
+        outs = [H.gpu_decode(a, w, q, layer_begin=lb, layer_count=lc) for a in arenas]
+        H.check_decode_against_oracle(arenas[0], w, states[0], q64, outs[0], caches=range(8 * lb, 8 * (lb + lc)), layer_begin=lb,
+                                      tol=5 * 2.0 ** -17)  # two bf16 terms of a weight leave 2^-17 of it, elements of V are below 5
+        if lc == 8 and cus == 256:
+            assert np.array_equal(outs[0], outs[1])
+        for a in arenas:
+            a.flush_scores(lb, lc)
+    kn, vn = (H.to_device_storage(synth.payload(rng, (8, 1, 8, D), dtype), dtype, arenas[0].device) for _ in range(2))
+    q = H.to_device_storage(H.make_q(w, rng, 8)[0], dtype, arenas[0].device)
+    out = [torch.empty((8, 1, 8 * G, D), dtype=torch.float32, device=q.device) for _ in range(2)]
+    for t in range(3):
+        for a, o in zip(arenas, out):
+            a.append_decode_attn(1, 8, kn, vn, 9000 + t, q, o)
+        if cus == 256:
+            assert torch.equal(out[0], out[1])
+    got, want = (H.download(a, w) for a in arenas)
+    for c in range(arenas[0].n_caches):
+        # at most 7 calls of G weights, each from an fp32 logit of up to 16 in log2 units
+        assert np.max(np.abs(got.score[c] - want.score[c])) <= 2e-6 * 7 * G
+        assert np.array_equal(got.K[c], want.K[c]) and np.array_equal(got.pos[c], want.pos[c])
+    for a in arenas:
+        a.close()
