@@ -208,7 +208,7 @@ enum {
                                    otherwise five times that number, with a shortest run of 256 rows.
                                    The default schedules also cut runs of fewer rows where a launch of
                                    split caches would have fewer work items than compute units; setting
-                                   another run length or item target ends that                       */
+                                   a run length or an item target, also to the default, ends that    */
   BAKLAVA_OPT_TARGET_ITEMS_WHOLE = 6, /* the same for launches over all layers at once.  Default: two to
                                    five times the device's number of compute units, by the number of
                                    caches and rows                                                  */

@@ -684,7 +684,7 @@ extern "C" int baklava_set_option(baklava_ctx* ctx, int32_t option, int64_t valu
       if (value < 0 || value > (1 << 20)) return BAKLAVA_EINVAL;
       const int which = option == BAKLAVA_OPT_TARGET_ITEMS ? 0 : 1;
       int32_t& target = which == 0 ? ctx->target_items : ctx->target_items_whole;
-      if ((int32_t)value == target) return BAKLAVA_OK;
+      if ((int32_t)value == target && !ctx->sched[which].fill) return BAKLAVA_OK;
       target = (int32_t)value;
       return build_schedule(ctx, which, ctx->sched[which].chunk, false);
     }

@@ -662,3 +662,26 @@ def test_launches_over_several_layers(dtype, D, G, track):
         assert np.array_equal(got.K[c], want.K[c]) and np.array_equal(got.pos[c], want.pos[c])
     for a in arenas:
         a.close()
+
+
+@pytest.mark.parametrize("whole", [False, True])
+def test_item_target_set_to_its_default_is_followed(whole):
+    """An item target that equals the default ends the default's short runs like any other: the same work items (and
+    bits) as after a detour over another target."""
+    H = _h()
+    L = 1 if whole else 2
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="target", L=L, Hq=8, Hkv=2, batch=1, seed=141, sink=1, recent=1, slack=0)
+    budgets = [900, 2100, 700, 3000][:2 * L]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    option, default = (B.OPT_TARGET_ITEMS_WHOLE, 2 * cus) if whole else (B.OPT_TARGET_ITEMS, cus)
+    q = H.make_q(w, np.random.Generator(np.random.PCG64(142)), 1)[0]
+    outs = []
+    for targets in ([], [default], [default + 1, default]):
+        arena = H.make_arena(w, budgets)
+        H.fill_from_host(arena, w, budgets, np.random.Generator(np.random.PCG64(143)))
+        for t in targets:
+            arena.set_option(option, t)
+        outs.append(H.gpu_decode(arena, w, q, layer_begin=0, layer_count=1))
+        arena.close()
+    assert np.array_equal(outs[1], outs[2])
+    assert not np.array_equal(outs[0], outs[1])      # (short runs, so other sums)
