@@ -293,9 +293,9 @@ __device__ __forceinline__ int held_find_digit(HeldShared<KEYS>& sm, int& need) 
   return held_find_digit(c_hi, c_lo, need, sm.scan, &sm.digit, &sm.need);
 }
 
-// Scores of m rows, row i * 1024 + t as key i of thread t.  Places past the m rows hold key 0: no score but a NaN
-// maps there, it ranks last, and they come behind every row, so neither the threshold nor a survivor's place depends
-// on these.
+// Scores of m rows, row i * 1024 + t as key i of thread t.  Places past the m rows hold key 0, the lowest: no score
+// but a NaN of all ones maps there.  Behind every row of the cache neither the threshold nor a survivor's place depends
+// on them.
 template <int KEYS>
 __device__ __forceinline__ void held_load(const float* score, int m, uint32_t (&key)[KEYS]) {
 #pragma unroll
@@ -633,8 +633,14 @@ __global__ __launch_bounds__(kHeldThreads) void compact_spread_emit_kernel(Compa
   if (lane == 63 && sure != 0) atomicAdd(&sure_before, sure);
   if (lane == 63 && eq != 0) atomicAdd(&eq_before, eq);
   held_map(m, key);
+  uint32_t thr = (uint32_t)d1 << 21 | low;
+  if (thr == 0) {  // rows at the lowest key survive: the places past this tile's rows, in front of the next tile's, do not
+#pragma unroll
+    for (int i = 0; i < kTileKeys; ++i) key[i] = i * kHeldThreads + tid >= m ? 0u : key[i] == 0 ? 1u : 2u;
+    thr = 1;
+  }
   __syncthreads();
-  held_emit(sm, key, m, (uint32_t)d1 << 21 | low, need, sure_before, eq_before, lo, kept + g.mid_lo);
+  held_emit(sm, key, m, thr, need, sure_before, eq_before, lo, kept + g.mid_lo);
   if (tid == 0 && sm.first < m) atomicMin(&p.info[tl.c].first_moved, lo + sm.first);
 }
 

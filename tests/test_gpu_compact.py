@@ -311,6 +311,34 @@ def test_few_caches_ranked_by_several_workgroups(scores, policy):
     arena.close()
 
 
+@pytest.mark.parametrize("share", [0.3, 0.7, 1.0])
+def test_lowest_key_among_several_workgroups(share):
+    """Scores whose bits are all ones have the lowest key there is, which places without a row hold too.  Rows with it
+    that survive are the oldest ones, like rows of -inf if nothing else is below them, also where a cache is ranked by
+    several workgroups and its first rows, the sinks, leave the first one fewer than 8192."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="lowest", L=1, Hq=3, Hkv=3, batch=1, seed=29, sink=37, recent=5, slack=4000)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    lens = [20481, 33000, 60000]
+    arena = H.make_arena(w, [n - 4000 for n in lens])
+    st = H.fill_from_host(arena, w, lens, rng, scores="uniform")
+    kept_dev = torch.full((arena.total_tokens,), -1, dtype=torch.int32, device=arena.device)
+    for c, n in enumerate(lens):
+        ones = rng.random(n) < share
+        o = int(arena.off_host[c])
+        bits = np.where(ones, np.uint32(0xffffffff), st.score[c].view(np.uint32))
+        arena.score[o:o + n].copy_(torch.from_numpy(bits.view(np.float32)).to(arena.device))
+        st.score[c] = np.where(ones, np.float32(-np.inf), st.score[c])
+    arena.compact(0, 1, kept_dev)
+    after = H.download(arena, w)
+    for c, n in enumerate(lens):
+        kept = np.asarray(O.compact_select(st.score[c], n, n - 4000, w.sink, w.recent), dtype=np.int32)
+        o = int(arena.off_host[c])
+        assert np.array_equal(kept_dev[o:o + len(kept)].cpu().numpy(), kept), f"cache {c}"
+        assert np.array_equal(after.K[c], st.K[c][kept]) and np.array_equal(after.pos[c], st.pos[c][kept])
+    arena.close()
+
+
 @pytest.mark.parametrize("seed", list(range(500, 512)))
 def test_seeded_random_evictions(seed):
     """Random cache sizes on both sides of the threshold for tile-by-tile selection, random budgets, sink
