@@ -160,11 +160,14 @@ typedef struct {
 } baklava_desc;
 
 /*
- * Bytes of device workspace a context with this description needs (split partials, work-item
- * tables, kept-index lists, halo rows of the eviction move, the counters of the tile-by-tile
- * selection, and with track_scores the query rows and softmax normalisers of the attention calls
- * each cache has on record).  Pointer fields of `desc` are ignored.  cap_host HOST [n_caches],
- * budget_host HOST [L*Hkv].  Returns 0 on invalid arguments.
+ * Bytes of device workspace a context with this description needs: split partials (G * (D + 2)
+ * floats for each work item of 256 rows, or of 64 up to 256 items a layer), work-item tables,
+ * kept-index lists, halo rows of the eviction move, the tables and counters of the selection of
+ * caches of more than 8192 rows, and with track_scores the query rows and softmax normalisers of
+ * the attention calls each cache has on record (bf16 rows of 128 elements) or the logits of one
+ * call (F32 and rows of 64 elements: 4 * G bytes per cached row, which at bf16, D = 64 and eight
+ * query heads is an eighth of K and V).  Pointer fields of `desc` are ignored.  cap_host HOST
+ * [n_caches], budget_host HOST [L*Hkv].  Returns 0 on invalid arguments.
  */
 size_t baklava_workspace_bytes(const baklava_desc* desc, const int32_t* cap_host,
                                const int32_t* budget_host);

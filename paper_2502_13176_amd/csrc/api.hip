@@ -29,7 +29,7 @@ constexpr int kDefaultChunk = 512;        // launches over part of the model: sh
 constexpr int kDefaultChunkWhole = 256;   // launches over the whole model: shortest run; longer ones come from the item target
 constexpr int kWholeItemsPerCu = 5;       // launches over many caches aim at this many work items per compute unit
 constexpr int kShortestRun = 64;          // where those would leave compute units idle (see build_schedule)
-constexpr int kMostFillItems = 512;       // most work items such short runs are cut for (sizes the workspace)
+constexpr int kMostFillItems = 256;       // most work items such short runs are cut for: one per compute unit (sizes the workspace)
 constexpr int kMaxChunk = 1 << 22; // row offsets inside a work item stay below 2^32 bytes
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 

@@ -142,6 +142,20 @@ def test_workspace_bytes_is_a_pure_host_query():
     assert B.lib().baklava_workspace_bytes(C.byref(d), cap.ctypes.data_as(i32p), bud.ctypes.data_as(i32p)) == 0
 
 
+@pytest.mark.parametrize("rows,items", [(8192, 256), (2048, 256), (500, 64), (64, 8), (20000, 632)])
+def test_workspace_holds_partials_for_the_work_items_there_can_be(rows, items):
+    """Eight caches of one layer: split partials for runs of 256 rows, or of 64 while those are at most one work item
+    for each of 256 compute units.  A second query head adds D + 2 floats for each of them and nothing else here."""
+    size = {}
+    for G in (1, 2):
+        d = B.Desc()
+        d.L, d.Hq, d.Hkv, d.D, d.batch, d.dtype = 1, 8 * G, 8, 128, 1, B.F32
+        cap = np.full(8, rows, dtype=np.int32)
+        i32p = C.POINTER(C.c_int32)
+        size[G] = B.lib().baklava_workspace_bytes(C.byref(d), cap.ctypes.data_as(i32p), cap.ctypes.data_as(i32p))
+    assert size[2] - size[1] == items * 128 * 4 + (items * 16 + 255) // 256 * 256 - (items * 8 + 255) // 256 * 256
+
+
 @pytest.mark.parametrize("name,chunk", [("llama32", 512), ("llama32", 2048), ("qwen", 768), ("long", 4096), ("tiny", 256)])
 @pytest.mark.parametrize("whole", [False, True])
 @pytest.mark.parametrize("target", [0, 768])
