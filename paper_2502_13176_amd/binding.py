@@ -191,12 +191,16 @@ def plan_schedule(off, cap, L: int, caches_per_layer: int, chunk: int, whole_mod
 
 def _stream_ptr(stream=None) -> int:
     """The handle of `stream`, or of torch's current one.  Building a Stream object to ask it for its handle takes 2.9
-    us, nearly half of a small attention call (6.8 us on the host, 4.1 without); torch also gives the bare handle."""
+    us, nearly half of a small attention call (6.8 us on the host, 4.1 without); torch also gives the bare handle, though
+    under names that it does not promise to keep."""
     import torch
     if stream is not None:
         return int(stream.cuda_stream)
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
     return int(torch.cuda.current_stream().cuda_stream)
 
 

@@ -320,3 +320,17 @@ def test_inline_assembly_declares_the_m0_it_writes():
                 found += 1
                 assert re.search(r':[^:]*"m0"', stmt), (name, stmt)
     assert found > 0
+
+
+def test_current_stream_with_and_without_the_bare_handle(monkeypatch):
+    """The current stream's handle is asked of torch's private functions where it has them, else of a Stream object."""
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 1000 + device, raising=False)
+    assert B._stream_ptr() == 1003
+    assert B._stream_ptr(types.SimpleNamespace(cuda_stream=5)) == 5
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert B._stream_ptr() == 77
