@@ -343,20 +343,26 @@ int build_tiles(baklava_ctx* ctx) {
 }
 
 // Whether several workgroups rank each of the range's caches of more than kNarrowRows rows.  Every one of them reads the
-// scores of its cache, so this pays while they leave compute units idle.  us per eviction, one workgroup per cache /
-// spread (workgroups): caches of 20000 rows 64 102 / 91 (192), 128 160 / 161 (384), 256 302 / 317 (768); of 32768 rows
-// 64 140 / 127 (256), 128 225 / 228 (512); of 50000 rows 32 150 / 135 (224), 64 222 / 227 (448).
-// Beside caches that need one workgroup only the line lies further out: 104 caches of 16385 to 32832 rows (416) and 408
-// shorter ones, rankings of 53 us in two launches / 45.
+// scores of its cache, so this pays while they find compute units that would idle: far up to one for each, little from
+// there to three for two, beyond which it loses to caches of just over two tiles or without shorter ones beside them
+// (which one workgroup ranks, and which otherwise wait for a launch of their own).  us of ranking, one workgroup per
+// cache / spread (workgroups of the caches of more than kNarrowRows rows):
+//   alone                   16500 rows  29.6 / 30.8 (258)  29.6 / 32.8 (384)  29.7 / 32.6 (510)
+//                           32768       33.8 / 22.6 (256)  34.0 / 34.6 (384)  35.1 / 37.6 (512)
+//                           65536       43.3 / 28.4 (256)  43.6 / 43.8 (384)  44.2 / 46.3 (512)
+//   beside 64 shorter ones  16500       43.1 / 37.8 (258)  43.9 / 39.9 (384)  43.8 / 42.1 (510)
+//                           32768       48.0 / 31.1 (256)  48.5 / 42.1 (384)  49.2 / 47.5 (512)
+//   beside 500              16500       49.6 / 45.8 (258)  50.2 / 52.4 (384)  50.5 / 54.7 (510)
+//                           32768       54.2 / 40.2 (256)  55.0 / 52.1 (384)  54.3 / 65.6 (560)
+//                           65536       64.2 / 44.8 (256)  64.2 / 61.1 (384)  64.9 / 64.8 (512)
+// Whole evictions: 88 caches of 32768 rows (352) 347 / 346, 44 of 65536 (352) 355 / 353, 96 of 16500 (288) 234 / 234.
 bool spread_selection(const baklava_ctx* ctx, int64_t c0, int64_t c1) {
   int64_t tiles = 0;
-  bool all_wide = true;
   for (int64_t c = c0; c < c1; ++c) {
     const int32_t nt = ctx->spread_begin[c + 1] - ctx->spread_begin[c];
     tiles += nt > 1 ? nt : 0;
-    all_wide = all_wide && nt != 1;
   }
-  return tiles > 0 && 2 * tiles <= (all_wide ? 3 : 4) * (int64_t)ctx->n_cus;
+  return tiles > 0 && 2 * tiles <= 3 * (int64_t)ctx->n_cus;
 }
 
 bool range_ok(const baklava_ctx* ctx, int32_t lb, int32_t lc) {
