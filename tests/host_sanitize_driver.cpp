@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "baklava.h"
+#include "plan.h"
 
 static int fails = 0;
 #define CHECK(cond) do { if (!(cond)) { std::printf("FAILED: %s (line %d)\n", #cond, __LINE__); ++fails; } } while (0)
@@ -116,6 +117,57 @@ int main() {
     if (n_items > 1) {
       CHECK(baklava_plan_schedule(off.data(), cap.data(), L, cpl, chunk, target, whole, n_items - 1, items.data(), &n2) == BAKLAVA_ECAPACITY);
       CHECK(n2 == n_items);
+    }
+  }
+  // the planner with the short runs of the default schedules: a unit whose runs of `chunk` rows split some cache, but
+  // into fewer than `fill` work items, gets runs of 64 rows and more, at most as many as asked for; others are as without
+  for (int rep = 0; rep < 400; ++rep) {
+    const int L = 1 + (int)(rng() % 4), cpl = 1 + (int)(rng() % 40);
+    const int n = L * cpl;
+    const int most = rep % 4 == 0 ? 300 : rep % 4 == 1 ? 1500 : 40000;
+    std::vector<int32_t> cap(n);
+    std::vector<int64_t> off(n);
+    int64_t total = 0;
+    for (int c = 0; c < n; ++c) {
+      cap[c] = (int32_t)(rng() % (uint64_t)most);
+      off[c] = total;
+      total += cap[c];
+    }
+    const int chunk = rng() % 2 ? 256 : 512, fill = 1 + (int)(rng() % 300);
+    const int target = rng() % 2 ? 0 : 256 * (1 + (int)(rng() % 5));
+    const int whole = (int)(rng() % 2);
+    int64_t n_plain = -1, n_items = -1, n_again = -1;
+    CHECK(baklava_plan_schedule(off.data(), cap.data(), L, cpl, chunk, target, whole, 0, nullptr, &n_plain) == BAKLAVA_OK);
+    CHECK(baklava::plan_schedule(off.data(), cap.data(), L, cpl, chunk, target, 64, fill, whole, 0, nullptr, &n_items) == BAKLAVA_OK);
+    std::vector<baklava_work_item> plain((size_t)n_plain), items((size_t)n_items);
+    CHECK(baklava_plan_schedule(off.data(), cap.data(), L, cpl, chunk, target, whole, n_plain, plain.data(), &n_plain) == BAKLAVA_OK);
+    CHECK(baklava::plan_schedule(off.data(), cap.data(), L, cpl, chunk, target, 64, fill, whole, n_items, items.data(), &n_again) == BAKLAVA_OK);
+    CHECK(n_again == n_items);
+    if (n_items > 1)
+      CHECK(baklava::plan_schedule(off.data(), cap.data(), L, cpl, chunk, target, 64, fill, whole, n_items - 1, items.data(), &n_again) == BAKLAVA_ECAPACITY);
+    std::vector<int64_t> rows(n, 0), count(n, 0), plain_count(n, 0);
+    for (const baklava_work_item& it : plain) plain_count[it.cache] += 1;
+    for (const baklava_work_item& it : items) {
+      CHECK(it.start % 64 == 0 && it.start + (int64_t)it.count <= cap[it.cache] && it.row0 == off[it.cache] + it.start);
+      rows[it.cache] += it.count;
+      count[it.cache] += 1;
+    }
+    for (int c = 0; c < n; ++c) CHECK(rows[c] == cap[c]);
+    const int units = whole ? 1 : L, per = whole ? n : cpl;
+    for (int u = 0; u < units; ++u) {
+      int64_t at_chunk = 0, at_64 = 0, got = 0, without = 0;
+      for (int c = u * per; c < (u + 1) * per; ++c) {
+        at_chunk += cap[c] > chunk ? (cap[c] + chunk - 1) / chunk : 1;
+        at_64 += cap[c] > 64 ? (cap[c] + 63) / 64 : 1;
+        got += count[c];
+        without += plain_count[c];
+      }
+      if (at_chunk > per && at_chunk < fill) {
+        CHECK(got <= fill && got >= at_chunk);
+        CHECK(at_64 > fill || got == at_64);
+      } else {
+        CHECK(got == without);
+      }
     }
   }
   {

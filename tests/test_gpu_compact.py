@@ -201,10 +201,10 @@ def test_move_segments_of_every_length(layers, slack):
 
 @pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed", "infinite"])
 def test_caches_ranked_in_registers(scores):
-    """One workgroup ranks a cache of up to 65536 rows from its registers (blocks of 1024 rows, a narrow
-    kernel up to 16384 rows of capacity, tiles beyond 65536): middles of one row less, exactly and one
-    row more than a block, capacities on both sides of the two limits, one and all but one middle row to
-    keep, ties that span wavefronts and blocks, scores of the type's extremes."""
+    """Caches ranked from registers in blocks of 1024 rows: up to 16384 rows of capacity by one workgroup, beyond (so few
+    of them) by one per 8192 rows, tile by tile beyond 65536: middles of one row less, exactly and one row more than a
+    block, capacities on both sides of the two limits, one and all but one middle row to keep, ties that span wavefronts
+    and blocks, scores of the type's extremes."""
     H = _h()
     w = synth.shrink(synth.WORKLOADS["tiny"], name="held", L=1, Hq=12, Hkv=12, batch=1, seed=28, sink=3,
                      recent=5, slack=1100)
@@ -229,6 +229,48 @@ def test_caches_ranked_in_registers(scores):
         arena.score[o:o + n].copy_(torch.from_numpy(s).to(arena.device))
         st.score[c] = s
     run_compact_and_check(arena, w, st)
+    arena.close()
+
+
+@pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed", "infinite"])
+def test_wide_caches_ranked_by_one_workgroup_each(scores):
+    """Beside so many caches of more than 16384 rows that sharing them would not pay, one workgroup ranks each from its
+    registers: the middles, capacities and scores of the test above in that form."""
+    H = _h()
+    sink, recent, slack, n_more = 3, 5, 1100, 125
+    budgets = [9, 63, 1030, 1031, 1032, 2055, 15284, 15285, 40000, 64436, 64437, 8, 17500, 31700] + [15285] * n_more
+    lens = [10, 72, 1031 + 8, 1033, 1032 + 1024, 2055 + 1, 16384, 16385, 41100, 65536, 65537, 1108, 18438, 32776] + [16385] * n_more
+    n = len(budgets)
+    arena = B.Arena(1, n, n, 64, 1, "bf16", budgets, slack, sink, recent, B.POLICY_SCORE, False, workspace_fill=0xFF)
+    wide = [int(c) for c in arena.cap_host if 16384 < c <= 65536]
+    assert 2 * sum(-(-c // 8192) for c in wide) > 3 * torch.cuda.get_device_properties(0).multi_processor_count
+    gen = torch.Generator(device=arena.device)
+    gen.manual_seed(281)
+    arena.k.normal_(generator=gen)
+    arena.v.normal_(generator=gen)
+    arena.pos.copy_(torch.arange(arena.total_tokens, device=arena.device).to(torch.int32))
+    rng = np.random.Generator(np.random.PCG64(282))
+    big = np.finfo(np.float32).max
+    total = arena.total_tokens
+    s = {"uniform": lambda: rng.random(total), "equal": lambda: np.full(total, -0.5), "coarse": lambda: rng.integers(0, 3, total) / 2,
+         "signed": lambda: rng.standard_normal(total) * np.exp(rng.standard_normal(total) * 8),
+         "infinite": lambda: rng.choice(np.array([-np.inf, -big, -0.0, 0.0, 1e-45, big, np.inf], dtype=np.float32), total)}[scores]()
+    s = s.astype(np.float32)
+    arena.score.copy_(torch.from_numpy(s).to(arena.device))
+    arena.set_lengths(lens)
+    before = {name: getattr(arena, name).clone() for name in ("k", "v", "score", "pos")}
+    kept_dev = torch.full((total,), -1, dtype=torch.int32, device=arena.device)
+    arena.compact(0, 1, kept_dev)
+    assert arena.lengths().tolist() == arena.len.cpu().tolist() == [min(x, b) for x, b in zip(lens, budgets)]
+    for c in list(range(14)) + [n - 2, n - 1]:
+        o = int(arena.off_host[c])
+        kept = np.asarray(O.compact_select(s[o:o + lens[c]], lens[c], budgets[c], sink, recent))
+        assert np.array_equal(kept_dev[o:o + len(kept)].cpu().numpy(), kept.astype(np.int32)), f"cache {c}"
+        idx = torch.from_numpy(kept + o).to(arena.device)
+        for name in ("k", "v", "score", "pos"):
+            got, want = getattr(arena, name)[o:o + len(kept)], before[name][idx]
+            assert torch.equal(got.view(torch.int16 if got.dtype == torch.bfloat16 else torch.int32),
+                               want.view(torch.int16 if got.dtype == torch.bfloat16 else torch.int32)), f"cache {c}: {name}"
     arena.close()
 
 
@@ -273,10 +315,10 @@ def test_caches_selected_tile_by_tile(scores, policy):
 @pytest.mark.parametrize("policy", [B.POLICY_SCORE, B.POLICY_STREAMING])
 @pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed_zero", "negative", "close", "ends"])
 def test_few_caches_ranked_by_several_workgroups(scores, policy):
-    """Caches of 16385 to 65536 rows of capacity, few enough that each is ranked by one workgroup per 8192 rows, beside
-    short ones ranked by one: capacities at the edges of a tile and of the range, live lengths in the first, a middle and
-    the last tile and at the budget, no survivors in the middle, ties across tiles, more keys that share their leading
-    bits than LDS holds (equal and close scores), scores of both signs and at the ends of the type."""
+    """Caches of 41020 to 65536 rows of capacity (six to eight tiles), few enough that each is ranked by one workgroup per
+    8192 rows: live lengths at the edges of a tile, in the first, a middle and the last tile and at the budget, no
+    survivors in the middle, ties across tiles, more keys that share their leading bits than LDS holds (equal and close
+    scores), scores of both signs and at the ends of the type."""
     H = _h()
     w = synth.shrink(synth.WORKLOADS["tiny"], name="spread", L=2, Hq=5, Hkv=5, batch=1, seed=27, sink=4, recent=16,
                      slack=41000)
@@ -307,6 +349,35 @@ def test_few_caches_ranked_by_several_workgroups(scores, policy):
             st.score[c] = s
     after = run_compact_and_check(arena, w, st, policy=policy, layer_begin=1, layer_count=1)
     after = run_compact_and_check(arena, w, after, policy=policy)
+    run_compact_and_check(arena, w, after, policy=policy)                                      # nothing left to evict
+    arena.close()
+
+
+@pytest.mark.parametrize("policy", [B.POLICY_SCORE, B.POLICY_STREAMING])
+@pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "ends"])
+def test_shared_caches_beside_short_ones(scores, policy):
+    """Caches of up to 16384 rows of capacity, ranked by one workgroup, in one launch with caches of three to eight tiles
+    ranked by several: capacities of whole tiles and one row more, full and short live lengths, one of two layers and
+    both, and a range without a shared cache."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="beside", L=3, Hq=5, Hkv=5, batch=1, seed=30, sink=6, recent=20, slack=700)
+    rng = np.random.Generator(np.random.PCG64(w.seed + policy))
+    caps = [16384, 16385, 24576, 24577, 900, 32768, 32769, 8192, 5000, 40960, 16384, 8193, 730, 1024, 2000]
+    arena = H.make_arena(w, [c - 700 for c in caps], policy=policy)
+    lens = [16384, 16385, 24576, 24001, 900, 32768, 32069, 7900, 4300, 8193, 16383, 8193, 30, 1000, 1500]
+    st = H.fill_from_host(arena, w, lens, rng, scores="uniform")
+    for c, n in enumerate(lens):
+        if scores == "equal":
+            st.score[c] = np.full(n, 0.25, dtype=np.float32)
+        elif scores == "coarse":
+            st.score[c] = (rng.integers(0, 5, n) / 4 - 0.5).astype(np.float32)
+        elif scores == "ends":
+            st.score[c] = rng.choice(np.array([-np.inf, -3.4e38, -1e-45, -0.0, 0.0, 1e-45, 3.4e38, np.inf], dtype=np.float32), n)
+        o = int(arena.off_host[c])
+        arena.score[o:o + n].copy_(torch.from_numpy(st.score[c]).to(arena.device))
+    after = run_compact_and_check(arena, w, st, policy=policy, layer_begin=1, layer_count=1)
+    after = run_compact_and_check(arena, w, after, policy=policy, layer_begin=2, layer_count=1)   # no shared cache
+    after = run_compact_and_check(arena, w, after, policy=policy, layer_begin=0, layer_count=2)
     run_compact_and_check(arena, w, after, policy=policy)                                      # nothing left to evict
     arena.close()
 

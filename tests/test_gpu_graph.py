@@ -72,10 +72,10 @@ def test_decode_step_replays_from_a_graph(track, warm):
     arena.close()
 
 
-def _replay_setup(track, slack, seed):
+def _replay_setup(track, slack, seed, dtype="bf16", D=128):
     H = _h()
     w = synth.shrink(synth.WORKLOADS["llama32"], name="graphstep", L=3, Hq=8, Hkv=2, batch=2, seed=seed, slack=slack,
-                     interval=slack, sink=4, recent=16)
+                     interval=slack, sink=4, recent=16, dtype=dtype, D=D)
     rng = np.random.Generator(np.random.PCG64(w.seed))
     budgets = [900, 300, 2500, 80, 700, 1300]
     arena = H.make_arena(w, budgets, track=track)
@@ -84,9 +84,9 @@ def _replay_setup(track, slack, seed):
     st = H.fill_from_host(arena, w, lens, rng, scores="uniform")
     dev = arena.device
     bufs = {
-        "q": torch.zeros((w.L, w.batch, w.Hq, w.D), dtype=torch.bfloat16, device=dev),
-        "k": torch.zeros((w.L, w.batch, w.Hkv, w.D), dtype=torch.bfloat16, device=dev),
-        "v": torch.zeros((w.L, w.batch, w.Hkv, w.D), dtype=torch.bfloat16, device=dev),
+        "q": torch.zeros((w.L, w.batch, w.Hq, w.D), dtype=arena.k.dtype, device=dev),
+        "k": torch.zeros((w.L, w.batch, w.Hkv, w.D), dtype=arena.k.dtype, device=dev),
+        "v": torch.zeros((w.L, w.batch, w.Hkv, w.D), dtype=arena.k.dtype, device=dev),
         "out": torch.zeros((w.L, w.batch, w.Hq, w.D), dtype=torch.float32, device=dev),
         "pos": torch.zeros((1,), dtype=torch.int32, device=dev),
     }
@@ -101,13 +101,13 @@ def _replay_setup(track, slack, seed):
     return H, w, rng, budgets, arena, st, bufs, graph
 
 
-@pytest.mark.parametrize("track", [False, True])
-def test_fused_step_replays_from_a_graph_across_evictions(track):
+@pytest.mark.parametrize("track,dtype,D", [(False, "bf16", 128), (True, "bf16", 128), (True, "bf16", 64), (True, "f32", 64), (True, "f32", 128)])
+def test_fused_step_replays_from_a_graph_across_evictions(track, dtype, D):
     """One captured decode step (fused append + attention for every layer; the token position and the
     room left in each cache are read on the device) is replayed for 8 steps with an eviction after
     every third one.  Every replay is checked against the oracle and against a second arena that
     takes the same steps through the eager entry point."""
-    H, w, rng, budgets, arena, st, bufs, graph = _replay_setup(track, slack=3, seed=53)
+    H, w, rng, budgets, arena, st, bufs, graph = _replay_setup(track, slack=3, seed=53, dtype=dtype, D=D)
     eager = H.make_arena(w, budgets, track=track)
     rng_e = np.random.Generator(np.random.PCG64(w.seed))
     H.fill_from_host(eager, w, st.lens(), rng_e, scores="uniform")       # the same seeded contents

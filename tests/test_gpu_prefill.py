@@ -70,18 +70,29 @@ def test_prompt_lengths_around_every_tile_boundary(T):
     print(f"T={T}: worst relative score error {worst:.2e}", flush=True)
 
 
-# 65 x 8 sequences of short prompts: more than two workgroups per compute unit, the form without pipeline;
-# 24 x 8 of long ones: two key tiles per wavefront
+# 65 x 8 sequences of short prompts and 24 x 8 of up to 1599 tokens: more than two workgroups per compute unit, the form
+# without pipeline; 24 x 8 of 1793: two key tiles per wavefront
 @pytest.mark.parametrize("T,batch", [(T, 65) for T in (1, 31, 33, 63, 64, 65, 97, 128, 129, 255, 256, 257, 511, 513)] +
                          [(T, 24) for T in (1500, 1536, 1537, 1599, 1793)])
 def test_many_sequences(T, batch):
     """A launch of many sequences: every eighth prompt against the oracle, the others by their mass (each
     attention row sums to 1), and two of them in a launch of their own, which takes the pipelined form with one
     tile: all forms add a key's weights in the same order, so the bits are the same."""
+    run_many(T, batch, 2, 9900 + T)
+
+
+@pytest.mark.parametrize("T,G", [(1700, 2), (1727, 1), (1727, 3), (1791, 2), (1792, 1), (1794, 2), (1855, 3), (1920, 1), (2047, 2)])
+def test_many_sequences_with_two_tiles(T, G):
+    """Two key tiles per wavefront, 16 x 8 sequences: last tiles of 2 to 63 tokens and full ones, prompts that end all
+    over a block of 256 keys, numbers of stages that are and are not whole turns of the pipeline."""
+    run_many(T, 16, G, 9950 + T + G)
+
+
+def run_many(T, batch, G, seed):
     H = _h()
     dev = torch.device("cuda:0")
-    Hkv, Hq = 8, 16
-    rng = np.random.Generator(np.random.PCG64(9900 + T))
+    Hkv, Hq = 8, 8 * G
+    rng = np.random.Generator(np.random.PCG64(seed))
     qb, kb, vb = (synth.payload(rng, (batch, h, T, 128), "bf16") for h in (Hq, Hkv, Hkv))
     q, k, v = (H.to_device_storage(x, "bf16", dev) for x in (qb, kb, vb))
     _, _, lse = B.profile_similarity(q, k, v, want_cos=False, want_lse=True)
@@ -92,11 +103,11 @@ def test_many_sequences(T, batch):
     torch.cuda.synchronize()
     got = score.cpu().numpy().astype(np.float64).reshape(batch, Hkv, T)
     assert np.array_equal(got[:2].reshape(-1).astype(np.float32), few.cpu().numpy())
-    assert np.max(np.abs(got.sum(2) - 2 * T)) <= 1e-4 * 2 * T
+    assert np.max(np.abs(got.sum(2) - G * T)) <= 1e-4 * G * T
     for b in range(0, batch, 8):
         q64, k64 = synth.storage_to_f64(qb[b], "bf16"), synth.storage_to_f64(kb[b], "bf16")
         h = (b // 8) % Hkv
-        want = O.prefill_scores(q64[2 * h:2 * h + 2], k64[h])
+        want = O.prefill_scores(q64[G * h:G * h + G], k64[h])
         assert np.max(np.abs(got[b, h] - want) / np.maximum(1.0, want)) <= SCORE_RTOL
 
 

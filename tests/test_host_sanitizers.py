@@ -14,7 +14,7 @@ def test_host_code_under_asan_ubsan(tmp_path):
     exe = str(tmp_path / "host_sanitize_driver")
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
            "-static-libasan", "-static-libubsan",
-           "-I", os.path.join(ROOT, "include"),
+           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_13176_amd", "csrc"),
            os.path.join(ROOT, "tests", "host_sanitize_driver.cpp"),
            os.path.join(ROOT, "paper_2502_13176_amd", "csrc", "host_alloc.cpp"), "-o", exe]
     build = subprocess.run(cmd, capture_output=True, text=True)
