@@ -396,11 +396,14 @@ hipError_t launch_prefill_scores(const void* q, const void* k, const float* lse,
   p.n_blocks = 0;
   p.scale_log2e = 1.4426950408889634f / sqrtf((float)kD);
   // One tile per wavefront, pipelined, while that gives at most two workgroups to each of the 256 compute units (or
-  // three, for a prompt of some length), but for very short prompts; from 8192 tokens on two tiles as soon as they
-  // give every compute unit a workgroup.  Beyond, two tiles once they fill the chip twice over, if the prompt is long
-  // against a workgroup's masked stages (twice as many with two tiles) or the launch is large enough for fewer stages
-  // to outweigh them; otherwise the form without pipeline.  us with one tile / two tiles / without pipeline,
-  // sequences x tokens x query heads of each:
+  // three, for a prompt of some length), but for very short prompts, and but for the launches of at most two that two
+  // tiles turn into one for every compute unit, from 8192 tokens on: 8 sequences of 15873 to 16384 tokens, 4 of 32257
+  // to 32768, 2 of twice as many.  One tile / two tiles on both sides of these: 8 x 12000 x 4 810 / 834, 15360 1028 /
+  // 984, 15900 1077 / 1022, 16384 1131 / 1074, 16385 1282 / 1142, 17000 1629 / 1680; 4 x 32256 x 1 559 / 543, 32768 565 /
+  // 528, 36000 865 / 900 (just below and just above them two tiles would be better as well).
+  // Beyond, two tiles once they fill the chip twice over, if the prompt is long against a workgroup's masked stages
+  // (twice as many with two tiles) or the launch is large enough for fewer stages to outweigh them; otherwise the form
+  // without pipeline.  us with one tile / two tiles / without pipeline, sequences x tokens x query heads of each:
   //   8 x 2000 x 4        84 /  156 /  118      128 x 1999 x 4      295 /  295 /  298
   //   8 x 8192 x 4       316 /  498 /  489      256 x 700 x 4        94 /   93 /   89
   //   8 x 16384 x 4     1072 / 1024 / 1220      256 x 1300 x 8      626 /  626 /  603
