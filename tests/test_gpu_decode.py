@@ -361,7 +361,7 @@ def test_scores_from_the_logits_of_a_call(dtype, D, G):
         arena.close()
 
 
-@pytest.mark.parametrize("splits", [[2, 3, 8, 9, 15, 16], [1, 2, 17, 31, 63, 64, 65, 128, 129, 255, 256, 257, 300]])
+@pytest.mark.parametrize("splits", [[2, 3, 8, 9, 15, 16], [2, 4, 5, 6, 7, 8], [1, 2, 17, 31, 63, 64, 65, 128, 129, 255, 256, 257, 300]])
 @pytest.mark.parametrize("dtype,D,track", [("bf16", 128, False), ("bf16", 128, True), ("bf16", 64, False), ("f32", 64, True)])
 def test_merge_of_many_work_items(splits, dtype, D, track):
     """Caches of up to 300 work items, around the numbers of splits that a thread group, a wavefront's lanes and its
