@@ -200,8 +200,8 @@ __device__ __forceinline__ void emit_rows(const float* score, int32_t* kept, con
 // Bound by vector issue (about 40 instructions per key on one compute unit) and the latency of a dozen
 // barriers, not by bandwidth.  Sweeping the scores once per pass (four passes of 8 bits and the emit, 512
 // threads) took 90 us for 512 caches of 128 to 32768 rows, this takes 53; tile by tile (below) 8 caches of
-// 32768 rows took 46 us in five kernels, here 36 in one.  KEYS = 16 (caches of up to 16384 rows) needs 54
-// registers, so two workgroups fit a compute unit; KEYS = 64 takes the register file for one.
+// 32768 rows took 46 us in five kernels, here 36 in one.  KEYS = 16 (caches of up to 16384 rows) needs 52
+// registers, so two workgroups fit a compute unit; KEYS = 64 needs 100, so one does.
 constexpr int kHeldThreads = 1024;
 constexpr int kHeldWaves = kHeldThreads / 64;
 constexpr int kHeldBins = 2048;
@@ -295,11 +295,13 @@ __device__ __forceinline__ int held_find_digit(HeldShared<KEYS>& sm, int& need) 
 
 // Scores of m rows, row i * 1024 + t as key i of thread t.  Places past the m rows hold key 0, the lowest: no score
 // but a NaN of all ones maps there.  Behind every row of the cache neither the threshold nor a survivor's place depends
-// on them.
+// on them.  (A base for each block keeps 64 keys from spilling; up to 16 take fewer instructions with one for all: 1500
+// caches of up to 2064 rows ranked in 36.6 / 34.7 us.)
 template <int KEYS>
 __device__ __forceinline__ void held_load(const float* score, int m, uint32_t (&key)[KEYS]) {
 #pragma unroll
-  for (int i = 0; i < KEYS; ++i) key[i] = __float_as_uint(block_word(score, i * kHeldThreads, m));
+  for (int i = 0; i < KEYS; ++i)
+    key[i] = __float_as_uint(KEYS <= 16 ? score[min(i * kHeldThreads + (int)threadIdx.x, m - 1)] : block_word(score, i * kHeldThreads, m));
 }
 template <int KEYS>
 __device__ __forceinline__ void held_map(int m, uint32_t (&key)[KEYS]) {
