@@ -210,7 +210,8 @@ enum {
                                    workgroups) while a layer holds at most a quarter as many caches,
                                    otherwise five times that number, with a shortest run of 256 rows.
                                    The default schedules also cut runs of fewer rows where a launch of
-                                   split caches would have fewer work items than compute units; setting
+                                   split caches would have fewer work items than compute units (over
+                                   several layers: while that gives at most two for each); setting
                                    a run length or an item target, also to the default, ends that    */
   BAKLAVA_OPT_TARGET_ITEMS_WHOLE = 6, /* the same for launches over all layers at once.  Default: two to
                                    five times the device's number of compute units, by the number of
@@ -219,9 +220,12 @@ enum {
                                    record stay there until the next flush); 1: they resume.  Only a
                                    context created with track_scores can be switched to 1          */
   BAKLAVA_OPT_TILED_SELECT_ROWS = 8 /* eviction: caches whose capacity exceeds this many rows are ranked
-                                       by several workgroups (tiles of 8192 rows) instead of one.
+                                       tile by tile (8192 rows each, one launch per radix pass).
                                        >= 8192; default 65536, the most one workgroup ranks (larger
-                                       values act like it).  Synchronises like the CHUNK options    */
+                                       values act like it).  Shorter caches are ranked by one workgroup
+                                       each, those of more than 16384 rows by one per 8192 rows where
+                                       few of them would leave the device idle.  Synchronises like the
+                                       CHUNK options                                               */
 };
 int baklava_set_option(baklava_ctx* ctx, int32_t option, int64_t value);
 

@@ -647,9 +647,9 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     }
   }
   // Eviction: a cache of up to kHeldRows rows is ranked by one workgroup that holds its scores in
-  // registers, a longer one tile by tile.  Measured, us per eviction, one workgroup against tiles: 8
-  // caches of 15000 rows 57 / 90, of 30000 87 / 103, of 60000 121 / 132; 256 caches 449 / 489, 862 / 914,
-  // 1716 / 1838.
+  // registers, or by several (see spread_selection), a longer one tile by tile.  Measured, us per eviction,
+  // one workgroup against tiles: 8 caches of 15000 rows 57 / 90, of 30000 87 / 103, of 60000 121 / 132; 256
+  // caches 449 / 489, 862 / 914, 1716 / 1838.
   ctx->select_long_rows = kHeldRows;
   ctx->n_wide.assign(desc->L, 0);
   for (int64_t c = 0; c < n_caches; ++c) ctx->n_wide[c / ctx->cpl] += ctx->cap[c] > kNarrowRows ? 1 : 0;

@@ -1,6 +1,7 @@
 // Budget-enforcing eviction (f_evict, Eqs. 5-6): selection of the surviving rows (one workgroup
-// per cache, long caches first; caches beyond what a workgroup's registers hold are cut into tiles
-// and go through one kernel per radix pass), then a stable in-place move (one workgroup per segment).
+// per cache, long caches first, or several where few long caches would leave compute units idle; caches
+// beyond what a workgroup's registers hold are cut into tiles and go through one kernel per radix pass),
+// then a stable in-place move (one workgroup per segment).
 #include "common.h"
 
 #include <algorithm>
@@ -443,11 +444,11 @@ __global__ __launch_bounds__(kHeldThreads) void compact_select_kernel(CompactPar
 // one workgroup each, in two kernels.  The first counts the keys of every tile by their leading 11 bits and leaves
 // the counters in the workspace.  In the second every workgroup adds up the counters of its cache, finds the threshold's
 // leading digit, collects in LDS the keys of the whole cache that have it (an eighth of them, say), ranks those by their
-// other bits for itself, and emits its own tile.  Reading the cache's scores once more in every workgroup costs less than the launches that
-// would share the work (about 5 us each behind one another).  A cache of up to kNarrowRows rows is ranked whole by the
-// first kernel.  us per eviction, one workgroup per cache / spread: 8 caches of 20000 rows 47 / 35, of 32768 56 / 41, of
-// 64000 82 / 62; the ranking of 8 caches of 32768 rows takes 17 us in all (35), of which 4.7 pass until the other rows
-// with the digit are collected, 2.7 with the emit and the rest with barriers.
+// other bits for itself, and emits its own tile.  Reading the cache's scores once more in every workgroup costs less than
+// the launches that would share the work (about 5 us each behind one another).  A cache of up to kNarrowRows rows is
+// ranked whole by the first kernel.  us per eviction, one workgroup per cache / spread: 8 caches of 20000 rows 47 / 35, of 32768 56 / 41, of
+// 64000 82 / 62; the ranking of 8 caches of 32768 rows takes 20 us in all (35), 5 in the first kernel; of the 15 in the
+// second 4.7 pass until the other rows with the digit are collected, 2.7 with the emit and the rest with barriers.
 constexpr int kTileKeys = kTileRows / kHeldThreads;
 constexpr int kMostTiles = kHeldRows / kTileRows;
 constexpr int kListKeys = 2048;  // keys with the threshold's leading digit that LDS holds for each wavefront
