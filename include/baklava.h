@@ -162,7 +162,7 @@ typedef struct {
 /*
  * Bytes of device workspace a context with this description needs: split partials (G * (D + 2)
  * floats for each work item of 256 rows, or of 64 up to 256 items a layer), work-item tables,
- * kept-index lists, halo rows of the eviction move, the tables and counters of the selection of
+ * kept-index lists, the counters of the eviction move, the tables and counters of the selection of
  * caches of more than 8192 rows, and with track_scores the query rows and softmax normalisers of
  * the attention calls each cache has on record (bf16 rows of 128 elements) or the logits of one
  * call (F32 and rows of 64 elements: 4 * G bytes per cached row, which at bf16, D = 64 and eight

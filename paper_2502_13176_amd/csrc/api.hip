@@ -44,9 +44,8 @@ struct WorkspacePlan {
   // several layers where that of a single one would cut needlessly short runs (see schedule_for)
   size_t items[3], multi[3];
   size_t part_o, part_ml, final_ml, logits, lag_q, lag_ml, lag_n, lag_cnt, status, kept, info, order_all, order_layer;
-  size_t segs, seg_split, halo_k, halo_v, halo_score, halo_pos, tiles, spread, tile_hist, sel_state, total;
-  int64_t n_segs, halo_rows, n_tiles, n_long;
-  int32_t seg_rows;  // destination rows per segment of the eviction move
+  size_t move_ticket, move_flags, tiles, spread, tile_hist, sel_state, total;
+  int64_t n_tiles, n_long;
   int64_t max_items;
 };
 
@@ -68,43 +67,6 @@ bool shape_ok(const baklava_desc* d) {
 // Scores are deferred over bf16 rows of 128 elements only (see decode_impl).
 bool keeps_records(const baklava_desc* d) { return d->dtype == BAKLAVA_BF16 && d->D == 128; }
 
-// Destination rows per segment of the eviction move (one workgroup each).  A segment copies its rows
-// tile after tile (128 rows, a few microseconds each, of which little overlaps inside a workgroup), so
-// a small arena needs short segments to keep the chip busy; in a large one they only add rows that
-// travel through a halo slot.  Measured, us per eviction at segments of rows / 128, / 256, / 512, / 1024
-// (fixed 4096 before): 8 caches of 32768 rows to 78643 in all 116, 104, 99, 99 (415); 524288 rows, 64
-// evicted per cache, 281, 243, 220, 219 (285); 131072 rows likewise 137, 127, 123, 125 (240); from two
-// million rows on the maximum holds.
-constexpr int kSegDivisor = 512;
-int32_t move_seg_rows(const baklava_desc* d, const int32_t* budget) {
-  int64_t rows = 0;
-  for (int64_t i = 0; i < (int64_t)d->L * d->Hkv; ++i) rows += (int64_t)budget[i] * d->batch;
-  int32_t seg = kMoveSegMax;
-  while (seg > kMoveSegMin && seg > rows / kSegDivisor) seg /= 2;
-  return seg;
-}
-
-// Segments of the eviction move: the destination range [0, budget) of every cache in runs of
-// seg_rows rows; a segment that has a successor owns a halo slot for the rows whose source lies past
-// its end: at most its own rows, and at most cap - budget of them.
-int64_t halo_slot_rows(int64_t cap, int64_t budget, int32_t seg_rows) {
-  return std::max<int64_t>(0, std::min<int64_t>(seg_rows, cap - budget));
-}
-
-void count_segments(const baklava_desc* d, const int32_t* cap, const int32_t* budget, int32_t seg_rows,
-                    int64_t* n_segs, int64_t* halo_rows) {
-  const int64_t cpl = (int64_t)d->batch * d->Hkv;
-  const int64_t n_caches = (int64_t)d->L * cpl;
-  *n_segs = 0;
-  *halo_rows = 0;
-  for (int64_t c = 0; c < n_caches; ++c) {
-    const int64_t b = budget[(c / cpl) * d->Hkv + c % d->Hkv];
-    const int64_t ns = std::max<int64_t>(1, (b + seg_rows - 1) / seg_rows);
-    *n_segs += ns;
-    *halo_rows += (ns - 1) * halo_slot_rows(cap[c], b, seg_rows);
-  }
-}
-
 WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const int32_t* budget) {
   WorkspacePlan w{};
   const int64_t n_caches = (int64_t)d->L * d->batch * d->Hkv;
@@ -112,8 +74,6 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
   const size_t row_bytes = (size_t)d->D * (d->dtype == BAKLAVA_BF16 ? 2 : 4);
   int64_t total_tokens = 0;
   for (int64_t c = 0; c < n_caches; ++c) total_tokens += cap[c];
-  w.seg_rows = move_seg_rows(d, budget);
-  count_segments(d, cap, budget, w.seg_rows, &w.n_segs, &w.halo_rows);
   // runs of at least kSizingChunk rows, or the shorter ones of the layers that those would not fill the chip with
   const int64_t cpl = (int64_t)d->batch * d->Hkv;
   w.max_items = 0;
@@ -141,12 +101,8 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
   w.info = o;         o = align256(o + (size_t)n_caches * sizeof(CompactInfo));
   w.order_all = o;    o = align256(o + (size_t)n_caches * 4);
   w.order_layer = o;  o = align256(o + (size_t)n_caches * 4);
-  w.segs = o;         o = align256(o + (size_t)w.n_segs * sizeof(MoveSeg));
-  w.seg_split = o;    o = align256(o + (size_t)w.n_segs * 2 * 4);
-  w.halo_k = o;       o = align256(o + (size_t)w.halo_rows * row_bytes);
-  w.halo_v = o;       o = align256(o + (size_t)w.halo_rows * row_bytes);
-  w.halo_score = o;   o = align256(o + (size_t)w.halo_rows * 4);
-  w.halo_pos = o;     o = align256(o + (size_t)w.halo_rows * 4);
+  w.move_ticket = o;  o = align256(o + (size_t)n_caches * 4);
+  w.move_flags = o;   o = align256(o + (size_t)(total_tokens / kMoveRowsMin + n_caches) * 4);
   // selection of the caches too long for one workgroup: tile table and per-tile digit counters
   w.n_tiles = 0;
   w.n_long = 0;
@@ -174,7 +130,7 @@ struct baklava_ctx {
   std::vector<int64_t> off;
   std::vector<int32_t> cap, len, budget;
   std::vector<int32_t> order_all, order_layer;  // caches, longest first (whole model / inside each layer)
-  std::vector<int32_t> seg_begin;               // cache -> first segment of the eviction move
+  std::vector<int32_t> move_tiles;          // cache -> tiles of the eviction move for the caches before it
   std::vector<int32_t> tile_begin;              // cache -> first tile of the tiled selection (long caches only have any)
   std::vector<int32_t> spread_begin;            // cache -> first tile of the selection by several workgroups per cache
   std::vector<int32_t> n_wide;                  // layer -> caches with more than kNarrowRows rows of capacity
@@ -617,33 +573,14 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     delete ctx;
     return BAKLAVA_EHIP;
   }
-  // Segment table of the eviction move (depends on budgets and capacities only).
+  // Tiles of the eviction move, at most (a cache's rows move from the first evicted one on).
   {
-    std::vector<MoveSeg> segs;
-    segs.reserve((size_t)ctx->plan.n_segs);
-    ctx->seg_begin.assign(n_caches + 1, 0);
-    int64_t halo = 0;
+    const int64_t rows = move_rows(ctx->row_bytes / 16);
+    int64_t tiles = 0;
+    ctx->move_tiles.assign(n_caches + 1, 0);
     for (int64_t c = 0; c < n_caches; ++c) {
-      ctx->seg_begin[c] = (int32_t)segs.size();
-      const int64_t b = ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv];
-      const int32_t seg_rows = ctx->plan.seg_rows;
-      const int64_t hs = halo_slot_rows(ctx->cap[c], b, seg_rows);
-      const int64_t ns = std::max<int64_t>(1, (b + seg_rows - 1) / seg_rows);
-      for (int64_t k = 0; k < ns; ++k) {
-        MoveSeg sg;
-        sg.c = (int32_t)c;
-        sg.a = (int32_t)(k * seg_rows);
-        sg.halo_row = (k + 1 < ns && hs > 0) ? (int32_t)halo : -1;
-        sg.pad = 0;
-        if (k + 1 < ns) halo += hs;
-        segs.push_back(sg);
-      }
-    }
-    ctx->seg_begin[n_caches] = (int32_t)segs.size();
-    if ((int64_t)segs.size() != ctx->plan.n_segs || halo != ctx->plan.halo_rows || halo > INT32_MAX ||
-        !hip_ok(hipMemcpy(ctx->ws + ctx->plan.segs, segs.data(), segs.size() * sizeof(MoveSeg), hipMemcpyHostToDevice))) {
-      delete ctx;
-      return BAKLAVA_EHIP;
+      tiles += (ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv] + rows - 1) / rows;
+      ctx->move_tiles[c + 1] = (int32_t)std::min<int64_t>(tiles, INT32_MAX);
     }
   }
   // Eviction: a cache of up to kHeldRows rows is ranked by one workgroup that holds its scores in
@@ -859,15 +796,8 @@ extern "C" int baklava_compact(baklava_ctx* ctx, int32_t layer_begin, int32_t la
   p.sink = ctx->d.sink; p.recent = ctx->d.recent; p.policy = ctx->d.policy;
   p.row_bytes = ctx->row_bytes;
   p.write_identity = kept_idx_out ? 1 : 0;
-  const int32_t s0 = ctx->seg_begin[c0], s1 = ctx->seg_begin[c1];
-  p.segs = reinterpret_cast<const MoveSeg*>(ctx->ws + ctx->plan.segs) + s0;
-  p.seg_split = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.seg_split);
-  p.seg_base = s0;
-  p.seg_rows = ctx->plan.seg_rows;
-  p.halo_k = ctx->ws + ctx->plan.halo_k;
-  p.halo_v = ctx->ws + ctx->plan.halo_v;
-  p.halo_score = reinterpret_cast<float*>(ctx->ws + ctx->plan.halo_score);
-  p.halo_pos = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.halo_pos);
+  p.move_ticket = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.move_ticket);
+  p.move_flags = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.move_flags);
   hipStream_t s = (hipStream_t)stream;
   // The selection ranks rows by their scores: weights still owed to them are added first.
   {
@@ -887,7 +817,7 @@ extern "C" int baklava_compact(baklava_ctx* ctx, int32_t layer_begin, int32_t la
                                     reinterpret_cast<const SelTile*>(ctx->ws + ctx->plan.spread) + sp0,
                                     spread ? n_spread : 0, s)))
     return BAKLAVA_EHIP;
-  if (!hip_ok(launch_compact_move(p, s1 - s0, s))) return BAKLAVA_EHIP;
+  if (!hip_ok(launch_compact_move(p, (int)c0, (int)(c1 - c0), ctx->move_tiles.data() + c0, ctx->n_cus, s))) return BAKLAVA_EHIP;
   for (int64_t c = c0; c < c1; ++c) {
     const int32_t b = ctx->budget[(c / ctx->cpl) * ctx->d.Hkv + c % ctx->d.Hkv];
     ctx->len[c] = std::min(ctx->len[c], b);

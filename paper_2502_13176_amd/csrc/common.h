@@ -22,7 +22,11 @@ __device__ __forceinline__ void store_nt16(void* ptr, uint4 v) {
 
 constexpr int kLagRows = 32;   // packed query rows of a cache's record of pending calls (score tracking)
 constexpr int kLagCalls = 8;   // most calls such a record holds
-constexpr int kMoveSegMin = 128, kMoveSegMax = 4096;  // destination rows per workgroup of the eviction move
+// Eviction move: destination rows per tile by 16-byte pieces per row, threads per workgroup, caches per launch
+constexpr int kMoveRowsMin = 128;
+constexpr int move_rows(int pieces) { return pieces > 16 ? kMoveRowsMin : 2 * kMoveRowsMin; }
+constexpr int kMoveThreads = 512;
+constexpr int kMoveCaches = 8192;
 constexpr int kTileRows = 8192;     // rows per tile of a cache that is ranked tile by tile (one workgroup per tile and pass)
 constexpr int kHeldRows = 65536;     // most rows of a cache that one workgroup ranks, in its registers
 constexpr int kNarrowRows = kHeldRows / 4;  // most rows of a cache of which two such workgroups fit a compute unit
@@ -154,14 +158,6 @@ struct LengthsParams {
   int32_t value[kLengthsPerLaunch];
 };
 
-// One destination segment of the eviction move: rows [a, a + seg_rows) of cache c.  Segments that
-// have a successor own a halo slot (room for min(seg_rows, cap - budget) rows) in the workspace.
-struct MoveSeg {
-  int32_t c, a;
-  int32_t halo_row;  // first row of this segment's halo slot, or -1
-  int32_t pad;
-};
-
 struct CompactParams {
   void* k;
   void* v;
@@ -177,15 +173,8 @@ struct CompactParams {
   int32_t sink, recent, policy;
   int32_t row_bytes;
   int32_t write_identity;  // 1: also write 0..n-1 for caches that evict nothing
-  const MoveSeg* segs;     // segments of the launched cache range
-  int32_t* seg_split;      // [n_segs, 2] first destination row of a segment whose source lies past its end, and
-                           // first one whose source lies past all destination rows of the cache
-  void* halo_k;            // halo copies of the rows a segment needs from beyond its end
-  void* halo_v;
-  float* halo_score;
-  int32_t* halo_pos;
-  int32_t seg_base;        // index of segs[0] in seg_split
-  int32_t seg_rows;        // destination rows per segment
+  int32_t* move_ticket;    // [n_caches] tiles that workgroups of a launch of the move have taken (its first cache's counter)
+  int32_t* move_flags;     // tiles whose rows have been read (see move_flag_base)
   const int32_t* cap;
   const SelTile* tiles;    // tiles of the long caches of the launched range
   int32_t* tile_hist;      // [all tiles][4 passes][256] digit counters, indexed by first_tile + tile
@@ -228,7 +217,9 @@ hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s
 // n_spread > 0: the caches of up to p.long_rows rows are ranked by the workgroups spread[0 .. n_spread)
 hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
                                  const SelTile* spread, int n_spread, hipStream_t s);
-hipError_t launch_compact_move(const CompactParams& p, int n_segs, hipStream_t s);
+// the move of caches c0 .. c0 + n_caches; tiles_before[i]: tiles of the move of the caches before c0 + i, at most
+hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, const int32_t* tiles_before, int n_cus,
+                               hipStream_t s);
 hipError_t launch_stream_probe(void* dst, const void* src, int64_t bytes, int mode, hipStream_t s);
 
 }  // namespace baklava

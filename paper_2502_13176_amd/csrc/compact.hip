@@ -1,7 +1,7 @@
 // Budget-enforcing eviction (f_evict, Eqs. 5-6): selection of the surviving rows (one workgroup
 // per cache, long caches first, or several where few long caches would leave compute units idle; caches
 // beyond what a workgroup's registers hold are cut into tiles and go through one kernel per radix pass),
-// then a stable in-place move (one workgroup per segment).
+// then a stable in-place move (tiles of rows, several workgroups to a cache).
 #include "common.h"
 
 #include <algorithm>
@@ -24,6 +24,7 @@ __device__ __forceinline__ uint32_t score_key(float f) {
 
 // Exclusive prefix sum of `v` over the workgroup; `total` receives the sum.  `sm` holds one
 // word per wavefront.  Ends with a barrier, so `sm` can be reused right away.
+template <int WAVES = kSelWaves>
 __device__ __forceinline__ int block_exclusive_scan(int v, int* sm, int& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int incl = v;
@@ -36,7 +37,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* sm, int& total) 
   __syncthreads();
   int base = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < kSelWaves; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     const int x = sm[w];
     if (w < wave) base += x;
     tot += x;
@@ -62,6 +63,16 @@ __device__ __forceinline__ SelGoal sel_goal(const CompactParams& p, int c) {
   g.mid_lo = s;
   g.mid_hi = g.n - r;
   return g;
+}
+
+// First flag of a cache's tiles: each of the caches before it has at most one tile more than its rows fill.
+__device__ __forceinline__ int64_t move_flag_base(int64_t off, int c) { return off / kMoveRowsMin + c; }
+
+// The move behind the selection starts at the cache's first tile, with no tile read yet.  By one whole workgroup.
+__device__ __forceinline__ void clear_move_state(const CompactParams& p, int c, int64_t off, int budget) {
+  int32_t* flags = p.move_flags + move_flag_base(off, c);
+  for (int t = threadIdx.x; t * kMoveRowsMin < budget; t += blockDim.x) flags[t] = 0;
+  if (threadIdx.x == 0) p.move_ticket[c] = 0;
 }
 
 // One counting pass of the radix select over rows [j_begin, j_end) of the middle: keys whose digits
@@ -386,6 +397,7 @@ __device__ __forceinline__ void select_whole(const CompactParams& p, int c, Held
   const int n = g.n;
   const int64_t off = p.off[c];
   int32_t* kept = p.kept + off;
+  clear_move_state(p, c, off, g.b);
 
   if (n <= g.b) {
     if (p.write_identity)
@@ -468,6 +480,7 @@ __global__ __launch_bounds__(kHeldThreads) void compact_spread_count_kernel(Comp
   }
   const int tid = threadIdx.x;
   const SelGoal g = sel_goal(p, tl.c);
+  if (tl.tile == 0) clear_move_state(p, tl.c, p.off[tl.c], g.b);
   if (tl.tile == 0 && tid == 0)  // the second kernel lowers first_moved with atomicMin
     p.info[tl.c] = g.n <= g.b ? CompactInfo{g.n, g.n, g.n, 0} : CompactInfo{g.b, g.k > 0 ? g.n : g.mid_lo, g.n, 0};
   if (g.n <= g.b || g.k <= 0) return;
@@ -688,6 +701,7 @@ __global__ __launch_bounds__(kSelThreads) void compact_tile_count_kernel(Compact
   const int c = tl.c;
   const int tid = threadIdx.x;
   const SelGoal g = sel_goal(p, c);
+  if (PASS == 0 && tl.tile == 0) clear_move_state(p, c, p.off[c], g.b);
   if (PASS == 0 && tl.tile == 0 && tid == 0) {
     // the selection's result record; the emit kernel lowers first_moved with atomicMin
     p.info[c] = g.n <= g.b ? CompactInfo{g.n, g.n, g.n, 0} : CompactInfo{g.b, g.n, g.n, 0};
@@ -759,154 +773,107 @@ __global__ __launch_bounds__(kSelThreads) void compact_tile_emit_kernel(CompactP
   if (tid == 0 && sh_first < n) atomicMin(&p.info[c].first_moved, sh_first);
 }
 
-constexpr int kMoveThreads = 512;
-constexpr int kMoveRows = 128;  // rows per tile
-
-// The move is stable and in place: row p <- row kept[p], with kept[p] >= p and
-// kept[p] - p <= (rows evicted) <= capacity - budget.  A cache's destination range is cut into
-// segments of p.seg_rows rows, one workgroup each.  Inside a segment tiles go in ascending
-// order and every load of a tile finishes (barrier) before any store, so a tile's sources are
-// never rows an earlier tile wrote.  The only rows a segment reads that another segment writes
-// are those whose source lies past the segment but still inside the destination range [0, budget):
-// they are copied to a halo slot by a first kernel, before anything is overwritten.  A source past the
-// destination range is overwritten by nobody and is read where it is.  After a prompt that is most of
-// them: 256 caches of 16384 rows, us per eviction with every source past the segment in the halo, and
-// now: 20% kept 402 / 301, 50% kept 710 / 618.
-
-// K/V rows are read once and written once here: non-temporal loads and stores (measured: the move
-// of a full eviction is 14% faster with them).
-#define BAKLAVA_MOVE_LD(ptr) load_nt16(ptr)
-#define BAKLAVA_MOVE_ST(ptr, v) store_nt16(ptr, v)
-
-// Phase 1: save the halo of every segment that has a successor.  After a prompt (far more rows than
-// the budget) that can be all rows of a segment, so the copy goes at the move's own pace: the same
-// tiles, every load of a tile in flight before the first store.
-template <int PIECES>
-__global__ __launch_bounds__(kMoveThreads) void compact_halo_kernel(CompactParams p) {
-  const MoveSeg sg = p.segs[blockIdx.x];
-  const CompactInfo info = p.info[sg.c];
-  if (info.first_moved >= info.old_len) return;  // nothing evicted
-  const int b = info.new_len;
-  const int e = sg.a + p.seg_rows;
-  if (e >= b || sg.halo_row < 0) return;         // last segment: its far sources are overwritten by nobody
-  const int tid = threadIdx.x;
-  const int64_t off = p.off[sg.c];
-  const int32_t* kept = p.kept + off;
-  // destination rows whose source is at or past the segment end, and at or past the end of all
-  // destination rows (kept is ascending): the rows between go through the halo
-  auto first_at = [&](int lo, int bound) {
-    int hi = e;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (kept[mid] >= bound) hi = mid; else lo = mid + 1;
-    }
-    return lo;
-  };
-  const int split = first_at(sg.a, e), direct = first_at(split, b), n_halo = direct - split;
-  if (tid == 0) {
-    p.seg_split[2 * (p.seg_base + blockIdx.x)] = split;
-    p.seg_split[2 * (p.seg_base + blockIdx.x) + 1] = direct;
-  }
-  constexpr int PER_PLANE = kMoveRows * PIECES / kMoveThreads;
-  const uint4* K = reinterpret_cast<const uint4*>(p.k) + off * PIECES;
-  const uint4* V = reinterpret_cast<const uint4*>(p.v) + off * PIECES;
-  uint4* HK = reinterpret_cast<uint4*>(p.halo_k) + (int64_t)sg.halo_row * PIECES;
-  uint4* HV = reinterpret_cast<uint4*>(p.halo_v) + (int64_t)sg.halo_row * PIECES;
-  for (int r0 = 0; r0 < n_halo; r0 += kMoveRows) {
-    uint4 kb[PER_PLANE], vb[PER_PLANE];
-#pragma unroll
-    for (int i = 0; i < PER_PLANE; ++i) {
-      const int idx = tid + i * kMoveThreads;
-      const int64_t src = kept[split + min(r0 + idx / PIECES, n_halo - 1)];  // clamped: a row of this halo
-      kb[i] = BAKLAVA_MOVE_LD(K + src * PIECES + idx % PIECES);
-      vb[i] = BAKLAVA_MOVE_LD(V + src * PIECES + idx % PIECES);
-    }
-#pragma unroll
-    for (int i = 0; i < PER_PLANE; ++i) {
-      const int idx = tid + i * kMoveThreads;
-      const int r = r0 + idx / PIECES;
-      if (r < n_halo) {  // the move reads these soon: ordinary stores
-        HK[(int64_t)r * PIECES + idx % PIECES] = kb[i];
-        HV[(int64_t)r * PIECES + idx % PIECES] = vb[i];
-      }
-    }
-  }
-  for (int r = tid; r < n_halo; r += kMoveThreads) {
-    const int src = kept[split + r];
-    p.halo_score[sg.halo_row + r] = p.score[off + src];
-    p.halo_pos[sg.halo_row + r] = p.pos[off + src];
-  }
-}
-
-// Phase 2: the move itself.
+// The move is stable and in place: row p <- row kept[p], with kept[p] >= p and kept[p] - p <= (rows evicted).  The rows
+// of a cache from the first that moves on are cut into tiles.  The tiles of all caches, numbered in a row, are handed
+// out in ascending order by a counter (a ticket).  A tile's workgroup loads its rows, waits for them, raises the tile's
+// flag, and stores them once the flags of all earlier tiles of the cache are up whose sources may lie in its range:
+// those rows have been read.  A ticket is waited for only by later ones, and raising a flag waits for nothing, so every
+// wait ends whatever order the workgroups are started in.  No data passes between workgroups (each reads rows that no
+// one has written), only the permission to overwrite, so neither side needs a cache to be written back or invalidated:
+// the flags are relaxed device-scope atomics, raised behind an explicit wait for the loads.
+//
+// Bound by HBM.  What reads and writes together reach here depends on how far apart the rows in flight lie: a plain
+// copy of 1 GiB runs at 6.1 to 6.3 TB/s in 16 KiB pieces in address order, at 5.4 in pieces of 256 KiB.  Hence tiles in
+// order over the whole arena, 128 KiB each (half of it K), two workgroups to a compute unit.  A workgroup per run of 1024
+// to 4096 rows behind a kernel that saved the rows which cross a run's end took 1096 us for 5 million rows of 512 bytes,
+// of which nearly all move, and 19 for the rows across the ends; this takes 870.  Tried: tiles of 128 rows, 512 threads:
+// 960; the next ticket drawn while a tile's rows are on their way, 910 (the rows in flight lie further apart); a
+// workgroup for every tile: as fast, but 60 us for 20000 workgroups that find nothing to move; a counter for each cache
+// and four tiles per workgroup: 930.
 template <int PIECES>  // 16-byte pieces per row
-__global__ __launch_bounds__(kMoveThreads) void compact_move_kernel(CompactParams p) {
-  const MoveSeg sg = p.segs[blockIdx.x];
-  const int c = sg.c;
-  const CompactInfo info = p.info[c];
-  if (info.first_moved >= info.old_len) return;  // nothing evicted
+__global__ __launch_bounds__(kMoveThreads) void compact_move_kernel(CompactParams p, int c0, int n_caches) {
+  constexpr int ROWS = move_rows(PIECES);
+  static_assert(ROWS <= kMoveThreads && ROWS >= kMoveRowsMin, "a thread per score, a flag per tile");
+  extern __shared__ int sh_end[];  // tiles of the caches up to and with this one
+  __shared__ int sh_scan[kMoveThreads / 64];
+  __shared__ int sh_tile;
   const int tid = threadIdx.x;
-  const int b = info.new_len;
-  if (sg.a == 0 && tid == 0) p.len[c] = b;
-  const int e = min(sg.a + p.seg_rows, b);
-  if (e <= info.first_moved) return;             // every row of this segment stays where it is
-  // rows [split, direct) take their source from the halo slot
-  const bool has_halo = (sg.a + p.seg_rows < b) && sg.halo_row >= 0;
-  const int split = has_halo ? p.seg_split[2 * (p.seg_base + blockIdx.x)] : e;
-  const int direct = has_halo ? p.seg_split[2 * (p.seg_base + blockIdx.x) + 1] : e;
-  const int64_t off = p.off[c];
-  const int32_t* kept = p.kept + off;
-  constexpr int PER_PLANE = kMoveRows * PIECES / kMoveThreads;  // pieces per thread per plane
-  uint4* K = reinterpret_cast<uint4*>(p.k) + off * PIECES;
-  uint4* V = reinterpret_cast<uint4*>(p.v) + off * PIECES;
-  const uint4* HK = reinterpret_cast<const uint4*>(p.halo_k) + (int64_t)sg.halo_row * PIECES;
-  const uint4* HV = reinterpret_cast<const uint4*>(p.halo_v) + (int64_t)sg.halo_row * PIECES;
-  float* score = p.score + off;
-  int32_t* pos = p.pos + off;
-
-  const int first = max(sg.a, (info.first_moved / kMoveRows) * kMoveRows);
-  for (int p0 = first; p0 < e; p0 += kMoveRows) {
+  int* const ticket = p.move_ticket + c0;
+  int next = 0;
+  if (tid == 0) next = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int total = 0;
+  for (int i0 = 0; i0 < n_caches; i0 += kMoveThreads) {
+    const int i = i0 + tid;
+    int n = 0;
+    if (i < n_caches) {
+      const CompactInfo info = p.info[c0 + i];
+      n = max(0, info.new_len - info.first_moved + ROWS - 1) / ROWS;
+      if (blockIdx.x == 0 && info.first_moved < info.old_len) p.len[c0 + i] = info.new_len;
+    }
+    int all;
+    n += block_exclusive_scan<kMoveThreads / 64>(n, sh_scan, all);
+    if (i < n_caches) sh_end[i] = total + n;
+    total += all;
+  }
+  constexpr int PER_PLANE = ROWS * PIECES / kMoveThreads;  // pieces per thread and plane
+  for (;;) {
+    if (tid == 0) sh_tile = next;
+    __syncthreads();
+    const int g = sh_tile;
+    if (g >= total) return;  // (uniform over the workgroup)
+    int lo = 0;              // the first cache that ends behind tile g
+    for (int hi = n_caches - 1; lo < hi;) {
+      const int mid = (lo + hi) >> 1;
+      if (sh_end[mid] > g) hi = mid; else lo = mid + 1;
+    }
+    const int t = __builtin_amdgcn_readfirstlane(lo > 0 ? g - sh_end[lo - 1] : g), c = __builtin_amdgcn_readfirstlane(c0 + lo);
+    const CompactInfo info = p.info[c];
+    const int b = info.new_len, first = info.first_moved, evicted = info.old_len - b;
+    const int64_t off = p.off[c];
+    const int32_t* kept = p.kept + off;
+    uint4* K = reinterpret_cast<uint4*>(p.k) + off * PIECES;
+    uint4* V = reinterpret_cast<uint4*>(p.v) + off * PIECES;
+    float* score = p.score + off;
+    int32_t* pos = p.pos + off;
+    int32_t* flags = p.move_flags + move_flag_base(off, c);
+    const int p0 = first + t * ROWS, e = min(p0 + ROWS, b);
     uint4 kb[PER_PLANE], vb[PER_PLANE];
+#pragma unroll
+    for (int i = 0; i < PER_PLANE; ++i) {
+      const int idx = tid + i * kMoveThreads;
+      const int64_t src = kept[min(p0 + idx / PIECES, e - 1)];  // clamped: a row of this tile
+      kb[i] = load_nt16(K + src * PIECES + idx % PIECES);
+      vb[i] = load_nt16(V + src * PIECES + idx % PIECES);
+    }
     float sc = 0.f;
     int ps = 0;
-#pragma unroll
-    for (int i = 0; i < PER_PLANE; ++i) {
-      const int idx = tid + i * kMoveThreads;
-      const int row = min(p0 + idx / PIECES, e - 1), piece = idx % PIECES;  // clamped: a row of this segment
-      if (row >= split && row < direct) {
-        kb[i] = HK[(int64_t)(row - split) * PIECES + piece];
-        vb[i] = HV[(int64_t)(row - split) * PIECES + piece];
-      } else {
-        const int64_t src = kept[row];
-        kb[i] = BAKLAVA_MOVE_LD(K + src * PIECES + piece);
-        vb[i] = BAKLAVA_MOVE_LD(V + src * PIECES + piece);
-      }
+    if (tid < e - p0) {
+      const int src = kept[p0 + tid];
+      sc = score[src];
+      ps = pos[src];
     }
-    if (tid < kMoveRows && p0 + tid < e) {
-      const int row = p0 + tid;
-      if (row >= split && row < direct) {
-        sc = p.halo_score[sg.halo_row + row - split];
-        ps = p.halo_pos[sg.halo_row + row - split];
-      } else {
-        const int src = kept[row];
-        sc = score[src];
-        ps = pos[src];
-      }
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows are here
+    __syncthreads();                                  // and those of the others
+    if (tid == 0) __hip_atomic_store(flags + t, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // from the first of the earlier tiles that may hold a row whose source is at or past p0
+    for (int j = max(0, (t * ROWS - evicted) / ROWS - 1) + tid; j < t; j += kMoveThreads)
+      while (__hip_atomic_load(flags + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) __builtin_amdgcn_s_sleep(1);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PER_PLANE; ++i) {
       const int idx = tid + i * kMoveThreads;
-      const int row = p0 + idx / PIECES, piece = idx % PIECES;
+      const int row = p0 + idx / PIECES;
       if (row < e) {
-        BAKLAVA_MOVE_ST(K + (int64_t)row * PIECES + piece, kb[i]);
-        BAKLAVA_MOVE_ST(V + (int64_t)row * PIECES + piece, vb[i]);
+        store_nt16(K + (int64_t)row * PIECES + idx % PIECES, kb[i]);
+        store_nt16(V + (int64_t)row * PIECES + idx % PIECES, vb[i]);
       }
     }
-    if (tid < kMoveRows && p0 + tid < e) {
+    if (tid < e - p0) {
       score[p0 + tid] = sc;
       pos[p0 + tid] = ps;
     }
+    if (total <= (int)gridDim.x) return;  // a tile for each
+    if (tid == 0) next = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -943,23 +910,20 @@ hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wid
   return hipGetLastError();
 }
 
-hipError_t launch_compact_move(const CompactParams& p, int n_segs, hipStream_t s) {
-  if (n_segs <= 0) return hipSuccess;
-  const dim3 grid(n_segs);
-  switch (p.row_bytes / 16) {
-    case 8:
-      compact_halo_kernel<8><<<grid, dim3(kMoveThreads), 0, s>>>(p);
-      compact_move_kernel<8><<<grid, dim3(kMoveThreads), 0, s>>>(p);
-      break;
-    case 16:
-      compact_halo_kernel<16><<<grid, dim3(kMoveThreads), 0, s>>>(p);
-      compact_move_kernel<16><<<grid, dim3(kMoveThreads), 0, s>>>(p);
-      break;
-    case 32:
-      compact_halo_kernel<32><<<grid, dim3(kMoveThreads), 0, s>>>(p);
-      compact_move_kernel<32><<<grid, dim3(kMoveThreads), 0, s>>>(p);
-      break;
-    default: return hipErrorInvalidValue;
+hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, const int32_t* tiles_before, int n_cus,
+                               hipStream_t s) {
+  const dim3 block(kMoveThreads);
+  for (int at = 0; at < n_caches; at += kMoveCaches) {
+    const int n = std::min(kMoveCaches, n_caches - at);
+    const int tiles = tiles_before[at + n] - tiles_before[at];
+    const dim3 grid(std::max(1, std::min(tiles, 2 * n_cus)));
+    const size_t lds = (size_t)n * 4;
+    switch (p.row_bytes / 16) {
+      case 8: compact_move_kernel<8><<<grid, block, lds, s>>>(p, c0 + at, n); break;
+      case 16: compact_move_kernel<16><<<grid, block, lds, s>>>(p, c0 + at, n); break;
+      case 32: compact_move_kernel<32><<<grid, block, lds, s>>>(p, c0 + at, n); break;
+      default: return hipErrorInvalidValue;
+    }
   }
   return hipGetLastError();
 }

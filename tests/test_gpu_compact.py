@@ -199,6 +199,44 @@ def test_move_segments_of_every_length(layers, slack):
     arena.close()
 
 
+@pytest.mark.parametrize("dtype,D,tile", [("bf16", 64, 256), ("bf16", 128, 256), ("f32", 128, 128)])
+@pytest.mark.parametrize("slack", [1, 255, 257, 5000])
+def test_move_tiles_wait_for_one_another(dtype, D, tile, slack):
+    """The move takes its rows in tiles, each of which may be overwritten once the tiles before it have been read:
+    destination ranges of one row less, exactly and one row more than whole tiles, rows that move by less than a tile and
+    by many, from random places and all from the front, beside caches (the first one among them) that stay as they are."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["llama32"], name="tiles", L=3, Hq=5, Hkv=5, D=D, dtype=dtype, batch=1, seed=29,
+                     sink=0, recent=0, slack=slack)
+    rng = np.random.Generator(np.random.PCG64(w.seed + slack))
+    budgets = [60, tile - 1, tile, 2 * tile + 1, 40 * tile] * w.L
+    arena = H.make_arena(w, budgets)
+    lens = [b if c % 5 == 0 else b + slack for c, b in enumerate(budgets)]
+    st = H.fill_from_host(arena, w, lens, rng, scores="uniform")
+    for c in range(5, 10):
+        st.score[c][:slack] = 0.0
+        o = int(arena.off_host[c])
+        arena.score[o:o + lens[c]].copy_(torch.from_numpy(st.score[c]).to(arena.device))
+    after = run_compact_and_check(arena, w, st, layer_begin=1, layer_count=2)
+    for c in range(5, 15):
+        st.K[c], st.V[c], st.score[c], st.pos[c] = after.K[c], after.V[c], after.score[c], after.pos[c]
+    run_compact_and_check(arena, w, st)
+    arena.close()
+
+
+def test_move_of_more_caches_than_a_launch_serves():
+    """8190 + 5 caches of a few rows: the move takes 8192 per launch."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["llama32"], name="many", L=1, Hq=5, Hkv=5, D=64, batch=1639, seed=30, sink=1,
+                     recent=2, slack=3)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    budgets = [3, 4, 5, 9, 17]
+    arena = H.make_arena(w, budgets)
+    st = H.fill_from_host(arena, w, [budgets[c % 5] + c % 4 for c in range(arena.n_caches)], rng, scores="uniform")
+    run_compact_and_check(arena, w, st)
+    arena.close()
+
+
 @pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed", "infinite"])
 def test_caches_ranked_in_registers(scores):
     """Caches ranked from registers in blocks of 1024 rows: up to 16384 rows of capacity by one workgroup, beyond (so few
