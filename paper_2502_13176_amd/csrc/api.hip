@@ -241,8 +241,17 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk, bool fill) {
   return BAKLAVA_OK;
 }
 
-// fp32 rows for four query heads and more: the vector kernel is bound by its arithmetic, so short runs pay earlier.
+// fp32 rows for four query heads and more: the kernels are bound by their arithmetic, so short runs pay earlier (from
+// five heads on, on the matrix kernel, equal: a layer of 8 caches of 1000 to 32768 rows within 4% with either rule).
 bool slow_rows(const baklava_ctx* ctx) { return ctx->d.dtype == BAKLAVA_F32 && ctx->G >= 4; }
+
+// fp32 rows from five query heads on: the vector kernel, which takes eight then, is bound by its arithmetic, the matrix
+// kernel (which always takes sixteen) by HBM.  us per call, vector / matrix kernel, without scores and tracked, 32 caches of 4096 rows
+// a layer and 64 in one launch: D = 128, one head 25.0 / 27.5 and 43.9 / 48.8; four 29.7 / 30.0, 32.1 / 31.2 and 49.7 /
+// 52.5, 53.7 / 54.9; five 44.0 / 30.5, 47.4 / 33.2 and 69.0 / 51.9, 82.3 / 56.4; eight 44.0 / 31.2, 50.6 / 35.2 and 76.4 /
+// 52.2, 85.3 / 60.6; D = 64, four 18.0 / 18.0 and 27.3 / 28.1, eight 26.0 / 19.9 and 38.6 / 30.7.  8 caches of 300 rows,
+// D = 128, eight heads 13.3 / 11.9, of 32768 rows 67.7 / 52.2.
+bool f32_on_matrix_cores(const baklava_ctx* ctx) { return ctx->d.dtype == BAKLAVA_F32 && ctx->G >= 5; }
 
 // Which schedule a launch over the layers takes.  The short runs of schedule 0 give a single layer a work item for every
 // compute unit; over several layers that is more work items than the launch needs, each with its share of the merge.
@@ -446,6 +455,8 @@ int decode_impl(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, cons
   const bool on_dispatch = ctx->time_kernel == 2 && use_mfma;
   hipError_t e = use_mfma ? launch_decode_mfma(p, ctx->d.D, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s,
                                                on_dispatch ? ev0 : nullptr, on_dispatch ? ev1 : nullptr)
+               : ctx->kernel_pref == 0 && f32_on_matrix_cores(ctx)
+                          ? launch_decode_mfma_f32(p, ctx->d.D, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s)
                           : launch_decode_valu(p, ctx->d.dtype, ctx->d.D, i1 - i0, longest, i1 - i0 <= ctx->n_cus, s);
   if (!hip_ok(e)) return BAKLAVA_EHIP;
   if (ctx->time_kernel) {
@@ -595,6 +606,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     if (st != BAKLAVA_OK) { delete ctx; return st; }
   }
   if (desc->dtype == BAKLAVA_BF16 && !hip_ok(prepare_decode_mfma())) { delete ctx; return BAKLAVA_EHIP; }
+  if (desc->dtype == BAKLAVA_F32 && !hip_ok(prepare_decode_mfma_f32())) { delete ctx; return BAKLAVA_EHIP; }
   const int chunk = ctx->layer_one_wave ? kDefaultChunk : kDefaultChunkWhole;
   const int chunk_layer = slow_rows(ctx) ? kDefaultChunkWhole : chunk;  // (see build_schedule)
   int st = build_schedule(ctx, 0, chunk_layer, true);

@@ -193,6 +193,8 @@ hipError_t launch_decode_valu(const DecodeParams& p, int dtype, int D, int n_ite
 hipError_t launch_decode_mfma(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s,
                               hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t prepare_decode_mfma();
+hipError_t launch_decode_mfma_f32(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s);
+hipError_t prepare_decode_mfma_f32();
 // the weights of the calls on record, from the K rows alone (bf16, D = 128; needs only the lag_*,
 // k, score, items, G and scale fields)
 hipError_t launch_score_flush_mfma(const DecodeParams& p, int n_items, int max_count, hipStream_t s);

@@ -292,6 +292,40 @@ def test_kernel_timing_record(kernel, mode):
     arena.close()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G", [5, 8])
+@pytest.mark.parametrize("batch", [1, 30])
+def test_fp32_matrix_kernel_slabs(D, G, batch):
+    """fp32 rows for five query heads and more: lengths around a wavefront's slab (16 or 32 rows), a workgroup's (128 or
+    256, half that where several workgroups share a compute unit) and a work item, outputs and tracked scores against the
+    oracle.  Bound: a logit is a sum of D products over at most 2 + log2(D) roundings of at most 2^-24 of the sum of their
+    sizes, so with |q|.|k| <= S (in log2 units) a weight is off by 2^-24 (2 + log2 D) S ln 2 and an output by that times
+    the largest |v|; the sums over n rows add 2^-24 (n / 8 + 8) likewise, here less than as much again."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["tiny"], name="slabs", L=1, Hq=5 * G, Hkv=5, D=D, batch=batch, ctx=2048, seed=47 + G,
+                     slack=0)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    arena = H.make_arena(w, [40, 130, 257, 520, 1100], track=True)
+    edges = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1099, 1100]
+    lens = [([e for e in edges if e <= arena.cap_host[c]] * 30)[-1 - c // 5] for c in range(arena.n_caches)]
+    st = H.fill_from_host(arena, w, lens, rng)
+    q, q64 = H.make_q(w, rng, 1)
+    out = H.gpu_decode(arena, w, q)
+    post = H.download(arena, w)
+    for c in range(arena.n_caches):
+        _, b, hs = H.q_rows_of_cache(w, c)
+        k, v = st.K[c].astype(np.float64), st.V[c].astype(np.float64)
+        ref, p = O.decode_attn(q64[0, b, hs], k, v)
+        size = float(np.max(np.abs(q64[0, b, hs]) @ np.abs(k).T)) / np.sqrt(D)
+        tol = 2.0 ** -24 * 2 * (2 + np.log2(D)) * size * max(1.0, float(np.max(np.abs(v))))
+        assert np.max(np.abs(out[0, b, hs] - ref)) <= tol, (c, lens[c])
+        assert np.max(np.abs(post.score[c] - p.sum(axis=0))) <= G * tol, (c, lens[c])
+    # the vector kernel on the same call
+    arena.set_option(B.OPT_KERNEL, B.KERNEL_VALU)
+    assert np.max(np.abs(H.gpu_decode(arena, w, q) - out)) <= 1e-5
+    arena.close()
+
+
 @pytest.mark.parametrize("dtype,D,G", [("f32", 64, 1), ("f32", 64, 4), ("f32", 128, 3), ("f32", 128, 8), ("bf16", 64, 1),
                                        ("bf16", 64, 5), ("bf16", 64, 8), ("bf16", 128, 1)])
 def test_vector_kernel_tiles_and_rising_logits(dtype, D, G):
