@@ -43,7 +43,7 @@ struct WorkspacePlan {
   // index 0: schedule for launches over a layer sub-range, 1: for launches over the whole model, 2: for launches over
   // several layers where that of a single one would cut needlessly short runs (see schedule_for)
   size_t items[3], multi[3];
-  size_t part_o, part_ml, final_ml, logits, lag_q, lag_ml, lag_n, lag_cnt, status, kept, info, order_all, order_layer;
+  size_t part_o, part_ml, final_ml, logits, lag_q, lag_ml, lag_n, lag_cnt, flush_ticket, status, kept, info, order_all, order_layer;
   size_t move_ticket, move_flags, tiles, spread, tile_hist, sel_state, total;
   int64_t n_tiles, n_long;
   int64_t max_items;
@@ -95,7 +95,8 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
   w.lag_q = o;        o = align256(o + (records ? (size_t)n_caches * kLagRows * row_bytes : 0));
   w.lag_ml = o;       o = align256(o + (records ? (size_t)n_caches * kLagRows * 2 * 4 : 0));
   w.lag_n = o;        o = align256(o + (size_t)n_caches * kLagCalls * 4);
-  w.lag_cnt = o;      o = align256(o + (size_t)n_caches * G * 4);
+  w.lag_cnt = o;      o = o + (size_t)n_caches * G * 4;
+  w.flush_ticket = o; o = align256(o + (size_t)n_caches * 4);
   w.status = o;       o = align256(o + 256);
   w.kept = o;         o = align256(o + (size_t)total_tokens * 4);
   w.info = o;         o = align256(o + (size_t)n_caches * sizeof(CompactInfo));
@@ -351,12 +352,12 @@ int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hi
   p.lag_ml = reinterpret_cast<float*>(ctx->ws + ctx->plan.lag_ml);
   p.lag_n = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.lag_n);
   p.lag_cnt = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.lag_cnt);
+  p.flush_ticket = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.flush_ticket);
   p.G = ctx->G; p.lag_gp_log2 = ctx->lag_gp_log2;
   p.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)ctx->d.D));
   const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
                                             sc.max_count.begin() + layer_begin + layer_count);
   if (!hip_ok(launch_score_flush_mfma(p, i1 - i0, longest, s))) return BAKLAVA_EHIP;
-  if (!hip_ok(launch_fill_i32(p.lag_cnt + c0 * ctx->G, 0, (c1 - c0) * ctx->G, s))) return BAKLAVA_EHIP;
   return BAKLAVA_OK;
 }
 
@@ -579,7 +580,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     }
   }
   // No call is pending for the score pass, and the status word is clear.
-  if (!hip_ok(hipMemset(ctx->ws + ctx->plan.lag_cnt, 0, (size_t)n_caches * ctx->G * 4)) ||
+  if (!hip_ok(hipMemset(ctx->ws + ctx->plan.lag_cnt, 0, (size_t)n_caches * (ctx->G + 1) * 4)) ||
       !hip_ok(hipMemset(ctx->ws + ctx->plan.status, 0, 256))) {
     delete ctx;
     return BAKLAVA_EHIP;

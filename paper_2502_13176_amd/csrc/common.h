@@ -95,6 +95,7 @@ struct DecodeParams {
   int32_t* lag_n;                  // [n_caches, kLagCalls] rows that were live at pending call s
   int32_t* lag_cnt;                // [n_caches, G] pending calls (one counter per head, all equal:
                                    // each block of the combine kernel reads and writes its own)
+  int32_t* flush_ticket;           // [n_caches] work items of a flush that have read the count (0 at rest)
   const int32_t* cap;
   float* score;
   int32_t* pos;
@@ -195,8 +196,8 @@ hipError_t launch_decode_mfma(const DecodeParams& p, int D, int n_items, int max
 hipError_t prepare_decode_mfma();
 hipError_t launch_decode_mfma_f32(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s);
 hipError_t prepare_decode_mfma_f32();
-// the weights of the calls on record, from the K rows alone (bf16, D = 128; needs only the lag_*,
-// k, score, items, G and scale fields)
+// the weights of the calls on record, from the K rows alone, after which the records are empty (bf16, D = 128; needs
+// only the lag_*, flush_ticket, k, score, items, G and scale fields, and all work items of a cache in the launch)
 hipError_t launch_score_flush_mfma(const DecodeParams& p, int n_items, int max_count, hipStream_t s);
 hipError_t launch_profile_similarity(const void* q, const void* k, const void* v, int batch, int Hq, int Hkv,
                                      int T, float* cos_out, float* sim_out, float* lse_out, float* tile_sum,

@@ -479,11 +479,25 @@ __global__ __launch_bounds__(64 * Shape<128>::kWaves) void score_flush_mfma(Deco
   const int G = p.G;
   const int pending = p.lag_cnt[(int64_t)it.c * G];
   if (pending == 0) return;
+  // The record is empty once every work item of the cache has read its count: the last of them to get here clears it,
+  // when it is done.  (A launch that clears it behind this one takes 4.7 us.)
+  __syncthreads();
+  int before = it.nsplit - 1;  // work items that have read it earlier (thread 0)
+  if (threadIdx.x == 0 && it.nsplit > 1)
+    before = __hip_atomic_fetch_add(p.flush_ticket + it.c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  auto clear_record = [&]() {
+    if (threadIdx.x != 0 || before != it.nsplit - 1) return;
+    __hip_atomic_store(p.flush_ticket + it.c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int g = 0; g < G; ++g) p.lag_cnt[(int64_t)it.c * G + g] = 0;
+  };
   int n_seen = 0;  // rows the latest recorded call saw: no earlier one saw more
   for (int s = 0; s < kRecCalls; ++s)
     if (s < pending) n_seen = max(n_seen, p.lag_n[(int64_t)it.c * kRecCalls + s]);
   const int cnt = min(it.start + it.count, n_seen) - it.start;
-  if (cnt <= 0) return;
+  if (cnt <= 0) {
+    clear_record();
+    return;
+  }
   Record rec;
   load_record(p, it.c, G, pending, n16, jg, rec);
   const int last = cnt - 1;
@@ -550,6 +564,7 @@ __global__ __launch_bounds__(64 * Shape<128>::kWaves) void score_flush_mfma(Deco
   }
 #undef BAKLAVA_LOAD_SLAB
   if (ring_n > 0) flush_ring();
+  clear_record();
 }
 
 }  // namespace
