@@ -828,7 +828,7 @@ extern "C" int baklava_compact(baklava_ctx* ctx, int32_t layer_begin, int32_t la
   const bool spread = spread_selection(ctx, c0, c1);
   if (!hip_ok(launch_compact_select(p, (int)(c1 - c0), n_wide, whole || layer_count == 1, t1 - t0,
                                     reinterpret_cast<const SelTile*>(ctx->ws + ctx->plan.spread) + sp0,
-                                    spread ? n_spread : 0, s)))
+                                    spread ? n_spread : 0, ctx->n_cus, s)))
     return BAKLAVA_EHIP;
   if (!hip_ok(launch_compact_move(p, (int)c0, (int)(c1 - c0), ctx->move_tiles.data() + c0, ctx->n_cus, s))) return BAKLAVA_EHIP;
   for (int64_t c = c0; c < c1; ++c) {

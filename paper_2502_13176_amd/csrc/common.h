@@ -219,7 +219,7 @@ hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s
 // n_wide: caches of the range with more than kNarrowRows rows of capacity; sorted: they come first in p.order
 // n_spread > 0: the caches of up to p.long_rows rows are ranked by the workgroups spread[0 .. n_spread)
 hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
-                                 const SelTile* spread, int n_spread, hipStream_t s);
+                                 const SelTile* spread, int n_spread, int n_cus, hipStream_t s);
 // the move of caches c0 .. c0 + n_caches; tiles_before[i]: tiles of the move of the caches before c0 + i, at most
 hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, const int32_t* tiles_before, int n_cus,
                                hipStream_t s);

@@ -451,6 +451,19 @@ __global__ __launch_bounds__(kHeldThreads) void compact_select_kernel(CompactPar
   select_whole<KEYS>(p, c, sm);
 }
 
+// Wide caches (the first n_wide of the launch order, of more than kNarrowRows rows) and all others in one launch.
+__global__ __launch_bounds__(kHeldThreads) void compact_select_both_kernel(CompactParams p, int n_wide) {
+  constexpr int kWide = kHeldRows / kHeldThreads, kNarrow = kNarrowRows / kHeldThreads;
+  __shared__ union {
+    HeldShared<kWide> wide;
+    HeldShared<kNarrow> narrow;
+  } sm;
+  const int c = p.order[blockIdx.x];
+  if (p.cap[c] > p.long_rows) return;  // ranked tile by tile
+  if ((int)blockIdx.x < n_wide) select_whole<kWide>(p, c, sm.wide);
+  else select_whole<kNarrow>(p, c, sm.narrow);
+}
+
 // ---- few caches: several workgroups to each ------------------------------------------------------
 // One workgroup on each of a few caches leaves most of the chip idle.  Here a cache is cut into tiles of kTileRows rows,
 // one workgroup each, in two kernels.  The first counts the keys of every tile by their leading 11 bits and leaves
@@ -881,7 +894,7 @@ __global__ __launch_bounds__(kMoveThreads) void compact_move_kernel(CompactParam
 
 // The launch order holds the n_wide caches of more than kNarrowRows rows first when `sorted`.
 hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
-                                 const SelTile* spread, int n_spread, hipStream_t s) {
+                                 const SelTile* spread, int n_spread, int n_cus, hipStream_t s) {
   if (n_caches <= 0) return hipSuccess;
   const dim3 held(kHeldThreads);
   CompactParams q = p;
@@ -889,6 +902,13 @@ hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wid
     q.tiles = spread;
     compact_spread_count_kernel<<<dim3(n_spread), held, 0, s>>>(q);
     compact_spread_emit_kernel<<<dim3(n_spread), held, 0, s>>>(q);
+  } else if (sorted && n_wide > 0 && n_wide < n_caches && n_caches - n_wide <= 6 * ((n_cus - n_wide % n_cus) % n_cus)) {
+    // One workgroup to a compute unit instead of two, but the narrow caches run beside the wide ones instead of behind
+    // them, on the compute units that the last round of those leaves, while there are few enough for that.  us per
+    // eviction, two launches / one, wide x rows and narrow x rows: 100 x 32768 and 8 x 8000 65.5 / 53.0, 400 x 8000
+    // 77.4 / 58.4, 1000 x 4000 94.9 / 87.1, 2000 x 8000 145 / 158; 200 x 32768 and 150 x 8000 70.8 / 65.6, 400 x 16000
+    // 91.0 / 93.7, 1000 x 4000 98.9 / 107; 300 x 30000 and 400 x 8000 117 / 97.5, 2000 x 8000 183 / 186.
+    compact_select_both_kernel<<<dim3(n_caches), held, 0, s>>>(p, n_wide);
   } else {
     if (n_wide > 0)
       compact_select_kernel<kHeldRows / kHeldThreads>

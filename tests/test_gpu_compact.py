@@ -270,6 +270,33 @@ def test_caches_ranked_in_registers(scores):
     arena.close()
 
 
+@pytest.mark.parametrize("free,n_narrow", [(4, 24), (4, 25), (0, 1), (60, 1), (-100, 200)])
+def test_wide_and_narrow_caches_in_one_launch_or_two(free, n_narrow):
+    """Wide caches that leave `free` compute units idle in their last round, beside up to six narrow ones for each (one
+    launch) and more (two)."""
+    sink, recent, slack = 3, 5, 40
+    n_wide = torch.cuda.get_device_properties(0).multi_processor_count - free
+    rng = np.random.Generator(np.random.PCG64(291))
+    budgets = rng.permutation([16385 - slack + i % 3 for i in range(n_wide)] + [8 + 37 * i % 3000 for i in range(n_narrow)])
+    n = len(budgets)
+    arena = B.Arena(1, n, n, 64, 1, "bf16", [int(b) for b in budgets], slack, sink, recent, B.POLICY_SCORE, False,
+                    workspace_fill=0xFF)
+    lens = [int(c) - i % 45 for i, c in enumerate(arena.cap_host)]
+    lens = [max(1, x) for x in lens]
+    s = rng.standard_normal(arena.total_tokens).astype(np.float32)
+    arena.score.copy_(torch.from_numpy(s).to(arena.device))
+    arena.set_lengths(lens)
+    kept_dev = torch.full((arena.total_tokens,), -1, dtype=torch.int32, device=arena.device)
+    arena.compact(0, 1, kept_dev)
+    got = kept_dev.cpu().numpy()
+    assert arena.lengths().tolist() == arena.len.cpu().tolist() == [min(x, int(b)) for x, b in zip(lens, budgets)]
+    for c in range(n):
+        o = int(arena.off_host[c])
+        kept = O.compact_select(s[o:o + lens[c]], lens[c], int(budgets[c]), sink, recent)
+        assert np.array_equal(got[o:o + len(kept)], np.asarray(kept, dtype=np.int32)), f"cache {c}"
+    arena.close()
+
+
 @pytest.mark.parametrize("scores", ["uniform", "equal", "coarse", "signed", "infinite"])
 def test_wide_caches_ranked_by_one_workgroup_each(scores):
     """Beside so many caches of more than 16384 rows that sharing them would not pay, one workgroup ranks each from its
