@@ -372,6 +372,138 @@ __global__ __launch_bounds__(64 * kWaves, PIPE ? 2 : 4) void prefill_score_kerne
   }
 }
 
+// The same for launches that would leave compute units idle.  There a workgroup is a serial chain of stages, 0.6 us each,
+// and 8 sequences of 2048 tokens are 64 workgroups.  Here eight wavefronts take the same 32 keys, each a tile of 32 tokens
+// in a turn.  So that a key's weights are added in the same order as there, and the bits are the same, the wavefronts
+// hand their weights over through LDS, and each adds up those of four keys (two of the 16 a lane holds), tile after tile.
+// A turn of eight tiles takes 1.6 us, with the wavefronts in step at its two barriers; 32 heads of 2048 tokens 56 us (83).
+// Tried: sums for each wavefront, added at the end, 42 us, but other bits; the products of a turn beside the additions of
+// the one before, 60 (the rows then come half a turn ahead instead of two).
+constexpr int kParts = 8;
+__global__ __launch_bounds__(64 * kParts, 2) void prefill_score_shared_kernel(PrefillParams p) {
+  constexpr int kTile = 32;
+  // Rows of Q of a wavefront's tile, then its weights: both are its own but for the reading of the weights.
+  __shared__ __attribute__((aligned(16))) unsigned char lds_q[2][kParts][kTile * kRow];
+  __shared__ __attribute__((aligned(16))) float lds_lse[2][kParts][64];
+
+  const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n32 = lane & 31, jh = lane >> 5;
+  const int T = p.T;
+  const int n_pairs = (p.n_blocks + 1) / 2;
+  const int n_seq = gridDim.x / n_pairs;      // batch * Hkv
+  const int seq = blockIdx.x % n_seq;         // (b, kv head)
+  const int pair = blockIdx.x / n_seq;
+  const int G = p.Hq / p.Hkv;
+  const int64_t row0 = p.row_off ? p.row_off[seq] : (int64_t)seq * T;
+  const unsigned char* Kb = p.k + row0 * kRow;
+  const int64_t head0 = (int64_t)(seq / p.Hkv) * p.Hq + (int64_t)(seq % p.Hkv) * G;
+  const float cs = p.scale_log2e;
+  const int last_t0 = (T - 1) / kTokTile * kTokTile;  // first token of the prompt's last 64, which are a stage above
+  const int left0 = T - last_t0;
+  const int nt = part & 1;                            // which 32 tokens of a stage
+
+#pragma unroll 1
+  for (int half = 0; half < 2; ++half) {
+    const int block = half == 0 ? pair : p.n_blocks - 1 - pair;
+    if (half == 1 && block == pair) break;  // odd number of blocks: the middle one is alone
+    const int j0 = block * 32;
+    bf16x8_t ka[kChunks];
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c)
+      ka[c] = as_bf16x8(*reinterpret_cast<const u32x4_t*>(Kb + (int64_t)min(j0 + n32, T - 1) * kRow + c * 32 + jh * 16));
+    // this wavefront's keys: registers 2 part and 2 part + 1 of a lane
+    float acc[2] = {0.f, 0.f};
+
+    // Stages as above (heads inside tokens, from the prompt's end); part k takes tile k % 2 of every fourth one.
+    const int n_stages = G * ((T + kTokTile - 1) / kTokTile - j0 / kTokTile);
+    const int n_turns = (2 * n_stages + kParts - 1) / kParts, mine = (n_stages - part / 2 + kParts / 2 - 1) / (kParts / 2);
+    struct Place {
+      int g, back;  // head, stages of 64 tokens before the prompt's last
+    };
+    auto next = [&](Place& at) {
+#pragma unroll
+      for (int k = 0; k < kParts / 2; ++k)
+        if (++at.g == G) { at.g = 0; ++at.back; }
+    };
+    Place ld = {__builtin_amdgcn_readfirstlane((part / 2) % G), __builtin_amdgcn_readfirstlane((part / 2) / G)}, st = ld;
+    // Rows to LDS as above, two turns ahead: piece c of row r lies in slot c ^ (r % 16).  Rows past the prompt repeat the
+    // last one.  Only this wavefront reads them, so waiting for its own copies is enough.
+    const int st_row = lane / 16;
+    const uint32_t st_slot = ((lane % 16) ^ st_row) * 16;  // 4 i rows further: ^ 64 i
+    const uint32_t lds_q0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)&lds_q[0][part][0];
+    const uint32_t lds_l0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)&lds_lse[0][part][0];
+    auto copy_tile = [&](int buf) {
+      const int64_t row = (head0 + ld.g) * T + last_t0 - (int64_t)ld.back * kTokTile;
+      const unsigned char* q = p.q + row * kRow;
+      const uint32_t dst = lds_q0 + buf * (kParts * kTile * kRow);
+      uint32_t l_off = (nt * kTile + n32) * 4u;
+      if (ld.back > 0 || left0 == kTokTile) {
+        const uint32_t o = (nt * kTile + st_row) * kRow + st_slot;
+        copy_rows_4(dst, q, o, o ^ 64, o ^ 128, o ^ 192);
+        copy_rows_4(dst + 4096, q + 4096, o, o ^ 64, o ^ 128, o ^ 192);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          copy_rows(dst + i * 1024, q, min(nt * kTile + st_row + 4 * i, left0 - 1) * kRow + (st_slot ^ (64 * (i % 4))));
+        l_off = min(nt * kTile + n32, left0 - 1) * 4u;
+      }
+      copy_words(lds_l0 + buf * (kParts * 64 * 4), p.lse + row, l_off);
+      next(ld);
+    };
+    if (mine > 0) copy_tile(0);
+    if (mine > 1) copy_tile(1);
+
+#pragma unroll 1
+    for (int turn = 0; turn < n_turns; ++turn) {
+      const int buf = turn & 1;
+      unsigned char* const my_q = lds_q[buf][part];
+      if (turn < mine) {
+        if (turn + 1 < mine) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");  // all but the next turn's copies
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        floatx16_t s;
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) {
+          const bf16x8_t q = as_bf16x8(*reinterpret_cast<const u32x4_t*>(my_q + n32 * kRow + ((2 * c + jh) ^ (n32 & 15)) * 16));
+          const floatx16_t zero = {};
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[c], q, c == 0 ? zero : s, 0, 0, 0);
+        }
+        const int tok0 = last_t0 - st.back * kTokTile + nt * kTile;
+        const float nl = tok0 + n32 < T ? lds_lse[buf][part][n32] : -kNegInf;
+        if (tok0 < j0 + 31) {  // crosses the diagonal
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (j0 + 8 * (i / 4) + 4 * jh + i % 4 > tok0 + n32) s[i] = kNegInf;
+        }
+        float* const out = reinterpret_cast<float*>(my_q) + lane * 2;  // [8 pairs of keys][64 lanes][2]
+        typedef float floatx2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int i = 0; i < 16; i += 2)
+          *reinterpret_cast<floatx2_t*>(out + i * 64) =
+              floatx2_t{fast_exp2(fmaf(s[i], cs, -nl)), fast_exp2(fmaf(s[i + 1], cs, -nl))};
+        next(st);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kParts; ++k)
+        if (turn * kParts + k < 2 * n_stages) {
+          const float* in = reinterpret_cast<const float*>(lds_q[buf][k]) + (part * 64 + lane) * 2;
+          acc[0] += in[0];
+          acc[1] += in[1];
+        }
+      __syncthreads();
+      if (turn + 2 < mine) copy_tile(buf);
+    }
+    // Sum over the 32 token lanes of each half, in the pairs of the kernel above.
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int off = 16; off > 0; off >>= 1) acc[i] += __shfl_xor(acc[i], off);
+      const int r = 2 * part + i, key = j0 + 8 * (r / 4) + 4 * jh + r % 4;
+      if (n32 == 0 && key < T) p.score[row0 + key] = acc[i];
+    }
+  }
+}
+
 template <int TILES, bool PIPE>
 hipError_t launch_tiles(PrefillParams p, int64_t n_seq, hipStream_t s) {
   constexpr int kKeysPerWg = kWaves * 32 * TILES;
@@ -413,6 +545,20 @@ hipError_t launch_prefill_scores(const void* q, const void* k, const float* lse,
   // Over 334 shapes (8 to 1024 sequences of 64 to 16384 tokens, 1 to 8 heads) the rule is within 0.4% of the best on
   // average and 15% at worst (512 x 200 x 1: 15.8 against 13.8).
   const int64_t n_seq = (int64_t)batch * Hkv;
+  // Eight wavefronts for the same 32 keys while that gives at most one workgroup to each of the 256 compute units (two do
+  // not fit), unless a workgroup has so few turns that handing the weights over costs more than the others save.  us with
+  // one tile / shared, sequences x tokens x query heads of each:
+  //   1 x 2556 x 7   174 /  114      8 x 2013 x 2   44.5 / 32.2      8 x 2120 x 1   28.3 / 37.0 (272 workgroups)
+  //   2 x 246 x 7   35.4 / 20.0      8 x 2048 x 4   83.3 / 56.4     16 x 1131 x 2   30.1 / 39.6 (288)
+  //   2 x 200 x 1    9.7 /  8.6     16 x 250 x 4    22.8 / 14.1      2 x 110 x 2     7.0 /  8.4
+  //   2 x 8192 x 1  78.8 / 55.1     64 x 227 x 1    11.0 /  9.0     16 x 147 x 1     8.9 /  9.3
+  //   4 x 1993 x 7   142 / 93.6     32 x 413 x 1    12.3 / 10.7     24 x 71 x 4     10.1 /  9.9
+  const int64_t shared = n_seq * ((((int64_t)T + 31) / 32 + 1) / 2);
+  if (shared <= 256 && T > 128 && (int64_t)(Hq / Hkv) * T >= 200) {
+    p.n_blocks = (T + 31) / 32;
+    prefill_score_shared_kernel<<<dim3((unsigned)shared), dim3(64 * kParts), 0, s>>>(p);
+    return hipGetLastError();
+  }
   const int64_t narrow = n_seq * ((((int64_t)T + 127) / 128 + 1) / 2);  // workgroups with one tile
   const int64_t wide = n_seq * ((((int64_t)T + 255) / 256 + 1) / 2);    // with two
   const int64_t tokens = (int64_t)(Hq / Hkv) * T;                       // rows of Q that a sequence streams

@@ -116,6 +116,40 @@ def test_head_grouping_and_batches(batch, Hq, Hkv):
     run_dense(batch, Hq, Hkv, 300, 9700 + Hq)
 
 
+@pytest.mark.parametrize("T,G", [(129, 2), (160, 4), (191, 7), (192, 2), (193, 3), (223, 1), (255, 5), (257, 1), (320, 3), (321, 1),
+                                 (449, 7), (961, 1)])
+def test_tiles_shared_among_wavefronts(T, G):
+    """Two sequences, whose tiles eight wavefronts share: the bits of the same sequences among many (a workgroup per 128
+    or 256 keys), and within the bound of the fp64 result.  Last tiles of one token to all, numbers of tiles that eight
+    divides and does not, fewer tiles than wavefronts in the last key block, rows of an arena."""
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(T + G)
+    q = torch.randn((2, G, T, 128), generator=gen, device=dev).to(torch.bfloat16)
+    k = torch.randn((2, 1, T, 128), generator=gen, device=dev).to(torch.bfloat16)
+    _, _, lse = B.profile_similarity(q, k, k, want_cos=False, want_lse=True)
+    score = torch.full((2 * T,), float("nan"), dtype=torch.float32, device=dev)
+    B.prefill_scores(q, k, lse, score, 2, G, 1, T)
+    n = 1 + 600 // T
+    many = torch.full((2 * 64 * n * T,), float("nan"), dtype=torch.float32, device=dev)
+    B.prefill_scores(q.repeat(64 * n, 1, 1, 1), k.repeat(64 * n, 1, 1, 1), lse.repeat(64 * n, 1, 1), many, 2 * 64 * n, G, 1, T)
+    assert torch.equal(many.reshape(64 * n, 2 * T).view(torch.int32), score.view(torch.int32).expand(64 * n, 2 * T))
+    plane = torch.full((2 * T + 50, 128), float("nan"), dtype=torch.bfloat16, device=dev)
+    plane[7:7 + T], plane[30 + T:30 + 2 * T] = k[1, 0], k[0, 0]
+    at = torch.tensor([30 + T, 7], dtype=torch.int64, device=dev)
+    rows = torch.full((2 * T + 50,), float("nan"), dtype=torch.float32, device=dev)
+    B.prefill_scores(q, plane, lse, rows, 2, G, 1, T, row_off=at)
+    assert torch.equal(torch.cat([rows[30 + T:30 + 2 * T], rows[7:7 + T]]).view(torch.int32), score.view(torch.int32))
+    assert int(torch.isnan(rows).sum()) == 50
+    mask = torch.ones((T, T), dtype=torch.bool, device=dev).triu_(1)
+    for b in range(2):
+        want = torch.zeros((T,), dtype=torch.float64, device=dev)
+        for g in range(G):
+            s = q[b, g].double() @ k[b, 0].double().t().contiguous() * (np.log2(np.e) / np.sqrt(128)) - lse[b, g].double()[:, None]
+            want += torch.exp2(s.masked_fill_(mask, float("-inf"))).sum(0)
+        assert float(((score[b * T:(b + 1) * T].double() - want).abs() / want.clamp(min=1.0)).max()) <= SCORE_RTOL
+
+
 @pytest.mark.parametrize("T", [320, 384, 448, 511, 513, 577, 640, 700, 1601])
 @pytest.mark.parametrize("G", [1, 3])
 def test_stages_around_a_turn_of_the_pipeline(T, G):
