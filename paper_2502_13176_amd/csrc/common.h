@@ -22,9 +22,10 @@ __device__ __forceinline__ void store_nt16(void* ptr, uint4 v) {
 
 constexpr int kLagRows = 32;   // packed query rows of a cache's record of pending calls (score tracking)
 constexpr int kLagCalls = 8;   // most calls such a record holds
-// Eviction move: destination rows per tile by 16-byte pieces per row, threads per workgroup, caches per launch
+// Eviction move: destination rows per tile by 16-byte pieces per row (128 KiB of K and V), threads per workgroup, caches
+// per launch
 constexpr int kMoveRowsMin = 128;
-constexpr int move_rows(int pieces) { return pieces > 16 ? kMoveRowsMin : 2 * kMoveRowsMin; }
+constexpr int move_rows(int pieces) { return pieces > 16 ? kMoveRowsMin : pieces > 8 ? 2 * kMoveRowsMin : 4 * kMoveRowsMin; }
 constexpr int kMoveThreads = 512;
 constexpr int kMoveCaches = 8192;
 constexpr int kTileRows = 8192;     // rows per tile of a cache that is ranked tile by tile (one workgroup per tile and pass)

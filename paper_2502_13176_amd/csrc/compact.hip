@@ -797,14 +797,15 @@ __global__ __launch_bounds__(kSelThreads) void compact_tile_emit_kernel(CompactP
 //
 // Bound by HBM.  What reads and writes together reach here depends on how far apart the rows in flight lie: a plain
 // copy of 1 GiB runs at 6.1 to 6.3 TB/s in 16 KiB pieces in address order, at 5.4 in pieces of 256 KiB.  Hence tiles in
-// order over the whole arena, 128 KiB each (half of it K), two workgroups to a compute unit.  A workgroup per run of 1024
-// to 4096 rows behind a kernel that saved the rows which cross a run's end took 1096 us for 5 million rows of 512 bytes,
-// of which nearly all move, and 19 for the rows across the ends; this takes 870.  Tried: tiles of 128 rows, 512 threads:
-// 960; the next ticket drawn while a tile's rows are on their way, 910 (the rows in flight lie further apart); a
-// workgroup for every tile: as fast, but 60 us for 20000 workgroups that find nothing to move; a counter for each cache
-// and four tiles per workgroup: 930.
+// order over the whole arena, 128 KiB each (half of it K), and one workgroup to a compute unit.  A workgroup per run of
+// 1024 to 4096 rows, behind a kernel that saved the rows which cross a run's end, took 1096 us for 5 million rows of 512
+// bytes, of which nearly all move, and 19 for the rows across the ends; this takes 850.  Whole evictions, us: two workgroups
+// to a compute unit 901 (904), but 266240 rows 71.0 (65.7) and 135168 rows of 256 bytes 34.3 (30.5); half as many bytes per
+// tile 985; the next ticket drawn while a tile's rows are on their way 958 (the rows in flight lie further apart); a
+// workgroup for every tile 920, and where few rows move 155 (60.8), for 20000 workgroups that find nothing to do; a counter
+// for each cache and four tiles per workgroup 985.
 template <int PIECES>  // 16-byte pieces per row
-__global__ __launch_bounds__(kMoveThreads) void compact_move_kernel(CompactParams p, int c0, int n_caches) {
+__global__ __launch_bounds__(kMoveThreads, 4) void compact_move_kernel(CompactParams p, int c0, int n_caches) {
   constexpr int ROWS = move_rows(PIECES);
   static_assert(ROWS <= kMoveThreads && ROWS >= kMoveRowsMin, "a thread per score, a flag per tile");
   extern __shared__ int sh_end[];  // tiles of the caches up to and with this one
@@ -936,7 +937,7 @@ hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, con
   for (int at = 0; at < n_caches; at += kMoveCaches) {
     const int n = std::min(kMoveCaches, n_caches - at);
     const int tiles = tiles_before[at + n] - tiles_before[at];
-    const dim3 grid(std::max(1, std::min(tiles, 2 * n_cus)));
+    const dim3 grid(std::max(1, std::min(tiles, n_cus)));
     const size_t lds = (size_t)n * 4;
     switch (p.row_bytes / 16) {
       case 8: compact_move_kernel<8><<<grid, block, lds, s>>>(p, c0 + at, n); break;

@@ -199,7 +199,7 @@ def test_move_segments_of_every_length(layers, slack):
     arena.close()
 
 
-@pytest.mark.parametrize("dtype,D,tile", [("bf16", 64, 256), ("bf16", 128, 256), ("f32", 128, 128)])
+@pytest.mark.parametrize("dtype,D,tile", [("bf16", 64, 512), ("bf16", 128, 256), ("f32", 128, 128)])
 @pytest.mark.parametrize("slack", [1, 255, 257, 5000])
 def test_move_tiles_wait_for_one_another(dtype, D, tile, slack):
     """The move takes its rows in tiles, each of which may be overwritten once the tiles before it have been read:
