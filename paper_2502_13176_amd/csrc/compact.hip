@@ -799,7 +799,7 @@ __global__ __launch_bounds__(kSelThreads) void compact_tile_emit_kernel(CompactP
 // copy of 1 GiB runs at 6.1 to 6.3 TB/s in 16 KiB pieces in address order, at 5.4 in pieces of 256 KiB.  Hence tiles in
 // order over the whole arena, 128 KiB each (half of it K), and one workgroup to a compute unit.  A workgroup per run of
 // 1024 to 4096 rows, behind a kernel that saved the rows which cross a run's end, took 1096 us for 5 million rows of 512
-// bytes, of which nearly all move, and 19 for the rows across the ends; this takes 850.  Whole evictions, us: two workgroups
+// bytes, of which nearly all move, and 19 for the rows across the ends; this takes 877.  Whole evictions, us: two workgroups
 // to a compute unit 901 (904), but 266240 rows 71.0 (65.7) and 135168 rows of 256 bytes 34.3 (30.5); half as many bytes per
 // tile 985; the next ticket drawn while a tile's rows are on their way 958 (the rows in flight lie further apart); a
 // workgroup for every tile 920, and where few rows move 155 (60.8), for 20000 workgroups that find nothing to do; a counter
