@@ -72,9 +72,9 @@ def test_decode_step_replays_from_a_graph(track, warm):
     arena.close()
 
 
-def _replay_setup(track, slack, seed, dtype="bf16", D=128):
+def _replay_setup(track, slack, seed, dtype="bf16", D=128, Hq=8):
     H = _h()
-    w = synth.shrink(synth.WORKLOADS["llama32"], name="graphstep", L=3, Hq=8, Hkv=2, batch=2, seed=seed, slack=slack,
+    w = synth.shrink(synth.WORKLOADS["llama32"], name="graphstep", L=3, Hq=Hq, Hkv=2, batch=2, seed=seed, slack=slack,
                      interval=slack, sink=4, recent=16, dtype=dtype, D=D)
     rng = np.random.Generator(np.random.PCG64(w.seed))
     budgets = [900, 300, 2500, 80, 700, 1300]
@@ -193,3 +193,47 @@ def test_replayed_step_finds_a_cache_full():
     assert arena.lengths().tolist() == arena.cap_host.tolist() == arena.len.cpu().tolist()
     arena.sync_lengths()                           # reported once
     arena.close()
+
+
+@pytest.mark.parametrize("Hq,D", [(16, 128), (10, 64)])
+def test_fp32_matrix_step_replays_from_a_graph(Hq, D):
+    """fp32 with five query heads per cache and more: six replays, with an eviction after every third, against the oracle
+    and, bit for bit, against a second arena that takes the same steps eagerly."""
+    H, w, rng, budgets, arena, st, bufs, graph = _replay_setup(True, slack=3, seed=59, dtype="f32", D=D, Hq=Hq)
+    eager = H.make_arena(w, budgets, track=True)
+    H.fill_from_host(eager, w, st.lens(), np.random.Generator(np.random.PCG64(w.seed)), scores="uniform")
+    dev = arena.device
+    for t in range(1, 7):
+        before = H.download(arena, w)
+        q, q64 = H.make_q(w, rng, w.L)
+        knew = synth.payload(rng, (w.L, w.batch, w.Hkv, w.D), w.dtype)
+        vnew = synth.payload(rng, (w.L, w.batch, w.Hkv, w.D), w.dtype)
+        for name, a in (("q", q), ("k", knew), ("v", vnew)):
+            bufs[name].copy_(H.to_device_storage(a, w.dtype, dev))
+        bufs["pos"].fill_(7000 + t)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        out_e = torch.full_like(bufs["out"], float("nan"))
+        for l in range(w.L):
+            eager.append_decode_attn(l, 1, bufs["k"][l], bufs["v"][l], 7000 + t, bufs["q"][l], out_e[l])
+        torch.cuda.synchronize()
+        assert torch.equal(out_e, bufs["out"]), f"step {t}: replay and eager launches differ"
+        out = bufs["out"].cpu().numpy().astype(np.float64)
+        k64, v64 = synth.storage_to_f64(knew, w.dtype), synth.storage_to_f64(vnew, w.dtype)
+        for c in range(arena.n_caches):
+            l, b, hs = H.q_rows_of_cache(w, c)
+            ref, _, _ = O.decode_step(H.oracle_cache(w, before, c), q64[l, b, hs], k64[l, b, c % w.Hkv],
+                                      v64[l, b, c % w.Hkv], 7000 + t, t, 0, 0, 0, 0, False)
+            assert float(np.max(np.abs(out[l, b, hs] - ref))) <= H.ATTN_TOL, f"step {t} cache {c}"
+        arena.sync_lengths()                       # the replays move the lengths on the device only
+        if t % 3 == 0:
+            arena.compact(0, w.L)
+            eager.compact(0, w.L)
+            torch.cuda.synchronize()
+        a, e = H.download(arena, w), H.download(eager, w)
+        for c in range(arena.n_caches):
+            assert np.array_equal(a.K[c], e.K[c]) and np.array_equal(a.V[c], e.V[c]) and np.array_equal(a.pos[c], e.pos[c])
+            assert np.array_equal(a.score[c].view(np.uint32), e.score[c].view(np.uint32))
+    arena.close()
+    eager.close()
