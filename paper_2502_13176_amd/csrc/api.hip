@@ -585,13 +585,15 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     delete ctx;
     return BAKLAVA_EHIP;
   }
-  // Tiles of the eviction move, at most (a cache's rows move from the first evicted one on).
+  // Tiles of the eviction move, at most (a cache's rows move from the first evicted one on; none of one whose budget is
+  // not below its capacity).
   {
     const int64_t rows = move_rows(ctx->row_bytes / 16);
     int64_t tiles = 0;
     ctx->move_tiles.assign(n_caches + 1, 0);
     for (int64_t c = 0; c < n_caches; ++c) {
-      tiles += (ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv] + rows - 1) / rows;
+      const int32_t b = ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv];
+      tiles += b < ctx->cap[c] ? (b + rows - 1) / rows : 0;
       ctx->move_tiles[c + 1] = (int32_t)std::min<int64_t>(tiles, INT32_MAX);
     }
   }

@@ -68,10 +68,13 @@ __device__ __forceinline__ SelGoal sel_goal(const CompactParams& p, int c) {
 // First flag of a cache's tiles: each of the caches before it has at most one tile more than its rows fill.
 __device__ __forceinline__ int64_t move_flag_base(int64_t off, int c) { return off / kMoveRowsMin + c; }
 
-// The move behind the selection starts at the cache's first tile, with no tile read yet.  By one whole workgroup.
-__device__ __forceinline__ void clear_move_state(const CompactParams& p, int c, int64_t off, int budget) {
+// The move behind the selection starts at the cache's first tile, with no tile read yet.  By one whole workgroup.  A
+// cache within its budget has no tile, and its flags would not hold one per 128 rows of the budget, which may lie above
+// the capacity; a cache beyond its budget has more rows of capacity than that.
+__device__ __forceinline__ void clear_move_state(const CompactParams& p, int c, int64_t off, const SelGoal& g) {
   int32_t* flags = p.move_flags + move_flag_base(off, c);
-  for (int t = threadIdx.x; t * kMoveRowsMin < budget; t += blockDim.x) flags[t] = 0;
+  const int n_flags = g.n > g.b ? (int)(((int64_t)g.b + kMoveRowsMin - 1) / kMoveRowsMin) : 0;
+  for (int t = threadIdx.x; t < n_flags; t += blockDim.x) flags[t] = 0;
   if (threadIdx.x == 0) p.move_ticket[c] = 0;
 }
 
@@ -397,7 +400,7 @@ __device__ __forceinline__ void select_whole(const CompactParams& p, int c, Held
   const int n = g.n;
   const int64_t off = p.off[c];
   int32_t* kept = p.kept + off;
-  clear_move_state(p, c, off, g.b);
+  clear_move_state(p, c, off, g);
 
   if (n <= g.b) {
     if (p.write_identity)
@@ -493,7 +496,7 @@ __global__ __launch_bounds__(kHeldThreads) void compact_spread_count_kernel(Comp
   }
   const int tid = threadIdx.x;
   const SelGoal g = sel_goal(p, tl.c);
-  if (tl.tile == 0) clear_move_state(p, tl.c, p.off[tl.c], g.b);
+  if (tl.tile == 0) clear_move_state(p, tl.c, p.off[tl.c], g);
   if (tl.tile == 0 && tid == 0)  // the second kernel lowers first_moved with atomicMin
     p.info[tl.c] = g.n <= g.b ? CompactInfo{g.n, g.n, g.n, 0} : CompactInfo{g.b, g.k > 0 ? g.n : g.mid_lo, g.n, 0};
   if (g.n <= g.b || g.k <= 0) return;
@@ -714,7 +717,7 @@ __global__ __launch_bounds__(kSelThreads) void compact_tile_count_kernel(Compact
   const int c = tl.c;
   const int tid = threadIdx.x;
   const SelGoal g = sel_goal(p, c);
-  if (PASS == 0 && tl.tile == 0) clear_move_state(p, c, p.off[c], g.b);
+  if (PASS == 0 && tl.tile == 0) clear_move_state(p, c, p.off[c], g);
   if (PASS == 0 && tl.tile == 0 && tid == 0) {
     // the selection's result record; the emit kernel lowers first_moved with atomicMin
     p.info[c] = g.n <= g.b ? CompactInfo{g.n, g.n, g.n, 0} : CompactInfo{g.b, g.n, g.n, 0};

@@ -1,5 +1,7 @@
 """GPU parity: baklava_compact against the oracle's eviction -- kept-index lists and lengths
 bit-exact, moved K/V/score/pos rows bit-identical to the rows they came from."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -221,6 +223,44 @@ def test_move_tiles_wait_for_one_another(dtype, D, tile, slack):
     for c in range(5, 15):
         st.K[c], st.V[c], st.score[c], st.pos[c] = after.K[c], after.V[c], after.score[c], after.pos[c]
     run_compact_and_check(arena, w, st)
+    arena.close()
+
+
+@pytest.mark.parametrize("policy", [B.POLICY_SCORE, B.POLICY_STREAMING])
+@pytest.mark.parametrize("never,tiled_rows", [("cap", None), ("cap + 1", None), (10**6, 8192), (2**31 - 1, None), (2**31 - 1, 8192)])
+def test_budgets_at_and_above_the_capacity(policy, never, tiled_rows):
+    """A budget that is not below the capacity is a cache that never evicts, on every way the selection takes (one
+    workgroup, several, tile by tile), in front of, between and behind caches that do.  A layer of such caches alone
+    leaves 20 bytes of a result each in the workspace, and nothing is written behind the workspace."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["llama32"], name="never", L=3, Hq=6, Hkv=6, D=64, batch=1, seed=33, sink=2,
+                     recent=0 if policy == B.POLICY_STREAMING else 3, slack=40)
+    rows = [24, 300, 130, 17000, 70000, 24]
+    arena = H.make_arena(w, rows * w.L, policy=policy)
+    arena.close()
+    cap = np.asarray(arena.cap_host, dtype=np.int64)
+    unlimited = [True] * 6 + [True, False, True, False, True, False] + [False, True, False, True, False, True]
+    arena.budget_host = np.array([{"cap": cap[c], "cap + 1": cap[c] + 1}.get(never, never) if u else rows[c % 6]
+                                  for c, u in enumerate(unlimited)]).astype(np.int32)
+    arena.budget.copy_(torch.from_numpy(arena.budget_host).to(arena.device))
+    d, i32, i64 = arena.desc, C.POINTER(C.c_int32), C.POINTER(C.c_int64)
+    cap_p, budget_p = arena.cap_host.ctypes.data_as(i32), arena.budget_host.ctypes.data_as(i32)
+    ws_bytes = B.lib().baklava_workspace_bytes(C.byref(d), cap_p, budget_p)
+    ws = torch.full((ws_bytes + (1 << 20),), 0xFF, dtype=torch.uint8, device=arena.device)
+    d.workspace, d.workspace_bytes = ws.data_ptr(), ws_bytes
+    ctx = C.c_void_p()
+    assert B.lib().baklava_create(C.byref(d), arena.off_host.ctypes.data_as(i64), cap_p, None, budget_p, C.byref(ctx)) == B.OK
+    arena.ctx = ctx
+    if tiled_rows:
+        arena.set_option(B.OPT_TILED_SELECT_ROWS, tiled_rows)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    st = H.fill_from_host(arena, w, cap.tolist(), rng, scores="uniform")
+    before = ws.clone()
+    run_compact_and_check(arena, w, st, policy, layer_begin=0, layer_count=1, want_lists=False)
+    assert int((ws != before).sum()) <= 20 * 6
+    after = run_compact_and_check(arena, w, st, policy, layer_begin=2, layer_count=1)
+    run_compact_and_check(arena, w, after, policy)
+    assert bool((ws[ws_bytes:] == 0xFF).all())
     arena.close()
 
 
