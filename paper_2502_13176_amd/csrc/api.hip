@@ -131,7 +131,7 @@ struct baklava_ctx {
   std::vector<int64_t> off;
   std::vector<int32_t> cap, len, budget;
   std::vector<int32_t> order_all, order_layer;  // caches, longest first (whole model / inside each layer)
-  std::vector<int32_t> move_tiles;          // cache -> tiles of the eviction move for the caches before it
+  std::vector<MoveCount> move_before;           // cache -> work of the eviction move for the caches before it
   std::vector<int32_t> tile_begin;              // cache -> first tile of the tiled selection (long caches only have any)
   std::vector<int32_t> spread_begin;            // cache -> first tile of the selection by several workgroups per cache
   std::vector<int32_t> n_wide;                  // layer -> caches with more than kNarrowRows rows of capacity
@@ -585,17 +585,15 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     delete ctx;
     return BAKLAVA_EHIP;
   }
-  // Tiles of the eviction move, at most (a cache's rows move from the first evicted one on; none of one whose budget is
-  // not below its capacity).
-  {
-    const int64_t rows = move_rows(ctx->row_bytes / 16);
-    int64_t tiles = 0;
-    ctx->move_tiles.assign(n_caches + 1, 0);
-    for (int64_t c = 0; c < n_caches; ++c) {
-      const int32_t b = ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv];
-      tiles += b < ctx->cap[c] ? (b + rows - 1) / rows : 0;
-      ctx->move_tiles[c + 1] = (int32_t)std::min<int64_t>(tiles, INT32_MAX);
-    }
+  // Work of the eviction move, at most (rows move from the first evicted one on; none of a cache whose budget is not
+  // below its capacity).
+  ctx->move_before.assign(n_caches + 1, MoveCount{0, 0});
+  for (int64_t c = 0; c < n_caches; ++c) {
+    const int64_t rows = move_rows(ctx->row_bytes / 16), b = ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv];
+    MoveCount& m = ctx->move_before[c + 1];
+    m = ctx->move_before[c];
+    if (b < ctx->cap[c] && b > kMoveRowsMin) m.tiles += (b + rows - 1) / rows;
+    if (b < ctx->cap[c] && b <= kMoveRowsMin) m.short_caches += 1;
   }
   // Eviction: a cache of up to kHeldRows rows is ranked by one workgroup that holds its scores in
   // registers, or by several (see spread_selection), a longer one tile by tile.  Measured, us per eviction,
@@ -832,7 +830,7 @@ extern "C" int baklava_compact(baklava_ctx* ctx, int32_t layer_begin, int32_t la
                                     reinterpret_cast<const SelTile*>(ctx->ws + ctx->plan.spread) + sp0,
                                     spread ? n_spread : 0, ctx->n_cus, s)))
     return BAKLAVA_EHIP;
-  if (!hip_ok(launch_compact_move(p, (int)c0, (int)(c1 - c0), ctx->move_tiles.data() + c0, ctx->n_cus, s))) return BAKLAVA_EHIP;
+  if (!hip_ok(launch_compact_move(p, (int)c0, (int)(c1 - c0), ctx->move_before.data() + c0, ctx->n_cus, s))) return BAKLAVA_EHIP;
   for (int64_t c = c0; c < c1; ++c) {
     const int32_t b = ctx->budget[(c / ctx->cpl) * ctx->d.Hkv + c % ctx->d.Hkv];
     ctx->len[c] = std::min(ctx->len[c], b);

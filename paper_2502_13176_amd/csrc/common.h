@@ -221,8 +221,14 @@ hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s
 // n_spread > 0: the caches of up to p.long_rows rows are ranked by the workgroups spread[0 .. n_spread)
 hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
                                  const SelTile* spread, int n_spread, int n_cus, hipStream_t s);
-// the move of caches c0 .. c0 + n_caches; tiles_before[i]: tiles of the move of the caches before c0 + i, at most
-hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, const int32_t* tiles_before, int n_cus,
+// Sums over the caches before one, of those that can evict: tiles of the move for caches of more than kMoveRowsMin rows of
+// budget, at most, and caches of no more.
+struct MoveCount {
+  int64_t tiles;
+  int32_t short_caches;
+};
+// the move of caches c0 .. c0 + n_caches, behind the selection; before[i]: the sums for cache c0 + i
+hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, const MoveCount* before, int n_cus,
                                hipStream_t s);
 hipError_t launch_stream_probe(void* dst, const void* src, int64_t bytes, int mode, hipStream_t s);
 

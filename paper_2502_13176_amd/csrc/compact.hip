@@ -807,10 +807,91 @@ __global__ __launch_bounds__(kSelThreads) void compact_tile_emit_kernel(CompactP
 // tile 985; the next ticket drawn while a tile's rows are on their way 958 (the rows in flight lie further apart); a
 // workgroup for every tile 920, and where few rows move 155 (60.8), for 20000 workgroups that find nothing to do; a counter
 // for each cache and four tiles per workgroup 985.
-template <int PIECES>  // 16-byte pieces per row
-__global__ __launch_bounds__(kMoveThreads, 4) void compact_move_kernel(CompactParams p, int c0, int n_caches) {
-  constexpr int ROWS = move_rows(PIECES);
+//
+// Caches of up to kMoveRowsMin rows are one tile, so they need neither tickets nor flags: a workgroup moves each.  As
+// tiles among the others they left a compute unit idle for most of the latency of a ticket, a table and a row, and were
+// slower than runs had been.  Whole evictions, us, runs / tiles / this, rows of 256 bytes where nothing else is said: 1263
+// caches of 19 rows 41.4 / 54.8 / 38.8, 695 of 50 33.0 / 38.6 / 30.4, 8 of 58 16.4 / 16.8 / 14.8, 2892 of 18 rows of 128
+// bytes 79.7 / 111 / 73.9.  Beside longer caches workgroups behind those that draw tickets serve them, two to a compute
+// unit, where they are a quarter of all or more (one that finds a longer cache is launched for nothing): 2253 caches of
+// up to 751 rows, 93% short, 81.2 / 91.6 / 73.2; 835 caches, 56% short, 51.8 / 51.1 / 46.2; 2292 caches, 27% short, 211 /
+// 164 / 161; 3296 caches of 128-byte rows, one of them of 20000, 125 / 145 / 117.
+
+// The rows of a tile on their way.  PIECES: 16-byte pieces per row.
+template <int PIECES, int ROWS>
+struct MoveTile {
   static_assert(ROWS <= kMoveThreads && ROWS >= kMoveRowsMin, "a thread per score, a flag per tile");
+  static constexpr int kPerPlane = ROWS * PIECES / kMoveThreads;  // pieces per thread and plane
+  uint4 kb[kPerPlane], vb[kPerPlane];
+  float sc;
+  int ps;
+
+  // Destination rows p0 .. e of the cache at `off`; ends with a barrier behind which the workgroup has read all of them.
+  __device__ __forceinline__ void load(const CompactParams& p, int64_t off, int p0, int e) {
+    const uint4* K = reinterpret_cast<const uint4*>(p.k) + off * PIECES;
+    const uint4* V = reinterpret_cast<const uint4*>(p.v) + off * PIECES;
+    const int32_t* kept = p.kept + off;
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < kPerPlane; ++i) {
+      const int idx = tid + i * kMoveThreads;
+      const int64_t src = kept[min(p0 + idx / PIECES, e - 1)];  // clamped: a row of this tile
+      kb[i] = load_nt16(K + src * PIECES + idx % PIECES);
+      vb[i] = load_nt16(V + src * PIECES + idx % PIECES);
+    }
+    sc = 0.f;
+    ps = 0;
+    if (tid < e - p0) {
+      const int src = kept[p0 + tid];
+      sc = p.score[off + src];
+      ps = p.pos[off + src];
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows are here
+    __syncthreads();                                  // and those of the others
+  }
+
+  __device__ __forceinline__ void store(const CompactParams& p, int64_t off, int p0, int e) const {
+    uint4* K = reinterpret_cast<uint4*>(p.k) + off * PIECES;
+    uint4* V = reinterpret_cast<uint4*>(p.v) + off * PIECES;
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < kPerPlane; ++i) {
+      const int idx = tid + i * kMoveThreads;
+      const int row = p0 + idx / PIECES;
+      if (row < e) {
+        store_nt16(K + (int64_t)row * PIECES + idx % PIECES, kb[i]);
+        store_nt16(V + (int64_t)row * PIECES + idx % PIECES, vb[i]);
+      }
+    }
+    if (tid < e - p0) {
+      p.score[off + p0 + tid] = sc;
+      p.pos[off + p0 + tid] = ps;
+    }
+  }
+};
+
+// The move of a cache of up to kMoveRowsMin rows by one workgroup.
+template <int PIECES>
+__device__ __forceinline__ void move_short(const CompactParams& p, int c) {
+  const CompactInfo info = p.info[c];
+  const int first = info.first_moved, b = info.new_len;
+  if (first >= b || b > kMoveRowsMin) return;  // no row moves, or the cache has tiles
+  const int64_t off = p.off[c];
+  MoveTile<PIECES, kMoveRowsMin> tile;
+  tile.load(p, off, first, b);
+  tile.store(p, off, first, b);
+}
+
+// Workgroups 0 .. n_tickets draw tiles; those behind them, if any, take the caches of up to short_rows rows, which then
+// have no tiles.
+template <int PIECES>
+__global__ __launch_bounds__(kMoveThreads, 4) void compact_move_kernel(CompactParams p, int c0, int n_caches, int n_tickets,
+                                                                       int short_rows) {
+  if ((int)blockIdx.x >= n_tickets) {
+    move_short<PIECES>(p, c0 + (int)blockIdx.x - n_tickets);
+    return;
+  }
+  constexpr int ROWS = move_rows(PIECES);
   extern __shared__ int sh_end[];  // tiles of the caches up to and with this one
   __shared__ int sh_scan[kMoveThreads / 64];
   __shared__ int sh_tile;
@@ -824,7 +905,7 @@ __global__ __launch_bounds__(kMoveThreads, 4) void compact_move_kernel(CompactPa
     int n = 0;
     if (i < n_caches) {
       const CompactInfo info = p.info[c0 + i];
-      n = max(0, info.new_len - info.first_moved + ROWS - 1) / ROWS;
+      n = info.new_len <= short_rows ? 0 : max(0, info.new_len - info.first_moved + ROWS - 1) / ROWS;
       if (blockIdx.x == 0 && info.first_moved < info.old_len) p.len[c0 + i] = info.new_len;
     }
     int all;
@@ -832,7 +913,6 @@ __global__ __launch_bounds__(kMoveThreads, 4) void compact_move_kernel(CompactPa
     if (i < n_caches) sh_end[i] = total + n;
     total += all;
   }
-  constexpr int PER_PLANE = ROWS * PIECES / kMoveThreads;  // pieces per thread and plane
   for (;;) {
     if (tid == 0) sh_tile = next;
     __syncthreads();
@@ -847,51 +927,30 @@ __global__ __launch_bounds__(kMoveThreads, 4) void compact_move_kernel(CompactPa
     const CompactInfo info = p.info[c];
     const int b = info.new_len, first = info.first_moved, evicted = info.old_len - b;
     const int64_t off = p.off[c];
-    const int32_t* kept = p.kept + off;
-    uint4* K = reinterpret_cast<uint4*>(p.k) + off * PIECES;
-    uint4* V = reinterpret_cast<uint4*>(p.v) + off * PIECES;
-    float* score = p.score + off;
-    int32_t* pos = p.pos + off;
     int32_t* flags = p.move_flags + move_flag_base(off, c);
     const int p0 = first + t * ROWS, e = min(p0 + ROWS, b);
-    uint4 kb[PER_PLANE], vb[PER_PLANE];
-#pragma unroll
-    for (int i = 0; i < PER_PLANE; ++i) {
-      const int idx = tid + i * kMoveThreads;
-      const int64_t src = kept[min(p0 + idx / PIECES, e - 1)];  // clamped: a row of this tile
-      kb[i] = load_nt16(K + src * PIECES + idx % PIECES);
-      vb[i] = load_nt16(V + src * PIECES + idx % PIECES);
-    }
-    float sc = 0.f;
-    int ps = 0;
-    if (tid < e - p0) {
-      const int src = kept[p0 + tid];
-      sc = score[src];
-      ps = pos[src];
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows are here
-    __syncthreads();                                  // and those of the others
+    MoveTile<PIECES, ROWS> tile;
+    tile.load(p, off, p0, e);
     if (tid == 0) __hip_atomic_store(flags + t, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // from the first of the earlier tiles that may hold a row whose source is at or past p0
     for (int j = max(0, (t * ROWS - evicted) / ROWS - 1) + tid; j < t; j += kMoveThreads)
       while (__hip_atomic_load(flags + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) __builtin_amdgcn_s_sleep(1);
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < PER_PLANE; ++i) {
-      const int idx = tid + i * kMoveThreads;
-      const int row = p0 + idx / PIECES;
-      if (row < e) {
-        store_nt16(K + (int64_t)row * PIECES + idx % PIECES, kb[i]);
-        store_nt16(V + (int64_t)row * PIECES + idx % PIECES, vb[i]);
-      }
-    }
-    if (tid < e - p0) {
-      score[p0 + tid] = sc;
-      pos[p0 + tid] = ps;
-    }
-    if (total <= (int)gridDim.x) return;  // a tile for each
+    tile.store(p, off, p0, e);
+    if (total <= n_tickets) return;  // a tile for each
     if (tid == 0) next = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+}
+
+// The same for launches in which no cache has more rows.
+template <int PIECES>
+__global__ __launch_bounds__(kMoveThreads, PIECES > 16 ? 4 : 8) void compact_move_short_kernel(CompactParams p, int c0) {
+  const int c = c0 + blockIdx.x;
+  if (threadIdx.x == 0) {
+    const CompactInfo info = p.info[c];
+    if (info.first_moved < info.old_len) p.len[c] = info.new_len;
+  }
+  move_short<PIECES>(p, c);
 }
 
 }  // namespace
@@ -934,18 +993,30 @@ hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wid
   return hipGetLastError();
 }
 
-hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, const int32_t* tiles_before, int n_cus,
-                               hipStream_t s) {
+template <int PIECES>
+void launch_move(const CompactParams& p, int c0, int n_caches, int64_t n_tiles, int n_short, int n_cus, hipStream_t s) {
   const dim3 block(kMoveThreads);
+  if (n_tiles == 0) {
+    compact_move_short_kernel<PIECES><<<dim3(n_caches), block, 0, s>>>(p, c0);
+    return;
+  }
+  const bool apart = 4 * (int64_t)n_short >= n_caches;
+  const int n_tickets = (int)std::min<int64_t>(apart ? n_tiles : n_tiles + n_short, n_cus);
+  compact_move_kernel<PIECES><<<dim3(n_tickets + (apart ? n_caches : 0)), block, (size_t)n_caches * 4, s>>>(
+      p, c0, n_caches, n_tickets, apart ? kMoveRowsMin : 0);
+}
+
+hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, const MoveCount* before, int n_cus,
+                               hipStream_t s) {
   for (int at = 0; at < n_caches; at += kMoveCaches) {
     const int n = std::min(kMoveCaches, n_caches - at);
-    const int tiles = tiles_before[at + n] - tiles_before[at];
-    const dim3 grid(std::max(1, std::min(tiles, n_cus)));
-    const size_t lds = (size_t)n * 4;
+    const int64_t n_tiles = before[at + n].tiles - before[at].tiles;
+    const int n_short = before[at + n].short_caches - before[at].short_caches;
+    if (n_tiles == 0 && n_short == 0) continue;  // no cache has more rows than its budget
     switch (p.row_bytes / 16) {
-      case 8: compact_move_kernel<8><<<grid, block, lds, s>>>(p, c0 + at, n); break;
-      case 16: compact_move_kernel<16><<<grid, block, lds, s>>>(p, c0 + at, n); break;
-      case 32: compact_move_kernel<32><<<grid, block, lds, s>>>(p, c0 + at, n); break;
+      case 8: launch_move<8>(p, c0 + at, n, n_tiles, n_short, n_cus, s); break;
+      case 16: launch_move<16>(p, c0 + at, n, n_tiles, n_short, n_cus, s); break;
+      case 32: launch_move<32>(p, c0 + at, n, n_tiles, n_short, n_cus, s); break;
       default: return hipErrorInvalidValue;
     }
   }
