@@ -96,7 +96,7 @@ WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const in
   w.lag_ml = o;       o = align256(o + (records ? (size_t)n_caches * kLagRows * 2 * 4 : 0));
   w.lag_n = o;        o = align256(o + (size_t)n_caches * kLagCalls * 4);
   w.lag_cnt = o;      o = o + (size_t)n_caches * G * 4;
-  w.flush_ticket = o; o = align256(o + (size_t)n_caches * 4);
+  w.flush_ticket = o; o = align256(o + (size_t)n_caches * kTicketStride * 4);
   w.status = o;       o = align256(o + 256);
   w.kept = o;         o = align256(o + (size_t)total_tokens * 4);
   w.info = o;         o = align256(o + (size_t)n_caches * sizeof(CompactInfo));
@@ -352,12 +352,17 @@ int flush_records(baklava_ctx* ctx, int32_t layer_begin, int32_t layer_count, hi
   p.lag_ml = reinterpret_cast<float*>(ctx->ws + ctx->plan.lag_ml);
   p.lag_n = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.lag_n);
   p.lag_cnt = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.lag_cnt);
-  p.flush_ticket = reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.flush_ticket);
+  // The flush empties the records itself while no cache has more work items than draw a ticket faster than a launch
+  // behind the flush takes (see score_flush_mfma).
+  const bool self_clear = *std::max_element(sc.max_split.begin() + layer_begin,
+                                            sc.max_split.begin() + layer_begin + layer_count) <= kMostTickets;
+  p.flush_ticket = self_clear ? reinterpret_cast<int32_t*>(ctx->ws + ctx->plan.flush_ticket) : nullptr;
   p.G = ctx->G; p.lag_gp_log2 = ctx->lag_gp_log2;
   p.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)ctx->d.D));
   const int32_t longest = *std::max_element(sc.max_count.begin() + layer_begin,
                                             sc.max_count.begin() + layer_begin + layer_count);
   if (!hip_ok(launch_score_flush_mfma(p, i1 - i0, longest, s))) return BAKLAVA_EHIP;
+  if (!self_clear && !hip_ok(launch_fill_i32(p.lag_cnt + c0 * ctx->G, 0, (c1 - c0) * ctx->G, s))) return BAKLAVA_EHIP;
   return BAKLAVA_OK;
 }
 
@@ -580,7 +585,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
     }
   }
   // No call is pending for the score pass, and the status word is clear.
-  if (!hip_ok(hipMemset(ctx->ws + ctx->plan.lag_cnt, 0, (size_t)n_caches * (ctx->G + 1) * 4)) ||
+  if (!hip_ok(hipMemset(ctx->ws + ctx->plan.lag_cnt, 0, (size_t)n_caches * (ctx->G + kTicketStride) * 4)) ||
       !hip_ok(hipMemset(ctx->ws + ctx->plan.status, 0, 256))) {
     delete ctx;
     return BAKLAVA_EHIP;

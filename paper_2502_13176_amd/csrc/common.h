@@ -22,6 +22,8 @@ __device__ __forceinline__ void store_nt16(void* ptr, uint4 v) {
 
 constexpr int kLagRows = 32;   // packed query rows of a cache's record of pending calls (score tracking)
 constexpr int kLagCalls = 8;   // most calls such a record holds
+constexpr int kTicketStride = 32;  // words from one cache's flush ticket to the next: a cache line each
+constexpr int kMostTickets = 128;  // most work items of a cache that draw them
 // Eviction move: destination rows per tile by 16-byte pieces per row (128 KiB of K and V), threads per workgroup, caches
 // per launch
 constexpr int kMoveRowsMin = 128;
@@ -96,7 +98,8 @@ struct DecodeParams {
   int32_t* lag_n;                  // [n_caches, kLagCalls] rows that were live at pending call s
   int32_t* lag_cnt;                // [n_caches, G] pending calls (one counter per head, all equal:
                                    // each block of the combine kernel reads and writes its own)
-  int32_t* flush_ticket;           // [n_caches] work items of a flush that have read the count (0 at rest)
+  int32_t* flush_ticket;           // [n_caches * kTicketStride] work items of a flush that are done (0 at rest), or
+                                   // null: a launch behind the flush empties the records
   const int32_t* cap;
   float* score;
   int32_t* pos;
@@ -197,8 +200,9 @@ hipError_t launch_decode_mfma(const DecodeParams& p, int D, int n_items, int max
 hipError_t prepare_decode_mfma();
 hipError_t launch_decode_mfma_f32(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s);
 hipError_t prepare_decode_mfma_f32();
-// the weights of the calls on record, from the K rows alone, after which the records are empty (bf16, D = 128; needs
-// only the lag_*, flush_ticket, k, score, items, G and scale fields, and all work items of a cache in the launch)
+// the weights of the calls on record, from the K rows alone, after which the records are empty where flush_ticket is not
+// null (bf16, D = 128; needs only the lag_*, flush_ticket, k, score, items, G and scale fields, and all work items of a
+// cache in the launch)
 hipError_t launch_score_flush_mfma(const DecodeParams& p, int n_items, int max_count, hipStream_t s);
 hipError_t launch_profile_similarity(const void* q, const void* k, const void* v, int batch, int Hq, int Hkv,
                                      int T, float* cos_out, float* sim_out, float* lse_out, float* tile_sum,

@@ -427,6 +427,34 @@ def test_256_step_trajectory_on_a_small_replica_of_the_long_workload():
     arena.close()
 
 
+@pytest.mark.parametrize("G", [1, 7])
+def test_flushes_empty_the_records_of_caches_of_any_number_of_work_items(G):
+    """A flush's last work item of each cache empties its record: caches of one to 256 work items beside each other, by
+    layer and over all layers, several flushes with one and two calls between them.  Every attention row sums to 1, so the
+    scores of a cache sum to G for each call; a flush right behind another changes no bit."""
+    H = _h()
+    w = synth.shrink(synth.WORKLOADS["long"], name="tickets", L=3, Hq=3 * G, Hkv=3, batch=1, slack=0, sink=0, recent=0, seed=89)
+    budgets = [63, 700, 16384, 40, 64, 65, 1500, 256, 9000]
+    arena = H.make_arena(w, budgets, track=True)
+    rng = np.random.Generator(np.random.PCG64(w.seed))
+    H.fill_from_host(arena, w, budgets, rng, scores="zero")
+    calls = np.zeros(3)
+    for lb, lc, n in ((0, 1, 1), (0, 3, 2), (2, 1, 2), (0, 2, 1), (1, 2, 1), (0, 3, 1)):
+        for _ in range(n):
+            q, _ = H.make_q(w, rng, lc)
+            H.gpu_decode(arena, w, q, layer_begin=lb, layer_count=lc)
+        calls[lb:lb + lc] += n
+        arena.flush_scores(lb, lc)
+        first = arena.score.clone()
+        arena.flush_scores(lb, lc)
+        arena.flush_scores(0, 3)
+        assert torch.equal(first, arena.score)
+        for c, b in enumerate(budgets):
+            got = float(first[int(arena.off_host[c]):int(arena.off_host[c]) + b].double().sum())
+            assert abs(got - G * calls[c // 3]) <= 1e-4 * G * calls[c // 3] + 1e-6, (lb, lc, c)
+    arena.close()
+
+
 def test_records_survive_option_changes_and_are_dropped_with_the_rows():
     """What the deferred score update has on record must come out right whatever happens between the
     calls: the other attention kernel takes over (it first adds what is on record), tracking is paused
