@@ -594,11 +594,12 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
   // below its capacity).
   ctx->move_before.assign(n_caches + 1, MoveCount{0, 0});
   for (int64_t c = 0; c < n_caches; ++c) {
-    const int64_t rows = move_rows(ctx->row_bytes / 16), b = ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv];
+    const int64_t rows = move_rows(ctx->row_bytes / 16), most_short = move_short_rows(ctx->row_bytes / 16);
+    const int64_t b = ctx->budget[(c / ctx->cpl) * desc->Hkv + c % desc->Hkv];
     MoveCount& m = ctx->move_before[c + 1];
     m = ctx->move_before[c];
-    if (b < ctx->cap[c] && b > kMoveRowsMin) m.tiles += (b + rows - 1) / rows;
-    if (b < ctx->cap[c] && b <= kMoveRowsMin) m.short_caches += 1;
+    if (b < ctx->cap[c] && b > most_short) m.tiles += (b + rows - 1) / rows;
+    if (b < ctx->cap[c] && b <= most_short) m.short_caches += 1;
   }
   // Eviction: a cache of up to kHeldRows rows is ranked by one workgroup that holds its scores in
   // registers, or by several (see spread_selection), a longer one tile by tile.  Measured, us per eviction,

@@ -28,6 +28,8 @@ constexpr int kMostTickets = 128;  // most work items of a cache that draw them
 // per launch
 constexpr int kMoveRowsMin = 128;
 constexpr int move_rows(int pieces) { return pieces > 16 ? kMoveRowsMin : pieces > 8 ? 2 * kMoveRowsMin : 4 * kMoveRowsMin; }
+// most rows of a cache that one workgroup moves (half a tile, or a whole one of 512-byte rows)
+constexpr int move_short_rows(int pieces) { return pieces > 8 ? kMoveRowsMin : 2 * kMoveRowsMin; }
 constexpr int kMoveThreads = 512;
 constexpr int kMoveCaches = 8192;
 constexpr int kTileRows = 8192;     // rows per tile of a cache that is ranked tile by tile (one workgroup per tile and pass)
@@ -225,8 +227,8 @@ hipError_t launch_fill_i32(int32_t* dst, int32_t value, int64_t n, hipStream_t s
 // n_spread > 0: the caches of up to p.long_rows rows are ranked by the workgroups spread[0 .. n_spread)
 hipError_t launch_compact_select(const CompactParams& p, int n_caches, int n_wide, bool sorted, int n_tiles,
                                  const SelTile* spread, int n_spread, int n_cus, hipStream_t s);
-// Sums over the caches before one, of those that can evict: tiles of the move for caches of more than kMoveRowsMin rows of
-// budget, at most, and caches of no more.
+// Sums over the caches before one, of those that can evict: tiles of the move for caches of more than move_short_rows rows
+// of budget, at most, and caches of no more.
 struct MoveCount {
   int64_t tiles;
   int32_t short_caches;

@@ -808,7 +808,7 @@ __global__ __launch_bounds__(kSelThreads) void compact_tile_emit_kernel(CompactP
 // workgroup for every tile 920, and where few rows move 155 (60.8), for 20000 workgroups that find nothing to do; a counter
 // for each cache and four tiles per workgroup 985.
 //
-// Caches of up to kMoveRowsMin rows are one tile, so they need neither tickets nor flags: a workgroup moves each.  As
+// Caches of up to move_short_rows rows are one tile, so they need neither tickets nor flags: a workgroup moves each.  As
 // tiles among the others they left a compute unit idle for most of the latency of a ticket, a table and a row, and were
 // slower than runs had been.  Whole evictions, us, runs / tiles / this, rows of 256 bytes where nothing else is said: 1263
 // caches of 19 rows 41.4 / 54.8 / 38.8, 695 of 50 33.0 / 38.6 / 30.4, 8 of 58 16.4 / 16.8 / 14.8, 2892 of 18 rows of 128
@@ -870,14 +870,14 @@ struct MoveTile {
   }
 };
 
-// The move of a cache of up to kMoveRowsMin rows by one workgroup.
+// The move of a cache of up to move_short_rows rows by one workgroup.
 template <int PIECES>
 __device__ __forceinline__ void move_short(const CompactParams& p, int c) {
   const CompactInfo info = p.info[c];
   const int first = info.first_moved, b = info.new_len;
-  if (first >= b || b > kMoveRowsMin) return;  // no row moves, or the cache has tiles
+  if (first >= b || b > move_short_rows(PIECES)) return;  // no row moves, or the cache has tiles
   const int64_t off = p.off[c];
-  MoveTile<PIECES, kMoveRowsMin> tile;
+  MoveTile<PIECES, move_short_rows(PIECES)> tile;
   tile.load(p, off, first, b);
   tile.store(p, off, first, b);
 }
@@ -1003,7 +1003,7 @@ void launch_move(const CompactParams& p, int c0, int n_caches, int64_t n_tiles, 
   const bool apart = 4 * (int64_t)n_short >= n_caches;
   const int n_tickets = (int)std::min<int64_t>(apart ? n_tiles : n_tiles + n_short, n_cus);
   compact_move_kernel<PIECES><<<dim3(n_tickets + (apart ? n_caches : 0)), block, (size_t)n_caches * 4, s>>>(
-      p, c0, n_caches, n_tickets, apart ? kMoveRowsMin : 0);
+      p, c0, n_caches, n_tickets, apart ? move_short_rows(PIECES) : 0);
 }
 
 hipError_t launch_compact_move(const CompactParams& p, int c0, int n_caches, const MoveCount* before, int n_cus,

@@ -266,11 +266,13 @@ def test_budgets_at_and_above_the_capacity(policy, never, tiled_rows):
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("f32", 128)])
 @pytest.mark.parametrize("budgets", [[20, 127, 128, 64], [20, 127, 128, 129], [129, 3000, 128, 20], [129, 700, 128, 3000],
-                                     [129, 700, 128, 3000, 511, 512, 513], [128, 3, 20, 128, 127]])
+                                     [129, 700, 128, 3000, 511, 512, 513], [128, 3, 20, 128, 127],
+                                     [255, 256, 20, 129], [257, 256, 3000, 600]])
 @pytest.mark.parametrize("slack", [1, 129, 1000])
 def test_short_caches_apart_from_tiles(dtype, D, budgets, slack):
-    """A workgroup moves a cache of up to 128 rows of budget where a quarter of all caches or more have no more: all of them,
-    that many, exactly a quarter and fewer, some of them within their budget, by the whole and by one layer."""
+    """A workgroup moves a cache of up to 128 rows of budget (256 of 128 bytes) where a quarter of all caches or more have no
+    more: all of them, that many, exactly a quarter and fewer, some of them within their budget, by the whole and by one
+    layer."""
     H = _h()
     n = len(budgets)
     w = synth.shrink(synth.WORKLOADS["llama32"], name="short", L=2, Hq=n, Hkv=n, D=D, dtype=dtype, batch=3, seed=34, sink=1,
@@ -284,15 +286,14 @@ def test_short_caches_apart_from_tiles(dtype, D, budgets, slack):
     arena.close()
 
 
-@pytest.mark.parametrize("longer", [None, 5, 131])
+@pytest.mark.parametrize("longer", [None, 5, 261])
 def test_move_of_more_caches_than_a_launch_serves(longer):
-    """8190 + 5 caches of a few rows, some of them in one of two forms with others of more than 128: the move takes 8192 per
-    launch."""
+    """8190 + 5 caches of a few rows, alone and beside others of more than 256: the move takes 8192 per launch."""
     H = _h()
     w = synth.shrink(synth.WORKLOADS["llama32"], name="many", L=1, Hq=5, Hkv=5, D=64, batch=1639, seed=30, sink=1,
                      recent=2, slack=3)
     rng = np.random.Generator(np.random.PCG64(w.seed))
-    budgets = [3, 4, 5, 9, 17] if longer is None else [129, longer, 4, 130, 129]
+    budgets = [3, 4, 5, 9, 17] if longer is None else [259, longer, 4, 260, 259]
     arena = H.make_arena(w, budgets)
     st = H.fill_from_host(arena, w, [budgets[c % 5] + c % 4 for c in range(arena.n_caches)], rng, scores="uniform")
     run_compact_and_check(arena, w, st)
