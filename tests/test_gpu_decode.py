@@ -326,19 +326,23 @@ def test_fp32_matrix_kernel_slabs(D, G, batch):
     arena.close()
 
 
-@pytest.mark.parametrize("dtype,D,G", [("f32", 64, 1), ("f32", 64, 4), ("f32", 128, 3), ("f32", 128, 8), ("bf16", 64, 1),
-                                       ("bf16", 64, 5), ("bf16", 64, 8), ("bf16", 128, 1)])
-def test_vector_kernel_tiles_and_rising_logits(dtype, D, G):
-    """The vector kernel's workgroups of 16 and of 8 wavefronts: lengths around a wavefront's and a
-    workgroup's tile, with logits that climb along the cache by less and by more than the reference
-    maximum may lag (8 in log2 units), and the scores its second pass adds."""
+F32_MATRIX = [("f32", D, G, B.KERNEL_AUTO) for D in (64, 128) for G in (5, 8)]
+
+
+@pytest.mark.parametrize("dtype,D,G,kernel", [(*shape, B.KERNEL_VALU) for shape in (
+    ("f32", 64, 1), ("f32", 64, 4), ("f32", 128, 3), ("f32", 128, 8), ("bf16", 64, 1), ("bf16", 64, 5), ("bf16", 64, 8),
+    ("bf16", 128, 1))] + F32_MATRIX)
+def test_kernel_tiles_and_rising_logits(dtype, D, G, kernel):
+    """The vector kernel's workgroups of 16 and of 8 wavefronts and the fp32 matrix kernel: lengths around a
+    wavefront's and a workgroup's tile, with logits that climb along the cache by little and by 40 a row, so that
+    every tile raises the maximum, and the scores that the vector kernel's second pass or the kept logits add."""
     H = _h()
     lens = [1, 15, 17, 32, 33, 127, 128, 129, 255, 257, 511, 512, 513, 1025]
     w = synth.shrink(synth.WORKLOADS["tiny"], name="valu", L=1, Hq=G * len(lens), Hkv=len(lens), D=D, batch=1,
                      dtype=dtype, seed=91, sink=1, recent=1, slack=0)
     rng = np.random.Generator(np.random.PCG64(w.seed + G))
     arena = H.make_arena(w, [2048] * len(lens), track=True)
-    arena.set_option(B.OPT_KERNEL, B.KERNEL_VALU)
+    arena.set_option(B.OPT_KERNEL, kernel)
     q, q64 = H.make_q(w, rng, w.L)
     for step in (0.0, 0.02, 40.0):                 # natural units of the logit per row
         st = H.fill_from_host(arena, w, lens, rng)
@@ -475,34 +479,37 @@ def test_matrix_kernel_with_half_size_rows(Hq, Hkv):
     arena.close()
 
 
-@pytest.mark.parametrize("D,kernel", [(64, B.KERNEL_AUTO), (64, B.KERNEL_VALU), (128, B.KERNEL_MFMA), (128, B.KERNEL_VALU)])
-def test_rows_whose_logits_are_minus_infinity(D, kernel):
+@pytest.mark.parametrize("dtype,D,G,kernel", [("bf16", 64, 4, B.KERNEL_AUTO), ("bf16", 64, 4, B.KERNEL_VALU),
+                                              ("bf16", 128, 4, B.KERNEL_MFMA), ("bf16", 128, 4, B.KERNEL_VALU),
+                                              ("f32", 64, 8, B.KERNEL_VALU), ("f32", 128, 3, B.KERNEL_AUTO)] + F32_MATRIX)
+def test_rows_whose_logits_are_minus_infinity(dtype, D, G, kernel):
     """Keys of the type's lowest value (a mask) give logits of -inf: such rows carry no weight, wherever they
     fill a wavefront's first rows, a work item's, or all but one row of a cache."""
     H = _h()
     lens = [40, 300, 700, 1300]
     masked = [39, 64, 512, 1299]                   # rows in front
-    w = synth.shrink(synth.WORKLOADS["llama1"], name="masked", L=1, Hq=16, Hkv=4, D=D, batch=1, seed=94, sink=1, recent=1,
-                     slack=0)
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="masked", L=1, Hq=4 * G, Hkv=4, D=D, batch=1, dtype=dtype, seed=94, sink=1,
+                     recent=1, slack=0)
     rng = np.random.Generator(np.random.PCG64(w.seed))
     arena = H.make_arena(w, [2048] * 4)
     arena.set_option(B.OPT_KERNEL, kernel)
     st = H.fill_from_host(arena, w, lens, rng)
     for c, n in enumerate(masked):
-        st.K[c][:n] = 0xFF7F                       # -3.4e38, times queries above zero
+        st.K[c][:n] = 0xFF7F if dtype == "bf16" else np.finfo(np.float32).min   # -3.4e38, times queries above zero
         o = int(arena.off_host[c])
         arena.k[o:o + lens[c]].copy_(H.to_device_storage(st.K[c], w.dtype, arena.device))
     q, q64 = H.make_q(w, rng, w.L)
-    q, q64 = q & 0x7FFF, np.abs(q64)
+    q, q64 = q & 0x7FFF if dtype == "bf16" else np.abs(q), np.abs(q64)
     for chunk in (256, 512, 2048):
         H.set_chunk(arena, chunk)
         H.check_decode_against_oracle(arena, w, st, q64, H.gpu_decode(arena, w, q))
     arena.close()
 
 
-@pytest.mark.parametrize("dtype,D,G", [("f32", 64, 1), ("f32", 128, 4), ("f32", 64, 8), ("bf16", 64, 2), ("bf16", 128, 8)])
-def test_values_near_the_ends_of_the_range(dtype, D, G):
-    """The vector kernel on values whose plain sum over the rows just fits fp32 and on values close to the
+@pytest.mark.parametrize("dtype,D,G,kernel", [(*shape, B.KERNEL_VALU) for shape in (
+    ("f32", 64, 1), ("f32", 128, 4), ("f32", 64, 8), ("bf16", 64, 2), ("bf16", 128, 8))] + F32_MATRIX)
+def test_values_near_the_ends_of_the_range(dtype, D, G, kernel):
+    """The vector kernel and the fp32 matrix kernel on values whose plain sum over the rows just fits fp32 and on values close to the
     smallest normal number, with logits that rise along the cache by less than 8 in log2 units: weights above
     1 would overflow the one, weights far below 1 would lose the other."""
     H = _h()
@@ -511,7 +518,7 @@ def test_values_near_the_ends_of_the_range(dtype, D, G):
                      recent=1, slack=0)
     rng = np.random.Generator(np.random.PCG64(w.seed + G))
     arena = H.make_arena(w, [n])
-    arena.set_option(B.OPT_KERNEL, B.KERNEL_VALU)
+    arena.set_option(B.OPT_KERNEL, kernel)
     H.set_chunk(arena, 2048)                       # one work item
     st = H.fill_from_host(arena, w, [n], rng)
     q = np.zeros((1, 1, G, D), dtype=np.float32)
@@ -531,26 +538,33 @@ def test_values_near_the_ends_of_the_range(dtype, D, G):
     arena.close()
 
 
-@pytest.mark.parametrize("kernel", [B.KERNEL_AUTO, B.KERNEL_VALU])
-def test_infinite_values_with_half_size_rows(kernel):
-    """bf16 rows of 64 elements: an infinite element of V makes that element of the outputs infinite, also in the
-    row with the largest weight (1, which needs one bf16 term only), and leaves the others alone."""
+@pytest.mark.parametrize("dtype,D,G,kernel", [("bf16", 64, 4, B.KERNEL_AUTO), ("bf16", 64, 4, B.KERNEL_VALU),
+                                              ("f32", 128, 8, B.KERNEL_VALU)] + F32_MATRIX)
+def test_infinite_values(dtype, D, G, kernel):
+    """bf16 rows of 64 elements and fp32 rows: an infinite element of V makes that element of the outputs infinite, also in
+    the row with the largest weight (1, which needs one bf16 term only), and leaves the others alone.  On the fp32 matrix
+    kernel in the cache's last row too, which stands in for the rows past the end."""
     H = _h()
-    n, G = 700, 4
-    w = synth.shrink(synth.WORKLOADS["llama1"], name="inf", L=1, Hq=G, Hkv=1, D=64, batch=1, seed=96, sink=1, recent=1, slack=0)
+    n = 700
+    w = synth.shrink(synth.WORKLOADS["llama1"], name="inf", L=1, Hq=G, Hkv=1, D=D, batch=1, dtype=dtype, seed=96, sink=1,
+                     recent=1, slack=0)
     rng = np.random.Generator(np.random.PCG64(w.seed))
     arena = H.make_arena(w, [n])
     arena.set_option(B.OPT_KERNEL, kernel)
     st = H.fill_from_host(arena, w, [n], rng)
     q, q64 = H.make_q(w, rng, w.L)
-    K = synth.storage_to_f64(st.K[0], "bf16")
-    _, p = O.decode_attn(q64[0, 0], K, synth.storage_to_f64(st.V[0], "bf16"))
+    K = synth.storage_to_f64(st.K[0], dtype)
+    _, p = O.decode_attn(q64[0, 0], K, synth.storage_to_f64(st.V[0], dtype))
+    inf, minus_inf = (0x7F80, 0xFF80) if dtype == "bf16" else (np.inf, -np.inf)
     for g in range(G):
-        st.V[0][np.argmax(p[g]), g] = 0x7F80                     # +inf
-        st.V[0][np.argsort(p[g])[n // 2], 8 + g] = 0xFF80        # -inf
-    arena.v[:n].copy_(H.to_device_storage(st.V[0], "bf16", arena.device))
-    ref, _ = O.decode_attn(q64[0, 0], K, synth.storage_to_f64(st.V[0], "bf16"))
-    assert np.isinf(ref).sum() == 2 * G * G
+        st.V[0][np.argmax(p[g]), g] = inf
+        st.V[0][np.argsort(p[g])[n // 2], 8 + g] = minus_inf
+    last = kernel == B.KERNEL_AUTO and dtype == "f32"
+    if last:
+        st.V[0][n - 1, 20] = inf
+    arena.v[:n].copy_(H.to_device_storage(st.V[0], dtype, arena.device))
+    ref, _ = O.decode_attn(q64[0, 0], K, synth.storage_to_f64(st.V[0], dtype))
+    assert np.isinf(ref).sum() == (2 * G + last) * G
     for chunk in (256, 1024):
         H.set_chunk(arena, chunk)
         out = H.gpu_decode(arena, w, q)[0, 0]

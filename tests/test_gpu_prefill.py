@@ -76,8 +76,9 @@ def test_prompt_lengths_around_every_tile_boundary(T):
                          [(T, 24) for T in (1500, 1536, 1537, 1599, 1793)])
 def test_many_sequences(T, batch):
     """A launch of many sequences: every eighth prompt against the oracle, the others by their mass (each
-    attention row sums to 1), and two of them in a launch of their own, which takes the pipelined form with one
-    tile: all forms add a key's weights in the same order, so the bits are the same."""
+    attention row sums to 1), and 16 of them in a launch of their own, whose tiles eight wavefronts share (129 to 513
+    tokens) or which takes the pipelined form with one tile (the others): all forms add a key's weights in the same order,
+    so the bits are the same."""
     run_many(T, batch, 2, 9900 + T)
 
 
@@ -152,10 +153,15 @@ def test_tiles_shared_among_wavefronts(T, G):
 
 @pytest.mark.parametrize("T", [320, 384, 448, 511, 513, 577, 640, 700, 1601])
 @pytest.mark.parametrize("G", [1, 3])
-def test_stages_around_a_turn_of_the_pipeline(T, G):
+@pytest.mark.parametrize("batch", [1, 8])
+def test_stages_around_a_turn_of_the_pipeline(T, G, batch):
     """One and three query heads per KV head: the stages below the diagonal end anywhere in a turn of four, and
-    few follow, so that the copies ahead meet the end of the prompt inside a turn."""
-    run_dense(1, G, 1, T, 9750 + T + G)
+    few follow, so that the copies ahead meet the end of the prompt inside a turn.  One sequence, whose tiles eight
+    wavefronts share, and 8 x 8 of them, which take the pipelined form with one tile."""
+    if batch == 1:
+        run_dense(1, G, 1, T, 9750 + T + G)
+    else:
+        run_many(T, batch, G, 9750 + T + G)
 
 
 def test_peaked_and_large_logits():

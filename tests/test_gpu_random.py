@@ -19,7 +19,7 @@ SHAPES = [
     ("bf16", 128, 8, 2, (B.KERNEL_VALU, B.KERNEL_MFMA)), ("bf16", 128, 7, 1, (B.KERNEL_VALU, B.KERNEL_MFMA)),
     ("bf16", 128, 4, 4, (B.KERNEL_VALU, B.KERNEL_MFMA)), ("bf16", 128, 12, 1, (B.KERNEL_MFMA,)),
     ("bf16", 128, 32, 2, (B.KERNEL_MFMA,)), ("bf16", 128, 5, 5, (B.KERNEL_VALU, B.KERNEL_MFMA)),
-    ("bf16", 64, 6, 2, (B.KERNEL_VALU,)), ("f32", 64, 8, 1, (B.KERNEL_VALU,)), ("f32", 128, 3, 1, (B.KERNEL_VALU,)),
+    ("bf16", 64, 6, 2, (B.KERNEL_VALU,)), ("f32", 64, 8, 1, (B.KERNEL_VALU, B.KERNEL_AUTO)), ("f32", 128, 3, 1, (B.KERNEL_VALU,)),
 ]
 
 
