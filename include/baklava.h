@@ -154,7 +154,7 @@ typedef struct {
   const int64_t* off;     /* DEVICE [n_caches] first row of cache c                                  */
   const int32_t* cap;     /* DEVICE [n_caches] rows cache c can hold                                 */
   int32_t* len;           /* DEVICE [n_caches] live rows of cache c (authoritative copy)             */
-  const int32_t* budget;  /* DEVICE [L*Hkv]                                                          */
+  const int32_t* budget;  /* DEVICE [L*Hkv]; one that is not below a cache's capacity: it never evicts */
   void* workspace;        /* DEVICE scratch, 256-byte aligned, baklava_workspace_bytes() bytes       */
   size_t workspace_bytes;
 } baklava_desc;
@@ -162,8 +162,8 @@ typedef struct {
 /*
  * Bytes of device workspace a context with this description needs: split partials (G * (D + 2)
  * floats for each work item of 256 rows, or of 64 up to 256 items a layer), work-item tables,
- * kept-index lists, the counters of the eviction move, the tables and counters of the selection of
- * caches of more than 8192 rows, and with track_scores the query rows and softmax normalisers of
+ * kept-index lists, the counters of the eviction move and of the flush, the tables and counters of the
+ * selection of caches of more than 8192 rows, and with track_scores the query rows and softmax normalisers of
  * the attention calls each cache has on record (bf16 rows of 128 elements) or the logits of one
  * call (F32 and rows of 64 elements: 4 * G bytes per cached row, which at bf16, D = 64 and eight
  * query heads is an eighth of K and V).  Pointer fields of `desc` are ignored.  cap_host HOST
@@ -194,13 +194,15 @@ enum {
   BAKLAVA_OPT_CHUNK_TOKENS = 1, /* shortest run of rows per split-K work item for launches over part of
                                    the layers (multiple of 64, >= 256); the item target below may
                                    lengthen it                                                        */
-  BAKLAVA_OPT_KERNEL = 2,       /* 0 = automatic (MFMA kernel for bf16, vector-ALU kernel for F32), 1 =
+  BAKLAVA_OPT_KERNEL = 2,       /* 0 = automatic (MFMA kernel for bf16; for F32 the vector-ALU kernel up to
+                                   four query heads per KV head, an fp32 MFMA kernel from five on), 1 =
                                    vector-ALU kernel, 2 = MFMA kernel with recorded scores (bf16, D=128;
-                                   EINVAL otherwise, also at D=64, where automatic choice takes it)   */
+                                   EINVAL otherwise, also at D=64 and for F32, where automatic choice
+                                   takes an MFMA kernel)                                              */
   BAKLAVA_OPT_TIME_KERNEL = 3,  /* time every attention partial-kernel launch with a pair of HIP events
                                    (baklava_profile_read): 1 = recorded on the stream before and
-                                   after the launch, 2 = carried by the kernel's own dispatch (MFMA
-                                   kernel; the other kernel is timed as under 1), 0 = off.  ESTATE
+                                   after the launch, 2 = carried by the kernel's own dispatch (bf16
+                                   MFMA kernel; the others are timed as under 1), 0 = off.  ESTATE
                                    while timings taken in another mode are still unread.  A
                                    measurement aid: leave it off while a stream is being captured  */
   BAKLAVA_OPT_CHUNK_TOKENS_WHOLE = 4, /* the same for launches over all layers at once               */

@@ -67,7 +67,7 @@ bool shape_ok(const baklava_desc* d) {
 // Scores are deferred over bf16 rows of 128 elements only (see decode_impl).
 bool keeps_records(const baklava_desc* d) { return d->dtype == BAKLAVA_BF16 && d->D == 128; }
 
-WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap, const int32_t* budget) {
+WorkspacePlan plan_workspace(const baklava_desc* d, const int32_t* cap) {
   WorkspacePlan w{};
   const int64_t n_caches = (int64_t)d->L * d->batch * d->Hkv;
   const int G = d->Hq / d->Hkv;
@@ -242,16 +242,17 @@ int build_schedule(baklava_ctx* ctx, int which, int chunk, bool fill) {
   return BAKLAVA_OK;
 }
 
-// fp32 rows for four query heads and more: the kernels are bound by their arithmetic, so short runs pay earlier (from
-// five heads on, on the matrix kernel, equal: a layer of 8 caches of 1000 to 32768 rows within 4% with either rule).
+// fp32 rows for four query heads and more: the vector kernel is bound by its arithmetic there, so short runs pay earlier.
+// The matrix kernel, which takes over from five on, is bound by HBM and indifferent: a layer of 8 caches of 1000 to 32768
+// rows within 4% with either rule.
 bool slow_rows(const baklava_ctx* ctx) { return ctx->d.dtype == BAKLAVA_F32 && ctx->G >= 4; }
 
 // fp32 rows from five query heads on: the vector kernel, which takes eight then, is bound by its arithmetic, the matrix
-// kernel (which always takes sixteen) by HBM.  us per call, vector / matrix kernel, without scores and tracked, 32 caches of 4096 rows
-// a layer and 64 in one launch: D = 128, one head 25.0 / 27.5 and 43.9 / 48.8; four 29.7 / 30.0, 32.1 / 31.2 and 49.7 /
+// kernel (which always takes sixteen, of which at most eight are there) by HBM.  us per call, vector / matrix kernel,
+// without scores and tracked, 32 caches of 4096 rows a layer and 64 in one launch: D = 128, one head 25.0 / 27.5 and 43.9 / 48.8; four 29.7 / 30.0, 32.1 / 31.2 and 49.7 /
 // 52.5, 53.7 / 54.9; five 44.0 / 30.5, 47.4 / 33.2 and 69.0 / 51.9, 82.3 / 56.4; eight 44.0 / 31.2, 50.6 / 35.2 and 76.4 /
 // 52.2, 85.3 / 60.6; D = 64, four 18.0 / 18.0 and 27.3 / 28.1, eight 26.0 / 19.9 and 38.6 / 30.7.  8 caches of 300 rows,
-// D = 128, eight heads 13.3 / 11.9, of 32768 rows 67.7 / 52.2.
+// D = 128, eight heads 13.3 / 11.9, of 32768 rows 67.7 / 52.2; 40 of 30 rows 7.8 / 7.8, tracked 11.7 / 11.9.
 bool f32_on_matrix_cores(const baklava_ctx* ctx) { return ctx->d.dtype == BAKLAVA_F32 && ctx->G >= 5; }
 
 // Which schedule a launch over the layers takes.  The short runs of schedule 0 give a single layer a work item for every
@@ -499,7 +500,7 @@ extern "C" size_t baklava_workspace_bytes(const baklava_desc* desc, const int32_
     if (cap_host[c] < 0) return 0;
   for (int64_t i = 0; i < (int64_t)desc->L * desc->Hkv; ++i)
     if (budget_host[i] < 0) return 0;
-  return plan_workspace(desc, cap_host, budget_host).total;
+  return plan_workspace(desc, cap_host).total;
 }
 
 extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host, const int32_t* cap_host,
@@ -562,7 +563,7 @@ extern "C" int baklava_create(const baklava_desc* desc, const int64_t* off_host,
   ctx->time_kernel = 0;
   ctx->track_on = desc->track_scores != 0;
   ctx->ev_used = 0;
-  ctx->plan = plan_workspace(desc, cap_host, budget_host);
+  ctx->plan = plan_workspace(desc, cap_host);
   ctx->ws = reinterpret_cast<char*>(desc->workspace);
   if (desc->workspace_bytes < ctx->plan.total) { delete ctx; return BAKLAVA_ECAPACITY; }
 

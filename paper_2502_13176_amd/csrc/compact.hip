@@ -215,8 +215,8 @@ __device__ __forceinline__ void emit_rows(const float* score, int32_t* kept, con
 // Bound by vector issue (about 40 instructions per key on one compute unit) and the latency of a dozen
 // barriers, not by bandwidth.  Sweeping the scores once per pass (four passes of 8 bits and the emit, 512
 // threads) took 90 us for 512 caches of 128 to 32768 rows, this takes 53; tile by tile (below) 8 caches of
-// 32768 rows took 46 us in five kernels, here 36 in one.  KEYS = 16 (caches of up to 16384 rows) needs 52
-// registers, so two workgroups fit a compute unit; KEYS = 64 needs 100, so one does.
+// 32768 rows took 46 us in five kernels, here 36 in one.  KEYS = 16 (caches of up to 16384 rows) needs at
+// most 64 registers, so two workgroups fit a compute unit; KEYS = 64 needs more, so one does.
 constexpr int kHeldThreads = 1024;
 constexpr int kHeldWaves = kHeldThreads / 64;
 constexpr int kHeldBins = 2048;

@@ -1,5 +1,5 @@
-// Decode attention over ragged caches of fp32 rows, matrix version (D = 128 or 64, up to 16 query heads per KV head; taken
-// from five heads on).
+// Decode attention over ragged caches of fp32 rows, matrix version (D = 128 or 64, up to 8 query heads per KV head, the most
+// that fp32 caches may have; taken from five on).
 //
 // Both products of a tile of 16 rows run on v_mfma_f32_16x16x4_f32, whose operands, products and sums are fp32, with
 // the G query heads on the N side (padded to 16):
@@ -314,7 +314,7 @@ hipError_t prepare_decode_mfma_f32() {
 
 hipError_t launch_decode_mfma_f32(const DecodeParams& p, int D, int n_items, int max_count, bool one_wave, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  if (p.G > 16 || p.lag || (D != 128 && D != 64)) return hipErrorInvalidValue;
+  if (p.G > 8 || p.lag || (D != 128 && D != 64)) return hipErrorInvalidValue;
   if (D == 128) one_wave ? launch<128, 8>(p, n_items, max_count, s) : launch<128, 4>(p, n_items, max_count, s);
   else one_wave ? launch<64, 8>(p, n_items, max_count, s) : launch<64, 4>(p, n_items, max_count, s);
   return hipGetLastError();

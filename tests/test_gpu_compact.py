@@ -156,11 +156,11 @@ def test_infeasible_budget_is_refused_at_creation():
 
 
 @pytest.mark.parametrize("slack", [1, 64, 700])
-def test_long_caches_move_in_several_segments(slack):
-    """Budgets around and above the move's segment size (4096 rows): rows whose source lies in the
-    next segment travel through the halo copy."""
+def test_long_caches_move_in_many_tiles(slack):
+    """Caches of 16 to 51 tiles of the move (256 rows): budgets of one row less than whole tiles, of whole tiles and of one
+    row more, rows that move by fewer and by more than a tile has, from random places and all from the front."""
     H = _h()
-    w = synth.shrink(synth.WORKLOADS["llama32"], name="segs", L=1, Hq=8, Hkv=4, batch=2, seed=25, sink=4,
+    w = synth.shrink(synth.WORKLOADS["llama32"], name="far", L=1, Hq=8, Hkv=4, batch=2, seed=25, sink=4,
                      recent=16, slack=slack)
     rng = np.random.Generator(np.random.PCG64(w.seed + slack))
     budgets = [4095, 4096, 4097, 13000]
@@ -181,12 +181,12 @@ def test_long_caches_move_in_several_segments(slack):
 
 
 @pytest.mark.parametrize("layers,slack", [(1, 1), (1, 127), (1, 5000), (24, 200), (24, 6000)])
-def test_move_segments_of_every_length(layers, slack):
-    """The length of a move segment follows the size of the arena (128 rows for one layer here, 1024 for
-    24): budgets around multiples of it, evictions of fewer and of more rows than a segment has (the
-    halo slot is the smaller of the two), from random places and all from the front."""
+def test_move_of_fewer_and_of_more_tiles_than_compute_units(layers, slack):
+    """One layer has about 100 tiles of the move, so every workgroup takes at most one, 24 have 2300, so each takes several
+    and waits for tiles that others hold: evictions of fewer and of more rows than a tile has, from random places and
+    all from the front, beside caches that one workgroup moves."""
     H = _h()
-    w = synth.shrink(synth.WORKLOADS["llama32"], name="seglen", L=layers, Hq=6, Hkv=6, batch=1, seed=27, sink=4,
+    w = synth.shrink(synth.WORKLOADS["llama32"], name="tickets", L=layers, Hq=6, Hkv=6, batch=1, seed=27, sink=4,
                      recent=16, slack=slack)
     rng = np.random.Generator(np.random.PCG64(w.seed + slack))
     budgets = [127, 128, 129, 2047, 2049, 20001] * layers
